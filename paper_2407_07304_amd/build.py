@@ -1,7 +1,9 @@
 """Builds ``libslimattn.so`` (the C-ABI library) and ``libslimprobe.so`` (the measurement kernels of
-``include/slimprobe.h``) from ``csrc/`` with hipcc for gfx950."""
+``include/slimprobe.h``) from ``csrc/`` with hipcc for gfx950, and ``_slimbind.so`` (the CPython binding of the
+former, host code only) with the host compiler."""
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -45,10 +47,32 @@ def _build_lib(lib, sources, verbose):
     return lib
 
 
+BINDING = os.path.join(HERE, "_slimbind.so")
+
+
+def _build_binding(verbose):
+    import torch
+    inc, libs = os.path.join(torch.__path__[0], "include"), os.path.join(torch.__path__[0], "lib")
+    tmp = BINDING + ".tmp.%d" % os.getpid()
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch.compiled_with_cxx11_abi()),
+           "-I" + sysconfig.get_paths()["include"], "-isystem", inc, "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"),
+           "-isystem", os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include"), os.path.join(CSRC, "binding.cpp"), "-o", tmp,
+           "-L" + libs, "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", "-L" + HERE, "-l:" + os.path.basename(LIB), "-Wl,-rpath,$ORIGIN"]
+    if verbose:
+        print(" ".join(cmd))
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("the host compiler failed on binding.cpp:\n%s" % r.stdout)
+    os.replace(tmp, BINDING)
+
+
 def build(verbose: bool = False) -> str:
     """Compiles every source every time it is called; returns the path of the attention library."""
     _build_lib(PROBE_LIB, PROBE_SOURCES, verbose)
-    return _build_lib(LIB, SOURCES, verbose)
+    _build_lib(LIB, SOURCES, verbose)
+    _build_binding(verbose)
+    return LIB
 
 
 if __name__ == "__main__":
