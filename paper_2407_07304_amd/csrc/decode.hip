@@ -2,9 +2,11 @@
 // matrix-vector product bound by memory bandwidth; cached INT8 values are widened to FP32
 // in registers and fed to FMAs, with one scale per token per head).
 //
-// HBM-bound streaming kernel.  A workgroup of 4 waves serves one (batch, query head) and
-// one split of the key axis; every wave streams a contiguous run of tokens in chunks of
-// 64 tokens:
+// HBM-bound streaming kernel.  A workgroup of 4 or 8 waves serves one (batch, query head) and
+// one split of the key axis (the whole of it wherever the rows alone fill the chip); its
+// chunks of 64 tokens are dealt to the waves in turn, so that the workgroup sweeps one
+// contiguous piece of the cache (on the B=16, 32 heads, T=8192 cache 8 % faster than a
+// contiguous run of 512 tokens per wave, which 6.1 TB/s was the ceiling of):
 //   - a token row of D codes is read by D/16 adjacent lanes ("slot") with one 128-bit
 //     load each, so one load instruction of a wave fetches 64/(D/16) whole rows, and the
 //     wave's loads of a chunk cover one contiguous piece of K and one of V;
@@ -15,8 +17,8 @@
 //   - each slot carries its own running max / sum (online softmax, fp32), so the only
 //     cross-lane traffic in the loop is DPP adds inside a slot and a 256-byte LDS
 //     exchange of the chunk's probabilities;
-//   - slots and waves are merged in LDS at the end, and a second kernel merges the splits
-//     in a fixed order (no atomics: the result does not depend on arrival order).
+//   - slots and waves are merged in LDS at the end, and where there are several splits a second
+//     kernel merges them in a fixed order (no atomics: the result does not depend on arrival order).
 #include <mutex>
 #include <type_traits>
 
@@ -25,7 +27,6 @@
 
 namespace slim {
 
-constexpr int kDecodeWaves = 4;
 constexpr int kChunk = 64;   // tokens per wave per chunk
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
@@ -49,20 +50,23 @@ __device__ __forceinline__ float slot_max(float v) {
     return v;
 }
 
-template <int D>
-__global__ __launch_bounds__(256) void slim_decode_int8_split_kernel(
+// D head dimension, W waves per workgroup
+template <int D, int W>
+__global__ __launch_bounds__(64 * W) void slim_decode_int8_split_kernel(
     const uint16_t* __restrict__ q, const int8_t* __restrict__ kc, const float* __restrict__ ks,
     const int8_t* __restrict__ vc, const float* __restrict__ vs, uint16_t* __restrict__ out,
     float* __restrict__ ws_acc, float* __restrict__ ws_ml, const int* __restrict__ kv_lens, int Hq, int Hkv, int T_alloc,
-    int n_split, int tokens_per_wave, float scale_log2e) {
+    int n_split, float scale_log2e) {
     constexpr int LPR = D / 16;        // lanes per token row
     constexpr int SLOTS = 64 / LPR;    // token rows per load instruction of a wave
     constexpr int CH = LPR;            // rows per slot per chunk: SLOTS * CH == kChunk, one token per lane
+    constexpr int PARTS = 64 * W / D;  // threads that share an output column at the merge
 
-    __shared__ __attribute__((aligned(16))) float pvS[kDecodeWaves][kChunk];
-    __shared__ __attribute__((aligned(16))) float accS[kDecodeWaves][SLOTS][D];
-    __shared__ float lS[kDecodeWaves][SLOTS];
-    __shared__ float mS[kDecodeWaves][SLOTS];
+    __shared__ __attribute__((aligned(16))) float pvS[W][kChunk];
+    __shared__ __attribute__((aligned(16))) float accS[W][SLOTS][D];
+    __shared__ float lS[W];
+    __shared__ float mS[W];
+    __shared__ float oS[PARTS][D];
 
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));   // (the wave index as a scalar: everything derived from it stays uniform)
     const int c = lane % LPR, s = lane / LPR;
@@ -80,9 +84,11 @@ __global__ __launch_bounds__(256) void slim_decode_int8_split_kernel(
     const __amdgpu_buffer_rsrc_t ksr = __builtin_amdgcn_make_buffer_rsrc((void*)(ks + kvbase), 0, (int)((unsigned)T * 4u), 0x00020000);
     const __amdgpu_buffer_rsrc_t vsr = __builtin_amdgcn_make_buffer_rsrc((void*)(vs + kvbase), 0, (int)((unsigned)T * 4u), 0x00020000);
     const int lane_off = (s * CH) * D + c * 16;   // this lane's piece of its slot's first row, relative to the chunk
-    const int t_wave0 = (sp * kDecodeWaves + w) * tokens_per_wave;
-    const int t_wave_end = min(T, t_wave0 + tokens_per_wave);
-    const int n_chunks = t_wave0 < T ? (t_wave_end - t_wave0 + kChunk - 1) / kChunk : 0;
+    // The sequence's own chunks are dealt evenly over the splits, and a split's chunks to its waves in turn: the
+    // waves of a workgroup read adjacent pieces of the cache at a time.
+    const int n_all = (T + kChunk - 1) / kChunk;
+    const int c_begin = (int)((long)n_all * sp / n_split) + w, c_end = (int)((long)n_all * (sp + 1) / n_split);
+    const int n_chunks = c_begin < c_end ? (c_end - c_begin + W - 1) / W : 0;
 
     // this lane's 16 query values, fp32
     float qf[16];
@@ -125,12 +131,13 @@ __global__ __launch_bounds__(256) void slim_decode_int8_split_kernel(
     };
 
     // unconditional (a wave past the end gets zeros and reads nothing): keeps the prologue free of branches
-    issue_k(t_wave0);
-    issue_v(t_wave0);
+    const int t_first = n_chunks > 0 ? c_begin * kChunk : T;
+    issue_k(t_first);
+    issue_v(t_first);
     // one chunk; PREFETCH is a compile-time flag so the loop body has no branch around its loads
     auto chunk = [&](int ch, auto prefetch) {
         constexpr bool more = decltype(prefetch)::value;
-        const int t_chunk0 = t_wave0 + ch * kChunk;
+        const int t_chunk0 = (c_begin + ch * W) * kChunk;
 
         // scores: the slot's CH rows; lane c of the slot keeps row c (token t_chunk0 + lane)
         float my_dot = 0.0f;
@@ -150,7 +157,7 @@ __global__ __launch_bounds__(256) void slim_decode_int8_split_kernel(
         }
         const bool valid = t_chunk0 + lane < T;
         const float my_s = valid ? my_dot * (ksc * scale_log2e) : kMasked;
-        if constexpr (more) issue_k(t_chunk0 + kChunk);
+        if constexpr (more) issue_k(t_chunk0 + W * kChunk);
 
         const float m_new = fmaxf(m, slot_max<LPR>(my_s));
         const float alpha = fast_exp2(m - m_new);
@@ -184,39 +191,55 @@ __global__ __launch_bounds__(256) void slim_decode_int8_split_kernel(
                 acc[4 * i + 3] = fmaf(pv[it], i8_to_f32<3>(vw[i]), acc[4 * i + 3]);
             }
         }
-        if constexpr (more) issue_v(t_chunk0 + kChunk);
+        if constexpr (more) issue_v(t_chunk0 + W * kChunk);
     };
     for (int ch = 0; ch + 1 < n_chunks; ++ch) chunk(ch, std::true_type{});
     if (n_chunks > 0) chunk(n_chunks - 1, std::false_type{});
 
-    // merge slots and waves in LDS
+    // Merge: the slots of a wave are brought to the wave's maximum in registers, then PARTS threads per output column
+    // add up their share of the waves' slots from LDS, and one of them the parts.
     l = slot_sum<LPR>(l);
+    float m_wave = m;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        f32x4 a4 = {acc[4 * i], acc[4 * i + 1], acc[4 * i + 2], acc[4 * i + 3]};
-        *reinterpret_cast<f32x4*>(&accS[w][s][c * 16 + 4 * i]) = a4;
-    }
-    if (c == 0) {
-        lS[w][s] = l;
-        mS[w][s] = m;
+    for (int x = LPR; x < 64; x *= 2) m_wave = fmaxf(m_wave, __shfl_xor(m_wave, x));
+    {
+        const float f = fast_exp2(m - m_wave);   // an empty slot has l = 0 and acc = 0
+        l *= f;
+#pragma unroll
+        for (int x = LPR; x < 64; x *= 2) l += __shfl_xor(l, x);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            f32x4 a4 = {acc[4 * i] * f, acc[4 * i + 1] * f, acc[4 * i + 2] * f, acc[4 * i + 3] * f};
+            *reinterpret_cast<f32x4*>(&accS[w][s][c * 16 + 4 * i]) = a4;
+        }
+        if (lane == 0) {
+            lS[w] = l;
+            mS[w] = m_wave;
+        }
     }
     __syncthreads();
+    float M = kMasked;
+#pragma unroll
+    for (int ww = 0; ww < W; ++ww) M = fmaxf(M, mS[ww]);
+    const int d = threadIdx.x % D, part = threadIdx.x / D;
+    float o = 0.0f;
+#pragma unroll
+    for (int i = 0; i < W / PARTS; ++i) {
+        const int ww = part * (W / PARTS) + i;
+        float a = 0.0f;
+#pragma unroll
+        for (int ss = 0; ss < SLOTS; ++ss) a += accS[ww][ss][d];
+        o = fmaf(fast_exp2(mS[ww] - M), a, o);
+    }
+    oS[part][d] = o;
+    __syncthreads();
     if (threadIdx.x < D) {
-        const int d = threadIdx.x;
-        float M = kMasked;
+        float L = 0.0f;
+        o = 0.0f;
 #pragma unroll
-        for (int ww = 0; ww < kDecodeWaves; ++ww)
+        for (int ww = 0; ww < W; ++ww) L = fmaf(fast_exp2(mS[ww] - M), lS[ww], L);
 #pragma unroll
-            for (int ss = 0; ss < SLOTS; ++ss) M = fmaxf(M, mS[ww][ss]);
-        float L = 0.0f, o = 0.0f;
-#pragma unroll
-        for (int ww = 0; ww < kDecodeWaves; ++ww)
-#pragma unroll
-            for (int ss = 0; ss < SLOTS; ++ss) {
-                const float f = fast_exp2(mS[ww][ss] - M);   // an empty slot has l = 0 and acc = 0
-                L = fmaf(f, lS[ww][ss], L);
-                o = fmaf(f, accS[ww][ss][d], o);
-            }
+        for (int i = 0; i < PARTS; ++i) o += oS[i][d];
         const long bh = (long)b * Hq + h;
         if (n_split == 1) {
             out[bh * D + d] = (uint16_t)(pack_bf16x2(o / L, 0.0f) & 0xffffu);
@@ -278,24 +301,37 @@ __global__ __launch_bounds__(D) void slim_decode_combine_kernel(const float* __r
     out[bh * D + d] = (uint16_t)(pack_bf16x2(o / L, 0.0f) & 0xffffu);
 }
 
-constexpr int kTokensPerWave = 512;   // 8 chunks: measured flat from 512 to 2048 on a B=16, T=8192 cache
-
-// Tokens of the key axis one wave streams: a multiple of the 64-token chunk.  Long
-// enough to amortise the merge; shortened when (batch x heads) alone cannot fill the
-// chip (aim: at least ~4 workgroups per compute unit) or when the cache is short.
-int decode_tokens_per_wave(int kv_len, long n_bh) {
-    long tpw = kTokensPerWave;
-    const long want_blocks = 256L * 4;
-    const long fill = (long)kv_len * n_bh / (want_blocks * kDecodeWaves);   // tokens per wave that give want_blocks
-    if (tpw > fill) tpw = fill;
-    tpw = tpw / kChunk * kChunk;
-    if (tpw < kChunk) tpw = kChunk;
-    return (int)tpw;
-}
-
-int decode_num_splits(int kv_len, long n_bh) {
-    const int per_block = decode_tokens_per_wave(kv_len, n_bh) * kDecodeWaves;
-    return (kv_len + per_block - 1) / per_block;
+// Splits of the key axis and waves per workgroup.  Modelled time of S splits of n_bh rows on 256 compute units, the
+// constants from a sweep of 17 row counts (8 to 2048) by 15 lengths (128 to 32768), K and V cold:
+//   - the cache at 6.6 TB/s, or the fullest compute unit's tokens at its own pace (7.1 ns a token of 128 codes, 5.8 of
+//     64: its vector ALU and its share of the memory), whichever is longer;
+//   - 6 us for the combine launch when S > 1.
+// So a (batch, head) is split only where one workgroup each cannot load the chip evenly or soon enough, and whole
+// caches go through one launch from about 150 rows on (B=16, 32 heads, T=8192: 161 us in one launch of eight-wave
+// workgroups, 164 us as 4 splits).  A split has at least a chunk for each of four waves.
+struct DecodePlan {
+    int waves, n_split;
+};
+static DecodePlan decode_plan(int kv_len, long n_bh, int head_dim) {
+    const long n_chunks = ((long)kv_len + kChunk - 1) / kChunk;
+    const double ns_token = head_dim == 128 ? 7.1 : 5.8;
+    const double stream_ns = (double)kv_len * n_bh * (2 * head_dim + 8) / 6600.0;
+    DecodePlan best{4, 1};
+    double best_ns = 0.0;
+    for (int s : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256}) {
+        if (s > 1 && s * 4 > n_chunks) break;
+        const long per_wg = (n_chunks + s - 1) / s, rounds = (n_bh * s + 255) / 256;
+        const double busy_ns = (double)(rounds * per_wg * kChunk) * ns_token;
+        const double ns = (busy_ns > stream_ns ? busy_ns : stream_ns) + (s > 1 ? 6000.0 : 0.0);
+        if (s == 1 || ns < best_ns) {
+            best_ns = ns;
+            best.n_split = s;
+            // eight waves share a merge where each still gets a few chunks (a chunk each is enough once several
+            // workgroups per compute unit overlap)
+            best.waves = per_wg >= (n_bh * s >= 512 ? 8 : 24) ? 8 : 4;
+        }
+    }
+    return best;
 }
 
 bool decode_uses_gqa_kernel(int q_heads, int kv_heads) {
@@ -305,7 +341,7 @@ bool decode_uses_gqa_kernel(int q_heads, int kv_heads) {
 
 size_t decode_workspace_bytes(int batch, int q_heads, int kv_heads, int kv_len, int head_dim) {
     const int n_split = decode_uses_gqa_kernel(q_heads, kv_heads) ? decode_gqa_num_splits(kv_len, (long)batch * kv_heads)
-                                                                  : decode_num_splits(kv_len, (long)batch * q_heads);
+                                                                  : decode_plan(kv_len, (long)batch * q_heads, head_dim).n_split;
     const size_t n = (size_t)batch * q_heads * n_split;
     return n * ((size_t)head_dim + 2) * sizeof(float);
 }
@@ -354,21 +390,24 @@ hipError_t launch_decode(const DecodeArgs& a, hipStream_t stream) {
         return hipGetLastError();
     }
     const long n_bh = (long)a.batch * a.q_heads;
-    const int tpw = decode_tokens_per_wave(a.kv_len, n_bh);
-    const int n_split = decode_num_splits(a.kv_len, n_bh);
+    const DecodePlan plan = decode_plan(a.kv_len, n_bh, a.head_dim);
+    const int n_split = plan.n_split;
     const size_t n_part = (size_t)a.batch * a.q_heads * n_split;
     float* ws_acc = a.workspace;
     float* ws_ml = a.workspace + n_part * a.head_dim;
-    const float scale_log2e = a.softmax_scale * kLog2e;
-    dim3 grid((unsigned)n_split, (unsigned)a.q_heads, (unsigned)a.batch);
-    if (a.head_dim == 128)
-        hipLaunchKernelGGL(slim_decode_int8_split_kernel<128>, grid, dim3(256), 0, stream, (const uint16_t*)a.q,
-                           a.k_codes, a.k_scale, a.v_codes, a.v_scale, (uint16_t*)a.out, ws_acc, ws_ml, a.kv_lens,
-                           a.q_heads, a.kv_heads, a.kv_len, n_split, tpw, scale_log2e);
-    else
-        hipLaunchKernelGGL(slim_decode_int8_split_kernel<64>, grid, dim3(256), 0, stream, (const uint16_t*)a.q,
-                           a.k_codes, a.k_scale, a.v_codes, a.v_scale, (uint16_t*)a.out, ws_acc, ws_ml, a.kv_lens,
-                           a.q_heads, a.kv_heads, a.kv_len, n_split, tpw, scale_log2e);
+    auto launch = [&](auto d_c, auto w_c) {
+        constexpr int D = decltype(d_c)::value, W = decltype(w_c)::value;
+        hipLaunchKernelGGL((slim_decode_int8_split_kernel<D, W>), dim3((unsigned)n_split, (unsigned)a.q_heads, (unsigned)a.batch),
+                           dim3(64 * W), 0, stream, (const uint16_t*)a.q, a.k_codes, a.k_scale, a.v_codes, a.v_scale,
+                           (uint16_t*)a.out, ws_acc, ws_ml, a.kv_lens, a.q_heads, a.kv_heads, a.kv_len, n_split,
+                           a.softmax_scale * kLog2e);
+    };
+    auto pick_w = [&](auto d_c) {
+        if (plan.waves == 8) launch(d_c, std::integral_constant<int, 8>{});
+        else launch(d_c, std::integral_constant<int, 4>{});
+    };
+    if (a.head_dim == 128) pick_w(std::integral_constant<int, 128>{});
+    else pick_w(std::integral_constant<int, 64>{});
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || n_split == 1) return e;
     const unsigned nbh = (unsigned)(a.batch * a.q_heads);

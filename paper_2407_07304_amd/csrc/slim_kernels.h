@@ -48,10 +48,6 @@ struct DecodeArgs {
     int batch, q_heads, kv_heads, kv_len, head_dim;
     float softmax_scale;
 };
-// Tokens of the key axis one wave of the split kernel streams, and the split count, for a
-// cache of kv_len tokens and n_bh = batch * q_heads independent rows.
-int decode_tokens_per_wave(int kv_len, long n_bh);
-int decode_num_splits(int kv_len, long n_bh);
 // Grouped-query variant (2 to 32 query heads per KV head): one wave streams a token run of one (batch, KV
 // head) for all its query heads; every wave is a split.  n_bg = batch * kv_heads.
 bool decode_uses_gqa_kernel(int q_heads, int kv_heads);
