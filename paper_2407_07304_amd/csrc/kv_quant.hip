@@ -70,23 +70,24 @@ __global__ __launch_bounds__(256) void kv_quant_int8_pair_kernel(const QuantPair
     kv_quant_rows<D, STREAM, U>(t == 0 ? p.x[0] : p.x[1], t == 0 ? p.codes[0] : p.codes[1], t == 0 ? p.scales[0] : p.scales[1], n_rows);
 }
 
-// One new token per (batch, KV head): row r = b * Hkv + g of x goes to token positions[b] of that head's cache.
+// One new token per (batch, KV head): row b * Hkv + g of x goes to token positions[b] of that head's cache, blockIdx.y is
+// the sequence.  Nothing but latency (a launch moves a few kilobytes): the position is a scalar load that goes out with
+// the row's, where a division of the row index by Hkv and a load behind the arithmetic were a second trip to memory.
+constexpr int kAppendThreads = 128;
 template <int D>
-__global__ __launch_bounds__(256) void kv_quant_int8_append_kernel(const uint16_t* __restrict__ x, int8_t* __restrict__ codes,
+__global__ __launch_bounds__(kAppendThreads) void kv_quant_int8_append_kernel(const uint16_t* __restrict__ x, int8_t* __restrict__ codes,
                                                                    float* __restrict__ scales,
-                                                                   const int* __restrict__ positions, int n_rows, int Hkv,
-                                                                   int T) {
+                                                                   const int* __restrict__ positions, int Hkv, int T) {
     constexpr int LPR = D / 8;
-    constexpr int ROWS = 256 / LPR;
     const int lane_in_row = threadIdx.x % LPR;
-    const int row = blockIdx.x * ROWS + threadIdx.x / LPR;
-    if (row >= n_rows) return;   // (whole row groups leave together: the shuffles below stay inside a row)
+    const int b = blockIdx.y, g = (int)(blockIdx.x * kAppendThreads + threadIdx.x) / LPR;
+    const int pos = positions[b];
+    const int row = b * Hkv + min(g, Hkv - 1);
     const u32x4 raw = *reinterpret_cast<const u32x4*>(x + (long)row * D + lane_in_row * 8);
     u32x2 out2;
     float scale;
     quant_row_piece<LPR>(raw, out2, scale);
-    const int pos = positions[row / Hkv];
-    if (pos < 0 || pos >= T) return;   // no room in this sequence's cache: nothing is written
+    if (g >= Hkv || pos < 0 || pos >= T) return;   // (no room in this sequence's cache: nothing is written)
     const long out_row = (long)row * T + pos;
     *reinterpret_cast<u32x2*>(codes + out_row * D + lane_in_row * 8) = out2;
     if (lane_in_row == 0) scales[out_row] = scale;
@@ -138,15 +139,14 @@ hipError_t launch_kv_quant_int8_pair(const void* k, const void* v, int8_t* k_cod
 
 hipError_t launch_kv_quant_int8_append(const void* x, int8_t* codes, float* scales, const int* positions, int batch,
                                        int kv_heads, int kv_len, int head_dim, hipStream_t stream) {
-    const int n_rows = batch * kv_heads;
-    const int rows_per_block = 256 / (head_dim / 8);
-    const unsigned blocks = (unsigned)((n_rows + rows_per_block - 1) / rows_per_block);
+    const unsigned threads = (unsigned)kv_heads * (unsigned)(head_dim / 8);
+    const dim3 grid((threads + kAppendThreads - 1) / kAppendThreads, (unsigned)batch), block(kAppendThreads);
     if (head_dim == 128)
-        hipLaunchKernelGGL(kv_quant_int8_append_kernel<128>, dim3(blocks), dim3(256), 0, stream, (const uint16_t*)x, codes,
-                           scales, positions, n_rows, kv_heads, kv_len);
+        hipLaunchKernelGGL(kv_quant_int8_append_kernel<128>, grid, block, 0, stream, (const uint16_t*)x, codes, scales,
+                           positions, kv_heads, kv_len);
     else
-        hipLaunchKernelGGL(kv_quant_int8_append_kernel<64>, dim3(blocks), dim3(256), 0, stream, (const uint16_t*)x, codes,
-                           scales, positions, n_rows, kv_heads, kv_len);
+        hipLaunchKernelGGL(kv_quant_int8_append_kernel<64>, grid, block, 0, stream, (const uint16_t*)x, codes, scales,
+                           positions, kv_heads, kv_len);
     return hipGetLastError();
 }
 
