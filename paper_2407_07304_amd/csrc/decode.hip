@@ -257,27 +257,30 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_split_kernel(
 // Merges the n_split partial (max, sum, accumulator) triples of one (batch, head) in split order and writes the
 // bf16 output row.  The launch is latency-bound (a few kilobytes per workgroup, just written by the split kernel),
 // so all loads of up to kCombineChunk splits are issued before anything is computed: one round trip to memory
-// instead of one for the maxima and another for the sums and accumulators.  More splits than that (short batches of
-// long caches) are merged a chunk at a time with a running (max, sum, accumulator), still in split order.  Slots
-// past the last split re-read the last one and count as empty (max = kMasked, sum = 0).
+// instead of one for the maxima and another for the sums and accumulators.  Longer runs are merged a chunk at a time
+// with a running (max, sum, accumulator), still in split order; with more than a chunk of splits (short batches of
+// long caches) PARTS groups of D threads take a contiguous share of the splits each and are merged through LDS, so
+// that 64 splits are still one round trip (64 query heads of one sequence at T=32768: 6.1 -> 4.5 us a launch).  Slots past
+// the last split re-read the last one and count as empty (max = kMasked, sum = 0).
 constexpr int kCombineChunk = 16;
 
-template <int D>
-__global__ __launch_bounds__(D) void slim_decode_combine_kernel(const float* __restrict__ ws_acc,
-                                                                const float* __restrict__ ws_ml,
-                                                                uint16_t* __restrict__ out, int n_split) {
+template <int D, int PARTS>
+__global__ __launch_bounds__(D * PARTS) void slim_decode_combine_kernel(const float* __restrict__ ws_acc,
+                                                                        const float* __restrict__ ws_ml,
+                                                                        uint16_t* __restrict__ out, int n_split) {
     constexpr int CH = kCombineChunk;
     const long bh = blockIdx.x;
-    const int d = threadIdx.x;
+    const int d = threadIdx.x % D, part = threadIdx.x / D;
+    const int s_begin = PARTS == 1 ? 0 : n_split * part / PARTS, s_end = PARTS == 1 ? n_split : n_split * (part + 1) / PARTS;
     const float* const ml = ws_ml + bh * n_split * 2;
     const float* const acc = ws_acc + bh * n_split * D + d;
     float M = kMasked, L = 0.0f, o = 0.0f;
-    for (int s0 = 0; s0 < n_split; s0 += CH) {
+    for (int s0 = s_begin; s0 < s_end; s0 += CH) {
         float m[CH], l[CH], a[CH];
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
-            const int sp = min(s0 + i, n_split - 1);
-            const bool there = s0 + i < n_split;
+            const int sp = min(s0 + i, s_end - 1);
+            const bool there = s0 + i < s_end;
             const f32x2 t = *reinterpret_cast<const f32x2*>(ml + 2 * sp);
             const float av = acc[(long)sp * D];
             m[i] = there ? t[0] : kMasked;
@@ -298,13 +301,48 @@ __global__ __launch_bounds__(D) void slim_decode_combine_kernel(const float* __r
         }
         M = m_new;
     }
+    if constexpr (PARTS > 1) {
+        __shared__ float oS[PARTS][D], mS[PARTS], lS[PARTS];
+        oS[part][d] = o;
+        if (d == 0) {
+            mS[part] = M;
+            lS[part] = L;
+        }
+        __syncthreads();
+        if (part != 0) return;
+        float top = kMasked;
+#pragma unroll
+        for (int i = 0; i < PARTS; ++i) top = fmaxf(top, mS[i]);
+        L = 0.0f;
+        o = 0.0f;
+#pragma unroll
+        for (int i = 0; i < PARTS; ++i) {
+            const float f = fast_exp2(mS[i] - top);
+            L = fmaf(f, lS[i], L);
+            o = fmaf(f, oS[i][d], o);
+        }
+    }
     out[bh * D + d] = (uint16_t)(pack_bf16x2(o / L, 0.0f) & 0xffffu);
+}
+
+static hipError_t launch_combine(const DecodeArgs& a, const float* ws_acc, const float* ws_ml, int n_split, hipStream_t stream) {
+    auto launch = [&](auto d_c, auto parts_c) {
+        constexpr int D = decltype(d_c)::value, PARTS = decltype(parts_c)::value;
+        hipLaunchKernelGGL((slim_decode_combine_kernel<D, PARTS>), dim3((unsigned)(a.batch * a.q_heads)), dim3(D * PARTS), 0, stream,
+                           ws_acc, ws_ml, (uint16_t*)a.out, n_split);
+        return hipGetLastError();
+    };
+    auto pick = [&](auto d_c) {
+        return n_split > kCombineChunk ? launch(d_c, std::integral_constant<int, 4>{}) : launch(d_c, std::integral_constant<int, 1>{});
+    };
+    return a.head_dim == 128 ? pick(std::integral_constant<int, 128>{}) : pick(std::integral_constant<int, 64>{});
 }
 
 // Splits of the key axis and waves per workgroup.  Modelled time of S splits of n_bh rows on 256 compute units, the
 // constants from a sweep of 17 row counts (8 to 2048) by 15 lengths (128 to 32768), K and V cold:
 //   - the cache at 6.6 TB/s, or the fullest compute unit's tokens at its own pace (7.1 ns a token of 128 codes, 5.8 of
-//     64: its vector ALU and its share of the memory), whichever is longer;
+//     64: its vector ALU and its share of the memory): the longer of the two and a fifth of the
+//     shorter;
 //   - 6 us for the combine launch when S > 1.
 // So a (batch, head) is split only where one workgroup each cannot load the chip evenly or soon enough, and whole
 // caches go through one launch from about 150 rows on (B=16, 32 heads, T=8192: 161 us in one launch of eight-wave
@@ -322,7 +360,8 @@ static DecodePlan decode_plan(int kv_len, long n_bh, int head_dim) {
         if (s > 1 && s * 4 > n_chunks) break;
         const long per_wg = (n_chunks + s - 1) / s, rounds = (n_bh * s + 255) / 256;
         const double busy_ns = (double)(rounds * per_wg * kChunk) * ns_token;
-        const double ns = (busy_ns > stream_ns ? busy_ns : stream_ns) + (s > 1 ? 6000.0 : 0.0);
+        const double longer = busy_ns > stream_ns ? busy_ns : stream_ns, shorter = busy_ns > stream_ns ? stream_ns : busy_ns;
+        const double ns = longer + 0.2 * shorter + (s > 1 ? 6000.0 : 0.0);
         if (s == 1 || ns < best_ns) {
             best_ns = ns;
             best.n_split = s;
@@ -340,10 +379,13 @@ bool decode_uses_gqa_kernel(int q_heads, int kv_heads) {
 }
 
 size_t decode_workspace_bytes(int batch, int q_heads, int kv_heads, int kv_len, int head_dim) {
-    const int n_split = decode_uses_gqa_kernel(q_heads, kv_heads) ? decode_gqa_num_splits(kv_len, (long)batch * kv_heads)
-                                                                  : decode_plan(kv_len, (long)batch * q_heads, head_dim).n_split;
-    const size_t n = (size_t)batch * q_heads * n_split;
-    return n * ((size_t)head_dim + 2) * sizeof(float);
+    int n_split = decode_plan(kv_len, (long)batch * q_heads, head_dim).n_split;
+    if (decode_uses_gqa_kernel(q_heads, kv_heads)) {
+        // (never less than two records a row: the shapes the static scratch array is too small for stay what they were)
+        n_split = decode_gqa_num_splits(kv_len, (long)batch * kv_heads, head_dim);
+        if (n_split < 2) n_split = 2;
+    }
+    return (size_t)batch * q_heads * n_split * ((size_t)head_dim + 2) * sizeof(float);
 }
 
 // Scratch of the decode entry point that may not allocate: the same (max, sum, accumulator) partials as the
@@ -372,52 +414,28 @@ hipError_t decode_static_scratch(float** ptr) {
 }
 
 hipError_t launch_decode(const DecodeArgs& a, hipStream_t stream) {
-    if (decode_uses_gqa_kernel(a.q_heads, a.kv_heads)) {
-        // the query heads of a KV head share one pass over its cache; every wave's token run is a split
-        const int n_split = decode_gqa_num_splits(a.kv_len, (long)a.batch * a.kv_heads);
-        const size_t n_part = (size_t)a.batch * a.q_heads * n_split;
-        float* ws_acc = a.workspace;
-        float* ws_ml = a.workspace + n_part * a.head_dim;
-        hipError_t e = launch_decode_gqa_split(a, ws_acc, ws_ml, n_split, stream);
-        if (e != hipSuccess) return e;
-        const unsigned nbh = (unsigned)(a.batch * a.q_heads);
-        if (a.head_dim == 128)
-            hipLaunchKernelGGL(slim_decode_combine_kernel<128>, dim3(nbh), dim3(128), 0, stream, ws_acc, ws_ml,
-                               (uint16_t*)a.out, n_split);
-        else
-            hipLaunchKernelGGL(slim_decode_combine_kernel<64>, dim3(nbh), dim3(64), 0, stream, ws_acc, ws_ml,
-                               (uint16_t*)a.out, n_split);
-        return hipGetLastError();
-    }
-    const long n_bh = (long)a.batch * a.q_heads;
-    const DecodePlan plan = decode_plan(a.kv_len, n_bh, a.head_dim);
-    const int n_split = plan.n_split;
-    const size_t n_part = (size_t)a.batch * a.q_heads * n_split;
-    float* ws_acc = a.workspace;
-    float* ws_ml = a.workspace + n_part * a.head_dim;
+    // (the query heads of a KV head share one pass over its cache in the grouped-query kernel)
+    const bool gqa = decode_uses_gqa_kernel(a.q_heads, a.kv_heads);
+    const DecodePlan plan = decode_plan(a.kv_len, (long)a.batch * a.q_heads, a.head_dim);
+    const int n_split = gqa ? decode_gqa_num_splits(a.kv_len, (long)a.batch * a.kv_heads, a.head_dim) : plan.n_split;
+    float* const ws_acc = a.workspace;
+    float* const ws_ml = a.workspace + (size_t)a.batch * a.q_heads * n_split * a.head_dim;
     auto launch = [&](auto d_c, auto w_c) {
         constexpr int D = decltype(d_c)::value, W = decltype(w_c)::value;
         hipLaunchKernelGGL((slim_decode_int8_split_kernel<D, W>), dim3((unsigned)n_split, (unsigned)a.q_heads, (unsigned)a.batch),
                            dim3(64 * W), 0, stream, (const uint16_t*)a.q, a.k_codes, a.k_scale, a.v_codes, a.v_scale,
                            (uint16_t*)a.out, ws_acc, ws_ml, a.kv_lens, a.q_heads, a.kv_heads, a.kv_len, n_split,
                            a.softmax_scale * kLog2e);
+        return hipGetLastError();
     };
     auto pick_w = [&](auto d_c) {
-        if (plan.waves == 8) launch(d_c, std::integral_constant<int, 8>{});
-        else launch(d_c, std::integral_constant<int, 4>{});
+        return plan.waves == 8 ? launch(d_c, std::integral_constant<int, 8>{}) : launch(d_c, std::integral_constant<int, 4>{});
     };
-    if (a.head_dim == 128) pick_w(std::integral_constant<int, 128>{});
-    else pick_w(std::integral_constant<int, 64>{});
-    hipError_t e = hipGetLastError();
+    const hipError_t e = gqa                 ? launch_decode_gqa_split(a, ws_acc, ws_ml, n_split, stream)
+                         : a.head_dim == 128 ? pick_w(std::integral_constant<int, 128>{})
+                                             : pick_w(std::integral_constant<int, 64>{});
     if (e != hipSuccess || n_split == 1) return e;
-    const unsigned nbh = (unsigned)(a.batch * a.q_heads);
-    if (a.head_dim == 128)
-        hipLaunchKernelGGL(slim_decode_combine_kernel<128>, dim3(nbh), dim3(128), 0, stream, ws_acc, ws_ml,
-                           (uint16_t*)a.out, n_split);
-    else
-        hipLaunchKernelGGL(slim_decode_combine_kernel<64>, dim3(nbh), dim3(64), 0, stream, ws_acc, ws_ml,
-                           (uint16_t*)a.out, n_split);
-    return hipGetLastError();
+    return launch_combine(a, ws_acc, ws_ml, n_split, stream);
 }
 
 }  // namespace slim

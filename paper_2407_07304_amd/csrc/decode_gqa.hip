@@ -3,23 +3,30 @@
 // the bandwidth: every byte of it is read once per KV head here, not once per query head.
 //
 // With G query heads per KV head the step is a (G x D) by (D x T) product followed by a
-// (G x T) by (T x D) one: dense enough for the matrix cores.  One wave streams a run of
-// tokens of one (batch, KV head) in 32-token tiles and serves all G heads at once:
+// (G x T) by (T x D) one: dense enough for the matrix cores.  A workgroup sweeps a run of
+// tokens of one (batch, KV head) for all G heads, its 32-token tiles dealt to the waves in
+// turn:
 //   - K and V tiles are read with coalesced 128-bit loads (a load instruction of a wave
-//     covers whole rows), widened exactly to bf16 and written to a wave-private LDS tile
+//     covers whole rows) and written, as the INT8 codes they are, to a wave-private LDS tile
 //     each.  No other wave touches them: no barriers, LDS runs a wave's accesses in order.
-//   - scores, transposed: S^T = K Q^T with v_mfma_f32_32x32x16_bf16, the K tile as A operand
-//     (lane = token, 128-bit LDS reads), Q^T as B operand (held in registers, columns = the
-//     G heads, the rest zero).
-//   - every lane then holds one head's column and 16 of the 32 tokens: the token's
-//     k_scale multiplies the fp32 score, max and sum are in-lane plus one exchange between
-//     the wave's halves, the probability takes the token's v_scale before it is rounded
-//     to bf16 and is the B operand of O^T += V^T P^T as it stands; V^T comes from the
-//     row-major V tile through the LDS transpose read.
-//   - two tiles of loads are in flight per wave: the registers of a tile are refilled with
-//     the tile after the next as soon as they are consumed.
-// Each wave writes its (max, sum, accumulator) per head as one split of the workspace; the
-// combine kernel of decode.hip merges the splits in fixed order.
+//   - scores, transposed, on the INT8 matrix instruction: S^T = K Q^T with
+//     v_mfma_i32_16x16x64_i8, the K tile as A operand (lane = token, 128-bit LDS reads, no
+//     widening), Q^T as B operand (columns = heads).  Q enters as three signed base-256
+//     digits of its value in fixed point (23 bits and sign below the power of two above the
+//     row's largest magnitude: exact for every bf16 value down to 2^-15 of it), one product
+//     per digit, so a score is an exact integer sum until it is put together in fp32.
+//   - a lane then holds one head's column and 4 of every 16 tokens: k_scale multiplies the
+//     fp32 score, the running max is lazy (it moves when a score passes it by 2^8), the
+//     probability takes the token's v_scale before it is rounded to bf16 and is the B operand
+//     of O^T += V^T P^T (v_mfma_f32_16x16x32_bf16) as it stands; V^T comes from the row-major
+//     INT8 tile through the LDS byte transpose read and is widened to bf16 in registers.
+//   - a wave's next tile is in flight while it works on one: its registers are refilled as soon
+//     as they are in LDS.  At three waves per SIMD (154 vector registers) that covers the
+//     memory latency; a second tile in flight took the third wave and was 5 % slower.
+// (Before, K and V were widened to bf16 on their way through LDS and both products ran on
+// 32-column bf16 tiles: 378 vector instructions per 32 tokens, 230 vector registers.)
+// The waves of a workgroup are merged in LDS; where a (batch, KV head) is split over several
+// workgroups, the combine kernel of decode.hip merges them in fixed order.
 #include <type_traits>
 
 #include "slim_common.h"
@@ -27,321 +34,378 @@
 
 namespace slim {
 
-constexpr int kGqaWaves = 2;    // waves per workgroup, each with a token run of its own (the waves share nothing: on B=16, 64/8 heads,
-                                // T=8192 two-wave workgroups run 8 % faster than four-wave ones with the same runs, one-wave ones the same)
 constexpr int kGqaTile = 32;    // tokens per tile
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x2 __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) i32x2 lds_i32x2;
 
-// 16 INT8 codes -> 16 bf16, exact: the first and the second eight
-__device__ __forceinline__ void widen16(const u32x4 cw, u32x4& lo, u32x4& hi) {
+// 8 INT8 codes -> 8 bf16, exact
+__device__ __forceinline__ bf16x8 widen8(const i32x2 cw) {
+    u32x4 r;
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
-        lo[2 * e] = pack_bf16x2(i8_to_f32<0>(cw[e]), i8_to_f32<1>(cw[e]));
-        lo[2 * e + 1] = pack_bf16x2(i8_to_f32<2>(cw[e]), i8_to_f32<3>(cw[e]));
-        hi[2 * e] = pack_bf16x2(i8_to_f32<0>(cw[2 + e]), i8_to_f32<1>(cw[2 + e]));
-        hi[2 * e + 1] = pack_bf16x2(i8_to_f32<2>(cw[2 + e]), i8_to_f32<3>(cw[2 + e]));
+        r[2 * e] = pack_bf16x2(i8_to_f32<0>(cw[e]), i8_to_f32<1>(cw[e]));
+        r[2 * e + 1] = pack_bf16x2(i8_to_f32<2>(cw[e]), i8_to_f32<3>(cw[e]));
     }
+    return __builtin_bit_cast(bf16x8, r);
 }
 
+// D head dimension, W waves per workgroup, NC groups of 16 heads.
 // TRAFFIC_ONLY: the measurement form of the kernel (include/slimprobe.h): the same workgroups, waves, token runs and
 // loads, issued at the same points, but a tile's registers are only XORed together before they are refilled.  What it
 // takes is what the memory system charges for this access pattern on this shape, arithmetic aside.
-template <int D, bool TRAFFIC_ONLY = false>
-__global__ __launch_bounds__(64 * kGqaWaves) void slim_decode_int8_gqa_kernel(
+template <int D, int W, int NC, bool TRAFFIC_ONLY = false>
+__global__ __launch_bounds__(64 * W) void slim_decode_int8_gqa_kernel(
     const uint16_t* __restrict__ q, const int8_t* __restrict__ kc, const float* __restrict__ ks,
-    const int8_t* __restrict__ vc, const float* __restrict__ vs, float* __restrict__ ws_acc,
+    const int8_t* __restrict__ vc, const float* __restrict__ vs, uint16_t* __restrict__ out, float* __restrict__ ws_acc,
     float* __restrict__ ws_ml, const int* __restrict__ kv_lens, int Hq, int Hkv, int T_alloc, int n_split,
-    int tokens_per_wave, float scale_log2e) {
-    constexpr int KS = D / 16;            // k-steps of the score MFMA
-    constexpr int DT = D / 32;            // 32-row tiles of O^T
+    float scale_log2e) {
+    constexpr int KS = D / 64;            // k-steps of the score MFMA
+    constexpr int DT = D / 16;            // 16-row tiles of O^T
     constexpr int CPR = D / 16;           // 16-byte pieces per row
     constexpr int NP = kGqaTile * CPR / 64;   // 128-bit loads per lane, tile and tensor
-    // LDS row pitches of the bf16 tiles: the padding spreads the 128-bit K row reads and the V transpose reads over the banks
-    constexpr int ROWLK = 2 * D + 16, ROWLV = 2 * D + 64;
-    constexpr int TILEK = kGqaTile * ROWLK, TILEV = kGqaTile * ROWLV;
-    // one tile buffer per wave: the K tile, and once its fragments are read (LDS runs a wave's accesses in order)
-    // the V tile; then the tile's 32 + 32 scales
-    constexpr int WAVE_LDS = (TILEK > TILEV ? TILEK : TILEV) + 256;
+    constexpr int PITCH = D + 16;         // LDS row pitch: 16 rows' pieces of a read fall on 16 different groups of four banks
+    constexpr int TILE = kGqaTile * PITCH;
+    constexpr int WAVE_LDS = 2 * TILE + 256;   // K tile, V tile, the tile's 32 + 32 scales
+    constexpr int OPITCH = D + 4;         // floats per head in a wave's merge record (behind its maxima and sums)
+    constexpr int MERGE_LDS = 16 * NC * (OPITCH + 2) * 4;
+    constexpr int WAVE_BYTES = WAVE_LDS > MERGE_LDS ? WAVE_LDS : MERGE_LDS;
 
-    __shared__ __attribute__((aligned(16))) char smem[kGqaWaves * WAVE_LDS];
+    __shared__ __attribute__((aligned(16))) char smem[W * WAVE_BYTES];
 
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));   // (the wave index as a scalar: everything derived from it stays uniform)
-    const int l32 = lane & 31, hh = lane >> 5;
+    const int l16 = lane & 15, lq = lane >> 4;
     const int G = Hq / Hkv;
-    const int sp = blockIdx.x * kGqaWaves + w, g = blockIdx.y, b = blockIdx.z;
-    char* const kS = smem + w * WAVE_LDS;
-    char* const vS = kS;
-    float* const scS = reinterpret_cast<float*>(kS + WAVE_LDS - 256);   // [0,32) k_scale * c, [32,64) v_scale
+    const int sp = blockIdx.x, g = blockIdx.y, b = blockIdx.z;
+    char* const kS = smem + w * WAVE_BYTES;
+    char* const vS = kS + TILE;
+    float* const scS = reinterpret_cast<float*>(kS + 2 * TILE);   // [0,32) k_scale * c, [32,64) v_scale
 
-    // T_alloc is the cache's allocated length (the row stride); this sequence's first T tokens count
+    // T_alloc is the cache's allocated length (the row stride); this sequence's first T tokens count.  The sequence's
+    // own tiles are dealt evenly over the splits, and a split's tiles to its waves in turn.
     const int T = kv_lens ? min(max(kv_lens[b], 1), T_alloc) : T_alloc;
     const long kvrow0 = ((long)b * Hkv + g) * (long)T_alloc;
-    const int t_begin = sp * tokens_per_wave;
-    const int t_end = min(T, t_begin + tokens_per_wave);
-    const int n_tiles = t_begin < T ? (t_end - t_begin + kGqaTile - 1) / kGqaTile : 0;
+    const int n_all = (T + kGqaTile - 1) / kGqaTile;
+    const int first = (int)((long)n_all * sp / n_split) + w, end = (int)((long)n_all * (sp + 1) / n_split);
+    const int n_tiles = first < end ? (end - first + W - 1) / W : 0;
 
-    // Q^T B operands: lane holds head l32 (of the group), d = 16 s + 8 hh + [0,8)
-    bf16x8 qB[KS];
-    {
-        const uint16_t* qp = q + ((long)b * Hq + (long)g * G + min(l32, G - 1)) * D + 8 * hh;
+    // Q: lane holds head l16 of its group of 16, d = 64 s + 16 lq + [0,16)
+    u32x4 qraw[NC][KS][2];
 #pragma unroll
-        for (int s2 = 0; s2 < KS; ++s2) {
-            u32x4 a = *reinterpret_cast<const u32x4*>(qp + 16 * s2);
-            if (l32 >= G) a = u32x4{0u, 0u, 0u, 0u};
-            qB[s2] = __builtin_bit_cast(bf16x8, a);
-        }
+    for (int nc = 0; nc < NC; ++nc) {
+        const uint16_t* qp = q + ((long)b * Hq + (long)g * G + min(16 * nc + l16, G - 1)) * D + 16 * lq;
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) qraw[nc][s][e] = *reinterpret_cast<const u32x4*>(qp + 64 * s + 8 * e);
     }
 
     // Piece lane + 64 n of a tile (row-major, 16 codes each), through buffer descriptors that cover exactly this
     // (batch, KV head)'s slab: rows past the end of the cache read as zero (and are masked) and a load costs one
-    // vector add.  The codes are used once: non-temporal.  Two tiles of
-    // loads are in flight per wave (the registers of tile i are refilled with tile i+2 as soon as they are
-    // consumed): with 8 waves per compute unit that is what it takes to cover the memory latency.
+    // vector add.  The codes are used once: non-temporal.
     const __amdgpu_buffer_rsrc_t krs = __builtin_amdgcn_make_buffer_rsrc((void*)(kc + kvrow0 * D), 0, (int)((unsigned)T * D), 0x00020000);
     const __amdgpu_buffer_rsrc_t vrs = __builtin_amdgcn_make_buffer_rsrc((void*)(vc + kvrow0 * D), 0, (int)((unsigned)T * D), 0x00020000);
-    // (the scales through descriptors as well: lanes 0-31 want the K scale of token l32, lanes 32-63 the V scale; each
+    // (the scales through descriptors as well: lanes 0-31 want the K scale of token lane, lanes 32-63 the V scale; each
     // load asks the other half's lanes for an offset past the end, which reads nothing, so a tile's loads are the
     // same instructions whether the tile is wanted or not)
     const __amdgpu_buffer_rsrc_t ksr = __builtin_amdgcn_make_buffer_rsrc((void*)(ks + kvrow0), 0, (int)((unsigned)T * 4u), 0x00020000);
     const __amdgpu_buffer_rsrc_t vsr = __builtin_amdgcn_make_buffer_rsrc((void*)(vs + kvrow0), 0, (int)((unsigned)T * 4u), 0x00020000);
-    const int s_off_k = hh == 0 ? l32 * 4 : (int)0x7ffffff0, s_off_v = hh == 1 ? l32 * 4 : (int)0x7ffffff0;
-    int p_off[NP];
+    const bool k_half = lane < 32;
+    const int s_off_k = k_half ? lane * 4 : (int)0x7ffffff0, s_off_v = k_half ? (int)0x7ffffff0 : (lane - 32) * 4;
+    u32x4 kbuf[NP], vbuf[NP];
+    float sc = 0.0f;
+    auto issue = [&](const __amdgpu_buffer_rsrc_t rs, u32x4 (&buf)[NP], int t0) {
 #pragma unroll
-    for (int n = 0; n < NP; ++n) p_off[n] = ((lane + 64 * n) / CPR) * D + ((lane + 64 * n) % CPR) * 16;
-    u32x4 kbuf[2][NP], vbuf[2][NP];
-    float sc[2] = {0.0f, 0.0f};
-    auto issue = [&](auto par, const __amdgpu_buffer_rsrc_t rs, u32x4 (&buf)[2][NP], int t0) {
-        constexpr int P = decltype(par)::value;
-#pragma unroll
-        for (int n = 0; n < NP; ++n) buf[P][n] = __builtin_amdgcn_raw_buffer_load_b128(rs, p_off[n] + t0 * D, 0, 2 /* nt */);
+        for (int n = 0; n < NP; ++n) buf[n] = __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16 + n * 1024 + t0 * D, 0, 2 /* nt */);
     };
-    auto issue_k = [&](auto par, int t0) {
-        issue(par, krs, kbuf, t0);
+    auto issue_k = [&](int t0) {
+        issue(krs, kbuf, t0);
         const uint32_t a = __builtin_amdgcn_raw_buffer_load_b32(ksr, s_off_k + t0 * 4, 0, 0);
         const uint32_t c = __builtin_amdgcn_raw_buffer_load_b32(vsr, s_off_v + t0 * 4, 0, 0);
-        sc[decltype(par)::value] = __builtin_bit_cast(float, a | c);   // (the lanes a load left out received zero)
+        sc = __builtin_bit_cast(float, a | c);   // (the lanes a load left out received zero)
     };
-    auto issue_v = [&](auto par, int t0) { issue(par, vrs, vbuf, t0); };
-    auto stage = [&](auto par, const u32x4 (&buf)[2][NP], char* tile, int pitch) {   // widen a tile into LDS
-        constexpr int P = decltype(par)::value;
+    auto issue_v = [&](int t0) { issue(vrs, vbuf, t0); };
+    auto stage = [&](const u32x4 (&buf)[NP], char* tile) {   // a tile's codes into LDS
 #pragma unroll
-        for (int n = 0; n < NP; ++n) {
-            const int pid = lane + 64 * n;
-            u32x4 lo, hi;
-            widen16(buf[P][n], lo, hi);
-            char* dst = tile + (pid / CPR) * pitch + (pid % CPR) * 32;
-            *reinterpret_cast<u32x4*>(dst) = lo;
-            *reinterpret_cast<u32x4*>(dst + 16) = hi;
-        }
+        for (int n = 0; n < NP; ++n)
+            *reinterpret_cast<u32x4*>(tile + ((lane + 64 * n) / CPR) * PITCH + (lane % CPR) * 16) = buf[n];
     };
-    const int k_addr = l32 * ROWLK + 16 * hh;   // K fragment of k-step s: row l32, bytes 32 s + 16 hh + [0,16)
-    // LDS addresses of the V transpose reads: the 16 lanes of a group fetch rows k..k+3 (4 lanes per row, 4
-    // columns each) and lane i of the group receives column i of those 4 rows
-    int v_addr[DT];
-    {
-        const int rv = 4 * hh + ((lane & 15) >> 2);
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
-            v_addr[dt] = rv * ROWLV + (4 * dt + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) * 16 + 8 * (lane & 1);
-    }
-
-    f32x16 o[DT];
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) o[dt][r] = 0.0f;
-    float M = kMasked, lsum = 0.0f;   // running max of this lane's head (log2 units), this lane's part of the row sum
 
     // Every load of the kernel is issued unconditionally: a tile that is not wanted (past the end of this wave's
     // run) is asked for at token T, past the end of the descriptor, so zeros arrive and no memory is read.  The
     // compiler places a wait by counting the loads issued after the one it needs, along the worst path that leads
     // there; loads under a branch are not outstanding on the path that skips them, and at the loop's head the
     // worst path may be the one from the prologue.  So the prologue's four groups keep the order the loop issues
-    // them in (K, V of a tile, then the next tile's): with the sixteen loads interleaved by the scheduler, the first
-    // tile's K came last, and the loop began every pair of tiles by waiting for everything in flight, which
-    // drained the two tiles of loads that are meant to stay in flight.
+    // them in (K, V of a tile, then the next tile's).
+    auto t_of = [&](int i) { return i < n_tiles ? (first + i * W) * kGqaTile : T; };
     __builtin_amdgcn_sched_barrier(0);
-    issue_k(std::integral_constant<int, 0>{}, n_tiles > 0 ? t_begin : T);
+    issue_k(t_of(0));
     __builtin_amdgcn_sched_barrier(0);
-    issue_v(std::integral_constant<int, 0>{}, n_tiles > 0 ? t_begin : T);
+    issue_v(t_of(0));
     __builtin_amdgcn_sched_barrier(0);
-    issue_k(std::integral_constant<int, 1>{}, n_tiles > 1 ? t_begin + kGqaTile : T);
-    __builtin_amdgcn_sched_barrier(0);
-    issue_v(std::integral_constant<int, 1>{}, n_tiles > 1 ? t_begin + kGqaTile : T);
-    __builtin_amdgcn_sched_barrier(0);
-    auto tile = [&](auto par, int i) {
-        constexpr int P = decltype(par)::value;
-        const int t0 = t_begin + i * kGqaTile;
-        const int t_next = i + 2 < n_tiles ? t0 + 2 * kGqaTile : T;   // (T: nothing is read, zeros arrive)
+
+    // Q in fixed point: n = rint(q 2^(22-e)) with 2^e above the row's largest |q|, as digits n = 65536 d0 + 256 d1 + d2,
+    // d1 and d2 in [-128, 127].  unit: what a unit of the integer score is worth before the key's scale.
+    i32x4 qd[NC][3][KS];
+    float unit[NC];
+#pragma unroll
+    for (int nc = 0; nc < NC; ++nc) {
+        unsigned amax = 0u;
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const unsigned v = qraw[nc][s][e][i];
+                    amax = max(amax, max(v & 0x7fffu, (v >> 16) & 0x7fffu));   // (bf16 magnitudes order as integers)
+                }
+        amax = max(amax, (unsigned)__shfl_xor((int)amax, 16));
+        amax = max(amax, (unsigned)__shfl_xor((int)amax, 32));
+        const int e = max((int)(amax >> 7) - 126, -60);   // |q| < 2^e (below 2^-60 the digits run out: those scores vanish)
+        unit[nc] = __builtin_amdgcn_ldexpf(1.0f, e - 22);
+        const float up = 16 * nc + l16 < G ? __builtin_amdgcn_ldexpf(1.0f, 22 - e) : 0.0f;   // (a column without a head: zeros)
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+            for (int i4 = 0; i4 < 4; ++i4) {   // four values at a time: bytes d2, d1, d0 of four words -> a word per digit
+                unsigned x[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const unsigned v = qraw[nc][s][i4 / 2][2 * (i4 % 2) + i / 2];
+                    const float f = __uint_as_float((i & 1) ? (v & 0xffff0000u) : (v << 16));
+                    // f up + 1.5 2^23 + 0x8080 rounds to the integer and leaves n + 0x8080 in the low bits: bytes
+                    // d2 + 128, d1 + 128 and d0 + 64
+                    x[i] = (__float_as_uint(fmaf(f, up, 12615808.0f)) ^ 0x8080u) - 0x400000u;
+                }
+                const unsigned a01 = __builtin_amdgcn_perm(x[1], x[0], 0x05010400u), a23 = __builtin_amdgcn_perm(x[3], x[2], 0x05010400u);
+                const unsigned b01 = __builtin_amdgcn_perm(x[1], x[0], 0x0c0c0602u), b23 = __builtin_amdgcn_perm(x[3], x[2], 0x0c0c0602u);
+                qd[nc][2][s][i4] = (int)__builtin_amdgcn_perm(a23, a01, 0x05040100u);
+                qd[nc][1][s][i4] = (int)__builtin_amdgcn_perm(a23, a01, 0x07060302u);
+                qd[nc][0][s][i4] = (int)__builtin_amdgcn_perm(b23, b01, 0x05040100u);
+            }
+    }
+
+    // K fragment of token tile i, k-step s: row 16 i + l16, bytes 64 s + 16 lq + [0,16).  V^T fragment of tile dt: the
+    // 16 lanes of a group fetch 8 rows (2 lanes a row, 8 columns each) and lane j of the group receives column j of
+    // them; the rows of group lq are the tokens its probabilities belong to: 4 lq + [0,4) and 16 + 4 lq + [0,4).
+    const int k_addr = l16 * PITCH + 16 * lq;
+    const int v_row = l16 >> 1;
+    const int v_addr = (4 * lq + (v_row & 3) + 16 * (v_row >> 2)) * PITCH + 8 * (l16 & 1);
+
+    f32x4 o[NC][DT];
+    float M[NC], lsum[NC];   // running max of this lane's head (in units of unit), this lane's part of the row sum
+#pragma unroll
+    for (int nc = 0; nc < NC; ++nc) {
+        M[nc] = kMasked;
+        lsum[nc] = 0.0f;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) o[nc][dt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+
+    for (int i = 0; i < n_tiles; ++i) {
+        const int t0 = t_of(i);
+        const int t_next = t_of(i + 1);
         if constexpr (TRAFFIC_ONLY) {
             u32x4 x = {0u, 0u, 0u, 0u};
 #pragma unroll
-            for (int n = 0; n < NP; ++n) x ^= kbuf[P][n] ^ vbuf[P][n];
-            lsum += __uint_as_float((x[0] ^ x[1] ^ x[2] ^ x[3]) & 0x3fffffffu) + sc[P];
-            issue_k(par, t_next);
-            issue_v(par, t_next);
+            for (int n = 0; n < NP; ++n) x ^= kbuf[n] ^ vbuf[n];
+            lsum[0] += __uint_as_float((x[0] ^ x[1] ^ x[2] ^ x[3]) & 0x3fffffffu) + sc;
+            issue_k(t_next);
+            issue_v(t_next);
             // (each tile is consumed and refilled on its own, as in the full kernel: without this the compiler
             // folds the two tiles of a pair into one sum and waits for both at once)
-            asm volatile("" : "+v"(lsum));
+            asm volatile("" : "+v"(lsum[0]));
             __builtin_amdgcn_sched_barrier(0);
-            return;
+            continue;
         }
 
-        stage(par, kbuf, kS, ROWLK);
-        scS[lane] = hh == 0 ? sc[P] * scale_log2e : sc[P];
-        issue_k(par, t_next);
-
-        // scores of the tile, register r of a lane = token 8 (r/4) + 4 hh + r%4, column = head l32.  The V tile
-        // is widened behind the MFMAs, which need nothing from the vector ALU while they run.
-        f32x16 acc;
+        stage(kbuf, kS);
+        scS[lane] = k_half ? sc * scale_log2e : sc;
+        issue_k(t_next);
+        i32x4 kf[2][KS];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
-        bf16x8 kf[KS];
+        for (int tt = 0; tt < 2; ++tt)
 #pragma unroll
-        for (int s2 = 0; s2 < KS; ++s2) kf[s2] = *reinterpret_cast<const bf16x8*>(kS + k_addr + 32 * s2);
-#pragma unroll
-        for (int s2 = 0; s2 < KS; ++s2) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s2], qB[s2], acc, 0, 0, 0);
+            for (int s = 0; s < KS; ++s) kf[tt][s] = *reinterpret_cast<const i32x4*>(kS + k_addr + 16 * tt * PITCH + 64 * s);
         __builtin_amdgcn_sched_barrier(0);
-        stage(par, vbuf, vS, ROWLV);
-        issue_v(par, t_next);
+        stage(vbuf, vS);
+        issue_v(t_next);
         __builtin_amdgcn_sched_barrier(0);
 
-        // softmax over the tile's tokens (the K scale multiplies the fp32 score; tokens past the end are masked)
-        float u[16];
+        // scores: register r of token tile tt is token 16 tt + 4 lq + r, column = head l16 of the group
+        u32x4 pw[NC];
 #pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-            const f32x4 kf4 = *reinterpret_cast<const f32x4*>(&scS[8 * r4 + 4 * hh]);
+        for (int nc = 0; nc < NC; ++nc) {
+            i32x4 acc[2][3];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) u[4 * r4 + e] = acc[4 * r4 + e] * kf4[e];
-        }
-        if (t0 + kGqaTile > t_end) {   // the run ends inside this tile
+            for (int tt = 0; tt < 2; ++tt)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) u[r] = (t0 + 8 * (r / 4) + 4 * hh + r % 4 < t_end) ? u[r] : kMasked;
-        }
-        float umax = fmaxf(u[0], u[1]);
+                for (int p = 0; p < 3; ++p) acc[tt][p] = i32x4{0, 0, 0, 0};
 #pragma unroll
-        for (int r = 2; r < 16; r += 2) umax = fmaxf(umax, fmaxf(u[r], u[r + 1]));
-        const float m_new = fmaxf(M, half_max(umax));
-        if (__builtin_amdgcn_ballot_w64(m_new > M) != 0) {
-            const float alpha = fast_exp2(M - m_new);
+            for (int s = 0; s < KS; ++s)
 #pragma unroll
-            for (int dt = 0; dt < DT; ++dt)
+                for (int tt = 0; tt < 2; ++tt)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) o[dt][r] *= alpha;
-            lsum *= alpha;
-            M = m_new;
-        }
-        float ps0 = 0.0f, ps1 = 0.0f;
+                    for (int p = 0; p < 3; ++p) acc[tt][p] = __builtin_amdgcn_mfma_i32_16x16x64_i8(kf[tt][s], qd[nc][p][s], acc[tt][p], 0, 0, 0);
+            float u[8];
 #pragma unroll
-        for (int r = 0; r < 16; r += 2) {
-            u[r] = fast_exp2(u[r] - M);
-            u[r + 1] = fast_exp2(u[r + 1] - M);
-            ps0 += u[r];
-            ps1 += u[r + 1];
-        }
-        lsum += ps0 + ps1;
-        // the probabilities take their token's v_scale before they are rounded to bf16
-        u32x4 pw[2];
+            for (int tt = 0; tt < 2; ++tt) {
+                const f32x4 kf4 = *reinterpret_cast<const f32x4*>(&scS[16 * tt + 4 * lq]);
 #pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-            const f32x4 vf = *reinterpret_cast<const f32x4*>(&scS[32 + 8 * r4 + 4 * hh]);
-            pw[r4 >> 1][2 * (r4 & 1)] = pack_bf16x2(u[4 * r4] * vf[0], u[4 * r4 + 1] * vf[1]);
-            pw[r4 >> 1][2 * (r4 & 1) + 1] = pack_bf16x2(u[4 * r4 + 2] * vf[2], u[4 * r4 + 3] * vf[3]);
-        }
-
-        // O^T += V^T P^T: k-step u2 covers registers 8 u2 .. 8 u2 + 7 of the probabilities, i.e. tokens
-        // 16 u2 + {4 hh .. 4 hh + 3} and 16 u2 + 8 + {4 hh .. 4 hh + 3} of the tile
-#pragma unroll
-        for (int u2 = 0; u2 < 2; ++u2)
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt) {
-                const char* va = vS + v_addr[dt] + 16 * u2 * ROWLV;
-                const s16x4 lo = lds_read_tr16(reinterpret_cast<const uint16_t*>(va));
-                const s16x4 hi = lds_read_tr16(reinterpret_cast<const uint16_t*>(va + 8 * ROWLV));
-                const s16x8 av = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-                o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av),
-                                                                __builtin_bit_cast(bf16x8, pw[u2]), o[dt], 0, 0, 0);
+                for (int r = 0; r < 4; ++r) {
+                    const int hi = (acc[tt][0][r] << 8) + acc[tt][1][r];   // |hi| < 2^29
+                    u[4 * tt + r] = fmaf((float)hi, 256.0f, (float)acc[tt][2][r]) * kf4[r];
+                }
             }
-    };
-    // (tiles come in pairs without a branch between them, for the same reason: a run of an odd number of tiles ends
-    // on a tile that lies past its end, whose loads asked for nothing and whose tokens are all masked)
-    for (int i = 0; i < n_tiles; i += 2) {
-        tile(std::integral_constant<int, 0>{}, i);
-        tile(std::integral_constant<int, 1>{}, i + 1);
+            if (t0 + kGqaTile > T) {   // the sequence ends inside this tile (or before it)
+#pragma unroll
+                for (int r = 0; r < 8; ++r) u[r] = (t0 + 16 * (r / 4) + 4 * lq + r % 4 < T) ? u[r] : kMasked;
+            }
+            float umax = fmaxf(u[0], u[1]);
+#pragma unroll
+            for (int r = 2; r < 8; r += 2) umax = fmaxf(umax, fmaxf(u[r], u[r + 1]));
+            // the running max moves only when a score has passed it by 2^8 (always on a wave's first tile)
+            if (__builtin_amdgcn_ballot_w64((umax - M[nc]) * unit[nc] > 8.0f) != 0) {
+                float m_new = fmaxf(M[nc], umax);
+                m_new = fmaxf(m_new, __shfl_xor(m_new, 16));
+                m_new = fmaxf(m_new, __shfl_xor(m_new, 32));
+                const float alpha = fast_exp2((M[nc] - m_new) * unit[nc]);
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt) o[nc][dt] *= alpha;
+                lsum[nc] *= alpha;
+                M[nc] = m_new;
+            }
+            const float mu = M[nc] * unit[nc];
+            float ps0 = 0.0f, ps1 = 0.0f;
+#pragma unroll
+            for (int r = 0; r < 8; r += 2) {
+                u[r] = fast_exp2(fmaf(u[r], unit[nc], -mu));
+                u[r + 1] = fast_exp2(fmaf(u[r + 1], unit[nc], -mu));
+                ps0 += u[r];
+                ps1 += u[r + 1];
+            }
+            lsum[nc] += ps0 + ps1;
+            // the probabilities take their token's v_scale before they are rounded to bf16
+#pragma unroll
+            for (int tt = 0; tt < 2; ++tt) {
+                const f32x4 vf = *reinterpret_cast<const f32x4*>(&scS[32 + 16 * tt + 4 * lq]);
+                pw[nc][2 * tt] = pack_bf16x2(u[4 * tt] * vf[0], u[4 * tt + 1] * vf[1]);
+                pw[nc][2 * tt + 1] = pack_bf16x2(u[4 * tt + 2] * vf[2], u[4 * tt + 3] * vf[3]);
+            }
+        }
+
+        // O^T += V^T P^T over the tile's 32 tokens: element j of lane group lq is token 4 lq + j (j < 4) or 16 + 4 lq + j - 4
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) {
+            const i32x2 vw = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_i32x2*)(vS + v_addr + 16 * dt));
+            const bf16x8 va = widen8(vw);
+#pragma unroll
+            for (int nc = 0; nc < NC; ++nc)
+                o[nc][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, __builtin_bit_cast(bf16x8, pw[nc]), o[nc][dt], 0, 0, 0);
+        }
     }
 
-    // this wave's split: register r of tile dt is d = 32 dt + 8 (r/4) + 4 hh + r%4 of head l32
-    if (l32 < G) {
-        const long idx = ((long)b * Hq + (long)g * G + l32) * n_split + sp;
-        float* dst = ws_acc + idx * D + 4 * hh;
+    // Merge the waves: register r of tile dt is d = 16 dt + 4 lq + r of head l16.  A wave's record: 16 NC maxima (log2
+    // units), as many sums, then the accumulators, a row of OPITCH floats per head (over its own tiles, which are dead).
+    float* const rec = reinterpret_cast<float*>(kS);
+#pragma unroll
+    for (int nc = 0; nc < NC; ++nc) {
+        float L = lsum[nc];
+        L += __shfl_xor(L, 16);
+        L += __shfl_xor(L, 32);
+        if (lq == 0) {
+            rec[16 * nc + l16] = M[nc] * unit[nc];
+            rec[16 * NC + 16 * nc + l16] = L;
+        }
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
+            *reinterpret_cast<f32x4*>(rec + 32 * NC + (16 * nc + l16) * OPITCH + 16 * dt + 4 * lq) = o[nc][dt];
+    }
+    __syncthreads();
+    for (int x = threadIdx.x; x < G * D; x += 64 * W) {
+        const int h = x / D, d = x % D;
+        float m[W], top = kMasked;
 #pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4) {
-                const f32x4 ov = {o[dt][4 * r4], o[dt][4 * r4 + 1], o[dt][4 * r4 + 2], o[dt][4 * r4 + 3]};
-                *reinterpret_cast<f32x4*>(dst + 32 * dt + 8 * r4) = ov;
+        for (int ww = 0; ww < W; ++ww) {
+            m[ww] = reinterpret_cast<const float*>(smem + ww * WAVE_BYTES)[h];
+            top = ww == 0 ? m[ww] : fmaxf(top, m[ww]);
+        }
+        float L = 0.0f, acc = 0.0f;
+#pragma unroll
+        for (int ww = 0; ww < W; ++ww) {
+            const float* r = reinterpret_cast<const float*>(smem + ww * WAVE_BYTES);
+            const float f = fast_exp2(m[ww] - top);   // a wave without tiles has L = 0 and an accumulator of zeros
+            L = fmaf(f, r[16 * NC + h], L);
+            acc = fmaf(f, r[32 * NC + h * OPITCH + d], acc);
+        }
+        const long bh = (long)b * Hq + (long)g * G + h;
+        if (n_split == 1) {
+            out[bh * D + d] = (uint16_t)(pack_bf16x2(acc / L, 0.0f) & 0xffffu);
+        } else {
+            const long idx = bh * n_split + sp;
+            ws_acc[idx * D + d] = acc;
+            if (d == 0) {
+                ws_ml[idx * 2] = top;
+                ws_ml[idx * 2 + 1] = L;
             }
-        const float L = half_sum(lsum);
-        if (hh == 0) {
-            ws_ml[idx * 2] = M;
-            ws_ml[idx * 2 + 1] = L;
         }
     }
 }
 
-// One wave streams tokens_per_wave tokens (a multiple of the tile), a workgroup kGqaWaves such runs, and k
-// workgroups share one (batch, KV head).  A compute unit holds eight waves (230 VGPRs: two per SIMD), the chip 2048:
-// k is chosen so that (rounds of resident workgroups) x (tiles per wave + a wave's set-up, about two tiles' worth) is
-// smallest, which avoids a last round that is nearly empty and runs that differ in length.
-int decode_gqa_tokens_per_wave(int kv_len, long n_bg) {
-    const long tiles = ((long)kv_len + kGqaTile - 1) / kGqaTile;
-    long best_k = 1, best_cost = -1;
-    const long resident = 2048 / kGqaWaves;   // workgroups the chip holds at a time
-    for (long k = 1; k <= 64 / kGqaWaves; ++k) {
-        const long per_wave = (tiles + kGqaWaves * k - 1) / (kGqaWaves * k);
-        const long rounds = (n_bg * k + resident - 1) / resident;
-        const long cost = rounds * (per_wave + 2);
-        if (best_cost < 0 || cost < best_cost) {
-            best_cost = cost;
-            best_k = k;
+// Splits of the key axis and waves per workgroup, by the model of decode.hip's plan with this kernel's constants (from a
+// sweep of 16 row counts, 8 to 1024, by 12 lengths, 128 to 32768, K and V cold): the cache at 6.6 TB/s, or the fullest
+// compute unit's tokens at 5.9 ns each (7 where it holds several workgroups; 4.2 and 5 with 64 codes a token), the longer
+// of the two and a fifth of the shorter, and 5 us and
+// 40 ns a split for the combine launch.  Eight waves where a compute unit has at most one workgroup, four where the grid fills the
+// chip.  (8 rows at T=32768: 30.6 us before, on 512 waves, now 19.2; 128 rows at T=8192: 52.9 before, now 45.3 with 1024
+// waves in 256 workgroups, where 2048 waves take 49; both with the combine launch.)
+struct GqaPlan {
+    int waves, n_split;
+};
+static GqaPlan gqa_plan(int kv_len, long n_bg, int head_dim) {
+    const long n_tiles = ((long)kv_len + kGqaTile - 1) / kGqaTile;
+    const double stream_ns = (double)kv_len * n_bg * (2 * head_dim + 8) / 6600.0;
+    int best = 1;
+    double best_ns = 0.0;
+    for (int s : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256}) {
+        if (s > 1 && s * 4 > n_tiles) break;
+        const long per_wg = (n_tiles + s - 1) / s, rounds = (n_bg * s + 255) / 256;
+        const double ns_token = head_dim == 128 ? (rounds > 1 ? 7.0 : 5.9) : (rounds > 1 ? 5.0 : 4.2);
+        const double busy_ns = (double)(rounds * per_wg * kGqaTile) * ns_token;
+        const double longer = busy_ns > stream_ns ? busy_ns : stream_ns, shorter = busy_ns > stream_ns ? stream_ns : busy_ns;
+        const double ns = longer + 0.2 * shorter + (s > 1 ? 5000.0 + 40.0 * s : 0.0);
+        if (s == 1 || ns < best_ns) {
+            best_ns = ns;
+            best = s;
         }
-        if (per_wave == 1) break;
     }
-    const long per_wave = (tiles + kGqaWaves * best_k - 1) / (kGqaWaves * best_k);
-    return (int)(per_wave * kGqaTile);
+    return GqaPlan{n_bg * best < 240 ? 8 : 4, best};
 }
 
-int decode_gqa_num_splits(int kv_len, long n_bg) {
-    const int tpw = decode_gqa_tokens_per_wave(kv_len, n_bg);
-    const int waves = (kv_len + tpw - 1) / tpw;
-    return (waves + kGqaWaves - 1) / kGqaWaves * kGqaWaves;   // whole workgroups; a wave past the end writes an empty split
-}
+int decode_gqa_num_splits(int kv_len, long n_bg, int head_dim) { return gqa_plan(kv_len, n_bg, head_dim).n_split; }
 
 hipError_t launch_decode_gqa_split(const DecodeArgs& a, float* ws_acc, float* ws_ml, int n_split, hipStream_t stream,
                                    bool traffic_only) {
-    const long n_bg = (long)a.batch * a.kv_heads;
-    const int tpw = decode_gqa_tokens_per_wave(a.kv_len, n_bg);
+    const GqaPlan plan = gqa_plan(a.kv_len, (long)a.batch * a.kv_heads, a.head_dim);
     const float scale_log2e = a.softmax_scale * kLog2e;
-    dim3 grid((unsigned)(n_split / kGqaWaves), (unsigned)a.kv_heads, (unsigned)a.batch);
-    if (traffic_only) {
-        if (a.head_dim == 128)
-            hipLaunchKernelGGL((slim_decode_int8_gqa_kernel<128, true>), grid, dim3(64 * kGqaWaves), 0, stream,
-                               (const uint16_t*)a.q, a.k_codes, a.k_scale, a.v_codes, a.v_scale, ws_acc, ws_ml, a.kv_lens,
-                               a.q_heads, a.kv_heads, a.kv_len, n_split, tpw, scale_log2e);
-        else
-            hipLaunchKernelGGL((slim_decode_int8_gqa_kernel<64, true>), grid, dim3(64 * kGqaWaves), 0, stream,
-                               (const uint16_t*)a.q, a.k_codes, a.k_scale, a.v_codes, a.v_scale, ws_acc, ws_ml, a.kv_lens,
-                               a.q_heads, a.kv_heads, a.kv_len, n_split, tpw, scale_log2e);
+    const dim3 grid((unsigned)n_split, (unsigned)a.kv_heads, (unsigned)a.batch);
+    auto launch = [&](auto d_c, auto w_c, auto nc_c, auto traffic_c) {
+        constexpr int D = decltype(d_c)::value, W = decltype(w_c)::value, NC = decltype(nc_c)::value;
+        hipLaunchKernelGGL((slim_decode_int8_gqa_kernel<D, W, NC, decltype(traffic_c)::value>), grid, dim3(64 * W), 0, stream,
+                           (const uint16_t*)a.q, a.k_codes, a.k_scale, a.v_codes, a.v_scale, (uint16_t*)a.out, ws_acc, ws_ml,
+                           a.kv_lens, a.q_heads, a.kv_heads, a.kv_len, n_split, scale_log2e);
         return hipGetLastError();
-    }
-    if (a.head_dim == 128)
-        hipLaunchKernelGGL(slim_decode_int8_gqa_kernel<128>, grid, dim3(64 * kGqaWaves), 0, stream,
-                           (const uint16_t*)a.q, a.k_codes, a.k_scale, a.v_codes, a.v_scale, ws_acc, ws_ml, a.kv_lens,
-                           a.q_heads, a.kv_heads, a.kv_len, n_split, tpw, scale_log2e);
-    else
-        hipLaunchKernelGGL(slim_decode_int8_gqa_kernel<64>, grid, dim3(64 * kGqaWaves), 0, stream,
-                           (const uint16_t*)a.q, a.k_codes, a.k_scale, a.v_codes, a.v_scale, ws_acc, ws_ml, a.kv_lens,
-                           a.q_heads, a.kv_heads, a.kv_len, n_split, tpw, scale_log2e);
-    return hipGetLastError();
+    };
+    auto pick = [&](auto d_c) {
+        using std::integral_constant;
+        constexpr integral_constant<int, 4> w4{};
+        constexpr integral_constant<int, 1> one{};
+        if (traffic_only) return plan.waves == 8 ? launch(d_c, integral_constant<int, 8>{}, one, std::true_type{}) : launch(d_c, w4, one, std::true_type{});
+        if (a.q_heads / a.kv_heads > 16) return launch(d_c, w4, integral_constant<int, 2>{}, std::false_type{});
+        return plan.waves == 8 ? launch(d_c, integral_constant<int, 8>{}, one, std::false_type{}) : launch(d_c, w4, one, std::false_type{});
+    };
+    return a.head_dim == 128 ? pick(std::integral_constant<int, 128>{}) : pick(std::integral_constant<int, 64>{});
 }
 
 }  // namespace slim

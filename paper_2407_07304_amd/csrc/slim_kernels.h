@@ -48,11 +48,10 @@ struct DecodeArgs {
     int batch, q_heads, kv_heads, kv_len, head_dim;
     float softmax_scale;
 };
-// Grouped-query variant (2 to 32 query heads per KV head): one wave streams a token run of one (batch, KV
-// head) for all its query heads; every wave is a split.  n_bg = batch * kv_heads.
+// Grouped-query variant (2 to 32 query heads per KV head): a workgroup sweeps a run of tokens of one (batch, KV head)
+// for all its query heads and is a split.  n_bg = batch * kv_heads.
 bool decode_uses_gqa_kernel(int q_heads, int kv_heads);
-int decode_gqa_tokens_per_wave(int kv_len, long n_bg);
-int decode_gqa_num_splits(int kv_len, long n_bg);
+int decode_gqa_num_splits(int kv_len, long n_bg, int head_dim);
 // traffic_only: the measurement form (the kernel's loads without its arithmetic; what it writes is meaningless)
 hipError_t launch_decode_gqa_split(const DecodeArgs& a, float* ws_acc, float* ws_ml, int n_split, hipStream_t stream,
                                    bool traffic_only = false);

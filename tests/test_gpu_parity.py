@@ -466,6 +466,43 @@ def test_decode_grouped_all_zero_tokens_and_huge_scores(sa, oracle):
         check_close(host_f64(out), oracle.attn(q, kc, vc, scale, False, k_scale=ks, v_scale=vs), "grouped decode, scale %g" % scale)
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,T,D", [
+    # grouped heads: 16 to a column group and one past it, the end of a 32-token tile, waves without a tile
+    (1, 16, 1, 31, 128), (1, 17, 1, 33, 128), (2, 32, 2, 64, 64), (1, 31, 1, 95, 64), (5, 6, 2, 257, 128),
+    # eight- and four-wave workgroups, one split and several, more than a combine chunk of them
+    (1, 8, 1, 9000, 128), (1, 4, 2, 20001, 64), (60, 16, 4, 700, 128), (60, 16, 4, 300, 64), (1, 20, 1, 3000, 128),
+    # one head per KV head: the same edges (64-token chunks)
+    (1, 1, 1, 30000, 128), (3, 1, 1, 4097, 64), (20, 8, 8, 513, 128), (70, 8, 8, 520, 64), (1, 8, 8, 1537, 128)])
+def test_decode_plan_edges(sa, oracle, B, Hq, Hkv, T, D):
+    print("decode plan edges", B, Hq, Hkv, T, D, flush=True)
+    _decode_case(sa, oracle, B, Hq, Hkv, T, D, seed=T + D + Hq)
+
+
+@pytest.mark.parametrize("D,Hq", [(128, 8), (64, 5)])
+def test_decode_grouped_queries_of_mixed_magnitude(sa, oracle, D, Hq):
+    # the grouped kernel holds a query row in fixed point below its largest value: rows whose values span the range of
+    # that form, tiny and huge rows, a row of zeros, and a cache whose scales make up for the row's magnitude
+    rng = np.random.default_rng(7 + D)
+    B, Hkv, T = 1, 1, 500
+    x = rng.standard_normal((B, Hq, 1, D)).astype(np.float32)
+    x[0, 0] *= np.exp2(-rng.integers(0, 14, D)).astype(np.float32)
+    x[0, 1] *= np.float32(2.0 ** -30)
+    x[0, 2] *= np.float32(2.0 ** 40)
+    x[0, 3] = 0.0
+    x[0, 4, 0, 1:] = 0.0
+    q = (x.view(np.uint32) >> 16).astype(np.uint16)
+    kc, _ = oracle.kv_quant_int8(normal_bf16(rng, (B, Hkv, T, D)))
+    vc, vs = oracle.kv_quant_int8(normal_bf16(rng, (B, Hkv, T, D)))
+    for k_mag in (2.0 ** -45, 2.0 ** -6, 2.0 ** 24):
+        ks = (k_mag * (0.5 + rng.random((B, Hkv, T)))).astype(np.float32)
+        # (a row whose scores would pass the fp32 range of exp2's argument is not what is asked here)
+        rows = [h for h in range(Hq) if np.abs(x[0, h]).max() * k_mag < 2.0 ** 4]
+        out = sa.slim_attn_decode_int8(dev_bf16(q), dev(kc), dev(ks), dev(vc), dev(vs), 1.0 / math.sqrt(D))
+        torch.cuda.synchronize()
+        want = oracle.attn(q, kc, vc, 1.0 / math.sqrt(D), False, k_scale=ks, v_scale=vs)
+        check_close(host_f64(out)[:, rows], want[:, rows], "mixed magnitudes, k scale %g" % k_mag)
+
+
 @pytest.mark.parametrize("D,Hq,Hkv", [(128, 4, 4), (128, 16, 2), (64, 8, 8), (64, 6, 3)])
 def test_decode_per_sequence_lengths(sa, oracle, D, Hq, Hkv):
     # every sequence attends to its own number of cached tokens (one tile, ragged tails, the whole allocation);
