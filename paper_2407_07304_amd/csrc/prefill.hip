@@ -76,9 +76,17 @@ using int_c = std::integral_constant<int, N>;
 // of this kernel: MODE 1 computes the scores and keeps only the row maxima (one per row and wave group, written
 // to p.row_max), MODE 2 computes them again, exponentiates against those final maxima and multiplies by V:
 // no running maximum, no rescaling of the accumulator, 1.5 times the MFMAs.  MODE 0 is the kernel proper.
-template <int D, bool KV_I8, bool OUT_F32, int MODE = 0>
+//
+// WIDE (INT8 K/V): row blocks of 256 rows.  The eight waves own 32 rows each and every wave goes through all key tiles,
+// so a staged tile meets twice the query rows: the two groups stay in opposite phases, but on the same tile one phase
+// apart, group 1 stages K and group 0 V (half the widening per matrix phase), and there is nothing to merge at the end.
+// See launch_prefill for when it is taken and what it gives.
+template <int D, bool KV_I8, bool OUT_F32, int MODE = 0, bool WIDE = false>
 __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const PrefillParams p) {
     static_assert(!(MODE != 0 && KV_I8), "the two-sweep variant exists for bf16 K/V only");
+    static_assert(!WIDE || KV_I8, "the wide form stages through registers");
+    constexpr int BR = WIDE ? 2 * kBR : kBR;   // query rows per row block
+    constexpr int RK = WIDE ? 2 : kRingK, RV = WIDE ? 2 : kRingV;   // ring depth (see the phases for why two will do)
     constexpr bool stats_only = MODE == 1;
     constexpr int KS = D / 16;       // k-steps of the score MFMA
     constexpr int DT = D / 32;       // 32-row tiles of O^T
@@ -94,9 +102,10 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
     constexpr int TILEB = TILEBK;             // (bf16: both tensors)
     constexpr int CPL = ROWL / 16;            // 16-byte chunks per LDS row: 16 or 8
     constexpr int RPL = 256 / ROWL;           // rows per 256-byte line of banks: 1 or 2
-    constexpr int K_BYTES = kRingK * TILEBK, V_BYTES = kRingV * TILEBV;
+    constexpr int K_BYTES = RK * TILEBK, V_BYTES = RV * TILEBV;
     constexpr int NV = DT / 2 * 4 + 1;        // f32x4 vectors a wave hands to its partner at the merge
-    constexpr int MERGE_BYTES = 8 * NV * 64 * 16;
+    constexpr int OPITCH = (OUT_F32 ? 4 * D : 2 * D) + 16;   // output tile row pitch: spreads the column-wise writes over the banks
+    constexpr int MERGE_BYTES = WIDE ? BR * OPITCH : 8 * NV * 64 * 16;
     // (the merge buffer takes the place of the ring, which is quiet by then)
     constexpr int RING_BYTES = K_BYTES + V_BYTES > MERGE_BYTES ? K_BYTES + V_BYTES : MERGE_BYTES;
     auto swz_k = [](int r) { return KV_I8 ? 0 : (r / RPL) & (CPL - 1); };
@@ -131,6 +140,7 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
 
     // wave index as a scalar: everything derived from it (group, row group, last tile) stays uniform
     const int tid = (int)__builtin_amdgcn_workitem_id_x(), w8 = __builtin_amdgcn_readfirstlane(tid >> 6), grp = w8 >> 2, w = w8 & 3;
+    const int rg = WIDE ? w8 : w;   // this wave's 32 rows of the block
     const int l = tid & 63, l32 = l & 31, hh = l >> 5;
     const long kvrow0 = ((long)b * p.Hkv + g) * (long)S;
 
@@ -153,7 +163,7 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
     }
     auto request_q = [&](int rb_q) {
         if constexpr (!Q_LDS) {
-            const int q_row = min(rb_q * kBR + 32 * w + l32, S - 1);
+            const int q_row = min(rb_q * BR + 32 * rg + l32, S - 1);
             const uint16_t* qp = p.q + (((long)b * p.Hq + h) * S + q_row) * (long)D + 8 * hh;
 #pragma unroll
             for (int s = 0; s < KS; ++s) qreg[s] = *reinterpret_cast<const bf16x8*>(qp + 16 * s);
@@ -296,8 +306,8 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
             }
         }
     };
-    auto store_s = [&](int slot, float s) {
-        if (has_s) scS[slot * (2 * kBC) + (s_is_k ? 0 : kBC) + l32] = s_is_k ? s * c : s;
+    auto store_s = [&](int slot, float s, bool wanted) {
+        if (wanted) scS[slot * (2 * kBC) + (s_is_k ? 0 : kBC) + l32] = s_is_k ? s * c : s;
     };
     struct Stage {
         u32x4 k[NP], v[NP];
@@ -322,12 +332,12 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
         const int rb = pass == 0 ? x : p.n_rb - 1 - x;
         if (pass == 1 && rb == x) break;   // the middle row block of an odd count
         const bool has_next = pass == 0 && x != p.n_rb - 1 - x;
-        const int i0 = rb * kBR;
-        const int my_q = i0 + 32 * w + l32;             // this lane's query row (may be >= S in the last block)
-        const int wave_q_lo = i0 + 32 * w;
-        const int kend = p.causal ? min(S, i0 + kBR) : S;
+        const int i0 = rb * BR;
+        const int my_q = i0 + 32 * rg + l32;             // this lane's query row (may be >= S in the last block)
+        const int wave_q_lo = i0 + 32 * rg;
+        const int kend = p.causal ? min(S, i0 + BR) : S;
         const int n_tiles = (kend + kBC - 1) / kBC;
-        const int last_phase = 2 * ((n_tiles + 1) / 2);   // phases 0..last_phase, one barrier each
+        const int last_phase = WIDE ? 2 * n_tiles : 2 * ((n_tiles + 1) / 2);   // phases 0..last_phase, one barrier each
         // last tile of this row group: its diagonal under the causal mask, else the tail of the key axis
         // (always taken through the masked path); -1 if the row group lies past the sequence
         const int t_last = wave_q_lo >= S ? -1 : (p.causal ? min(n_tiles - 1, wave_q_lo / kBC) : n_tiles - 1);
@@ -366,6 +376,28 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
                 }
             }
             __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): this wave's requests have landed in LDS
+        } else if constexpr (WIDE) {
+            // LDS: K tiles 0 and 1, V tiles 0 and 1 (a group stages its number's); registers: what each group stores in its
+            // first matrix phase (group 1 in phase 0: K 2; group 0 in phase 1: V 2).  Addresses as below: put together here.
+            u32x4 ta[NP], td[NP];
+            float sa = 0.0f;
+            unsigned off_now[NP];
+#pragma unroll
+            for (int i = 0; i < NP; ++i) {
+                off_now[i] = p_off[i];
+                asm volatile("" : "+v"(off_now[i]));
+            }
+            int l32_now = l32, w_now = w;
+            asm volatile("" : "+v"(l32_now));
+            asm volatile("" : "+s"(w_now));
+            load_tile_at(krs, grp, ta, off_now);
+            load_tile_at(vrs, grp, td, off_now);
+            load_s_at(grp, sa, l32_now, w_now >= 2);
+            load_tile_at(grp == 1 ? krs : vrs, 2, sg.k, off_now);
+            load_s_at(2, sg.s, l32_now, w_now == 2 + grp);
+            store_tile(grp * TILEBK, p_kdst, ta);
+            store_tile(grp * TILEBV, p_vdst, td);
+            store_s(grp, sa, has_s);
         } else {
             // LDS: K tiles 0..4, V tiles 0..2 (group 0: K 0, 2, 4, V 0, 2; group 1: K 1, 3, V 1); registers: what
             // each group stores in its first matrix phase (group 1 in phase 0: K 5, V 3; group 0 in phase 1: K 6, V 4)
@@ -402,11 +434,11 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
             store_tile(grp * TILEBK, p_kdst, ta);
             store_tile((2 + grp) * TILEBK, p_kdst, tb);
             store_tile(grp * TILEBV, p_vdst, td);
-            store_s(grp, sa);
-            store_s(2 + grp, sb);
+            store_s(grp, sa, has_s);
+            store_s(2 + grp, sb, has_s);
             store_tile(4 * TILEBK, p_kdst, tc);
             store_tile(2 * TILEBV, p_vdst, te);
-            store_s(4, sc3);
+            store_s(4, sc3, has_s);
         }
         __syncthreads();
         read_q();
@@ -556,7 +588,8 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
                 } else {
                     // (MODE 2: the running maximum starts at the final one, so the overflow watch never
                     // fires and the masked tile's rescale is by one)
-                    softmax(phi & (kRingK - 1), phi, st, pw);
+                    const int t = WIDE ? (phi - G) >> 1 : phi;
+                    softmax(t & (kRingK - 1), t, st, pw);
                 }
             } else {
                 // Matrix phase of tile t = phi - 1: its P V MFMAs and the score MFMAs of tile t + 2, always all
@@ -565,8 +598,13 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
                 // right after the MFMA that consumed it, with the fragment the next matrix phase of this wave
                 // needs (K tile phi+3, V tile phi+1): the LDS reads, and the ring traffic, are issued in the
                 // shadow of the MFMAs.  (The fences keep the issue order as written.)
-                const int k_rd = ((phi + 3) & (kRingK - 1)) * TILEBK;
-                constexpr int v_rd = ((P4 + 1) & 3) * TILEBV;
+                // WIDE: tile t = (phi - 1) / 2 of group 0, phi / 2 - 1 of group 1; next are K tile t + 2 and V tile t + 1.
+                // Two slots a tensor will do: K tile u is read in phases 2u - 3 and 2u - 2 (by group 0, then 1) and
+                // group 1 stores it in phase 2u - 4, when K tile u - 2 was read for the last time two phases ago; V tile
+                // u is read in phases 2u - 1 and 2u, and group 0 stores it in phase 2u - 3, one after V tile u - 2's last.
+                constexpr int T2 = G == 0 ? (P4 >> 1) & 1 : ((P4 >> 1) + 1) & 1;   // WIDE: t's parity
+                const int k_rd = WIDE ? T2 * TILEBK : ((phi + 3) & (kRingK - 1)) * TILEBK;
+                constexpr int v_rd = WIDE ? (1 - T2) * TILEBV : ((P4 + 1) & 3) * TILEBV;
                 // the wave that feeds the matrix pipe goes first: without this the older wave of the SIMD wins
                 // the issue port whatever it is doing, and the matrix phases of group 1 run 30 % longer
                 __builtin_amdgcn_s_setprio(3);
@@ -610,11 +648,19 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
-                if constexpr (KV_I8) {
+                if constexpr (WIDE) {
+                    if constexpr (G == 1) {   // the pieces loaded two phases ago go to K tile phi / 2 + 2
+                        store_tile(((P4 >> 1) & 1) * TILEBK, p_kdst, sg.k);
+                        store_s(((phi >> 1) + 2) & (kRingK - 1), sg.s, w == 3);
+                    } else {                  // or to V tile (phi + 3) / 2
+                        store_tile((((P4 + 3) >> 1) & 1) * TILEBV, p_vdst, sg.k);
+                        store_s(((phi + 3) >> 1) & (kRingK - 1), sg.s, w == 2);
+                    }
+                } else if constexpr (KV_I8) {
                     // the pieces loaded two phases ago go to K tile phi+5 and V tile phi+3
                     store_tile(((phi + 5) & (kRingK - 1)) * TILEBK, p_kdst, sg.k);
                     store_tile(((P4 + 3) & 3) * TILEBV, p_vdst, sg.v);
-                    store_s((phi + 5) & (kRingK - 1), sg.s);
+                    store_s((phi + 5) & (kRingK - 1), sg.s, has_s);
                 }
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -635,6 +681,10 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
                 if constexpr (!KV_I8) {
                     // what this wave requested in its previous matrix phase is read from the next phase on
                     __builtin_amdgcn_s_waitcnt(0x0f70 | REQ);   // vmcnt(REQ), see the invariant above
+                } else if constexpr (WIDE) {
+                    const int u = G == 1 ? (phi >> 1) + 3 : (phi + 5) >> 1;
+                    load_tile(G == 1 ? krs : vrs, u, sg.k);
+                    load_s_at(u, sg.s, l32, w == 2 + G);
                 } else {
                     load_tile(krs, phi + 7, sg.k);
                     load_tile(vrs, phi + 5, sg.v);
@@ -655,7 +705,7 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
             constexpr int G = decltype(grp_c)::value;
             // Group 0 starts with the scores of tile 0 and then reads the operands of its matrix phase 1 (K
             // tile 2, V tile 0); group 1 reads those of its matrix phase 0 (K tile 1; there is no tile -1,
-            // and nothing but zeros may meet its zero probabilities).
+            // and nothing but zeros may meet its zero probabilities).  (WIDE: K tile 1 and K tile 0.)
             if (G == 0) {
 #pragma unroll
                 for (int s = 0; s < KS; ++s) fetch_k1(s, 0);
@@ -665,7 +715,7 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
                 for (int s = 0; s < KS; ++s) score_mfma(s, st);
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int s = 0; s < KS; ++s) fetch_k1(s, 2 * TILEBK);
+                for (int s = 0; s < KS; ++s) fetch_k1(s, (WIDE ? 1 : 2) * TILEBK);
                 if (!stats_only) {
 #pragma unroll
                     for (int dt = 0; dt < DT; ++dt) {
@@ -675,7 +725,7 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
                 }
             } else {
 #pragma unroll
-                for (int s = 0; s < KS; ++s) fetch_k1(s, TILEBK);
+                for (int s = 0; s < KS; ++s) fetch_k1(s, WIDE ? 0 : TILEBK);
 #pragma unroll
                 for (int u = 0; u < 2; ++u)
 #pragma unroll
@@ -717,6 +767,37 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
         // and stores of that shape (64 lanes, 32 rows, 8 or 16 bytes each) are taken lane by lane by the memory
         // pipe and land as partial lines.  The tile is put together in the merge records' place (once every wave
         // has read its partner's) and leaves as whole rows, 64 consecutive 16-byte pieces per instruction.
+        constexpr int OB = OUT_F32 ? 4 * D : 2 * D;   // bytes per output row
+        static_assert(BR * OPITCH <= RING_BYTES, "the output tile fits where the ring was");
+        auto put_tile = [&](const f32x16& ok, int dt) {   // register r of tile dt is d = 32 dt + 8 (r/4) + 4 hh + r%4
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4) {
+                const int d = 32 * dt + 8 * r4 + 4 * hh;
+                char* at = smem + (32 * rg + l32) * OPITCH;
+                if (OUT_F32) {
+                    const f32x4 ov = {ok[4 * r4], ok[4 * r4 + 1], ok[4 * r4 + 2], ok[4 * r4 + 3]};
+                    *reinterpret_cast<f32x4*>(at + 4 * d) = ov;
+                } else {
+                    u32x2 ov;
+                    ov[0] = pack_bf16x2(ok[4 * r4], ok[4 * r4 + 1]);
+                    ov[1] = pack_bf16x2(ok[4 * r4 + 2], ok[4 * r4 + 3]);
+                    *reinterpret_cast<u32x2*>(at + 2 * d) = ov;
+                }
+            }
+        };
+        auto copy_out = [&]() {
+            constexpr int PPR = OB / 16;                           // 16-byte pieces per row
+            constexpr int NST = BR * PPR / kPrefillThreads;        // pieces per thread
+            char* const obase = (char*)p.out + (((long)b * p.Hq + h) * S + i0) * (long)OB;
+#pragma unroll
+            for (int i = 0; i < NST; ++i) {
+                // (the thread id, counted afresh: keeping it alive through the phase loops costs spills)
+                const int lane_now = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+                const int pid = (w8 * 64 + lane_now) + kPrefillThreads * i, row = pid / PPR, col = pid % PPR;
+                const u32x4 piece = *reinterpret_cast<const u32x4*>(smem + row * OPITCH + col * 16);
+                if (i0 + row < S) *reinterpret_cast<u32x4*>(obase + (long)row * OB + col * 16) = piece;
+            }
+        };
         auto finish = [&](auto grp_c) {
             constexpr int G = decltype(grp_c)::value;
             constexpr int HALF = DT / 2;
@@ -749,41 +830,24 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
 #pragma unroll
                     for (int e = 0; e < 4; ++e) o[keep0 + dt][4 * r4 + e] = fmaf(o[keep0 + dt][4 * r4 + e], s_me, ot[e] * s_ot);
                 }
-            constexpr int OB = OUT_F32 ? 4 * D : 2 * D;   // bytes per output row
-            constexpr int OPITCH = OB + 16;               // tile row pitch: spreads the column-wise writes over the banks
-            static_assert(kBR * OPITCH <= RING_BYTES, "the output tile fits where the ring was");
             __syncthreads();
 #pragma unroll
-            for (int dt = 0; dt < HALF; ++dt)
-#pragma unroll
-                for (int r4 = 0; r4 < 4; ++r4) {
-                    // register r of tile dt is d = 32 dt + 8 (r/4) + 4 hh + r%4
-                    const int d = 32 * (keep0 + dt) + 8 * r4 + 4 * hh;
-                    char* at = smem + (32 * w + l32) * OPITCH;
-                    const f32x16& ok = o[keep0 + dt];
-                    if (OUT_F32) {
-                        const f32x4 ov = {ok[4 * r4], ok[4 * r4 + 1], ok[4 * r4 + 2], ok[4 * r4 + 3]};
-                        *reinterpret_cast<f32x4*>(at + 4 * d) = ov;
-                    } else {
-                        u32x2 ov;
-                        ov[0] = pack_bf16x2(ok[4 * r4], ok[4 * r4 + 1]);
-                        ov[1] = pack_bf16x2(ok[4 * r4 + 2], ok[4 * r4 + 3]);
-                        *reinterpret_cast<u32x2*>(at + 2 * d) = ov;
-                    }
-                }
+            for (int dt = 0; dt < HALF; ++dt) put_tile(o[keep0 + dt], keep0 + dt);
             __syncthreads();
-            constexpr int PPR = OB / 16;                           // 16-byte pieces per row
-            constexpr int NST = kBR * PPR / kPrefillThreads;       // pieces per thread
-            char* const obase = (char*)p.out + (((long)b * p.Hq + h) * S + i0) * (long)OB;
-#pragma unroll
-            for (int i = 0; i < NST; ++i) {
-                // (the thread id, counted afresh: keeping it alive through the phase loops costs spills)
-                const int lane_now = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-                const int pid = (w8 * 64 + lane_now) + kPrefillThreads * i, row = pid / PPR, col = pid % PPR;
-                const u32x4 piece = *reinterpret_cast<const u32x4*>(smem + row * OPITCH + col * 16);
-                if (i0 + row < S) *reinterpret_cast<u32x4*>(obase + (long)row * OB + col * 16) = piece;
-            }
+            copy_out();
         };
+        if constexpr (WIDE) {   // every wave has its rows' whole result
+            const float inv = 1.0f / half_sum(lsum);
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) o[dt][r] *= inv;
+                put_tile(o[dt], dt);
+            }
+            __syncthreads();
+            copy_out();
+            continue;
+        }
         if (grp == 0) finish(int_c<0>{});
         else finish(int_c<1>{});
 
@@ -827,10 +891,10 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
     }
 }
 
-template <int D, bool KV_I8, bool OUT_F32, int MODE = 0>
+template <int D, bool KV_I8, bool OUT_F32, int MODE = 0, bool WIDE = false>
 static hipError_t launch_one(const PrefillParams& p, hipStream_t stream) {
     const unsigned grid = (unsigned)(8 * p.chunk);
-    hipLaunchKernelGGL((slim_prefill_kernel<D, KV_I8, OUT_F32, MODE>), dim3(grid), dim3(kPrefillThreads), 0,
+    hipLaunchKernelGGL((slim_prefill_kernel<D, KV_I8, OUT_F32, MODE, WIDE>), dim3(grid), dim3(kPrefillThreads), 0,
                        stream, p);
     return hipGetLastError();
 }
@@ -851,10 +915,13 @@ hipError_t launch_prefill(const PrefillArgs& a, hipStream_t stream) {
     p.Hkv = a.kv_heads;
     p.S = a.seq_len;
     p.causal = a.causal ? 1 : 0;
-    p.n_rb = (a.seq_len + kBR - 1) / kBR;
-    p.n_pair = (p.n_rb + 1) / 2;
-    p.total = a.batch * a.q_heads * p.n_pair;
-    p.chunk = (p.total + 7) / 8;
+    auto blocks_of = [&](int rows) {
+        p.n_rb = (a.seq_len + rows - 1) / rows;
+        p.n_pair = (p.n_rb + 1) / 2;
+        p.total = a.batch * a.q_heads * p.n_pair;
+        p.chunk = (p.total + 7) / 8;
+    };
+    blocks_of(kBR);
     p.scale_log2e = a.softmax_scale * kLog2e;
     p.row_max = a.row_max;
     if (a.row_max) {   // the comparison variant: bf16 K/V only (checked by the caller); two launches
@@ -862,6 +929,18 @@ hipError_t launch_prefill(const PrefillArgs& a, hipStream_t stream) {
         if (e != hipSuccess) return e;
         if (a.head_dim == 128) return a.out_f32 ? launch_one<128, false, true, 2>(p, stream) : launch_one<128, false, false, 2>(p, stream);
         return a.out_f32 ? launch_one<64, false, true, 2>(p, stream) : launch_one<64, false, false, 2>(p, stream);
+    }
+    // INT8 K/V are widened to bf16 by the workgroup that stages them, and that is a quarter of the time with row blocks of
+    // 128 rows; blocks of 256 do it half as often per query row.  They are taken when they still give most compute units
+    // a pair of them, or when one block holds the whole sequence (B=1, 32 heads, S=4096: 175 -> 149 us, S=8192 637 ->
+    // 562, 64 on 8 heads, S=16384 4.82 -> 4.24 ms; S=2048 on 32 heads would take 76 us in 128 workgroups instead of 56).
+    if (a.kv_int8) {
+        blocks_of(2 * kBR);
+        if (p.total >= 192 || a.seq_len <= 2 * kBR) {
+            if (a.head_dim == 128) return a.out_f32 ? launch_one<128, true, true, 0, true>(p, stream) : launch_one<128, true, false, 0, true>(p, stream);
+            return a.out_f32 ? launch_one<64, true, true, 0, true>(p, stream) : launch_one<64, true, false, 0, true>(p, stream);
+        }
+        blocks_of(kBR);
     }
     const int sel = (a.head_dim == 128 ? 4 : 0) | (a.kv_int8 ? 2 : 0) | (a.out_f32 ? 1 : 0);
     switch (sel) {

@@ -143,6 +143,26 @@ def test_prefill_small_shapes(sa, oracle, B, Hq, Hkv, S, D, causal, kv_int8):
     _prefill_case(sa, oracle, B, Hq, Hkv, S, D, causal, kv_int8, out_f32=(S % 2 == 1), seed=40 + S)
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,S,D,causal,out_f32", [
+    # one block of 256 rows holds the sequence: row groups of 32 that end inside, key tiles that end inside, one row
+    (1, 2, 2, 1, 128, True, False), (2, 3, 1, 97, 64, True, True), (1, 2, 2, 160, 128, False, False),
+    (1, 2, 2, 255, 128, True, True), (1, 4, 2, 256, 64, False, False),
+    # enough heads for blocks of 256 rows on longer sequences: one row past a block, uneven halves, several blocks
+    (12, 16, 16, 257, 128, True, False), (12, 16, 4, 480, 64, True, False), (16, 16, 8, 300, 128, False, True),
+    (24, 16, 16, 545, 64, True, True), (4, 64, 8, 777, 128, True, False)])
+def test_prefill_int8_wide_row_blocks(sa, oracle, B, Hq, Hkv, S, D, causal, out_f32):
+    print("prefill wide", B, Hq, Hkv, S, D, causal, out_f32, flush=True)
+    rng = np.random.default_rng(B + S + D)
+    q = normal_bf16(rng, (B, Hq, S, D))
+    kc, ks = oracle.kv_quant_int8(normal_bf16(rng, (B, Hkv, S, D)))
+    vc, vs = oracle.kv_quant_int8(normal_bf16(rng, (B, Hkv, S, D)))
+    scale = 1.0 / math.sqrt(D)
+    out = sa.slim_attn_prefill(dev_bf16(q), dev(kc), dev(vc), scale, causal, k_scale=dev(ks), v_scale=dev(vs),
+                               out_dtype=torch.float32 if out_f32 else torch.bfloat16)
+    torch.cuda.synchronize()
+    check_close(host_f64(out), oracle.attn(q, kc, vc, scale, causal, k_scale=ks, v_scale=vs), "wide row blocks")
+
+
 def test_prefill_c1_full(sa, oracle):
     w = WORKLOADS["C1"]
     print("prefill C1 full tensor", flush=True)
