@@ -34,11 +34,11 @@
 //   - A wave reads its MFMA operands from LDS one matrix phase ahead, each fragment right after
 //     the MFMA that consumed its predecessor: the reads issue in the shadow of the MFMAs and
 //     the softmax phase is pure vector work.
-//   - Under the causal mask a workgroup takes the row-block pair (x, n-1-x) one after the
-//     other, so every workgroup does the same amount of work.  The short block goes first: the
-//     key tiles it read are still in the L2 when the long block starts over at tile 0 (the other
-//     order re-fetched them: 81.5 MB of HBM traffic on B=1, H=32, S=2048 against 68.8 MB now,
-//     which is Q, K, V and O once each).
+//   - A workgroup works off a list of (row block, head) items, one after the other; the lists are
+//     dealt so that every workgroup meets about the same number of key tiles, whatever the number
+//     of row blocks and heads (pairs of a short and a long block, as before, left up to half of the
+//     last round empty: B=1, 32 heads, S=3000 took 96 us and takes 83).  Short blocks go first: the
+//     key tiles they read are still in the L2 when a longer one starts over at tile 0.
 #include <type_traits>
 
 #include "slim_common.h"
@@ -64,9 +64,32 @@ struct PrefillParams {
     float* kqs;
     int8_t* vq;
     float* vqs;
-    int Hq, Hkv, S, causal, n_rb, n_pair, total, chunk;
+    int S, causal;
+    int n_rb, n_bh, row_off;     // row blocks per head, heads in all, rows that the first block lies before row 0
+    int slots, rounds;           // workgroups per XCD, items a workgroup takes at most
+    unsigned heads, last_heads;  // heads of a batch of items, of the last batch
+    unsigned group;              // query heads per KV head
+    unsigned batch_magic, heads_magic, last_heads_magic, group_magic;   // floor(2^32 / d) of n_rb * heads and of the others
     float scale_log2e;
 };
+
+// n / d for uniform n and d with m = floor(2^32 / d) from the host: scalar arithmetic only (a division by a value known
+// at run time is some forty vector instructions long, and the first loads of an item wait for it)
+__device__ __forceinline__ unsigned div_magic(unsigned n, unsigned d, unsigned m) {
+    unsigned q = (unsigned)(((unsigned long long)n * m) >> 32);
+    if (n - q * d >= d) ++q;   // (m is low by less than one part, so q is low by at most one)
+    return q;
+}
+
+// The kernel's own arguments, as a pointer the compiler cannot see through: what is read through it is loaded where it
+// is used.  Left to itself the compiler keeps every argument in scalar registers from the start, and those run out (14
+// were spilled into the lanes of vector registers; 1 % of B=1, 32 heads, S=2048).
+typedef const __attribute__((address_space(4))) PrefillParams* KernelArgs;
+__device__ __forceinline__ KernelArgs kernel_args_now() {
+    KernelArgs a = (KernelArgs)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(a));
+    return a;
+}
 
 template <int N>
 using int_c = std::integral_constant<int, N>;
@@ -123,18 +146,33 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
     __shared__ __attribute__((aligned(16))) char smem[Q_OFF + (Q_LDS ? kBR * ROWQ : 0)];
     float* const scS = reinterpret_cast<float*>(smem + RING_BYTES);   // INT8: per slot [0,32) k_scale*c, [32,64) v_scale
 
-    // workgroup -> (batch*head, row-block pair).  Hardware deals workgroup ids round-robin over the 8
-    // XCDs, so consecutive virtual ids (which share K/V) are steered to one XCD.
-    int bh, x;
-    {
-        const int n = (int)__builtin_amdgcn_workgroup_id_x();   // the builtin, not a library call: stays a scalar
-        const int vid = (n % 8) * p.chunk + n / 8;
-        if (vid >= p.total) return;
-        bh = vid / p.n_pair;
-        x = vid % p.n_pair;
-    }
-    const int b = bh / p.Hq, h = bh % p.Hq;
-    const int g = h / (p.Hq / p.Hkv);
+    // Work items are (row block, batch*head).  They are listed in batches of `heads` heads (few enough that what an XCD
+    // works on at a time keeps its K/V in the L2), longest row block first within a batch; item j goes to XCD j % 8
+    // (workgroup ids are dealt round-robin over the XCDs), where `slots` workgroups deal the XCD's items out among
+    // themselves back and forth (0, 1, .., slots - 1, slots - 1, .., 0, 0, ..), which gives all of them about the same
+    // number of key tiles.  Where a batch is a multiple of 8 heads an XCD gets whole heads, consecutive ones: those share
+    // K/V.  A workgroup works its list off from the end: what a short block read is still in the L2 when a longer one
+    // starts over at tile 0.
+    int k = p.rounds - 1, rb, bh;
+    const int xcd = (int)__builtin_amdgcn_workgroup_id_x() & 7, slot = (int)__builtin_amdgcn_workgroup_id_x() >> 3;   // (the builtin, not a library call: stays a scalar)
+    const int n_items = (p.n_rb * p.n_bh - xcd + 7) >> 3;
+    auto index_of = [&](int round, int slots) { return round * slots + ((round & 1) ? slots - 1 - slot : slot); };
+    auto item_at = [&](int round, int& rb_i, int& bh_i) {
+        const KernelArgs a = kernel_args_now();
+        const unsigned j = (unsigned)(index_of(round, a->slots) * 8 + xcd), per_batch = (unsigned)a->n_rb * a->heads;
+        const unsigned batch = div_magic(j, per_batch, a->batch_magic), head0 = batch * a->heads, jj = j - batch * per_batch;
+        const bool last = head0 + a->heads > (unsigned)a->n_bh;
+        const unsigned heads = last ? a->last_heads : a->heads;
+        const unsigned blk = div_magic(jj, heads, last ? a->last_heads_magic : a->heads_magic), r = jj - blk * heads;
+        rb_i = a->n_rb - 1 - (int)blk;
+        // (in odd rounds the heads run backwards where that keeps a workgroup on one head: full batches, aligned rounds)
+        const unsigned per = heads >> 3, in = r >> 3;
+        const bool back = (round & 1) != 0 && !last && ((unsigned)a->slots & (per - 1)) == 0 && (per & (per - 1)) == 0;
+        bh_i = (int)(head0 + ((heads & 7) != 0 ? r : (r & 7) * per + (back ? per - 1 - in : in)));
+    };
+    if (index_of(k, p.slots) >= n_items) --k;
+    if (k < 0) return;
+    item_at(k, rb, bh);
     const int S = p.S;
     const float c = p.scale_log2e;
 
@@ -142,37 +180,34 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
     const int tid = (int)__builtin_amdgcn_workitem_id_x(), w8 = __builtin_amdgcn_readfirstlane(tid >> 6), grp = w8 >> 2, w = w8 & 3;
     const int rg = WIDE ? w8 : w;   // this wave's 32 rows of the block
     const int l = tid & 63, l32 = l & 31, hh = l >> 5;
-    const long kvrow0 = ((long)b * p.Hkv + g) * (long)S;
 
     // Q^T B-operands of a row block: lane holds row my_q, d = 16 s + 8 hh + [0,8).  With bf16 K/V the 128 rows come
     // in through LDS, by buffer loads with an LDS destination that move 64 consecutive 16-byte pieces each: loads
     // that give every lane a row of its own are taken lane by lane by the memory pipe (about 4 k cycles per row block
     // for the eight waves' fragments, with the first K and V tiles waiting behind them, against about 0.7 k this
-    // way); rows past the end of the sequence arrive as zeros.  The INT8 kernel loads its fragments straight into
+    // way); rows outside the sequence arrive as zeros.  The INT8 kernel loads its fragments straight into
     // the registers.  The first row block's are requested here, ahead of the address tables below: they come from
     // cold memory.
     bf16x8 qreg[KS];
     const unsigned smem_base = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem;
-    u32x4 qrs_raw;
-    {
-        const unsigned long long a64 = (unsigned long long)(p.q + ((long)b * p.Hq + h) * (long)S * D);
-        qrs_raw[0] = __builtin_amdgcn_readfirstlane((unsigned)a64);
-        qrs_raw[1] = __builtin_amdgcn_readfirstlane((unsigned)(a64 >> 32) & 0xffffu);
-        qrs_raw[2] = __builtin_amdgcn_readfirstlane((unsigned)S * ROWQ);
-        qrs_raw[3] = 0x00020000u;
-    }
-    auto request_q = [&](int rb_q) {
+    auto request_q = [&](int rb_q, int bh_q) {
         if constexpr (!Q_LDS) {
-            const int q_row = min(rb_q * BR + 32 * rg + l32, S - 1);
-            const uint16_t* qp = p.q + (((long)b * p.Hq + h) * S + q_row) * (long)D + 8 * hh;
+            const int q_row = min(max(rb_q * BR - p.row_off + 32 * rg + l32, 0), S - 1);
+            const uint16_t* qp = p.q + ((long)bh_q * S + q_row) * (long)D + 8 * hh;
 #pragma unroll
             for (int s = 0; s < KS; ++s) qreg[s] = *reinterpret_cast<const bf16x8*>(qp + 16 * s);
             return;
         }
+        u32x4 qrs_raw;
+        const unsigned long long a64 = (unsigned long long)(p.q + (long)bh_q * S * D);
+        qrs_raw[0] = __builtin_amdgcn_readfirstlane((unsigned)a64);
+        qrs_raw[1] = __builtin_amdgcn_readfirstlane((unsigned)(a64 >> 32) & 0xffffu);
+        qrs_raw[2] = __builtin_amdgcn_readfirstlane((unsigned)S * ROWQ);
+        qrs_raw[3] = 0x00020000u;
 #pragma unroll
         for (int j = 0; j < NQ; ++j) {
             const int r = 16 * w8 + RPQ * j + l / CPQ, pos = l % CPQ;   // row of the block, chunk position in LDS
-            const unsigned voff = (unsigned)(rb_q * kBR + r) * ROWQ + (unsigned)((pos ^ qswz(r)) * 16);
+            const unsigned voff = (unsigned)(rb_q * BR - p.row_off + r) * ROWQ + (unsigned)((pos ^ qswz(r)) * 16);
             const unsigned dst = __builtin_amdgcn_readfirstlane(smem_base + (unsigned)(Q_OFF + (16 * w8 + RPQ * j) * ROWQ));
             asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
                          :
@@ -187,17 +222,12 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
         for (int s = 0; s < KS; ++s)
             qreg[s] = *reinterpret_cast<const bf16x8*>(smem + Q_OFF + (32 * w + l32) * ROWQ + (((2 * s + hh) ^ qswz(l32)) * 16));
     };
-    request_q(x);
+    request_q(rb, bh);
     __builtin_amdgcn_sched_barrier(0);
 
     // ---- staging.  The buffer descriptors cover exactly this head's K (V) slab: pieces past the end of
     // the sequence read as zero (those keys are masked in the softmax).  A tile is staged by the four
     // waves of ONE group.
-    const char* const kslab = (const char*)p.k + kvrow0 * ROWB;
-    const char* const vslab = (const char*)p.v + kvrow0 * ROWB;
-    const __amdgpu_buffer_rsrc_t krs = __builtin_amdgcn_make_buffer_rsrc((void*)kslab, 0, (int)((unsigned)S * ROWB), 0x00020000);
-    const __amdgpu_buffer_rsrc_t vrs = __builtin_amdgcn_make_buffer_rsrc((void*)vslab, 0, (int)((unsigned)S * ROWB), 0x00020000);
-
     // bf16: one buffer load with an LDS destination moves 64 consecutive 16-byte chunk positions (RPW whole
     // rows); lane i fills position i, so it asks for the chunk the swizzle puts there.  The load is
     // written as inline assembly on purpose: the compiler then keeps no book on it, and neither its
@@ -214,7 +244,6 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
         d[3] = 0x00020000u;
         return d;
     };
-    const u32x4 krs_raw = raw_rsrc(kslab), vrs_raw = raw_rsrc(vslab);
     unsigned d_koff[NLD], d_voff[NLD];
 #pragma unroll
     for (int j = 0; j < NLD; ++j) {
@@ -262,8 +291,6 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
     // a spill, through the whole kernel).  Both halves of the wave load and store the same 32 values.
     const bool has_s = KV_I8 && w >= 2;
     const bool s_is_k = w == 3;
-    const float* const sbase = KV_I8 ? ((s_is_k ? p.ks : p.vs) + kvrow0) : nullptr;
-    const __amdgpu_buffer_rsrc_t srs = __builtin_amdgcn_make_buffer_rsrc((void*)sbase, 0, KV_I8 ? (int)((unsigned)S * 4u) : 0, 0x00020000);
     unsigned p_off[NP];
     int p_kdst[NP][2], p_vdst[NP][2];
 #pragma unroll
@@ -284,6 +311,7 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
         }
     };
     auto load_tile = [&](const __amdgpu_buffer_rsrc_t rs, int t, u32x4 (&dst)[NP]) { load_tile_at(rs, t, dst, p_off); };
+    __amdgpu_buffer_rsrc_t srs;
     auto load_s_at = [&](int t, float& dst, int lane32, bool wanted) {   // (a key past the end of the sequence gets scale 0: it is masked anyway)
         if (wanted) dst = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(srs, (t * kBC + lane32) * 4, 0, 0));
     };
@@ -328,22 +356,32 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
             v_addr[dt] = K_BYTES + rv * ROWLV + (((4 * dt + 2 * ((l >> 4) & 1) + ((l & 3) >> 1)) ^ swz_v(rv)) * 16) + 8 * (l & 1);
     }
 
-    for (int pass = 0; pass < 2; ++pass) {
-        const int rb = pass == 0 ? x : p.n_rb - 1 - x;
-        if (pass == 1 && rb == x) break;   // the middle row block of an odd count
-        const bool has_next = pass == 0 && x != p.n_rb - 1 - x;
-        const int i0 = rb * BR;
-        const int my_q = i0 + 32 * rg + l32;             // this lane's query row (may be >= S in the last block)
+    for (;;) {   // the workgroup's items
+        const int kvh = (int)div_magic((unsigned)bh, p.group, p.group_magic);   // (batch, KV head): heads per batch are a multiple of the group
+        const long kvrow0 = (long)kvh * (long)S;
+        // the buffer descriptors cover exactly this head's K (V) slab
+        const char* const kslab = (const char*)p.k + kvrow0 * ROWB;
+        const char* const vslab = (const char*)p.v + kvrow0 * ROWB;
+        const __amdgpu_buffer_rsrc_t krs = __builtin_amdgcn_make_buffer_rsrc((void*)kslab, 0, (int)((unsigned)S * ROWB), 0x00020000);
+        const __amdgpu_buffer_rsrc_t vrs = __builtin_amdgcn_make_buffer_rsrc((void*)vslab, 0, (int)((unsigned)S * ROWB), 0x00020000);
+        const u32x4 krs_raw = raw_rsrc(kslab), vrs_raw = raw_rsrc(vslab);
+        {
+            const float* const sbase = KV_I8 ? ((s_is_k ? p.ks : p.vs) + kvrow0) : nullptr;
+            srs = __builtin_amdgcn_make_buffer_rsrc((void*)sbase, 0, KV_I8 ? (int)((unsigned)S * 4u) : 0, 0x00020000);
+        }
+        const int i0 = rb * BR - p.row_off;              // (negative in a first block that starts before row 0)
+        const int my_q = i0 + 32 * rg + l32;             // this lane's query row (may lie outside [0, S))
         const int wave_q_lo = i0 + 32 * rg;
         const int kend = p.causal ? min(S, i0 + BR) : S;
         const int n_tiles = (kend + kBC - 1) / kBC;
         const int last_phase = WIDE ? 2 * n_tiles : 2 * ((n_tiles + 1) / 2);   // phases 0..last_phase, one barrier each
         // last tile of this row group: its diagonal under the causal mask, else the tail of the key axis
-        // (always taken through the masked path); -1 if the row group lies past the sequence
-        const int t_last = wave_q_lo >= S ? -1 : (p.causal ? min(n_tiles - 1, wave_q_lo / kBC) : n_tiles - 1);
+        // (always taken through the masked path); -1 if the row group lies outside the sequence
+        // (row_off is a multiple of 32: all of a row group's rows lie before row 0 or none does)
+        const int t_last = wave_q_lo >= S || wave_q_lo < 0 ? -1 : (p.causal ? min(n_tiles - 1, wave_q_lo / kBC) : n_tiles - 1);
         const int lim = p.causal ? min(my_q, S - 1) : S - 1;   // last key this lane's row may see
 
-        // (the first pass's Q was requested at the top of the kernel, the second pass's is before the first one's merge)
+        // (the first item's Q was requested at the top of the kernel, the next one's is before this one's merge)
         float M = kMasked, lsum = 0.0f;   // running max in scaled (log2) units; per-lane partial row sum
 
         // ---- prologue.  In the steady state a group stages in its matrix phase phi: bf16 requests K tile
@@ -351,12 +389,12 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
         // and V tile phi+3 from registers and loads K tile phi+7, V tile phi+5 into them.  Everything
         // earlier is staged here, all requests issued together.  Every V slot gets a tile (zeros past the
         // end of the sequence): whatever a skipped tile later leaves in place is finite data of this row
-        // block, never the previous pass's merge buffer.
+        // block, never the previous item's merge buffer.
         if constexpr (MODE == 2) {   // the final maximum of this lane's row over this group's tiles
-            M = p.row_max[((((long)b * p.Hq + h) * S + min(my_q, S - 1)) * 2) + grp];
+            M = p.row_max[(((long)bh * S + min(max(my_q, 0), S - 1)) * 2) + grp];
         }
         Stage sg;
-        __syncthreads();   // the previous pass (or sweep) has finished with the ring and the merge buffer that lies over it
+        __syncthreads();   // the previous item has finished with the ring and the merge buffer that lies over it
         if constexpr (!KV_I8) {
             if (grp == 0) {
                 dma_tile(krs_raw, d_koff, 0, 0);
@@ -404,7 +442,7 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
             u32x4 ta[NP], tb[NP], tc[NP], td[NP], te[NP];
             float sa = 0.0f, sb = 0.0f, sc3 = 0.0f;
             // The addresses of these loads are put together here, from copies the compiler cannot see through: left
-            // to itself it computes all of them ahead of the pass loop, spills them, and reloads them one by one
+            // to itself it computes all of them ahead of the item loop, spills them, and reloads them one by one
             // between the loads, and a reload is a memory access that waits, in order, for the tile loads before it
             // (eight trips to cold memory one after the other instead of one).
             unsigned off_now[NP];
@@ -755,11 +793,18 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
             asm volatile("" ::: "memory");
         }
         if constexpr (MODE == 1) {   // this sweep's result: the row maxima; nothing to merge, nothing to store
-            if (hh == 0 && my_q < S) p.row_max[((((long)b * p.Hq + h) * S + my_q) * 2) + grp] = M;
-            if (has_next) request_q(p.n_rb - 1 - x);
+            if (hh == 0 && my_q >= 0 && my_q < S) p.row_max[(((long)bh * S + my_q) * 2) + grp] = M;
+            if (--k < 0) break;
+            item_at(k, rb, bh);
+            request_q(rb, bh);
             continue;
         }
-        if (has_next) request_q(p.n_rb - 1 - x);   // in flight during the merge (every wave read its fragments of this block's Q long ago)
+        const int bh_now = bh;
+        if (--k >= 0) {
+            item_at(k, rb, bh);
+            request_q(rb, bh);
+        }
+        // (the next item's Q is in flight during the merge: every wave read its fragments of this one's long ago)
 
         // ---- merge the two groups' partial results.  A wave keeps half of its O^T tiles and hands the
         // other half, with its max and row sum, to its partner (same rows, other group) through LDS.
@@ -788,14 +833,14 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
         auto copy_out = [&]() {
             constexpr int PPR = OB / 16;                           // 16-byte pieces per row
             constexpr int NST = BR * PPR / kPrefillThreads;        // pieces per thread
-            char* const obase = (char*)p.out + (((long)b * p.Hq + h) * S + i0) * (long)OB;
+            char* const obase = (char*)kernel_args_now()->out + ((long)bh_now * S + i0) * (long)OB;
 #pragma unroll
             for (int i = 0; i < NST; ++i) {
                 // (the thread id, counted afresh: keeping it alive through the phase loops costs spills)
                 const int lane_now = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
                 const int pid = (w8 * 64 + lane_now) + kPrefillThreads * i, row = pid / PPR, col = pid % PPR;
                 const u32x4 piece = *reinterpret_cast<const u32x4*>(smem + row * OPITCH + col * 16);
-                if (i0 + row < S) *reinterpret_cast<u32x4*>(obase + (long)row * OB + col * 16) = piece;
+                if (i0 + row >= 0 && i0 + row < S) *reinterpret_cast<u32x4*>(obase + (long)row * OB + col * 16) = piece;
             }
         };
         auto finish = [&](auto grp_c) {
@@ -846,41 +891,44 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
             }
             __syncthreads();
             copy_out();
+            if (k < 0) break;
             continue;
         }
         if (grp == 0) finish(int_c<0>{});
         else finish(int_c<1>{});
 
-        // ---- the INT8 cache of this row block's own K and V rows, if asked for (section 2.2): the workgroup of
-        // a KV head's first query head quantises them, 16 rows per wave, with the quantiser's row routine.
-        // The rows were this row block's last tiles, so they come from the L2.
+        // ---- the INT8 cache of this row block's own K and V rows, if asked for (section 2.2), with the quantiser's row
+        // routine.  The rows were this row block's last tiles, so they come from the L2.  The block's pieces of a
+        // wave-wide access each are dealt to the query heads that share the KV head, and to the waves: left to the
+        // first head's workgroup alone they were 10 us of B=4, 32 on 8 heads, S=777.
         if constexpr (!KV_I8) {
-            if (p.kq != nullptr && h % (p.Hq / p.Hkv) == 0) {
+            const KernelArgs args = kernel_args_now();
+            if (args->kq != nullptr) {
                 constexpr int LPR = D / 8;          // lanes per row
                 constexpr int RPI = 64 / LPR;       // rows per wave-wide access
-                constexpr int NJ = 16 / RPI;        // accesses per wave and tensor
-                u32x4 raw[2][NJ];
+                constexpr int UNITS = kBR / RPI;    // accesses per tensor
+                const int step = (int)args->group, first = bh_now - kvh * step;
+                const int piece = l % LPR;
+                for (int u0 = first + step * w8; u0 < 2 * UNITS; u0 += 4 * 8 * step) {
+                    u32x4 raw[4];
 #pragma unroll
-                for (int ten = 0; ten < 2; ++ten) {   // all the loads first: their latencies overlap
-                    const uint16_t* src = (const uint16_t*)(ten == 0 ? p.k : p.v) + kvrow0 * D;
-#pragma unroll
-                    for (int j = 0; j < NJ; ++j) {
-                        const int row = i0 + 16 * w8 + RPI * j + l / LPR;
-                        raw[ten][j] = *reinterpret_cast<const u32x4*>(src + (long)min(row, S - 1) * D + (l % LPR) * 8);
+                    for (int j = 0; j < 4; ++j) {   // the loads first: their latencies overlap
+                        const int u = min(u0 + 8 * step * j, 2 * UNITS - 1);
+                        const uint16_t* src = (const uint16_t*)(u < UNITS ? args->k : args->v) + kvrow0 * D;
+                        const int row = i0 + RPI * (u % UNITS) + l / LPR;
+                        raw[j] = *reinterpret_cast<const u32x4*>(src + (long)min(max(row, 0), S - 1) * D + piece * 8);
                     }
-                }
 #pragma unroll
-                for (int ten = 0; ten < 2; ++ten) {
-                    int8_t* codes = (ten == 0 ? p.kq : p.vq) + kvrow0 * D;
-                    float* scales = (ten == 0 ? p.kqs : p.vqs) + kvrow0;
-#pragma unroll
-                    for (int j = 0; j < NJ; ++j) {
-                        const int row = i0 + 16 * w8 + RPI * j + l / LPR;
-                        const int piece = l % LPR;
+                    for (int j = 0; j < 4; ++j) {
+                        const int u = u0 + 8 * step * j;
+                        if (u >= 2 * UNITS) break;
+                        int8_t* codes = (u < UNITS ? args->kq : args->vq) + kvrow0 * D;
+                        float* scales = (u < UNITS ? args->kqs : args->vqs) + kvrow0;
+                        const int row = i0 + RPI * (u % UNITS) + l / LPR;
                         u32x2 cw;
                         float scale;
-                        quant_row_piece<LPR>(raw[ten][j], cw, scale);
-                        if (row < S) {
+                        quant_row_piece<LPR>(raw[j], cw, scale);
+                        if (row >= 0 && row < S) {
                             *reinterpret_cast<u32x2*>(codes + (long)row * D + piece * 8) = cw;
                             if (piece == 0) scales[row] = scale;
                         }
@@ -888,15 +936,37 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
                 }
             }
         }
+        if (k < 0) break;
     }
 }
 
 template <int D, bool KV_I8, bool OUT_F32, int MODE = 0, bool WIDE = false>
 static hipError_t launch_one(const PrefillParams& p, hipStream_t stream) {
-    const unsigned grid = (unsigned)(8 * p.chunk);
+    const unsigned grid = (unsigned)(8 * p.slots);
     hipLaunchKernelGGL((slim_prefill_kernel<D, KV_I8, OUT_F32, MODE, WIDE>), dim3(grid), dim3(kPrefillThreads), 0,
                        stream, p);
     return hipGetLastError();
+}
+
+// Microseconds the fullest workgroup takes: us_phase a phase (phases_per_tile of them a key tile) and us_item an item
+// (prologue, merge and output).  Of a long list of items the mean, else the longest of the first, middle and last lists.
+static double modelled_us(const PrefillParams& p, double us_phase, double us_item, int rows, int phases_per_tile) {
+    const long n = (long)p.n_rb * p.n_bh;
+    if (p.rounds > 8)
+        return (double)n / (8.0 * p.slots) * ((p.causal ? ((double)p.S + rows) / 64 : p.S / 32.0) * phases_per_tile * us_phase + us_item);
+    double most = 0.0;
+    for (const int slot : {0, p.slots / 2, p.slots - 1}) {
+        double us = 0.0;
+        for (int k = 0; k < p.rounds; ++k) {
+            const long j = 8L * ((long)k * p.slots + ((k & 1) ? p.slots - 1 - slot : slot));
+            if (j >= n) continue;
+            const long kend = (p.n_rb - j / p.n_bh) * rows - p.row_off;   // (one batch: longest row blocks first)
+            const long keys = p.causal && kend < p.S ? kend : p.S;
+            us += (double)((keys + kBC - 1) / kBC * phases_per_tile) * us_phase + us_item;
+        }
+        if (us > most) most = us;
+    }
+    return most;
 }
 
 hipError_t launch_prefill(const PrefillArgs& a, hipStream_t stream) {
@@ -911,15 +981,29 @@ hipError_t launch_prefill(const PrefillArgs& a, hipStream_t stream) {
     p.kqs = a.k_scale_out;
     p.vq = a.v_codes_out;
     p.vqs = a.v_scale_out;
-    p.Hq = a.q_heads;
-    p.Hkv = a.kv_heads;
     p.S = a.seq_len;
     p.causal = a.causal ? 1 : 0;
     auto blocks_of = [&](int rows) {
         p.n_rb = (a.seq_len + rows - 1) / rows;
-        p.n_pair = (p.n_rb + 1) / 2;
-        p.total = a.batch * a.q_heads * p.n_pair;
-        p.chunk = (p.total + 7) / 8;
+        // Under the causal mask the rows that do not fill a block go to the first one, which has the fewest keys, and not
+        // to the last (S = 777: 91 key tiles per head instead of 109); the offset keeps the diagonal on tile bounds.
+        p.row_off = p.causal ? (p.n_rb * rows - a.seq_len) / 32 * 32 : 0;
+        p.n_bh = a.batch * a.q_heads;
+        const int per_xcd = (p.n_rb * p.n_bh + 7) / 8;
+        p.slots = per_xcd < 32 ? per_xcd : 32;
+        p.rounds = (per_xcd + p.slots - 1) / p.slots;
+        // A batch has 4 KV heads an XCD, or all heads up to twice that: with 32 heads and 32 workgroups an XCD no two of
+        // them read the same K/V (B=8, 32 heads, S=4096: 1600 us, 1110 in batches); smaller batches leave ends of
+        // rounds unfilled (B=1, 32 heads, S=6000: 334 us in batches of two heads an XCD, 287 with all four).
+        p.group = (unsigned)(a.q_heads / a.kv_heads);
+        const unsigned per_batch = 8 * 4 * p.group;
+        p.heads = (unsigned)p.n_bh > 2 * per_batch ? per_batch : (unsigned)p.n_bh;
+        p.last_heads = (unsigned)p.n_bh % p.heads != 0 ? (unsigned)p.n_bh % p.heads : p.heads;
+        auto magic = [](unsigned long long d) { return d == 1 ? 0xffffffffu : (unsigned)((1ull << 32) / d); };   // (div_magic's correction covers 2^32 - 1 for d = 1)
+        p.batch_magic = magic((unsigned long long)p.n_rb * p.heads);
+        p.heads_magic = magic(p.heads);
+        p.last_heads_magic = magic(p.last_heads);
+        p.group_magic = magic(p.group);
     };
     blocks_of(kBR);
     p.scale_log2e = a.softmax_scale * kLog2e;
@@ -931,13 +1015,16 @@ hipError_t launch_prefill(const PrefillArgs& a, hipStream_t stream) {
         return a.out_f32 ? launch_one<64, false, true, 2>(p, stream) : launch_one<64, false, false, 2>(p, stream);
     }
     // INT8 K/V are widened to bf16 by the workgroup that stages them, and that is a quarter of the time with row blocks of
-    // 128 rows; blocks of 256 do it half as often per query row.  They are taken when they still give most compute units
-    // a pair of them, or when one block holds the whole sequence (B=1, 32 heads, S=4096: 175 -> 149 us, S=8192 637 ->
-    // 562, 64 on 8 heads, S=16384 4.82 -> 4.24 ms; S=2048 on 32 heads would take 76 us in 128 workgroups instead of 56).
+    // 128 rows; blocks of 256 do it half as often per query row (B=1, 32 heads, S=4096: 175 -> 149 us, S=8192 637 ->
+    // 562, 64 on 8 heads, S=16384 4.82 -> 4.24 ms), but there are half as many to fill the chip with (S=2048 on 32 heads:
+    // 64 us instead of 55).  The modelled times decide (constants from a sweep of 8 head counts by 11 lengths, of which
+    // they pick the faster form every time).
     if (a.kv_int8) {
+        const bool d128 = a.head_dim == 128;
+        const double narrow = modelled_us(p, d128 ? 0.50 : 0.42, d128 ? 7.0 : 4.0, kBR, 1);
         blocks_of(2 * kBR);
-        if (p.total >= 192 || a.seq_len <= 2 * kBR) {
-            if (a.head_dim == 128) return a.out_f32 ? launch_one<128, true, true, 0, true>(p, stream) : launch_one<128, true, false, 0, true>(p, stream);
+        if (modelled_us(p, d128 ? 0.44 : 0.37, d128 ? 5.0 : 4.0, 2 * kBR, 2) < narrow) {
+            if (d128) return a.out_f32 ? launch_one<128, true, true, 0, true>(p, stream) : launch_one<128, true, false, 0, true>(p, stream);
             return a.out_f32 ? launch_one<64, true, true, 0, true>(p, stream) : launch_one<64, true, false, 0, true>(p, stream);
         }
         blocks_of(kBR);

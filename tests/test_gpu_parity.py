@@ -850,6 +850,26 @@ def test_prefill_that_emits_the_int8_cache(sa, oracle, B, Hq, Hkv, S, D, causal)
 
 # ---------------------------------------------------------------- the two-sweep comparison variant
 
+@pytest.mark.parametrize("B,Hq,Hkv,S,D", [
+    # how the row blocks and heads are listed: fewer than eight heads, no multiple of eight, one batch of heads, two and
+    # a rest; a first row block of 1, 32 and 33 rows; lists of several items per workgroup
+    (1, 5, 5, 289, 128), (1, 7, 7, 160, 64), (3, 12, 4, 385, 128), (10, 8, 8, 140, 128), (11, 7, 7, 200, 64),
+    (9, 32, 4, 161, 64), (20, 16, 16, 300, 64), (1, 40, 8, 1281, 64)])
+@pytest.mark.parametrize("causal", [True, False])
+def test_prefill_item_lists(sa, oracle, B, Hq, Hkv, S, D, causal):
+    print("prefill item lists", B, Hq, Hkv, S, D, causal, flush=True)
+    rng = np.random.default_rng(3 * B + Hq + S)
+    q, k, v = normal_bf16(rng, (B, Hq, S, D)), normal_bf16(rng, (B, Hkv, S, D)), normal_bf16(rng, (B, Hkv, S, D))
+    scale = 1.0 / math.sqrt(D)
+    out, kc, ks, vc, vs = sa.slim_attn_prefill_emit_int8(dev_bf16(q), dev_bf16(k), dev_bf16(v), scale, causal)
+    torch.cuda.synchronize()
+    check_close(host_f64(out), oracle.attn(q, k, v, scale, causal), "item lists")
+    for got_c, got_s, x in ((kc, ks, k), (vc, vs, v)):
+        want_c, want_s = oracle.kv_quant_int8(x)
+        assert np.array_equal(got_c.cpu().numpy(), want_c)
+        assert np.array_equal(got_s.cpu().numpy().view(np.uint32), want_s.view(np.uint32))
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,S,D", SMALL)
 @pytest.mark.parametrize("causal", [True, False])
 def test_prefill_two_sweep_small_shapes(sa, oracle, B, Hq, Hkv, S, D, causal):
