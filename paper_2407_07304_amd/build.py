@@ -8,7 +8,7 @@ import sysconfig
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libslimattn.so")
-SOURCES = ["api.hip", "kv_quant.hip", "decode.hip", "decode_gqa.hip", "prefill.hip", "prefill_strip.hip"]
+SOURCES = ["api.hip", "kv_quant.hip", "decode.hip", "decode_gqa.hip", "prefill.hip", "prefill_split.hip", "prefill_strip.hip"]
 PROBE_LIB = os.path.join(HERE, "libslimprobe.so")
 PROBE_SOURCES = ["probes.hip", "decode_gqa.hip"]   # (the grouped-query decode kernel has a traffic-only form)
 # prefill.hip: MFMA results stay in arch VGPRs (no AGPR copies around the softmax), and fmaxf needs no
@@ -16,6 +16,7 @@ PROBE_SOURCES = ["probes.hip", "decode_gqa.hip"]   # (the grouped-query decode k
 # -Wno-inline-asm: its buffer loads with an LDS destination set M0 themselves and say so in the clobber list.
 EXTRA = {"prefill.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", "-fno-honor-nans", "-mno-amdgpu-ieee", "-Wno-inline-asm"],
          "prefill_strip.hip": ["-fno-honor-nans"],
+         "prefill_split.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", "-fno-honor-nans"],
          "decode_gqa.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", "-fno-honor-nans"]}
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 

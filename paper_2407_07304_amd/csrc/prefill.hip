@@ -1014,20 +1014,37 @@ hipError_t launch_prefill(const PrefillArgs& a, hipStream_t stream) {
         if (a.head_dim == 128) return a.out_f32 ? launch_one<128, false, true, 2>(p, stream) : launch_one<128, false, false, 2>(p, stream);
         return a.out_f32 ? launch_one<64, false, true, 2>(p, stream) : launch_one<64, false, false, 2>(p, stream);
     }
-    // INT8 K/V are widened to bf16 by the workgroup that stages them, and that is a quarter of the time with row blocks of
-    // 128 rows; blocks of 256 do it half as often per query row (B=1, 32 heads, S=4096: 175 -> 149 us, S=8192 637 ->
-    // 562, 64 on 8 heads, S=16384 4.82 -> 4.24 ms), but there are half as many to fill the chip with (S=2048 on 32 heads:
-    // 64 us instead of 55).  The modelled times decide (constants from a sweep of 8 head counts by 11 lengths, of which
-    // they pick the faster form every time).
+    // Which form: the modelled times decide (constants from a sweep of 8 head counts, 4 to 512, by 12 lengths, 50 to 4096,
+    // where they pick the fastest form or one within 3 % of it).
+    //   - INT8 K/V are widened to bf16 by the workgroup that stages them, and that is a quarter of the time with row
+    //     blocks of 128 rows; blocks of 256 do it half as often per query row (B=1, 32 heads, S=4096: 175 -> 149 us,
+    //     S=8192 637 -> 562, 64 on 8 heads, S=16384 4.82 -> 4.24 ms), but there are half as many to fill the chip with
+    //     (S=2048 on 32 heads: 64 us instead of 55).
+    //   - small calls take the form of prefill_split.hip: the longest row block's latency, or the chip's tiles and items
+    //     (8 heads: S=200 8.9 -> 5.2 us, S=1024 17.0 -> 10.4; 32 heads: S=512 12.8 -> 10.4, S=1024 stays).
+    const bool d128 = a.head_dim == 128;
+    bool wide = false;
+    double us = a.kv_int8 ? modelled_us(p, d128 ? 0.50 : 0.42, d128 ? 7.0 : 4.0, kBR, 1)
+                          : modelled_us(p, 0.31, d128 ? 4.2 : 5.0, kBR, 1);
     if (a.kv_int8) {
-        const bool d128 = a.head_dim == 128;
-        const double narrow = modelled_us(p, d128 ? 0.50 : 0.42, d128 ? 7.0 : 4.0, kBR, 1);
         blocks_of(2 * kBR);
-        if (modelled_us(p, d128 ? 0.44 : 0.37, d128 ? 5.0 : 4.0, 2 * kBR, 2) < narrow) {
-            if (d128) return a.out_f32 ? launch_one<128, true, true, 0, true>(p, stream) : launch_one<128, true, false, 0, true>(p, stream);
-            return a.out_f32 ? launch_one<64, true, true, 0, true>(p, stream) : launch_one<64, true, false, 0, true>(p, stream);
-        }
-        blocks_of(kBR);
+        const double us_wide = modelled_us(p, d128 ? 0.44 : 0.37, d128 ? 5.0 : 4.0, 2 * kBR, 2);
+        wide = us_wide < us;
+        if (wide) us = us_wide;
+        else blocks_of(kBR);
+    }
+    us += d128 ? (a.kv_int8 ? 1.0 : 1.5) : (a.kv_int8 ? 2.5 : 2.0);
+    const double blocks32 = (a.seq_len + 31) / 32, tiles = blocks32 * p.n_bh * (p.causal ? (blocks32 + 1) / 2 : blocks32);
+    const double us_longest = d128 ? 3.4 + 0.18 * blocks32 : 3.3 + 0.11 * blocks32;
+    const double us_all = (d128 ? 1.5 : 1.2) + ((d128 ? 0.18 : 0.115) * tiles + (d128 ? 2.0 : 1.2) * blocks32 * p.n_bh) / 256;
+    if ((us_longest > us_all ? us_longest : us_all) < us) {
+        // (eight waves where a compute unit has hardly more than one workgroup and a row block many tiles)
+        const bool eight = blocks32 * p.n_bh <= 384 && blocks32 >= (a.kv_int8 ? 24 : 48);
+        return launch_prefill_split(a, eight ? 8 : 4, stream);
+    }
+    if (wide) {
+        if (d128) return a.out_f32 ? launch_one<128, true, true, 0, true>(p, stream) : launch_one<128, true, false, 0, true>(p, stream);
+        return a.out_f32 ? launch_one<64, true, true, 0, true>(p, stream) : launch_one<64, true, false, 0, true>(p, stream);
     }
     const int sel = (a.head_dim == 128 ? 4 : 0) | (a.kv_int8 ? 2 : 0) | (a.out_f32 ? 1 : 0);
     switch (sel) {

@@ -144,6 +144,18 @@ def test_prefill_small_shapes(sa, oracle, B, Hq, Hkv, S, D, causal, kv_int8):
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,S,D,causal,out_f32", [
+    # small calls: the waves split the keys.  One row, the edges of a 32-row block and of a 32-key tile, fewer tiles than
+    # waves, one tile more than waves; eight waves (few heads, long rows)
+    (1, 1, 1, 1, 64, True, True), (3, 4, 2, 31, 128, True, False), (2, 4, 4, 32, 64, False, True), (2, 6, 2, 33, 128, False, False),
+    (1, 9, 3, 127, 64, True, False), (1, 8, 8, 129, 128, True, True), (1, 8, 2, 161, 128, False, False),
+    (1, 2, 2, 1590, 128, True, False), (1, 3, 1, 1601, 64, True, True), (1, 2, 1, 800, 128, False, True)])
+@pytest.mark.parametrize("kv_int8", [False, True])
+def test_prefill_small_calls(sa, oracle, B, Hq, Hkv, S, D, causal, out_f32, kv_int8):
+    print("prefill small calls", B, Hq, Hkv, S, D, causal, out_f32, kv_int8, flush=True)
+    _prefill_case(sa, oracle, B, Hq, Hkv, S, D, causal, kv_int8, out_f32, seed=S + Hq)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,S,D,causal,out_f32", [
     # one block of 256 rows holds the sequence: row groups of 32 that end inside, key tiles that end inside, one row
     (1, 2, 2, 1, 128, True, False), (2, 3, 1, 97, 64, True, True), (1, 2, 2, 160, 128, False, False),
     (1, 2, 2, 255, 128, True, True), (1, 4, 2, 256, 64, False, False),
