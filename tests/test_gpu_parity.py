@@ -175,6 +175,14 @@ def test_prefill_int8_wide_row_blocks(sa, oracle, B, Hq, Hkv, S, D, causal, out_
     check_close(host_f64(out), oracle.attn(q, kc, vc, scale, causal, k_scale=ks, v_scale=vs), "wide row blocks")
 
 
+@pytest.mark.parametrize("Hq,Hkv,S,D,causal", [(32, 32, 1500, 128, True), (40, 8, 1281, 64, True), (48, 16, 1057, 128, False), (36, 36, 1340, 128, True)])
+def test_prefill_int8_128_row_blocks(sa, oracle, Hq, Hkv, S, D, causal):
+    # between the small calls and those with enough heads for blocks of 256 rows
+    rows = np.unique(np.concatenate([np.arange(0, 40), np.arange(S - 150, S), np.arange(0, S, 37)])).astype(np.int32)
+    print("prefill int8 128-row blocks", Hq, Hkv, S, D, causal, flush=True)
+    _prefill_case(sa, oracle, 1, Hq, Hkv, S, D, causal, True, False, seed=S, rows=rows)
+
+
 def test_prefill_c1_full(sa, oracle):
     w = WORKLOADS["C1"]
     print("prefill C1 full tensor", flush=True)
@@ -866,7 +874,10 @@ def test_prefill_that_emits_the_int8_cache(sa, oracle, B, Hq, Hkv, S, D, causal)
     # how the row blocks and heads are listed: fewer than eight heads, no multiple of eight, one batch of heads, two and
     # a rest; a first row block of 1, 32 and 33 rows; lists of several items per workgroup
     (1, 5, 5, 289, 128), (1, 7, 7, 160, 64), (3, 12, 4, 385, 128), (10, 8, 8, 140, 128), (11, 7, 7, 200, 64),
-    (9, 32, 4, 161, 64), (20, 16, 16, 300, 64), (1, 40, 8, 1281, 64)])
+    (9, 32, 4, 161, 64), (20, 16, 16, 300, 64), (1, 40, 8, 1281, 64),
+    # the same on calls that are large enough for 128-row blocks
+    (43, 7, 7, 200, 64), (33, 8, 8, 140, 128), (19, 16, 4, 161, 128), (38, 8, 8, 257, 128), (33, 8, 2, 385, 64), (65, 4, 4, 289, 128),
+    (37, 7, 7, 129, 128)])
 @pytest.mark.parametrize("causal", [True, False])
 def test_prefill_item_lists(sa, oracle, B, Hq, Hkv, S, D, causal):
     print("prefill item lists", B, Hq, Hkv, S, D, causal, flush=True)
