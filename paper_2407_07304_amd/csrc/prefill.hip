@@ -100,16 +100,15 @@ using int_c = std::integral_constant<int, N>;
 // to p.row_max), MODE 2 computes them again, exponentiates against those final maxima and multiplies by V:
 // no running maximum, no rescaling of the accumulator, 1.5 times the MFMAs.  MODE 0 is the kernel proper.
 //
-// WIDE (INT8 K/V): row blocks of 256 rows.  The eight waves own 32 rows each and every wave goes through all key tiles,
-// so a staged tile meets twice the query rows: the two groups stay in opposite phases, but on the same tile one phase
-// apart, group 1 stages K and group 0 V (half the widening per matrix phase), and there is nothing to merge at the end.
-// See launch_prefill for when it is taken and what it gives.
+// WIDE (not D = 64 with bf16 K/V): row blocks of 256 rows.  The eight waves own 32 rows each and every wave goes through
+// all key tiles, so a staged tile meets twice the query rows: the two groups stay in opposite phases, but on the same tile
+// one phase apart, group 1 stages K and group 0 V (half the widening, or half the ring's requests, per matrix phase), and
+// there is nothing to merge at the end.  See launch_prefill for when it is taken and what it gives.
 template <int D, bool KV_I8, bool OUT_F32, int MODE = 0, bool WIDE = false>
 __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const PrefillParams p) {
-    static_assert(!(MODE != 0 && KV_I8), "the two-sweep variant exists for bf16 K/V only");
-    static_assert(!WIDE || KV_I8, "the wide form stages through registers");
+    static_assert(!(MODE != 0 && (KV_I8 || WIDE)), "the two-sweep variant exists for bf16 K/V and 128 rows only");
     constexpr int BR = WIDE ? 2 * kBR : kBR;   // query rows per row block
-    constexpr int RK = WIDE ? 2 : kRingK, RV = WIDE ? 2 : kRingV;   // ring depth (see the phases for why two will do)
+    constexpr int RK = WIDE ? (KV_I8 ? 2 : 4) : kRingK, RV = WIDE ? (KV_I8 ? 2 : 4) : kRingV;   // ring depth (see the phases)
     constexpr bool stats_only = MODE == 1;
     constexpr int KS = D / 16;       // k-steps of the score MFMA
     constexpr int DT = D / 32;       // 32-row tiles of O^T
@@ -138,12 +137,12 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
     constexpr int ROWQ = 2 * D;                // bytes per Q row, in memory and in LDS
     constexpr int CPQ = ROWQ / 16;             // 16-byte chunks per row: 16 or 8
     constexpr int RPQ = 64 / CPQ;              // rows per wave-wide load: 4 or 8
-    constexpr int NQ = kBR / 8 / RPQ;          // loads per wave and row block (a wave brings in 16 rows): 4 or 2
+    constexpr int NQ = BR / 8 / RPQ;           // loads per wave and row block (a wave brings in an eighth of the rows)
     constexpr int Q_OFF = RING_BYTES + kRingK * 2 * kBC * 4;
     auto qswz = [](int r) { return (r / (256 / ROWQ)) & (CPQ - 1); };
 
     constexpr bool Q_LDS = !KV_I8;             // (the INT8 kernel keeps plain loads into the registers: measured faster there)
-    __shared__ __attribute__((aligned(16))) char smem[Q_OFF + (Q_LDS ? kBR * ROWQ : 0)];
+    __shared__ __attribute__((aligned(16))) char smem[Q_OFF + (Q_LDS ? BR * ROWQ : 0)];
     float* const scS = reinterpret_cast<float*>(smem + RING_BYTES);   // INT8: per slot [0,32) k_scale*c, [32,64) v_scale
 
     // Work items are (row block, batch*head).  They are listed in batches of `heads` heads (few enough that what an XCD
@@ -206,9 +205,9 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
         qrs_raw[3] = 0x00020000u;
 #pragma unroll
         for (int j = 0; j < NQ; ++j) {
-            const int r = 16 * w8 + RPQ * j + l / CPQ, pos = l % CPQ;   // row of the block, chunk position in LDS
+            const int r = BR / 8 * w8 + RPQ * j + l / CPQ, pos = l % CPQ;   // row of the block, chunk position in LDS
             const unsigned voff = (unsigned)(rb_q * BR - p.row_off + r) * ROWQ + (unsigned)((pos ^ qswz(r)) * 16);
-            const unsigned dst = __builtin_amdgcn_readfirstlane(smem_base + (unsigned)(Q_OFF + (16 * w8 + RPQ * j) * ROWQ));
+            const unsigned dst = __builtin_amdgcn_readfirstlane(smem_base + (unsigned)(Q_OFF + (BR / 8 * w8 + RPQ * j) * ROWQ));
             asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
                          :
                          : "s"(dst), "v"(voff), "s"(qrs_raw)
@@ -220,7 +219,7 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
         if constexpr (!Q_LDS) return;
 #pragma unroll
         for (int s = 0; s < KS; ++s)
-            qreg[s] = *reinterpret_cast<const bf16x8*>(smem + Q_OFF + (32 * w + l32) * ROWQ + (((2 * s + hh) ^ qswz(l32)) * 16));
+            qreg[s] = *reinterpret_cast<const bf16x8*>(smem + Q_OFF + (32 * rg + l32) * ROWQ + (((2 * s + hh) ^ qswz(l32)) * 16));
     };
     request_q(rb, bh);
     __builtin_amdgcn_sched_barrier(0);
@@ -395,7 +394,18 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
         }
         Stage sg;
         __syncthreads();   // the previous item has finished with the ring and the merge buffer that lies over it
-        if constexpr (!KV_I8) {
+        if constexpr (WIDE && !KV_I8) {
+            if (grp == 0) {
+                dma_tile(krs_raw, d_koff, 0, 0);
+                dma_tile(krs_raw, d_koff, 2, 2 * TILEB);
+                dma_tile(vrs_raw, d_voff, 1, K_BYTES + TILEB);
+            } else {
+                dma_tile(krs_raw, d_koff, 1, TILEB);
+                dma_tile(vrs_raw, d_voff, 0, K_BYTES);
+                dma_tile(vrs_raw, d_voff, 2, K_BYTES + 2 * TILEB);
+            }
+            __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): this wave's requests have landed in LDS
+        } else if constexpr (!KV_I8) {
             if (grp == 0) {
                 dma_tile(krs_raw, d_koff, 0, 0);
                 dma_tile(krs_raw, d_koff, 2, 2 * TILEB);
@@ -567,7 +577,7 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
                 const float alpha = fast_exp2(M - m_new);
                 // (the accumulator is still zero on a group's first tile, and on the diagonal tile the maximum has
                 // usually been met already: the 16 DT multiplications are skipped when they would change nothing)
-                if (KV_I8 || (t >= 2 && __builtin_amdgcn_ballot_w64(m_new > M) != 0)) {   // (INT8: the branch costs registers the kernel does not have)
+                if (KV_I8 || (t >= (WIDE ? 1 : 2) && __builtin_amdgcn_ballot_w64(m_new > M) != 0)) {   // (INT8: the branch costs registers the kernel does not have)
 #pragma unroll
                     for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
@@ -637,12 +647,16 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
                 // needs (K tile phi+3, V tile phi+1): the LDS reads, and the ring traffic, are issued in the
                 // shadow of the MFMAs.  (The fences keep the issue order as written.)
                 // WIDE: tile t = (phi - 1) / 2 of group 0, phi / 2 - 1 of group 1; next are K tile t + 2 and V tile t + 1.
-                // Two slots a tensor will do: K tile u is read in phases 2u - 3 and 2u - 2 (by group 0, then 1) and
+                // INT8: two slots a tensor will do: K tile u is read in phases 2u - 3 and 2u - 2 (by group 0, then 1) and
                 // group 1 stores it in phase 2u - 4, when K tile u - 2 was read for the last time two phases ago; V tile
                 // u is read in phases 2u - 1 and 2u, and group 0 stores it in phase 2u - 3, one after V tile u - 2's last.
+                // bf16: four slots.  Group 1 requests K tile u in phase 2u - 6 and waits for it at the end of phase
+                // 2u - 4 (K tile u - 4 was read last in phase 2u - 10), group 0 V tile u in phase 2u - 5, waiting at the
+                // end of 2u - 3 (V tile u - 4: phase 2u - 8).
                 constexpr int T2 = G == 0 ? (P4 >> 1) & 1 : ((P4 >> 1) + 1) & 1;   // WIDE: t's parity
-                const int k_rd = WIDE ? T2 * TILEBK : ((phi + 3) & (kRingK - 1)) * TILEBK;
-                constexpr int v_rd = WIDE ? (1 - T2) * TILEBV : ((P4 + 1) & 3) * TILEBV;
+                const int t_w = ((phi + G) >> 1) - G;   // WIDE: t
+                const int k_rd = !WIDE ? ((phi + 3) & (kRingK - 1)) * TILEBK : KV_I8 ? T2 * TILEBK : ((t_w + 2) & 3) * TILEBK;
+                const int v_rd = !WIDE ? ((P4 + 1) & 3) * TILEBV : KV_I8 ? (1 - T2) * TILEBV : ((t_w + 1) & 3) * TILEBV;
                 // the wave that feeds the matrix pipe goes first: without this the older wave of the SIMD wins
                 // the issue port whatever it is doing, and the matrix phases of group 1 run 30 % longer
                 __builtin_amdgcn_s_setprio(3);
@@ -658,11 +672,12 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
                 // Invariant the hand-written wait below rests on: a matrix phase issues exactly REQ ring requests
                 // (steps i < NLD of the loop: the K tile's, the remaining DT - NLD steps: the V tile's, none of
                 // those in the maxima-only sweep), buffer loads complete in the order they were issued, and the
-                // requests of the wave's PREVIOUS matrix phase are the ones that must have landed.  So the wait
+                // requests of the wave's PREVIOUS matrix phase are the ones that must have landed (WIDE: a phase has one
+                // tensor's, every other step).  So the wait
                 // at the end of the phase is vmcnt(REQ): everything but this phase's own requests.
-                constexpr int REQ = KV_I8 ? 0 : NLD + (stats_only ? 0 : DT - NLD);
+                constexpr int REQ = KV_I8 ? 0 : WIDE ? NLD : NLD + (stats_only ? 0 : DT - NLD);
                 static_assert(KV_I8 || DT == 2 * NLD, "one ring load per step of the first MFMA loop");
-                static_assert(KV_I8 || REQ == (stats_only ? NLD : 2 * NLD), "requests per matrix phase");
+                static_assert(KV_I8 || REQ == (stats_only || WIDE ? NLD : 2 * NLD), "requests per matrix phase");
                 static_assert(REQ < 16, "vmcnt is written into the low four bits of the wait's immediate");
 #pragma unroll
                 for (int i = 0; i < DT; ++i) {
@@ -670,7 +685,10 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
                     score_mfma(i, acc);
                     __builtin_amdgcn_sched_barrier(0);
                     fetch_k1(i, k_rd);
-                    if constexpr (!KV_I8) {
+                    if constexpr (!KV_I8 && WIDE) {
+                        const int u = G == 1 ? (phi >> 1) + 3 : (phi + 5) >> 1;
+                        if (i % 2 == 0) dma_prep(G == 1 ? d_koff : d_voff, i / 2, u, (G == 1 ? 0 : K_BYTES) + (u & 3) * TILEB, u < n_tiles, dma_dst, dma_voff);
+                    } else if constexpr (!KV_I8) {
                         if (i < NLD) dma_prep(d_koff, i, phi + 6, ((phi + 6) & (kRingK - 1)) * TILEB, phi + 6 < n_tiles, dma_dst, dma_voff);
                         else if (!stats_only) dma_prep(d_voff, i - NLD, phi + 4, K_BYTES + P4 * TILEB, phi + 4 < n_tiles, dma_dst, dma_voff);
                     }
@@ -680,13 +698,15 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
                         __builtin_amdgcn_sched_barrier(0);
                         fetch_v1(0, i, v_rd);
                     }
-                    if constexpr (!KV_I8) {
+                    if constexpr (!KV_I8 && WIDE) {
+                        if (i % 2 == 0) dma_fire(G == 1 ? krs_raw : vrs_raw, dma_dst, dma_voff);
+                    } else if constexpr (!KV_I8) {
                         if (i < NLD) dma_fire(krs_raw, dma_dst, dma_voff);
                         else if (!stats_only) dma_fire(vrs_raw, dma_dst, dma_voff);
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
-                if constexpr (WIDE) {
+                if constexpr (WIDE && KV_I8) {
                     if constexpr (G == 1) {   // the pieces loaded two phases ago go to K tile phi / 2 + 2
                         store_tile(((P4 >> 1) & 1) * TILEBK, p_kdst, sg.k);
                         store_s(((phi >> 1) + 2) & (kRingK - 1), sg.s, w == 3);
@@ -881,32 +901,17 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
             __syncthreads();
             copy_out();
         };
-        if constexpr (WIDE) {   // every wave has its rows' whole result
-            const float inv = 1.0f / half_sum(lsum);
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) o[dt][r] *= inv;
-                put_tile(o[dt], dt);
-            }
-            __syncthreads();
-            copy_out();
-            if (k < 0) break;
-            continue;
-        }
-        if (grp == 0) finish(int_c<0>{});
-        else finish(int_c<1>{});
-
         // ---- the INT8 cache of this row block's own K and V rows, if asked for (section 2.2), with the quantiser's row
         // routine.  The rows were this row block's last tiles, so they come from the L2.  The block's pieces of a
         // wave-wide access each are dealt to the query heads that share the KV head, and to the waves: left to the
         // first head's workgroup alone they were 10 us of B=4, 32 on 8 heads, S=777.
-        if constexpr (!KV_I8) {
+        auto emit_cache = [&]() {
+            if constexpr (KV_I8) return;
             const KernelArgs args = kernel_args_now();
             if (args->kq != nullptr) {
                 constexpr int LPR = D / 8;          // lanes per row
                 constexpr int RPI = 64 / LPR;       // rows per wave-wide access
-                constexpr int UNITS = kBR / RPI;    // accesses per tensor
+                constexpr int UNITS = BR / RPI;     // accesses per tensor
                 const int step = (int)args->group, first = bh_now - kvh * step;
                 const int piece = l % LPR;
                 for (int u0 = first + step * w8; u0 < 2 * UNITS; u0 += 4 * 8 * step) {
@@ -935,7 +940,25 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
                     }
                 }
             }
+        };
+        if constexpr (WIDE) {   // every wave has its rows' whole result
+            const float inv = 1.0f / half_sum(lsum);
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) o[dt][r] *= inv;
+                put_tile(o[dt], dt);
+            }
+            __syncthreads();
+            copy_out();
+            emit_cache();
+            if (k < 0) break;
+            continue;
         }
+        if (grp == 0) finish(int_c<0>{});
+        else finish(int_c<1>{});
+
+        emit_cache();
         if (k < 0) break;
     }
 }
@@ -1020,15 +1043,20 @@ hipError_t launch_prefill(const PrefillArgs& a, hipStream_t stream) {
     //     blocks of 128 rows; blocks of 256 do it half as often per query row (B=1, 32 heads, S=4096: 175 -> 149 us,
     //     S=8192 637 -> 562, 64 on 8 heads, S=16384 4.82 -> 4.24 ms), but there are half as many to fill the chip with
     //     (S=2048 on 32 heads: 64 us instead of 55).
+    //   - bf16 K/V, D = 128: half the ring's requests per matrix phase and no merge are worth 3 to 10 % where there are
+    //     enough items (32 heads: S=4096 142 -> 136 us, S=8192 504 -> 489, B=4, 32 on 8 heads, S=777 39.5 -> 36.6; S=2048
+    //     43 -> 53, stays).  fp32 results stay too (their staging area and 256 query rows are more than the LDS holds),
+    //     and so does D = 64, where the wide form gains and loses 6 % in turn.
     //   - small calls take the form of prefill_split.hip: the longest row block's latency, or the chip's tiles and items
     //     (8 heads: S=200 8.9 -> 5.2 us, S=1024 17.0 -> 10.4; 32 heads: S=512 12.8 -> 10.4, S=1024 stays).
     const bool d128 = a.head_dim == 128;
     bool wide = false;
     double us = a.kv_int8 ? modelled_us(p, d128 ? 0.50 : 0.42, d128 ? 7.0 : 4.0, kBR, 1)
                           : modelled_us(p, 0.31, d128 ? 4.2 : 5.0, kBR, 1);
-    if (a.kv_int8) {
+    if (a.kv_int8 || (d128 && !a.out_f32)) {
         blocks_of(2 * kBR);
-        const double us_wide = modelled_us(p, d128 ? 0.44 : 0.37, d128 ? 5.0 : 4.0, 2 * kBR, 2);
+        const double us_wide = a.kv_int8 ? modelled_us(p, d128 ? 0.44 : 0.37, d128 ? 5.0 : 4.0, 2 * kBR, 2)
+                                         : modelled_us(p, 0.30, 5.5, 2 * kBR, 2);
         wide = us_wide < us;
         if (wide) us = us_wide;
         else blocks_of(kBR);
@@ -1043,6 +1071,7 @@ hipError_t launch_prefill(const PrefillArgs& a, hipStream_t stream) {
         return launch_prefill_split(a, eight ? 8 : 4, stream);
     }
     if (wide) {
+        if (!a.kv_int8) return launch_one<128, false, false, 0, true>(p, stream);
         if (d128) return a.out_f32 ? launch_one<128, true, true, 0, true>(p, stream) : launch_one<128, true, false, 0, true>(p, stream);
         return a.out_f32 ? launch_one<64, true, true, 0, true>(p, stream) : launch_one<64, true, false, 0, true>(p, stream);
     }

@@ -893,6 +893,29 @@ def test_prefill_item_lists(sa, oracle, B, Hq, Hkv, S, D, causal):
         assert np.array_equal(got_s.cpu().numpy().view(np.uint32), want_s.view(np.uint32))
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,S,causal", [
+    # bf16 K/V in blocks of 256 rows: one block that ends inside, one row less and none, one row past it; row groups and
+    # key tiles that end inside, several blocks, several items per workgroup
+    (16, 32, 8, 129, True), (25, 16, 16, 255, False), (16, 32, 8, 256, True), (28, 16, 4, 257, True), (20, 16, 16, 480, False),
+    (40, 8, 8, 545, True), (4, 32, 8, 777, True), (4, 32, 32, 777, False), (26, 5, 5, 1025, True)])
+def test_prefill_bf16_wide_row_blocks(sa, oracle, B, Hq, Hkv, S, causal):
+    print("prefill bf16 wide", B, Hq, Hkv, S, causal, flush=True)
+    rng = np.random.default_rng(5 * B + Hq + S)
+    D = 128
+    q, k, v = normal_bf16(rng, (B, Hq, S, D)), normal_bf16(rng, (B, Hkv, S, D)), normal_bf16(rng, (B, Hkv, S, D))
+    scale = 1.0 / math.sqrt(D)
+    dq, dk, dv = dev_bf16(q), dev_bf16(k), dev_bf16(v)
+    plain = sa.slim_attn_prefill(dq, dk, dv, scale, causal)
+    out, kc, ks, vc, vs = sa.slim_attn_prefill_emit_int8(dq, dk, dv, scale, causal)
+    torch.cuda.synchronize()
+    check_close(host_f64(out), oracle.attn(q, k, v, scale, causal), "bf16 wide row blocks")
+    assert torch.equal(plain.view(torch.int16), out.view(torch.int16))
+    for got_c, got_s, x in ((kc, ks, k), (vc, vs, v)):
+        want_c, want_s = oracle.kv_quant_int8(x)
+        assert np.array_equal(got_c.cpu().numpy(), want_c)
+        assert np.array_equal(got_s.cpu().numpy().view(np.uint32), want_s.view(np.uint32))
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,S,D", SMALL)
 @pytest.mark.parametrize("causal", [True, False])
 def test_prefill_two_sweep_small_shapes(sa, oracle, B, Hq, Hkv, S, D, causal):
