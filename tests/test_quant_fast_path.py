@@ -68,3 +68,16 @@ def test_the_guard_matters(model):
     out = (ctypes.c_long * 4)()
     assert model.model_code_sweep(lo, hi, ctypes.c_float(0.0), 8, out) == 0
     assert out[2] > 0
+
+
+def test_the_corrected_quotient_is_the_ieee_quotient(model, tmp_path):
+    # values within the guard of a tie: the product corrected by its remainder, for every bf16 pair and reciprocal
+    so = str(tmp_path / "libquant_near_tie.so")
+    subprocess.run(["gcc", "-O2", "-mfma", "-fopenmp", "-shared", "-fPIC", "-Wall", "-Wextra", "-fno-fast-math", "-ffp-contract=off",
+                    "-o", so, os.path.join(HERE, "host_models", "quant_near_tie.c"), "-lm"], check=True)
+    lib = ctypes.CDLL(so)
+    lib.model_near_tie_sweep.argtypes = [ctypes.c_float, ctypes.c_float, ctypes.c_float, ctypes.c_void_p]
+    out = (ctypes.c_long * 3)()
+    assert lib.model_near_tie_sweep(*kernel_constants(), out) == 0
+    cases, near_ties, bad = out[0], out[1], out[2]
+    assert cases > 10 ** 7 and near_ties > 10 ** 4 and bad == 0, (cases, near_ties, bad)
