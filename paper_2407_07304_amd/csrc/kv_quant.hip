@@ -12,9 +12,10 @@
 
 namespace slim {
 
-// STREAM: input and output together are larger than the last-level cache, so the input is read with
-// non-temporal loads and every thread keeps U = 4 rows in flight (all loads issued before any is used): 5.6 TB/s on
-// a 1.6 GB stream, where the same loads and stores with no arithmetic in between reach 5.9.  A smaller input may
+// STREAM: input and output together are larger than the last-level cache, so the input is read and the codes are
+// written past it, non-temporal, and every thread keeps U = 2 rows in flight (all loads issued before any is used):
+// 6.4 to 6.6 TB/s on 0.4 to 1.6 GB, where cached stores reach 5.8 (16 x 32 heads, 8192 tokens: 281 -> 250 us), one row
+// a thread 5.9 and four rows 6.3; the same loads and stores with no arithmetic in between reach 6.5.  A smaller input may
 // be what the next kernel reads again (the K/V of a prefill): it is left to the caches, one row per thread, which
 // finishes a launch-bound call soonest.
 template <int D, bool STREAM, int U>
@@ -43,7 +44,9 @@ __device__ __forceinline__ void kv_quant_rows(const uint16_t* __restrict__ x, in
             float scale;
             quant_row_piece<LPR>(raw[u], out2, scale);
             if (row < n_rows) {
-                *reinterpret_cast<u32x2*>(codes + row * D + lane_in_row * 8) = out2;
+                u32x2* dst = reinterpret_cast<u32x2*>(codes + row * D + lane_in_row * 8);
+                if (STREAM) __builtin_nontemporal_store(out2, dst);
+                else *dst = out2;
                 if (lane_in_row == 0) scales[row] = scale;
             }
         }
@@ -96,17 +99,17 @@ __global__ __launch_bounds__(kAppendThreads) void kv_quant_int8_append_kernel(co
 hipError_t launch_kv_quant_int8(const void* x, int8_t* codes, float* scales, long n_rows, int head_dim,
                                 hipStream_t stream) {
     const bool stream_in = n_rows * head_dim * 3 > (256L << 20);   // input + codes beyond the 256 MB last-level cache
-    const int rows_per_block = 256 / (head_dim / 8) * (stream_in ? 4 : 1);
+    const int rows_per_block = 256 / (head_dim / 8) * (stream_in ? 2 : 1);
     long blocks = (n_rows + rows_per_block - 1) / rows_per_block;
     // one pass per workgroup (measured faster than fewer workgroups that loop); the loop is for grids beyond this
     const long max_blocks = 1L << 20;
     if (blocks > max_blocks) blocks = max_blocks;
     const dim3 grid((unsigned)blocks), block(256);
     if (head_dim == 128) {
-        if (stream_in) hipLaunchKernelGGL((kv_quant_int8_kernel<128, true, 4>), grid, block, 0, stream, (const uint16_t*)x, codes, scales, n_rows);
+        if (stream_in) hipLaunchKernelGGL((kv_quant_int8_kernel<128, true, 2>), grid, block, 0, stream, (const uint16_t*)x, codes, scales, n_rows);
         else hipLaunchKernelGGL((kv_quant_int8_kernel<128, false, 1>), grid, block, 0, stream, (const uint16_t*)x, codes, scales, n_rows);
     } else {
-        if (stream_in) hipLaunchKernelGGL((kv_quant_int8_kernel<64, true, 4>), grid, block, 0, stream, (const uint16_t*)x, codes, scales, n_rows);
+        if (stream_in) hipLaunchKernelGGL((kv_quant_int8_kernel<64, true, 2>), grid, block, 0, stream, (const uint16_t*)x, codes, scales, n_rows);
         else hipLaunchKernelGGL((kv_quant_int8_kernel<64, false, 1>), grid, block, 0, stream, (const uint16_t*)x, codes, scales, n_rows);
     }
     return hipGetLastError();
@@ -115,7 +118,7 @@ hipError_t launch_kv_quant_int8(const void* x, int8_t* codes, float* scales, lon
 hipError_t launch_kv_quant_int8_pair(const void* k, const void* v, int8_t* k_codes, float* k_scale, int8_t* v_codes,
                                      float* v_scale, long n_rows, int head_dim, hipStream_t stream) {
     const bool stream_in = 2 * n_rows * head_dim * 3 > (256L << 20);   // both inputs + both code tensors beyond the last-level cache
-    const int rows_per_block = 256 / (head_dim / 8) * (stream_in ? 4 : 1);
+    const int rows_per_block = 256 / (head_dim / 8) * (stream_in ? 2 : 1);
     long blocks = (n_rows + rows_per_block - 1) / rows_per_block;
     const long max_blocks = 1L << 20;
     if (blocks > max_blocks) blocks = max_blocks;
@@ -128,10 +131,10 @@ hipError_t launch_kv_quant_int8_pair(const void* k, const void* v, int8_t* k_cod
     p.scales[0] = k_scale;
     p.scales[1] = v_scale;
     if (head_dim == 128) {
-        if (stream_in) hipLaunchKernelGGL((kv_quant_int8_pair_kernel<128, true, 4>), grid, block, 0, stream, p, n_rows);
+        if (stream_in) hipLaunchKernelGGL((kv_quant_int8_pair_kernel<128, true, 2>), grid, block, 0, stream, p, n_rows);
         else hipLaunchKernelGGL((kv_quant_int8_pair_kernel<128, false, 1>), grid, block, 0, stream, p, n_rows);
     } else {
-        if (stream_in) hipLaunchKernelGGL((kv_quant_int8_pair_kernel<64, true, 4>), grid, block, 0, stream, p, n_rows);
+        if (stream_in) hipLaunchKernelGGL((kv_quant_int8_pair_kernel<64, true, 2>), grid, block, 0, stream, p, n_rows);
         else hipLaunchKernelGGL((kv_quant_int8_pair_kernel<64, false, 1>), grid, block, 0, stream, p, n_rows);
     }
     return hipGetLastError();
