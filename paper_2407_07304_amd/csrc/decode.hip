@@ -346,7 +346,9 @@ static hipError_t launch_combine(const DecodeArgs& a, const float* ws_acc, const
 //   - 6 us for the combine launch when S > 1.
 // So a (batch, head) is split only where one workgroup each cannot load the chip evenly or soon enough, and whole
 // caches go through one launch from about 150 rows on (B=16, 32 heads, T=8192: 161 us in one launch of eight-wave
-// workgroups, 164 us as 4 splits).  A split has at least a chunk for each of four waves.
+// workgroups, 164 us as 4 splits).  A split has at least a chunk for each of four waves, and a call is not split into more
+// records than the library's own scratch holds (that many are 126 workgroups per compute unit and more, where a finer
+// split gains nothing): what decides whether slim_attn_decode_int8_static takes a shape is then its rows alone.
 struct DecodePlan {
     int waves, n_split;
 };
@@ -357,7 +359,7 @@ static DecodePlan decode_plan(int kv_len, long n_bh, int head_dim) {
     DecodePlan best{4, 1};
     double best_ns = 0.0;
     for (int s : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256}) {
-        if (s > 1 && s * 4 > n_chunks) break;
+        if (s > 1 && (s * 4 > n_chunks || decode_records_bytes(n_bh, s, head_dim) > kDecodeStaticScratchBytes)) break;
         const long per_wg = (n_chunks + s - 1) / s, rounds = (n_bh * s + 255) / 256;
         const double busy_ns = (double)(rounds * per_wg * kChunk) * ns_token;
         const double longer = busy_ns > stream_ns ? busy_ns : stream_ns, shorter = busy_ns > stream_ns ? stream_ns : busy_ns;
@@ -382,10 +384,10 @@ size_t decode_workspace_bytes(int batch, int q_heads, int kv_heads, int kv_len, 
     int n_split = decode_plan(kv_len, (long)batch * q_heads, head_dim).n_split;
     if (decode_uses_gqa_kernel(q_heads, kv_heads)) {
         // (never less than two records a row: the shapes the static scratch array is too small for stay what they were)
-        n_split = decode_gqa_num_splits(kv_len, (long)batch * kv_heads, head_dim);
+        n_split = decode_gqa_num_splits(kv_len, (long)batch * kv_heads, q_heads / kv_heads, head_dim);
         if (n_split < 2) n_split = 2;
     }
-    return (size_t)batch * q_heads * n_split * ((size_t)head_dim + 2) * sizeof(float);
+    return decode_records_bytes((long)batch * q_heads, n_split, head_dim);
 }
 
 // Scratch of the decode entry point that may not allocate: the same (max, sum, accumulator) partials as the
@@ -417,7 +419,7 @@ hipError_t launch_decode(const DecodeArgs& a, hipStream_t stream) {
     // (the query heads of a KV head share one pass over its cache in the grouped-query kernel)
     const bool gqa = decode_uses_gqa_kernel(a.q_heads, a.kv_heads);
     const DecodePlan plan = decode_plan(a.kv_len, (long)a.batch * a.q_heads, a.head_dim);
-    const int n_split = gqa ? decode_gqa_num_splits(a.kv_len, (long)a.batch * a.kv_heads, a.head_dim) : plan.n_split;
+    const int n_split = gqa ? decode_gqa_num_splits(a.kv_len, (long)a.batch * a.kv_heads, a.q_heads / a.kv_heads, a.head_dim) : plan.n_split;
     float* const ws_acc = a.workspace;
     float* const ws_ml = a.workspace + (size_t)a.batch * a.q_heads * n_split * a.head_dim;
     auto launch = [&](auto d_c, auto w_c) {

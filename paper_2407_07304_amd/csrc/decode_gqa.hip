@@ -363,13 +363,13 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_gqa_kernel(
 struct GqaPlan {
     int waves, n_split;
 };
-static GqaPlan gqa_plan(int kv_len, long n_bg, int head_dim) {
+static GqaPlan gqa_plan(int kv_len, long n_bg, int group, int head_dim) {
     const long n_tiles = ((long)kv_len + kGqaTile - 1) / kGqaTile;
     const double stream_ns = (double)kv_len * n_bg * (2 * head_dim + 8) / 6600.0;
     int best = 1;
     double best_ns = 0.0;
     for (int s : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256}) {
-        if (s > 1 && s * 4 > n_tiles) break;
+        if (s > 1 && (s * 4 > n_tiles || decode_records_bytes(n_bg * group, s, head_dim) > kDecodeStaticScratchBytes)) break;
         const long per_wg = (n_tiles + s - 1) / s, rounds = (n_bg * s + 255) / 256;
         const double ns_token = head_dim == 128 ? (rounds > 1 ? 7.0 : 5.9) : (rounds > 1 ? 5.0 : 4.2);
         const double busy_ns = (double)(rounds * per_wg * kGqaTile) * ns_token;
@@ -383,11 +383,11 @@ static GqaPlan gqa_plan(int kv_len, long n_bg, int head_dim) {
     return GqaPlan{n_bg * best < 240 ? 8 : 4, best};
 }
 
-int decode_gqa_num_splits(int kv_len, long n_bg, int head_dim) { return gqa_plan(kv_len, n_bg, head_dim).n_split; }
+int decode_gqa_num_splits(int kv_len, long n_bg, int group, int head_dim) { return gqa_plan(kv_len, n_bg, group, head_dim).n_split; }
 
 hipError_t launch_decode_gqa_split(const DecodeArgs& a, float* ws_acc, float* ws_ml, int n_split, hipStream_t stream,
                                    bool traffic_only) {
-    const GqaPlan plan = gqa_plan(a.kv_len, (long)a.batch * a.kv_heads, a.head_dim);
+    const GqaPlan plan = gqa_plan(a.kv_len, (long)a.batch * a.kv_heads, a.q_heads / a.kv_heads, a.head_dim);
     const float scale_log2e = a.softmax_scale * kLog2e;
     const dim3 grid((unsigned)n_split, (unsigned)a.kv_heads, (unsigned)a.batch);
     auto launch = [&](auto d_c, auto w_c, auto nc_c, auto traffic_c) {

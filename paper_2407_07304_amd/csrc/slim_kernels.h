@@ -51,9 +51,9 @@ struct DecodeArgs {
     float softmax_scale;
 };
 // Grouped-query variant (2 to 32 query heads per KV head): a workgroup sweeps a run of tokens of one (batch, KV head)
-// for all its query heads and is a split.  n_bg = batch * kv_heads.
+// for all its query heads and is a split.  n_bg = batch * kv_heads, group = query heads per KV head.
 bool decode_uses_gqa_kernel(int q_heads, int kv_heads);
-int decode_gqa_num_splits(int kv_len, long n_bg, int head_dim);
+int decode_gqa_num_splits(int kv_len, long n_bg, int group, int head_dim);
 // traffic_only: the measurement form (the kernel's loads without its arithmetic; what it writes is meaningless)
 hipError_t launch_decode_gqa_split(const DecodeArgs& a, float* ws_acc, float* ws_ml, int n_split, hipStream_t stream,
                                    bool traffic_only = false);
@@ -63,5 +63,9 @@ hipError_t launch_decode(const DecodeArgs& a, hipStream_t stream);
 // allocate: its address on the current device, looked up on the first call there.
 constexpr size_t kDecodeStaticScratchBytes = (size_t)16 << 20;
 hipError_t decode_static_scratch(float** ptr);
+// Partial results (accumulator, max, sum) of n_rows (batch, query head) rows in n_split splits each
+inline size_t decode_records_bytes(long n_rows, int n_split, int head_dim) {
+    return (size_t)n_rows * n_split * ((size_t)head_dim + 2) * sizeof(float);
+}
 
 }  // namespace slim

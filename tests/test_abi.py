@@ -117,6 +117,18 @@ def test_decode_workspace_is_a_whole_number_of_split_records_for_every_geometry(
                 assert 1 <= splits <= (T + 31) // 32 + 1, (B, Hq, Hkv, T, D, splits)
 
 
+def test_rows_that_fit_the_static_scratch_fit_it_at_every_length(lib):
+    """The static entry point refuses a call for its rows, never for how many splits the plan would like: up to two
+    records a row within the scratch array, every cache length is taken (one record is enough for the per-head kernel)."""
+    limit = lib.slim_attn_decode_int8_static_max_bytes()
+    for D in (64, 128):
+        rec = (D + 2) * 4
+        for (B, Hq, Hkv) in ((200, 16, 2), (26, 120, 3), (127, 200, 5), (467, 32, 1), (375, 4, 4), (425, 16, 16), (1000, 16, 16), (1, 64, 8)):
+            for T in (64, 500, 1761, 4061, 8066, 16384, 65464):
+                n = lib.slim_attn_decode_int8_workspace_bytes(B, Hq, Hkv, T, D)
+                assert 0 < n <= max(limit, B * Hq * rec * (1 if Hq == Hkv else 2)), (B, Hq, Hkv, T, D, n)
+
+
 def test_varlen_decode_rejects_bad_arguments(lib):
     f = lib.slim_attn_decode_int8_varlen
 
