@@ -543,6 +543,19 @@ def test_decode_grouped_queries_of_mixed_magnitude(sa, oracle, D, Hq):
         check_close(host_f64(out)[:, rows], want[:, rows], "mixed magnitudes, k scale %g" % k_mag)
 
 
+def test_measurement_form_of_the_grouped_decode_on_an_unsplit_call(sa):
+    # it has a workspace and no output: a call that the plan does not split writes its records there as well
+    from paper_2407_07304_amd import probes
+    B, Hq, Hkv, T, D = 2, 8, 2, 100, 128
+    codes, scales = torch.ones((B, Hkv, T, D), dtype=torch.int8, device="cuda"), torch.ones((B, Hkv, T), device="cuda")
+    q = torch.ones((B, Hq, 1, D), dtype=torch.bfloat16, device="cuda")
+    need = sa.slim_attn_decode_int8_workspace_bytes(B, Hq, Hkv, T, D)
+    ws = torch.full((need // 4 + 64,), 7.0, device="cuda")
+    probes.slim_probe_gqa_decode_traffic(q, codes, scales, codes, scales, ws[:need // 4].view(torch.uint8))
+    torch.cuda.synchronize()
+    assert bool((ws[:B * Hq * D] == 0.0).all()) and bool((ws[need // 4:] == 7.0).all())
+
+
 @pytest.mark.parametrize("D,Hq,Hkv", [(128, 4, 4), (128, 16, 2), (64, 8, 8), (64, 6, 3)])
 def test_decode_per_sequence_lengths(sa, oracle, D, Hq, Hkv):
     # every sequence attends to its own number of cached tokens (one tile, ragged tails, the whole allocation);
