@@ -9,6 +9,7 @@
 
 #include <ATen/core/Tensor.h>
 #include <ATen/ops/empty.h>
+#include <c10/core/DefaultDtype.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -68,7 +69,14 @@ Dims4 dims4(const at::Tensor& t) {
 // Sizes reach the library as C ints; one that does not fit is passed on as 0, which the library refuses.
 inline int c_int(int64_t v) { return v >= 0 && v <= 0x7fffffff ? (int)v : 0; }
 
+// Lets other Python threads run: an allocation may have to wait for the device.
+struct WithoutInterpreterLock {
+    PyThreadState* const state = PyEval_SaveThread();
+    ~WithoutInterpreterLock() { PyEval_RestoreThread(state); }
+};
+
 at::Tensor make(std::initializer_list<int64_t> shape, at::ScalarType dtype, const at::Tensor& like) {
+    const WithoutInterpreterLock unlocked;
     return at::empty(at::IntArrayRef(shape.begin(), shape.size()), like.options().dtype(dtype).requires_grad(false));
 }
 
@@ -82,8 +90,9 @@ int as_flag(PyObject* o) {
     if (v < 0) throw Failed();
     return v;
 }
-// torch.bfloat16 or torch.float32, as the library's code
+// The result's type; None is torch's default type, as for torch.empty
 at::ScalarType out_type(PyObject* o) {
+    if (!given(o)) return c10::typeMetaToScalarType(c10::get_default_dtype());
     if (!THPDtype_Check(o)) fail(PyExc_TypeError, "out_dtype must be a torch.dtype");
     return reinterpret_cast<THPDtype*>(o)->scalar_type;
 }

@@ -1114,3 +1114,9 @@ def test_sharp_softmax_decode_stays_within_the_rounding_bound(sa, oracle, Hq, Hk
     err = np.abs(host_f64(out) - want)
     worst = np.unravel_index(np.argmax(err - bound), err.shape)
     assert (err <= bound).all(), "element %s: error %.3e above its bound %.3e" % (worst, err[worst], bound[worst])
+
+
+def test_prefill_output_type_left_to_torch(sa):
+    # out_dtype=None stands for torch's default type, as in torch.empty
+    q = dev_bf16(normal_bf16(np.random.default_rng(5), (1, 2, 40, 64)))
+    assert torch.equal(sa.slim_attn_prefill(q, q, q, 0.125, out_dtype=None), sa.slim_attn_prefill(q, q, q, 0.125, out_dtype=torch.float32))
