@@ -163,7 +163,11 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_gqa_kernel(
         amax = max(amax, (unsigned)__shfl_xor((int)amax, 16));
         amax = max(amax, (unsigned)__shfl_xor((int)amax, 32));
         const int e = max((int)(amax >> 7) - 126, -60);   // |q| < 2^e (below 2^-60 the digits run out: those scores vanish)
-        unit[nc] = __builtin_amdgcn_ldexpf(1.0f, e - 22);
+        // (a row with an infinity or a NaN has no fixed point: its scores become NaN, and so does its result, as they would in
+        // floating point.  The compiler is told that there are no NaNs and must not see this one.)
+        unsigned unit_bits = amax < 0x7f80u ? __float_as_uint(__builtin_amdgcn_ldexpf(1.0f, e - 22)) : 0x7fc00000u;
+        asm volatile("" : "+v"(unit_bits));
+        unit[nc] = __uint_as_float(unit_bits);
         const float up = 16 * nc + l16 < G ? __builtin_amdgcn_ldexpf(1.0f, 22 - e) : 0.0f;   // (a column without a head: zeros)
 #pragma unroll
         for (int s = 0; s < KS; ++s)
@@ -315,7 +319,7 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_gqa_kernel(
         L += __shfl_xor(L, 16);
         L += __shfl_xor(L, 32);
         if (lq == 0) {
-            rec[16 * nc + l16] = M[nc] * unit[nc];
+            rec[16 * nc + l16] = n_tiles > 0 ? M[nc] * unit[nc] : kMasked;   // (kMasked in units may be any size: inf where q is huge)
             rec[16 * NC + 16 * nc + l16] = L;
         }
 #pragma unroll

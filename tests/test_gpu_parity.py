@@ -592,6 +592,39 @@ def test_decode_per_sequence_lengths(sa, oracle, D, Hq, Hkv):
     check_close(host_f64(out2), expect([1, 1, 1, 1500, 1500, 1500]), "decode with clamped lengths")
 
 
+@pytest.mark.parametrize("D,Hq,Hkv", [(128, 16, 2), (64, 6, 3)])
+def test_grouped_decode_of_extreme_queries(sa, oracle, D, Hq, Hkv):
+    # the grouped kernel takes a query row in fixed point: rows around 2^60 and around 2^-50, with sequences that leave
+    # most splits empty, and a row with an infinity or a NaN, whose result is not a number while every other row's is
+    rng = np.random.default_rng(83 + D + Hq)
+    B, T = 4, 1500
+    lens = np.array([1, 33, 700, 1500], dtype=np.int32)
+    q = normal_bf16(rng, (B, Hq, 1, D))
+    k, v = normal_bf16(rng, (B, Hkv, T, D)), normal_bf16(rng, (B, Hkv, T, D))
+    kc, ks = oracle.kv_quant_int8(k)
+    vc, vs = oracle.kv_quant_int8(v)
+    scale = 1.0 / math.sqrt(D)
+    args = (dev(kc), dev(ks), dev(vc), dev(vs), torch.from_numpy(lens).cuda(), scale)
+    for shift in (60, -50):
+        qs = np.where(q & 0x7fff, q.astype(np.int32) + shift * 128, q).astype(np.uint16)   # times 2^shift, exact
+        got = host_f64(sa.slim_attn_decode_int8_varlen(dev_bf16(qs), *args))
+        for b, n in enumerate(lens):
+            want = oracle.attn(qs[b:b + 1], kc[b:b + 1, :, :n], vc[b:b + 1, :, :n], scale, False, k_scale=ks[b:b + 1, :, :n],
+                               v_scale=vs[b:b + 1, :, :n])
+            # p * v_scale and the result are rounded to bf16: 2^-8 of sum p |v| and of the result.  At 2^60 one key has
+            # all of p, at 2^-50 all keys have the same
+            v_abs = np.repeat(np.abs(vc[b, :, :n] * vs[b, :, :n, None].astype(np.float64)).mean(axis=1), Hq // Hkv, axis=0)[None, :, None]
+            bound = 2.0 ** -8 * (np.abs(want) + (np.abs(want) if shift > 0 else v_abs)) + 1e-6
+            assert (np.abs(got[b:b + 1] - want) <= bound).all(), (shift, n, float(np.abs(got[b:b + 1] - want).max()))
+    for bad in (0x7f80, 0xff80, 0x7fc0):
+        qn = q.copy()
+        qn[1, 1, 0, 5] = bad
+        got = host_f64(sa.slim_attn_decode_int8_varlen(dev_bf16(qn), *args))
+        assert np.isnan(got[1, 1]).all()
+        got[1, 1] = 0.0
+        assert np.isfinite(got).all()
+
+
 @pytest.mark.parametrize("D,Hq,Hkv", [(128, 8, 2), (64, 4, 4)])
 def test_append_then_decode_serving_step(sa, oracle, D, Hq, Hkv):
     # one step of a serving loop: the new token's K and V rows are quantised into each sequence's cache at its
