@@ -9,22 +9,23 @@
 //   - K and V tiles are read with coalesced 128-bit loads (a load instruction of a wave
 //     covers whole rows) and written, as the INT8 codes they are, to a wave-private LDS tile
 //     each.  No other wave touches them: no barriers, LDS runs a wave's accesses in order.
-//   - scores, transposed, on the INT8 matrix instruction: S^T = K Q^T with
-//     v_mfma_i32_16x16x64_i8, the K tile as A operand (lane = token, 128-bit LDS reads, no
-//     widening), Q^T as B operand (columns = heads).  Q enters as three signed base-256
-//     digits of its value in fixed point (23 bits and sign below the power of two above the
-//     row's largest magnitude: exact for every bf16 value down to 2^-15 of it), one product
-//     per digit, so a score is an exact integer sum until it is put together in fp32.
+//   - scores, transposed, S^T = K Q^T with v_mfma_f32_16x16x32_bf16: the K tile as A operand
+//     (lane = token, 128-bit LDS reads, widened to bf16 in registers, exact), Q^T as B operand
+//     (columns = heads) as the caller gave it.  (Q cut into three INT8 digits for the INT8
+//     instruction, K unwidened, took the same time and lost bits of values far below their
+//     row's largest: B=16, 64 on 8 heads, T=8192 49.5 us against 49.3, 48 sequences of up to
+//     3001 tokens, 32 on 8 heads 41.2 against 41.6.)
 //   - a lane then holds one head's column and 4 of every 16 tokens: k_scale multiplies the
 //     fp32 score, the running max is lazy (it moves when a score passes it by 2^8), the
 //     probability takes the token's v_scale before it is rounded to bf16 and is the B operand
-//     of O^T += V^T P^T (v_mfma_f32_16x16x32_bf16) as it stands; V^T comes from the row-major
+//     of O^T += V^T P^T (the same instruction) as it stands; V^T comes from the row-major
 //     INT8 tile through the LDS byte transpose read and is widened to bf16 in registers.
 //   - a wave's next tile is in flight while it works on one: its registers are refilled as soon
-//     as they are in LDS.  At three waves per SIMD (154 vector registers) that covers the
+//     as they are in LDS.  At three waves per SIMD (146 vector registers) that covers the
 //     memory latency; a second tile in flight took the third wave and was 5 % slower.
-// (Before, K and V were widened to bf16 on their way through LDS and both products ran on
-// 32-column bf16 tiles: 378 vector instructions per 32 tokens, 230 vector registers.)
+// (Before, K and V were widened to bf16 on their way into LDS and both products ran on
+// 32-column tiles, half of them empty for 16 heads: 230 vector registers, 57.7 us for B=16,
+// 64 on 8 heads, T=8192.)
 // The waves of a workgroup are merged in LDS; where a (batch, KV head) is split over several
 // workgroups, the combine kernel of decode.hip merges them in fixed order.
 #include <type_traits>
@@ -60,7 +61,7 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_gqa_kernel(
     const int8_t* __restrict__ vc, const float* __restrict__ vs, uint16_t* __restrict__ out, float* __restrict__ ws_acc,
     float* __restrict__ ws_ml, const int* __restrict__ kv_lens, int Hq, int Hkv, int T_alloc, int n_split,
     float scale_log2e) {
-    constexpr int KS = D / 64;            // k-steps of the score MFMA
+    constexpr int KS = D / 64;            // 16-byte pieces of a K row per lane (two k-steps of the score MFMA each)
     constexpr int DT = D / 16;            // 16-row tiles of O^T
     constexpr int CPR = D / 16;           // 16-byte pieces per row
     constexpr int NP = kGqaTile * CPR / 64;   // 128-bit loads per lane, tile and tensor
@@ -89,15 +90,16 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_gqa_kernel(
     const int first = (int)((long)n_all * sp / n_split) + w, end = (int)((long)n_all * (sp + 1) / n_split);
     const int n_tiles = first < end ? (end - first + W - 1) / W : 0;
 
-    // Q: lane holds head l16 of its group of 16, d = 64 s + 16 lq + [0,16)
-    u32x4 qraw[NC][KS][2];
+    // Q^T B operands: lane holds head l16 of its group of 16 (a column past the last head: the last head again),
+    // d = 64 s + 16 lq + 8 e + [0,8)
+    bf16x8 qB[NC][KS][2];
 #pragma unroll
     for (int nc = 0; nc < NC; ++nc) {
         const uint16_t* qp = q + ((long)b * Hq + (long)g * G + min(16 * nc + l16, G - 1)) * D + 16 * lq;
 #pragma unroll
         for (int s = 0; s < KS; ++s)
 #pragma unroll
-            for (int e = 0; e < 2; ++e) qraw[nc][s][e] = *reinterpret_cast<const u32x4*>(qp + 64 * s + 8 * e);
+            for (int e = 0; e < 2; ++e) qB[nc][s][e] = *reinterpret_cast<const bf16x8*>(qp + 64 * s + 8 * e);
     }
 
     // Piece lane + 64 n of a tile (row-major, 16 codes each), through buffer descriptors that cover exactly this
@@ -144,53 +146,7 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_gqa_kernel(
     issue_v(t_of(0));
     __builtin_amdgcn_sched_barrier(0);
 
-    // Q in fixed point: n = rint(q 2^(22-e)) with 2^e above the row's largest |q|, as digits n = 65536 d0 + 256 d1 + d2,
-    // d1 and d2 in [-128, 127].  unit: what a unit of the integer score is worth before the key's scale.
-    i32x4 qd[NC][3][KS];
-    float unit[NC];
-#pragma unroll
-    for (int nc = 0; nc < NC; ++nc) {
-        unsigned amax = 0u;
-#pragma unroll
-        for (int s = 0; s < KS; ++s)
-#pragma unroll
-            for (int e = 0; e < 2; ++e)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const unsigned v = qraw[nc][s][e][i];
-                    amax = max(amax, max(v & 0x7fffu, (v >> 16) & 0x7fffu));   // (bf16 magnitudes order as integers)
-                }
-        amax = max(amax, (unsigned)__shfl_xor((int)amax, 16));
-        amax = max(amax, (unsigned)__shfl_xor((int)amax, 32));
-        const int e = max((int)(amax >> 7) - 126, -60);   // |q| < 2^e (below 2^-60 the digits run out: those scores vanish)
-        // (a row with an infinity or a NaN has no fixed point: its scores become NaN, and so does its result, as they would in
-        // floating point.  The compiler is told that there are no NaNs and must not see this one.)
-        unsigned unit_bits = amax < 0x7f80u ? __float_as_uint(__builtin_amdgcn_ldexpf(1.0f, e - 22)) : 0x7fc00000u;
-        asm volatile("" : "+v"(unit_bits));
-        unit[nc] = __uint_as_float(unit_bits);
-        const float up = 16 * nc + l16 < G ? __builtin_amdgcn_ldexpf(1.0f, 22 - e) : 0.0f;   // (a column without a head: zeros)
-#pragma unroll
-        for (int s = 0; s < KS; ++s)
-#pragma unroll
-            for (int i4 = 0; i4 < 4; ++i4) {   // four values at a time: bytes d2, d1, d0 of four words -> a word per digit
-                unsigned x[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const unsigned v = qraw[nc][s][i4 / 2][2 * (i4 % 2) + i / 2];
-                    const float f = __uint_as_float((i & 1) ? (v & 0xffff0000u) : (v << 16));
-                    // f up + 1.5 2^23 + 0x8080 rounds to the integer and leaves n + 0x8080 in the low bits: bytes
-                    // d2 + 128, d1 + 128 and d0 + 64
-                    x[i] = (__float_as_uint(fmaf(f, up, 12615808.0f)) ^ 0x8080u) - 0x400000u;
-                }
-                const unsigned a01 = __builtin_amdgcn_perm(x[1], x[0], 0x05010400u), a23 = __builtin_amdgcn_perm(x[3], x[2], 0x05010400u);
-                const unsigned b01 = __builtin_amdgcn_perm(x[1], x[0], 0x0c0c0602u), b23 = __builtin_amdgcn_perm(x[3], x[2], 0x0c0c0602u);
-                qd[nc][2][s][i4] = (int)__builtin_amdgcn_perm(a23, a01, 0x05040100u);
-                qd[nc][1][s][i4] = (int)__builtin_amdgcn_perm(a23, a01, 0x07060302u);
-                qd[nc][0][s][i4] = (int)__builtin_amdgcn_perm(b23, b01, 0x05040100u);
-            }
-    }
-
-    // K fragment of token tile i, k-step s: row 16 i + l16, bytes 64 s + 16 lq + [0,16).  V^T fragment of tile dt: the
+    // K fragments of token tile tt, k-steps 2 s and 2 s + 1: row 16 tt + l16, bytes 64 s + 16 lq + [0,16).  V^T fragment of tile dt: the
     // 16 lanes of a group fetch 8 rows (2 lanes a row, 8 columns each) and lane j of the group receives column j of
     // them; the rows of group lq are the tokens its probabilities belong to: 4 lq + [0,4) and 16 + 4 lq + [0,4).
     const int k_addr = l16 * PITCH + 16 * lq;
@@ -198,7 +154,7 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_gqa_kernel(
     const int v_addr = (4 * lq + (v_row & 3) + 16 * (v_row >> 2)) * PITCH + 8 * (l16 & 1);
 
     f32x4 o[NC][DT];
-    float M[NC], lsum[NC];   // running max of this lane's head (in units of unit), this lane's part of the row sum
+    float M[NC], lsum[NC];   // running max of this lane's head (log2 units), this lane's part of the row sum
 #pragma unroll
     for (int nc = 0; nc < NC; ++nc) {
         M[nc] = kMasked;
@@ -227,40 +183,42 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_gqa_kernel(
         stage(kbuf, kS);
         scS[lane] = k_half ? sc * scale_log2e : sc;
         issue_k(t_next);
-        i32x4 kf[2][KS];
+        i32x4 kw[2][KS];
 #pragma unroll
         for (int tt = 0; tt < 2; ++tt)
 #pragma unroll
-            for (int s = 0; s < KS; ++s) kf[tt][s] = *reinterpret_cast<const i32x4*>(kS + k_addr + 16 * tt * PITCH + 64 * s);
+            for (int s = 0; s < KS; ++s) kw[tt][s] = *reinterpret_cast<const i32x4*>(kS + k_addr + 16 * tt * PITCH + 64 * s);
         __builtin_amdgcn_sched_barrier(0);
         stage(vbuf, vS);
         issue_v(t_next);
         __builtin_amdgcn_sched_barrier(0);
 
         // scores: register r of token tile tt is token 16 tt + 4 lq + r, column = head l16 of the group
+        bf16x8 kf[2][KS][2];
+#pragma unroll
+        for (int tt = 0; tt < 2; ++tt)
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                kf[tt][s][0] = widen8(i32x2{kw[tt][s][0], kw[tt][s][1]});
+                kf[tt][s][1] = widen8(i32x2{kw[tt][s][2], kw[tt][s][3]});
+            }
         u32x4 pw[NC];
 #pragma unroll
         for (int nc = 0; nc < NC; ++nc) {
-            i32x4 acc[2][3];
-#pragma unroll
-            for (int tt = 0; tt < 2; ++tt)
-#pragma unroll
-                for (int p = 0; p < 3; ++p) acc[tt][p] = i32x4{0, 0, 0, 0};
+            f32x4 acc[2] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}};
 #pragma unroll
             for (int s = 0; s < KS; ++s)
 #pragma unroll
-                for (int tt = 0; tt < 2; ++tt)
+                for (int e = 0; e < 2; ++e)
 #pragma unroll
-                    for (int p = 0; p < 3; ++p) acc[tt][p] = __builtin_amdgcn_mfma_i32_16x16x64_i8(kf[tt][s], qd[nc][p][s], acc[tt][p], 0, 0, 0);
+                    for (int tt = 0; tt < 2; ++tt)
+                        acc[tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[tt][s][e], qB[nc][s][e], acc[tt], 0, 0, 0);
             float u[8];
 #pragma unroll
             for (int tt = 0; tt < 2; ++tt) {
                 const f32x4 kf4 = *reinterpret_cast<const f32x4*>(&scS[16 * tt + 4 * lq]);
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int hi = (acc[tt][0][r] << 8) + acc[tt][1][r];   // |hi| < 2^29
-                    u[4 * tt + r] = fmaf((float)hi, 256.0f, (float)acc[tt][2][r]) * kf4[r];
-                }
+                for (int r = 0; r < 4; ++r) u[4 * tt + r] = acc[tt][r] * kf4[r];
             }
             if (t0 + kGqaTile > T) {   // the sequence ends inside this tile (or before it)
 #pragma unroll
@@ -270,22 +228,21 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_gqa_kernel(
 #pragma unroll
             for (int r = 2; r < 8; r += 2) umax = fmaxf(umax, fmaxf(u[r], u[r + 1]));
             // the running max moves only when a score has passed it by 2^8 (always on a wave's first tile)
-            if (__builtin_amdgcn_ballot_w64((umax - M[nc]) * unit[nc] > 8.0f) != 0) {
+            if (__builtin_amdgcn_ballot_w64(umax - M[nc] > 8.0f) != 0) {
                 float m_new = fmaxf(M[nc], umax);
                 m_new = fmaxf(m_new, __shfl_xor(m_new, 16));
                 m_new = fmaxf(m_new, __shfl_xor(m_new, 32));
-                const float alpha = fast_exp2((M[nc] - m_new) * unit[nc]);
+                const float alpha = fast_exp2(M[nc] - m_new);
 #pragma unroll
                 for (int dt = 0; dt < DT; ++dt) o[nc][dt] *= alpha;
                 lsum[nc] *= alpha;
                 M[nc] = m_new;
             }
-            const float mu = M[nc] * unit[nc];
             float ps0 = 0.0f, ps1 = 0.0f;
 #pragma unroll
             for (int r = 0; r < 8; r += 2) {
-                u[r] = fast_exp2(fmaf(u[r], unit[nc], -mu));
-                u[r + 1] = fast_exp2(fmaf(u[r + 1], unit[nc], -mu));
+                u[r] = fast_exp2(u[r] - M[nc]);
+                u[r + 1] = fast_exp2(u[r + 1] - M[nc]);
                 ps0 += u[r];
                 ps1 += u[r + 1];
             }
@@ -319,7 +276,7 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_gqa_kernel(
         L += __shfl_xor(L, 16);
         L += __shfl_xor(L, 32);
         if (lq == 0) {
-            rec[16 * nc + l16] = n_tiles > 0 ? M[nc] * unit[nc] : kMasked;   // (kMasked in units may be any size: inf where q is huge)
+            rec[16 * nc + l16] = M[nc];
             rec[16 * NC + 16 * nc + l16] = L;
         }
 #pragma unroll

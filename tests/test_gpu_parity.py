@@ -520,8 +520,8 @@ def test_decode_plan_edges(sa, oracle, B, Hq, Hkv, T, D):
 
 @pytest.mark.parametrize("D,Hq", [(128, 8), (64, 5)])
 def test_decode_grouped_queries_of_mixed_magnitude(sa, oracle, D, Hq):
-    # the grouped kernel holds a query row in fixed point below its largest value: rows whose values span the range of
-    # that form, tiny and huge rows, a row of zeros, and a cache whose scales make up for the row's magnitude
+    # rows whose values span 14 binades, tiny and huge rows, a row of zeros, and a cache whose scales make up for the
+    # row's magnitude
     rng = np.random.default_rng(7 + D)
     B, Hkv, T = 1, 1, 500
     x = rng.standard_normal((B, Hq, 1, D)).astype(np.float32)
@@ -541,6 +541,44 @@ def test_decode_grouped_queries_of_mixed_magnitude(sa, oracle, D, Hq):
         torch.cuda.synchronize()
         want = oracle.attn(q, kc, vc, 1.0 / math.sqrt(D), False, k_scale=ks, v_scale=vs)
         check_close(host_f64(out)[:, rows], want[:, rows], "mixed magnitudes, k scale %g" % k_mag)
+
+
+@pytest.mark.parametrize("D,Hq", [(128, 8), (64, 20)])
+def test_grouped_decode_query_values_enter_exactly(sa, oracle, D, Hq):
+    # Two values of a row that are each other's negative, on keys that have the same code in both places, or none: every
+    # score is exactly zero, every probability exactly 1, and as many values of +64 as of -64 add up to zero, exactly.
+    # The pair is the row's largest magnitude, with the largest mantissas, either sign first.
+    T = 64
+    kc, vc = np.zeros((1, 1, T, D), dtype=np.int8), np.full((1, 1, T, D), -64, dtype=np.int8)
+    kc[0, 0, ::2, :2], vc[0, 0, ::2] = 10, 64
+    ones = dev(np.ones((1, 1, T), dtype=np.float32))
+    for top in (0x7d, 0x7e, 0x7f):
+        x = np.zeros((1, Hq, 1, D), dtype=np.uint16)
+        for h in range(Hq):
+            mag = ((120 + h) << 7) | top
+            x[0, h, 0, h % 2], x[0, h, 0, 1 - h % 2] = mag, mag | 0x8000
+        got = host_f64(sa.slim_attn_decode_int8(dev_bf16(x), dev(kc), ones, dev(vc), ones, 1.0 / math.sqrt(D)))
+        assert (got == 0.0).all(), (hex(top), float(np.abs(got).max()))
+
+
+@pytest.mark.parametrize("D,Hq,Hkv", [(128, 8, 1), (64, 40, 2)])
+@pytest.mark.parametrize("outlier,shift", [(16, 0), (20, 0), (60, 0), (10, -75)])
+def test_grouped_decode_of_queries_with_an_outlier_channel(sa, oracle, D, Hq, Hkv, outlier, shift):
+    # one value of 2^outlier in rows of N(0, 1), on keys that are zero in that place: the rest of the row decides.  The
+    # rows are scaled by 2^shift and the keys' scales by its inverse
+    rng = np.random.default_rng(85 + D + outlier)
+    x = rng.standard_normal((1, Hq, 1, D)).astype(np.float32)
+    x[..., 5] = 2.0 ** outlier
+    q = f32_to_bf16_bits((x * 2.0 ** shift).astype(np.float32))
+    for T in (5, 400):
+        k = normal_bf16(rng, (1, Hkv, T, D))
+        k[..., 5] = 0
+        kc, ks = oracle.kv_quant_int8(k)
+        vc, vs = oracle.kv_quant_int8(normal_bf16(rng, (1, Hkv, T, D)))
+        ks = (ks * np.float32(2.0 ** -shift)).astype(np.float32)
+        scale = 4.0 / math.sqrt(D)
+        got = host_f64(sa.slim_attn_decode_int8(dev_bf16(q), dev(kc), dev(ks), dev(vc), dev(vs), scale))
+        check_close(got, oracle.attn(q, kc, vc, scale, False, k_scale=ks, v_scale=vs), "outlier 2^%d, T=%d" % (outlier, T))
 
 
 def test_measurement_form_of_the_grouped_decode_on_an_unsplit_call(sa):
@@ -594,8 +632,7 @@ def test_decode_per_sequence_lengths(sa, oracle, D, Hq, Hkv):
 
 @pytest.mark.parametrize("D,Hq,Hkv", [(128, 16, 2), (64, 6, 3)])
 def test_grouped_decode_of_extreme_queries(sa, oracle, D, Hq, Hkv):
-    # the grouped kernel takes a query row in fixed point: rows around 2^60 and around 2^-50, with sequences that leave
-    # most splits empty, and a row with an infinity or a NaN, whose result is not a number while every other row's is
+    # rows around 2^60 and around 2^-50, with sequences that leave most splits empty, and a row with an infinity or a NaN, whose result is not a number while every other row's is
     rng = np.random.default_rng(83 + D + Hq)
     B, T = 4, 1500
     lens = np.array([1, 33, 700, 1500], dtype=np.int32)
