@@ -58,8 +58,14 @@ inline void require_shape(const at::Tensor& t, std::initializer_list<int64_t> wa
     require(s.size() == want.size() && std::equal(s.begin(), s.end(), want.begin()), text);
 }
 
+// A result the caller passes is written densely from its first element: it has to hold all of it (its shape is the
+// caller's affair: a flat buffer, or one that has room for more, will do).
+inline void require_room(const at::Tensor& t, int64_t n, const char* text) { require(t.numel() >= n, text); }
+
 struct Dims4 {
     int64_t b, h, s, d;
+    int64_t rows() const { return b * h * s; }
+    int64_t count() const { return rows() * d; }
 };
 Dims4 dims4(const at::Tensor& t) {
     if (t.dim() != 4) fail(PyExc_ValueError, "expected a tensor of four dimensions");
@@ -145,6 +151,8 @@ PyObject* kv_quant(Args a) {
     const Dims4 n = dims4(x);
     const at::Tensor codes = out_or_new(a[1], {n.b, n.h, n.s, n.d}, at::kChar, x);
     const at::Tensor scales = out_or_new(a[2], {n.b, n.h, n.s}, at::kFloat, x);
+    require_room(codes, n.count(), "codes is too small");
+    require_room(scales, n.rows(), "scales is too small");
     void* const xp = bf16_ptr(x);
     int8_t* const cp = i8_ptr(codes);
     float* const sp = f32_ptr(scales);
@@ -197,7 +205,10 @@ PyObject* kv_quant_append(Args a) {
 
 // The result tensor of a prefill: [B, Hq, S, D], bf16 or fp32
 at::Tensor prefill_out(PyObject* out, PyObject* dtype, const Dims4& n, const at::Tensor& q) {
-    const at::Tensor o = given(out) ? tensor(out) : make({n.b, n.h, n.s, n.d}, out_type(dtype), q);
+    const at::ScalarType t = given(out) ? tensor(out).scalar_type() : out_type(dtype);
+    require(t == at::kBFloat16 || t == at::kFloat, "out is bf16 or fp32");
+    const at::Tensor o = given(out) ? tensor(out) : make({n.b, n.h, n.s, n.d}, t, q);
+    require_room(o, n.count(), "out is too small");
     return o;
 }
 int out_code(const at::Tensor& o) { return o.scalar_type() == at::kFloat ? SLIM_F32 : SLIM_BF16; }
@@ -218,7 +229,6 @@ PyObject* prefill(Args a) {
     }
     const at::Tensor out = prefill_out(a[7], a[8], n, q);
     require_shape(out, {n.b, n.h, n.s, n.d}, "shape of out");
-    require(out.scalar_type() == at::kBFloat16 || out.scalar_type() == at::kFloat, "out is bf16 or fp32");
     void *const qp = bf16_ptr(q), *const kp = ptr(k), *const vp = ptr(v);
     if (given(a[5])) ks = f32_ptr(tensor(a[5]));
     if (given(a[6])) vs = f32_ptr(tensor(a[6]));
@@ -299,7 +309,7 @@ struct DecodeIn {
     void* q;
     const int8_t *kc, *vc;
     const float *ks, *vs;
-    explicit DecodeIn(Args a) {
+    explicit DecodeIn(Args a) {   // the sizes
         const at::Tensor &qt = tensor(a[0]), &kct = tensor(a[1]), &kst = tensor(a[2]), &vct = tensor(a[3]), &vst = tensor(a[4]);
         const Dims4 n = dims4(qt), c = dims4(kct);
         require(n.s == 1, "one query token per sequence");
@@ -308,6 +318,9 @@ struct DecodeIn {
         require(vct.sizes() == kct.sizes(), "k_codes and v_codes have one shape");
         require_shape(kst, {b, hkv, t}, "shape of k_scale");
         require_shape(vst, {b, hkv, t}, "shape of v_scale");
+    }
+    void take_pointers(Args a) {   // (once the results are allocated: that may let other threads run)
+        const at::Tensor &qt = tensor(a[0]), &kct = tensor(a[1]), &kst = tensor(a[2]), &vct = tensor(a[3]), &vst = tensor(a[4]);
         q = bf16_ptr(qt), kc = i8_ptr(kct), ks = f32_ptr(kst), vc = i8_ptr(vct), vs = f32_ptr(vst);
     }
 };
@@ -315,20 +328,19 @@ struct DecodeIn {
 // q, k_codes, k_scale, v_codes, v_scale, softmax_scale, causal, out, workspace, and kv_lens with VARLEN
 template <bool VARLEN>
 PyObject* decode(Args a) {
-    const DecodeIn in(a);
+    DecodeIn in(a);
     const at::Tensor& q = tensor(a[0]);
-    const int32_t* lens = nullptr;
-    if (VARLEN) {
-        require_shape(tensor(a[9]), {in.b}, "one length per sequence");
-        lens = i32_ptr(tensor(a[9]));
-    }
+    if (VARLEN) require_shape(tensor(a[9]), {in.b}, "one length per sequence");
     const at::Tensor out = out_or_new(a[7], {in.b, in.hq, 1, in.d}, at::kBFloat16, q);
+    require_room(out, in.b * in.hq * in.d, "out is too small");
     at::Tensor fresh_ws;
     if (!given(a[8])) {
         const size_t need = slim_attn_decode_int8_workspace_bytes(c_int(in.b), c_int(in.hq), c_int(in.hkv), c_int(in.t), c_int(in.d));
         fresh_ws = make({(int64_t)std::max<size_t>(need, 16)}, at::kByte, q);
     }
     const at::Tensor& ws = given(a[8]) ? tensor(a[8]) : fresh_ws;
+    in.take_pointers(a);
+    const int32_t* const lens = VARLEN ? i32_ptr(tensor(a[9])) : nullptr;
     void *const op = bf16_ptr(out), *const wp = ptr(ws);
     const size_t ws_bytes = ws.nbytes();
     const int causal = as_flag(a[6]);
@@ -344,9 +356,10 @@ PyObject* decode(Args a) {
 
 // q, k_codes, k_scale, v_codes, v_scale, softmax_scale, out, causal
 PyObject* decode_static(Args a) {
-    const DecodeIn in(a);
+    DecodeIn in(a);
     const at::Tensor& out = tensor(a[6]);
     require_shape(out, {in.b, in.hq, 1, in.d}, "shape of out");
+    in.take_pointers(a);
     void* const op = bf16_ptr(out);
     const int causal = as_flag(a[7]);
     const float scale = as_float(a[5]);
