@@ -195,7 +195,8 @@ int slim_attn_prefill_emit_int8(const void* q_bf16, const void* k_bf16, const vo
 
 size_t slim_attn_decode_int8_workspace_bytes(int batch, int q_heads, int kv_heads, int kv_len, int head_dim) {
     if (check_shape(batch, q_heads, kv_heads, kv_len, head_dim) != SLIM_OK) return 0;
-    return slim::decode_workspace_bytes(batch, q_heads, kv_heads, kv_len, head_dim);
+    // (one answer for both entry points: the plan for sequences of different lengths never has fewer splits)
+    return slim::decode_workspace_bytes(batch, q_heads, kv_heads, kv_len, head_dim, true);
 }
 
 constexpr size_t kUseStaticScratch = ~(size_t)0;   // decode_common: workspace == NULL with this size selects the static array
@@ -215,7 +216,7 @@ static int decode_common(const void* q_bf16, const int8_t* k_codes, const float*
         misaligned(v_scale) || misaligned(out_bf16) || misaligned(workspace))
         return SLIM_ERR_ALIGN;
     if (kv_lens && ((uintptr_t)kv_lens & 3u)) return SLIM_ERR_ALIGN;
-    const size_t need = slim::decode_workspace_bytes(batch, q_heads, kv_heads, kv_len, head_dim);
+    const size_t need = slim::decode_workspace_bytes(batch, q_heads, kv_heads, kv_len, head_dim, false);
     if (use_static) {
         if (need > slim::kDecodeStaticScratchBytes) return SLIM_ERR_WORKSPACE;
         float* own = nullptr;
@@ -239,6 +240,8 @@ static int decode_common(const void* q_bf16, const int8_t* k_codes, const float*
     a.kv_len = kv_len;
     a.head_dim = head_dim;
     a.softmax_scale = softmax_scale;
+    // (a workspace that holds only the splits of equal lengths is enough for those)
+    a.ragged = kv_lens && workspace_bytes >= slim::decode_workspace_bytes(batch, q_heads, kv_heads, kv_len, head_dim, true);
     drop_stale_hip_error();
     const hipError_t e = slim::launch_decode(a, (hipStream_t)stream);
     return e == hipSuccess ? SLIM_OK : SLIM_ERR_LAUNCH;

@@ -3,7 +3,7 @@
 // in registers and fed to FMAs, with one scale per token per head).
 //
 // HBM-bound streaming kernel.  A workgroup of 4 or 8 waves serves one (batch, query head) and
-// one split of the key axis (the whole of it wherever the rows alone fill the chip); its
+// one split of the key axis (the whole of it wherever equal rows alone fill the chip); its
 // chunks of 64 tokens are dealt to the waves in turn, so that the workgroup sweeps one
 // contiguous piece of the cache (on the B=16, 32 heads, T=8192 cache 8 % faster than a
 // contiguous run of 512 tokens per wave, which 6.1 TB/s was the ceiling of):
@@ -19,6 +19,7 @@
 //     exchange of the chunk's probabilities;
 //   - slots and waves are merged in LDS at the end, and where there are several splits a second
 //     kernel merges them in a fixed order (no atomics: the result does not depend on arrival order).
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -56,7 +57,7 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_split_kernel(
     const uint16_t* __restrict__ q, const int8_t* __restrict__ kc, const float* __restrict__ ks,
     const int8_t* __restrict__ vc, const float* __restrict__ vs, uint16_t* __restrict__ out,
     float* __restrict__ ws_acc, float* __restrict__ ws_ml, const int* __restrict__ kv_lens, int Hq, int Hkv, int T_alloc,
-    int n_split, float scale_log2e) {
+    int n_split, unsigned split_rate, float scale_log2e) {
     constexpr int LPR = D / 16;        // lanes per token row
     constexpr int SLOTS = 64 / LPR;    // token rows per load instruction of a wave
     constexpr int CH = LPR;            // rows per slot per chunk: SLOTS * CH == kChunk, one token per lane
@@ -74,6 +75,8 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_split_kernel(
     const int g = h / (Hq / Hkv);
     // T_alloc is the cache's allocated length (the row stride); this sequence's first T tokens count
     const int T = kv_lens ? min(max(kv_lens[b], 1), T_alloc) : T_alloc;
+    const int n_used = splits_of(T, n_split, split_rate);
+    if (sp >= n_used) return;   // (nobody reads this split's record)
     const long kvbase = ((long)b * Hkv + g) * (long)T_alloc;
     // Buffer descriptors over exactly this (batch, KV head)'s first T tokens: a row past the end reads as zeros (and
     // is masked below), an address is one 32-bit offset per lane plus a constant per row, and the descriptors live in
@@ -84,10 +87,10 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_split_kernel(
     const __amdgpu_buffer_rsrc_t ksr = __builtin_amdgcn_make_buffer_rsrc((void*)(ks + kvbase), 0, (int)((unsigned)T * 4u), 0x00020000);
     const __amdgpu_buffer_rsrc_t vsr = __builtin_amdgcn_make_buffer_rsrc((void*)(vs + kvbase), 0, (int)((unsigned)T * 4u), 0x00020000);
     const int lane_off = (s * CH) * D + c * 16;   // this lane's piece of its slot's first row, relative to the chunk
-    // The sequence's own chunks are dealt evenly over the splits, and a split's chunks to its waves in turn: the
+    // The sequence's own chunks are dealt evenly over its splits, and a split's chunks to its waves in turn: the
     // waves of a workgroup read adjacent pieces of the cache at a time.
     const int n_all = (T + kChunk - 1) / kChunk;
-    const int c_begin = (int)((long)n_all * sp / n_split) + w, c_end = (int)((long)n_all * (sp + 1) / n_split);
+    const int c_begin = (int)((long)n_all * sp / n_used) + w, c_end = (int)((long)n_all * (sp + 1) / n_used);
     const int n_chunks = c_begin < c_end ? (c_end - c_begin + W - 1) / W : 0;
 
     // this lane's 16 query values, fp32
@@ -241,7 +244,7 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_split_kernel(
 #pragma unroll
         for (int i = 0; i < PARTS; ++i) o += oS[i][d];
         const long bh = (long)b * Hq + h;
-        if (n_split == 1) {
+        if (n_used == 1) {
             out[bh * D + d] = (uint16_t)(pack_bf16x2(o / L, 0.0f) & 0xffffu);
         } else {
             const long idx = bh * n_split + sp;
@@ -267,11 +270,15 @@ constexpr int kCombineChunk = 16;
 template <int D, int PARTS>
 __global__ __launch_bounds__(D * PARTS) void slim_decode_combine_kernel(const float* __restrict__ ws_acc,
                                                                         const float* __restrict__ ws_ml,
-                                                                        uint16_t* __restrict__ out, int n_split) {
+                                                                        uint16_t* __restrict__ out,
+                                                                        const int* __restrict__ kv_lens, int T_alloc,
+                                                                        int n_split, unsigned split_rate) {
     constexpr int CH = kCombineChunk;
-    const long bh = blockIdx.x;
+    const long bh = (long)blockIdx.y * gridDim.x + blockIdx.x;
     const int d = threadIdx.x % D, part = threadIdx.x / D;
-    const int s_begin = PARTS == 1 ? 0 : n_split * part / PARTS, s_end = PARTS == 1 ? n_split : n_split * (part + 1) / PARTS;
+    const int n_used = splits_of(kv_lens ? min(max(kv_lens[blockIdx.y], 1), T_alloc) : T_alloc, n_split, split_rate);
+    if (n_used == 1) return;   // (its one workgroup has written the result)
+    const int s_begin = PARTS == 1 ? 0 : n_used * part / PARTS, s_end = PARTS == 1 ? n_used : n_used * (part + 1) / PARTS;
     const float* const ml = ws_ml + bh * n_split * 2;
     const float* const acc = ws_acc + bh * n_split * D + d;
     float M = kMasked, L = 0.0f, o = 0.0f;
@@ -325,11 +332,12 @@ __global__ __launch_bounds__(D * PARTS) void slim_decode_combine_kernel(const fl
     out[bh * D + d] = (uint16_t)(pack_bf16x2(o / L, 0.0f) & 0xffffu);
 }
 
-static hipError_t launch_combine(const DecodeArgs& a, const float* ws_acc, const float* ws_ml, int n_split, hipStream_t stream) {
+static hipError_t launch_combine(const DecodeArgs& a, const float* ws_acc, const float* ws_ml, int n_split, unsigned split_rate,
+                                 hipStream_t stream) {
     auto launch = [&](auto d_c, auto parts_c) {
         constexpr int D = decltype(d_c)::value, PARTS = decltype(parts_c)::value;
-        hipLaunchKernelGGL((slim_decode_combine_kernel<D, PARTS>), dim3((unsigned)(a.batch * a.q_heads)), dim3(D * PARTS), 0, stream,
-                           ws_acc, ws_ml, (uint16_t*)a.out, n_split);
+        hipLaunchKernelGGL((slim_decode_combine_kernel<D, PARTS>), dim3((unsigned)a.q_heads, (unsigned)a.batch), dim3(D * PARTS), 0, stream,
+                           ws_acc, ws_ml, (uint16_t*)a.out, a.kv_lens, a.kv_len, n_split, split_rate);
         return hipGetLastError();
     };
     auto pick = [&](auto d_c) {
@@ -349,14 +357,11 @@ static hipError_t launch_combine(const DecodeArgs& a, const float* ws_acc, const
 // workgroups, 164 us as 4 splits).  A split has at least a chunk for each of four waves, and a call is not split into more
 // records than the library's own scratch holds (that many are 126 workgroups per compute unit and more, where a finer
 // split gains nothing): what decides whether slim_attn_decode_int8_static takes a shape is then its rows alone.
-struct DecodePlan {
-    int waves, n_split;
-};
 static DecodePlan decode_plan(int kv_len, long n_bh, int head_dim) {
     const long n_chunks = ((long)kv_len + kChunk - 1) / kChunk;
     const double ns_token = head_dim == 128 ? 7.1 : 5.8;
     const double stream_ns = (double)kv_len * n_bh * (2 * head_dim + 8) / 6600.0;
-    DecodePlan best{4, 1};
+    DecodePlan best{4, 1, kAllSplits};
     double best_ns = 0.0;
     for (int s : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256}) {
         if (s > 1 && (s * 4 > n_chunks || decode_records_bytes(n_bh, s, head_dim) > kDecodeStaticScratchBytes)) break;
@@ -375,18 +380,45 @@ static DecodePlan decode_plan(int kv_len, long n_bh, int head_dim) {
     return best;
 }
 
+// The plan for sequences of different lengths (kv_lens; the host knows only the allocated length).  The plan for equal
+// lengths cuts no finer than those need, and a sequence much longer than the others would then be a serial chain on an
+// idle chip.  So, where one sequence makes fewer than 128 workgroups, all at full length get about 1536 of them (768 of
+// the grouped kernel, whose tokens cost half as much) of at least 2048 tokens (the grouped kernel: 4096 of 128 codes);
+// a shorter sequence takes a split per 512 tokens until it has them all, and the workgroups past that leave at once.
+// Microseconds cut as for equal lengths -> now, one sequence of full length among sequences of 512 tokens, then lengths
+// spread over an eighth to all of the cache, then all equal, then all of 300 tokens:
+//   8 sequences, 32 heads, T=65536: 303 -> 87, 432 -> 373, 623 -> 629, 6 -> 13
+//   32 sequences, 8 heads, T=16384: 78 -> 24, 113 -> 107, 160 -> 165, 7 -> 13
+//   16 sequences, 32 on 8 heads, T=32768: 117 -> 47, 126 -> 108, 159 -> 167, 10 -> 9
+//   4 sequences, 64 on 8 heads, T=65536: 64 -> 39, 65 -> 60, 84 -> 87, 9 -> 12
+// (Two, four or eight workgroups a row are the worse choice: the long rows' workgroups meet on the same compute units.
+// With lengths spread as above and a split per T / n tokens 4 a row were 2 to 7 % slower than 6 with 256 rows.)
+static DecodePlan ragged_plan(DecodePlan plan, bool gqa, int batch, int q_heads, int kv_heads, int kv_len, int head_dim) {
+    const long heads = gqa ? kv_heads : q_heads, rows = batch * heads;
+    if (batch == 1 || heads * plan.n_split >= 128) return plan;   // (equal cuts: a lone sequence is dealt over all of them)
+    const long wanted = gqa ? 768 / rows : (1536 + rows - 1) / rows;
+    const long room = (long)(kDecodeStaticScratchBytes / decode_records_bytes((long)batch * q_heads, 1, head_dim));
+    const long n = std::min({wanted, (long)kv_len / (gqa ? 32 * head_dim : 2048), room});
+    return n <= plan.n_split ? plan : DecodePlan{gqa ? 4 : 8, (int)n, 1u << 23 /* 2^32 / 512 */};
+}
+
+// ragged: the sequences have lengths of their own
+static DecodePlan plan_of(bool ragged, int batch, int q_heads, int kv_heads, int kv_len, int head_dim) {
+    const bool gqa = decode_uses_gqa_kernel(q_heads, kv_heads);
+    const DecodePlan plan = gqa ? decode_gqa_plan(kv_len, (long)batch * kv_heads, q_heads / kv_heads, head_dim)
+                                : decode_plan(kv_len, (long)batch * q_heads, head_dim);
+    return ragged ? ragged_plan(plan, gqa, batch, q_heads, kv_heads, kv_len, head_dim) : plan;
+}
+
 bool decode_uses_gqa_kernel(int q_heads, int kv_heads) {
     const int G = q_heads / kv_heads;
     return G >= 2 && G <= 32;
 }
 
-size_t decode_workspace_bytes(int batch, int q_heads, int kv_heads, int kv_len, int head_dim) {
-    int n_split = decode_plan(kv_len, (long)batch * q_heads, head_dim).n_split;
-    if (decode_uses_gqa_kernel(q_heads, kv_heads)) {
-        // (never less than two records a row: the shapes the static scratch array is too small for stay what they were)
-        n_split = decode_gqa_num_splits(kv_len, (long)batch * kv_heads, q_heads / kv_heads, head_dim);
-        if (n_split < 2) n_split = 2;
-    }
+size_t decode_workspace_bytes(int batch, int q_heads, int kv_heads, int kv_len, int head_dim, bool ragged) {
+    int n_split = plan_of(ragged, batch, q_heads, kv_heads, kv_len, head_dim).n_split;
+    // (grouped heads: never less than two records a row, so that the shapes the static scratch array is too small for stay what they were)
+    if (decode_uses_gqa_kernel(q_heads, kv_heads) && n_split < 2) n_split = 2;
     return decode_records_bytes((long)batch * q_heads, n_split, head_dim);
 }
 
@@ -418,8 +450,8 @@ hipError_t decode_static_scratch(float** ptr) {
 hipError_t launch_decode(const DecodeArgs& a, hipStream_t stream) {
     // (the query heads of a KV head share one pass over its cache in the grouped-query kernel)
     const bool gqa = decode_uses_gqa_kernel(a.q_heads, a.kv_heads);
-    const DecodePlan plan = decode_plan(a.kv_len, (long)a.batch * a.q_heads, a.head_dim);
-    const int n_split = gqa ? decode_gqa_num_splits(a.kv_len, (long)a.batch * a.kv_heads, a.q_heads / a.kv_heads, a.head_dim) : plan.n_split;
+    const DecodePlan plan = plan_of(a.ragged, a.batch, a.q_heads, a.kv_heads, a.kv_len, a.head_dim);
+    const int n_split = plan.n_split;
     float* const ws_acc = a.workspace;
     float* const ws_ml = a.workspace + (size_t)a.batch * a.q_heads * n_split * a.head_dim;
     auto launch = [&](auto d_c, auto w_c) {
@@ -427,17 +459,17 @@ hipError_t launch_decode(const DecodeArgs& a, hipStream_t stream) {
         hipLaunchKernelGGL((slim_decode_int8_split_kernel<D, W>), dim3((unsigned)n_split, (unsigned)a.q_heads, (unsigned)a.batch),
                            dim3(64 * W), 0, stream, (const uint16_t*)a.q, a.k_codes, a.k_scale, a.v_codes, a.v_scale,
                            (uint16_t*)a.out, ws_acc, ws_ml, a.kv_lens, a.q_heads, a.kv_heads, a.kv_len, n_split,
-                           a.softmax_scale * kLog2e);
+                           plan.split_rate, a.softmax_scale * kLog2e);
         return hipGetLastError();
     };
     auto pick_w = [&](auto d_c) {
         return plan.waves == 8 ? launch(d_c, std::integral_constant<int, 8>{}) : launch(d_c, std::integral_constant<int, 4>{});
     };
-    const hipError_t e = gqa                 ? launch_decode_gqa_split(a, ws_acc, ws_ml, n_split, stream)
+    const hipError_t e = gqa                 ? launch_decode_gqa_split(a, ws_acc, ws_ml, plan, stream)
                          : a.head_dim == 128 ? pick_w(std::integral_constant<int, 128>{})
                                              : pick_w(std::integral_constant<int, 64>{});
     if (e != hipSuccess || n_split == 1) return e;
-    return launch_combine(a, ws_acc, ws_ml, n_split, stream);
+    return launch_combine(a, ws_acc, ws_ml, n_split, plan.split_rate, stream);
 }
 
 }  // namespace slim

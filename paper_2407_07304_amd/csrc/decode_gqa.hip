@@ -60,7 +60,7 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_gqa_kernel(
     const uint16_t* __restrict__ q, const int8_t* __restrict__ kc, const float* __restrict__ ks,
     const int8_t* __restrict__ vc, const float* __restrict__ vs, uint16_t* __restrict__ out, float* __restrict__ ws_acc,
     float* __restrict__ ws_ml, const int* __restrict__ kv_lens, int Hq, int Hkv, int T_alloc, int n_split,
-    float scale_log2e) {
+    unsigned split_rate, float scale_log2e) {
     constexpr int KS = D / 64;            // 16-byte pieces of a K row per lane (two k-steps of the score MFMA each)
     constexpr int DT = D / 16;            // 16-row tiles of O^T
     constexpr int CPR = D / 16;           // 16-byte pieces per row
@@ -83,11 +83,13 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_gqa_kernel(
     float* const scS = reinterpret_cast<float*>(kS + 2 * TILE);   // [0,32) k_scale * c, [32,64) v_scale
 
     // T_alloc is the cache's allocated length (the row stride); this sequence's first T tokens count.  The sequence's
-    // own tiles are dealt evenly over the splits, and a split's tiles to its waves in turn.
+    // own tiles are dealt evenly over its splits, and a split's tiles to its waves in turn.
     const int T = kv_lens ? min(max(kv_lens[b], 1), T_alloc) : T_alloc;
+    const int n_used = splits_of(T, n_split, split_rate);
+    if (sp >= n_used) return;   // (nobody reads this split's record)
     const long kvrow0 = ((long)b * Hkv + g) * (long)T_alloc;
     const int n_all = (T + kGqaTile - 1) / kGqaTile;
-    const int first = (int)((long)n_all * sp / n_split) + w, end = (int)((long)n_all * (sp + 1) / n_split);
+    const int first = (int)((long)n_all * sp / n_used) + w, end = (int)((long)n_all * (sp + 1) / n_used);
     const int n_tiles = first < end ? (end - first + W - 1) / W : 0;
 
     // Q^T B operands: lane holds head l16 of its group of 16 (a column past the last head: the last head again),
@@ -301,7 +303,7 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_gqa_kernel(
             acc = fmaf(f, r[32 * NC + h * OPITCH + d], acc);
         }
         const long bh = (long)b * Hq + (long)g * G + h;
-        if (!TRAFFIC_ONLY && n_split == 1) {   // (the measurement form has a workspace only)
+        if (!TRAFFIC_ONLY && n_used == 1) {   // (the measurement form has a workspace only)
             out[bh * D + d] = (uint16_t)(pack_bf16x2(acc / L, 0.0f) & 0xffffu);
         } else {
             const long idx = bh * n_split + sp;
@@ -321,10 +323,7 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_gqa_kernel(
 // 40 ns a split for the combine launch.  Eight waves where a compute unit has at most one workgroup, four where the grid fills the
 // chip.  (8 rows at T=32768: 30.6 us before, on 512 waves, now 19.2; 128 rows at T=8192: 52.9 before, now 45.3 with 1024
 // waves in 256 workgroups, where 2048 waves take 49; both with the combine launch.)
-struct GqaPlan {
-    int waves, n_split;
-};
-static GqaPlan gqa_plan(int kv_len, long n_bg, int group, int head_dim) {
+DecodePlan decode_gqa_plan(int kv_len, long n_bg, int group, int head_dim) {
     const long n_tiles = ((long)kv_len + kGqaTile - 1) / kGqaTile;
     const double stream_ns = (double)kv_len * n_bg * (2 * head_dim + 8) / 6600.0;
     int best = 1;
@@ -341,21 +340,18 @@ static GqaPlan gqa_plan(int kv_len, long n_bg, int group, int head_dim) {
             best = s;
         }
     }
-    return GqaPlan{n_bg * best < 240 ? 8 : 4, best};
+    return DecodePlan{n_bg * best < 240 ? 8 : 4, best, kAllSplits};
 }
 
-int decode_gqa_num_splits(int kv_len, long n_bg, int group, int head_dim) { return gqa_plan(kv_len, n_bg, group, head_dim).n_split; }
-
-hipError_t launch_decode_gqa_split(const DecodeArgs& a, float* ws_acc, float* ws_ml, int n_split, hipStream_t stream,
+hipError_t launch_decode_gqa_split(const DecodeArgs& a, float* ws_acc, float* ws_ml, const DecodePlan& plan, hipStream_t stream,
                                    bool traffic_only) {
-    const GqaPlan plan = gqa_plan(a.kv_len, (long)a.batch * a.kv_heads, a.q_heads / a.kv_heads, a.head_dim);
     const float scale_log2e = a.softmax_scale * kLog2e;
-    const dim3 grid((unsigned)n_split, (unsigned)a.kv_heads, (unsigned)a.batch);
+    const dim3 grid((unsigned)plan.n_split, (unsigned)a.kv_heads, (unsigned)a.batch);
     auto launch = [&](auto d_c, auto w_c, auto nc_c, auto traffic_c) {
         constexpr int D = decltype(d_c)::value, W = decltype(w_c)::value, NC = decltype(nc_c)::value;
         hipLaunchKernelGGL((slim_decode_int8_gqa_kernel<D, W, NC, decltype(traffic_c)::value>), grid, dim3(64 * W), 0, stream,
                            (const uint16_t*)a.q, a.k_codes, a.k_scale, a.v_codes, a.v_scale, (uint16_t*)a.out, ws_acc, ws_ml,
-                           a.kv_lens, a.q_heads, a.kv_heads, a.kv_len, n_split, scale_log2e);
+                           a.kv_lens, a.q_heads, a.kv_heads, a.kv_len, plan.n_split, plan.split_rate, scale_log2e);
         return hipGetLastError();
     };
     auto pick = [&](auto d_c) {

@@ -132,8 +132,8 @@ int slim_probe_gqa_decode_traffic(const void* q_bf16, const int8_t* k_codes, con
     if (batch <= 0 || q_heads <= 0 || kv_heads <= 0 || kv_len <= 0 || (head_dim != 64 && head_dim != 128)) return 1;
     if (q_heads % kv_heads != 0 || q_heads / kv_heads < 2 || q_heads / kv_heads > 32) return 1;   // the shapes the grouped kernel serves
     if (misaligned(q_bf16) || misaligned(k_codes) || misaligned(k_scale) || misaligned(v_codes) || misaligned(v_scale) || misaligned(workspace)) return 1;
-    const int n_split = slim::decode_gqa_num_splits(kv_len, (long)batch * kv_heads, q_heads / kv_heads, head_dim);
-    const size_t n_part = (size_t)batch * q_heads * n_split;
+    const slim::DecodePlan plan = slim::decode_gqa_plan(kv_len, (long)batch * kv_heads, q_heads / kv_heads, head_dim);
+    const size_t n_part = (size_t)batch * q_heads * plan.n_split;
     if (workspace_bytes < n_part * ((size_t)head_dim + 2) * sizeof(float)) return 1;
     slim::DecodeArgs a;
     a.q = q_bf16;
@@ -150,8 +150,9 @@ int slim_probe_gqa_decode_traffic(const void* q_bf16, const int8_t* k_codes, con
     a.kv_len = kv_len;
     a.head_dim = head_dim;
     a.softmax_scale = 1.0f;
+    a.ragged = false;
     (void)hipGetLastError();
-    const hipError_t e = slim::launch_decode_gqa_split(a, a.workspace, a.workspace + n_part * head_dim, n_split, (hipStream_t)stream, true);
+    const hipError_t e = slim::launch_decode_gqa_split(a, a.workspace, a.workspace + n_part * head_dim, plan, (hipStream_t)stream, true);
     return e == hipSuccess ? 0 : 2;
 }
 

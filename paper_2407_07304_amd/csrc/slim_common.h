@@ -149,4 +149,11 @@ __device__ __forceinline__ void quant_row_piece(const u32x4 raw, u32x2& out2, fl
     }
 }
 
+// Decode: how many of a call's n_split splits a sequence of T tokens uses: split_rate a token (in units of 2^-32; the plan
+// for equal lengths has no more splits than tokens and a rate that gives every sequence all of them).
+constexpr unsigned kAllSplits = 0xffffffffu;
+__device__ __forceinline__ int splits_of(int T, int n_split, unsigned split_rate) {
+    return min(n_split, (int)__umulhi((unsigned)T - 1u, split_rate) + 1);
+}
+
 }  // namespace slim

@@ -49,15 +49,22 @@ struct DecodeArgs {
     const int* kv_lens;   // device, [batch]: tokens of each sequence's cache that count (clamped to 1..kv_len), or null: all
     int batch, q_heads, kv_heads, kv_len, head_dim;
     float softmax_scale;
+    bool ragged;          // use the plan for sequences of different lengths (the workspace has room for it)
+};
+// How a decode call is cut up: waves per workgroup, splits of the key axis (workgroups per row), and how many of them a
+// sequence uses (splits_of).
+struct DecodePlan {
+    int waves, n_split;
+    unsigned split_rate;
 };
 // Grouped-query variant (2 to 32 query heads per KV head): a workgroup sweeps a run of tokens of one (batch, KV head)
 // for all its query heads and is a split.  n_bg = batch * kv_heads, group = query heads per KV head.
 bool decode_uses_gqa_kernel(int q_heads, int kv_heads);
-int decode_gqa_num_splits(int kv_len, long n_bg, int group, int head_dim);
+DecodePlan decode_gqa_plan(int kv_len, long n_bg, int group, int head_dim);
 // traffic_only: the measurement form (the kernel's loads without its arithmetic; what it writes is meaningless)
-hipError_t launch_decode_gqa_split(const DecodeArgs& a, float* ws_acc, float* ws_ml, int n_split, hipStream_t stream,
+hipError_t launch_decode_gqa_split(const DecodeArgs& a, float* ws_acc, float* ws_ml, const DecodePlan& plan, hipStream_t stream,
                                    bool traffic_only = false);
-size_t decode_workspace_bytes(int batch, int q_heads, int kv_heads, int kv_len, int head_dim);
+size_t decode_workspace_bytes(int batch, int q_heads, int kv_heads, int kv_len, int head_dim, bool ragged);
 hipError_t launch_decode(const DecodeArgs& a, hipStream_t stream);
 // The library's own decode scratch (one static device array per GPU) for the entry point that may not
 // allocate: its address on the current device, looked up on the first call there.

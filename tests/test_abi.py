@@ -129,6 +129,24 @@ def test_rows_that_fit_the_static_scratch_fit_it_at_every_length(lib):
                 assert 0 < n <= max(limit, B * Hq * rec * (1 if Hq == Hkv else 2)), (B, Hq, Hkv, T, D, n)
 
 
+def test_decode_leaves_no_long_sequence_to_a_few_workgroups(lib):
+    """Sequences of different lengths: one of full length among short ones still makes enough workgroups, or its
+    workgroups get few enough tokens, or the whole batch makes many, or the records fill the library's own scratch.
+    (The entry point cannot know the lengths: the plan has to hold for every mix of them.)"""
+    limit = lib.slim_attn_decode_int8_static_max_bytes()
+    for D in (64, 128):
+        for (B, Hq, Hkv) in ((8, 32, 32), (16, 32, 32), (32, 8, 8), (8, 8, 8), (100, 8, 8), (128, 4, 4), (6, 40, 1), (300, 32, 32),
+                             (16, 32, 8), (4, 64, 8), (32, 32, 8), (10, 32, 8), (3, 64, 2), (200, 16, 2)):
+            grouped = 2 <= Hq // Hkv <= 32
+            heads = Hkv if grouped else Hq
+            for T in (1000, 2300, 5000, 8192, 16384, 33000, 65536):
+                record = B * Hq * (D + 2) * 4
+                n = lib.slim_attn_decode_int8_workspace_bytes(B, Hq, Hkv, T, D) // record
+                few_tokens = T < (n + 1) * (32 * D if grouped else 2048)
+                many = B * heads * (n + 1) > 768 if grouped else B * heads * n >= 1536
+                assert few_tokens or many or heads * n >= 128 or (n + 1) * record > limit, (B, Hq, Hkv, T, D, n)
+
+
 def test_varlen_decode_rejects_bad_arguments(lib):
     f = lib.slim_attn_decode_int8_varlen
 

@@ -630,6 +630,39 @@ def test_decode_per_sequence_lengths(sa, oracle, D, Hq, Hkv):
     check_close(host_f64(out2), expect([1, 1, 1, 1500, 1500, 1500]), "decode with clamped lengths")
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,T,D", [(6, 32, 32, 6200, 128), (3, 64, 64, 4200, 64), (10, 32, 8, 12000, 64), (9, 32, 8, 30000, 128)])
+def test_decode_of_one_long_sequence_among_short_ones(sa, oracle, B, Hq, Hkv, T, D):
+    # shapes that are cut finer for lengths of their own than for equal ones: a sequence of full length, one at and one
+    # past a multiple of the 512 tokens that earn a split, one of a token; and the same call with a workspace that holds
+    # the splits of equal lengths only
+    import ctypes
+    rng = np.random.default_rng(T + D)
+    lens = np.array(([T, 1, 512, 513, T - 1, 2 * 512 + 1, 700] + [300] * B)[:B], dtype=np.int32)
+    q = normal_bf16(rng, (B, Hq, 1, D))
+    kc = rng.integers(-127, 128, (B, Hkv, T, D), dtype=np.int8)
+    vc = rng.integers(-127, 128, (B, Hkv, T, D), dtype=np.int8)
+    ks, vs = rng.uniform(0.005, 0.02, (B, Hkv, T)).astype(np.float32), rng.uniform(0.005, 0.02, (B, Hkv, T)).astype(np.float32)
+    scale = 1.0 / math.sqrt(D)
+    dq, dkc, dks, dvc, dvs, dl = dev_bf16(q), dev(kc), dev(ks), dev(vc), dev(vs), torch.from_numpy(lens).cuda()
+    out = sa.slim_attn_decode_int8_varlen(dq, dkc, dks, dvc, dvs, dl, scale)
+    lib, record = sa.load(), B * Hq * (D + 2) * 4
+    n = sa.slim_attn_decode_int8_workspace_bytes(B, Hq, Hkv, T, D) // record
+    ws, out2, P = torch.empty(n * record, dtype=torch.uint8, device="cuda"), torch.empty_like(out), ctypes.c_void_p
+    for fewer in range(1, n + 1):   # (5: the workspace is too small, nothing is enqueued)
+        status = lib.slim_attn_decode_int8_varlen(
+            P(dq.data_ptr()), P(dkc.data_ptr()), P(dks.data_ptr()), P(dvc.data_ptr()), P(dvs.data_ptr()), P(dl.data_ptr()), P(out2.data_ptr()),
+            P(ws.data_ptr()), fewer * record, B, Hq, Hkv, T, D, 0, scale, P(torch.cuda.current_stream().cuda_stream))
+        assert status in (0, 5)
+        if status == 0:
+            break
+    torch.cuda.synchronize()
+    assert fewer < n
+    want = np.concatenate([oracle.attn(q[b:b + 1], kc[b:b + 1, :, :m], vc[b:b + 1, :, :m], scale, False, k_scale=ks[b:b + 1, :, :m],
+                                       v_scale=vs[b:b + 1, :, :m]) for b, m in enumerate(lens.tolist())], axis=0)
+    check_close(host_f64(out), want, "one long sequence, %d splits" % n)
+    check_close(host_f64(out2), want, "one long sequence, %d splits" % fewer)
+
+
 @pytest.mark.parametrize("D,Hq,Hkv", [(128, 16, 2), (64, 6, 3)])
 def test_grouped_decode_of_extreme_queries(sa, oracle, D, Hq, Hkv):
     # rows around 2^60 and around 2^-50, with sequences that leave most splits empty, and a row with an infinity or a NaN, whose result is not a number while every other row's is
