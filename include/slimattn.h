@@ -126,6 +126,14 @@ int slim_attn_prefill(const void* q_bf16, const void* k, const void* v,
                       int causal, float softmax_scale, int kv_dtype, int out_dtype, void* stream);
 
 /*
+ * Rows of the row blocks that slim_attn_prefill (and, for bf16 K/V, slim_attn_prefill_emit_int8) cuts such a call
+ * into: 32, 128 or 256, each a kernel form of its own, chosen by the sizes alone.  0 if the arguments are invalid.
+ * Host arithmetic only; the answer for a shape may change from one version of the library to the next.
+ */
+int slim_attn_prefill_block_rows(int batch, int q_heads, int kv_heads, int seq_len, int head_dim,
+                                 int causal, int kv_dtype, int out_dtype);
+
+/*
  * Prefill attention on bf16 K/V that also writes their INT8 cache in the same launch (the
  * serving loop of section 2.2 keeps K/V in INT8 from the first token on): the attention
  * result is that of slim_attn_prefill with kv_dtype == SLIM_BF16, bit for bit, and

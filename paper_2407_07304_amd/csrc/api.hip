@@ -158,6 +158,22 @@ int slim_attn_prefill(const void* q_bf16, const void* k, const void* v, const fl
                           seq_len, head_dim, causal, softmax_scale, kv_dtype, out_dtype, nullptr, stream);
 }
 
+int slim_attn_prefill_block_rows(int batch, int q_heads, int kv_heads, int seq_len, int head_dim, int causal, int kv_dtype,
+                                 int out_dtype) {
+    if (check_shape(batch, q_heads, kv_heads, seq_len, head_dim) != SLIM_OK || (causal != 0 && causal != 1)) return 0;
+    if ((kv_dtype != SLIM_BF16 && kv_dtype != SLIM_I8) || (out_dtype != SLIM_BF16 && out_dtype != SLIM_F32)) return 0;
+    slim::PrefillArgs a = {};
+    a.batch = batch;
+    a.q_heads = q_heads;
+    a.kv_heads = kv_heads;
+    a.seq_len = seq_len;
+    a.head_dim = head_dim;
+    a.causal = causal;
+    a.kv_int8 = kv_dtype == SLIM_I8;
+    a.out_f32 = out_dtype == SLIM_F32;
+    return slim::prefill_block_rows(a);
+}
+
 size_t slim_attn_prefill_two_sweep_workspace_bytes(int batch, int q_heads, int kv_heads, int seq_len, int head_dim) {
     if (check_shape(batch, q_heads, kv_heads, seq_len, head_dim) != SLIM_OK) return 0;
     return (size_t)batch * q_heads * seq_len * 2 * sizeof(float);

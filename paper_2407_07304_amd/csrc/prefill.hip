@@ -992,6 +992,76 @@ static double modelled_us(const PrefillParams& p, double us_phase, double us_ite
     return most;
 }
 
+// The items of row blocks of `rows` rows and how they are listed
+static void set_blocks(PrefillParams& p, const PrefillArgs& a, int rows) {
+    p.n_rb = (a.seq_len + rows - 1) / rows;
+    // Under the causal mask the rows that do not fill a block go to the first one, which has the fewest keys, and not
+    // to the last (S = 777: 91 key tiles per head instead of 109); the offset keeps the diagonal on tile bounds.
+    p.row_off = p.causal ? (p.n_rb * rows - a.seq_len) / 32 * 32 : 0;
+    p.n_bh = a.batch * a.q_heads;
+    const int per_xcd = (p.n_rb * p.n_bh + 7) / 8;
+    p.slots = per_xcd < 32 ? per_xcd : 32;
+    p.rounds = (per_xcd + p.slots - 1) / p.slots;
+    // A batch has 4 KV heads an XCD, or all heads up to twice that: with 32 heads and 32 workgroups an XCD no two of
+    // them read the same K/V (B=8, 32 heads, S=4096: 1600 us, 1110 in batches); smaller batches leave ends of
+    // rounds unfilled (B=1, 32 heads, S=6000: 334 us in batches of two heads an XCD, 287 with all four).
+    p.group = (unsigned)(a.q_heads / a.kv_heads);
+    const unsigned per_batch = 8 * 4 * p.group;
+    p.heads = (unsigned)p.n_bh > 2 * per_batch ? per_batch : (unsigned)p.n_bh;
+    p.last_heads = (unsigned)p.n_bh % p.heads != 0 ? (unsigned)p.n_bh % p.heads : p.heads;
+    auto magic = [](unsigned long long d) { return d == 1 ? 0xffffffffu : (unsigned)((1ull << 32) / d); };   // (div_magic's correction covers 2^32 - 1 for d = 1)
+    p.batch_magic = magic((unsigned long long)p.n_rb * p.heads);
+    p.heads_magic = magic(p.heads);
+    p.last_heads_magic = magic(p.last_heads);
+    p.group_magic = magic(p.group);
+}
+
+// Which form a call takes (rows of its row blocks: 32, 128 or 256; p is left set for 128 or 256).  The modelled times
+// decide (constants from a sweep of 8 head counts, 4 to 512, by 12 lengths, 50 to 4096, where they pick the fastest form
+// or one within 3 % of it).
+//   - INT8 K/V are widened to bf16 by the workgroup that stages them, and that is a quarter of the time with row
+//     blocks of 128 rows; blocks of 256 do it half as often per query row (B=1, 32 heads, S=4096: 175 -> 149 us,
+//     S=8192 637 -> 562, 64 on 8 heads, S=16384 4.82 -> 4.24 ms), but there are half as many to fill the chip with
+//     (S=2048 on 32 heads: 64 us instead of 55).
+//   - bf16 K/V, D = 128: half the ring's requests per matrix phase and no merge are worth 3 to 10 % where there are
+//     enough items (32 heads: S=4096 142 -> 136 us, S=8192 504 -> 489, B=4, 32 on 8 heads, S=777 39.5 -> 36.6; S=2048
+//     43 -> 53, stays).  fp32 results stay too (their staging area and 256 query rows are more than the LDS holds),
+//     and so does D = 64, where the wide form gains and loses 6 % in turn.
+//   - small calls take the form of prefill_split.hip: the longest row block's latency, or the chip's tiles and items
+//     (8 heads: S=200 8.9 -> 5.2 us, S=1024 17.0 -> 10.4; 32 heads: S=512 12.8 -> 10.4, S=1024 stays).  That form has a
+//     workgroup per row block and head, and a launch less than 2^32 threads: more of them than that stay with the lists.
+static int choose_rows(PrefillParams& p, const PrefillArgs& a) {
+    const bool d128 = a.head_dim == 128;
+    int rows = kBR;
+    set_blocks(p, a, kBR);
+    double us = a.kv_int8 ? modelled_us(p, d128 ? 0.50 : 0.42, d128 ? 7.0 : 4.0, kBR, 1)
+                          : modelled_us(p, 0.31, d128 ? 4.2 : 5.0, kBR, 1);
+    if (a.kv_int8 || (d128 && !a.out_f32)) {
+        set_blocks(p, a, 2 * kBR);
+        const double us_wide = a.kv_int8 ? modelled_us(p, d128 ? 0.44 : 0.37, d128 ? 5.0 : 4.0, 2 * kBR, 2)
+                                         : modelled_us(p, 0.30, 5.5, 2 * kBR, 2);
+        if (us_wide < us) {
+            us = us_wide;
+            rows = 2 * kBR;
+        } else {
+            set_blocks(p, a, kBR);
+        }
+    }
+    us += d128 ? (a.kv_int8 ? 1.0 : 1.5) : (a.kv_int8 ? 2.5 : 2.0);
+    const double blocks32 = (a.seq_len + 31) / 32, tiles = blocks32 * p.n_bh * (p.causal ? (blocks32 + 1) / 2 : blocks32);
+    const double us_longest = d128 ? 3.4 + 0.18 * blocks32 : 3.3 + 0.11 * blocks32;
+    const double us_all = (d128 ? 1.5 : 1.2) + ((d128 ? 0.18 : 0.115) * tiles + (d128 ? 2.0 : 1.2) * blocks32 * p.n_bh) / 256;
+    const bool launchable = blocks32 * p.n_bh * 256 < 0x1p32;
+    return launchable && (us_longest > us_all ? us_longest : us_all) < us ? 32 : rows;
+}
+
+int prefill_block_rows(const PrefillArgs& a) {
+    PrefillParams p;
+    p.S = a.seq_len;
+    p.causal = a.causal ? 1 : 0;
+    return choose_rows(p, a);
+}
+
 hipError_t launch_prefill(const PrefillArgs& a, hipStream_t stream) {
     PrefillParams p;
     p.q = (const uint16_t*)a.q;
@@ -1006,76 +1076,29 @@ hipError_t launch_prefill(const PrefillArgs& a, hipStream_t stream) {
     p.vqs = a.v_scale_out;
     p.S = a.seq_len;
     p.causal = a.causal ? 1 : 0;
-    auto blocks_of = [&](int rows) {
-        p.n_rb = (a.seq_len + rows - 1) / rows;
-        // Under the causal mask the rows that do not fill a block go to the first one, which has the fewest keys, and not
-        // to the last (S = 777: 91 key tiles per head instead of 109); the offset keeps the diagonal on tile bounds.
-        p.row_off = p.causal ? (p.n_rb * rows - a.seq_len) / 32 * 32 : 0;
-        p.n_bh = a.batch * a.q_heads;
-        const int per_xcd = (p.n_rb * p.n_bh + 7) / 8;
-        p.slots = per_xcd < 32 ? per_xcd : 32;
-        p.rounds = (per_xcd + p.slots - 1) / p.slots;
-        // A batch has 4 KV heads an XCD, or all heads up to twice that: with 32 heads and 32 workgroups an XCD no two of
-        // them read the same K/V (B=8, 32 heads, S=4096: 1600 us, 1110 in batches); smaller batches leave ends of
-        // rounds unfilled (B=1, 32 heads, S=6000: 334 us in batches of two heads an XCD, 287 with all four).
-        p.group = (unsigned)(a.q_heads / a.kv_heads);
-        const unsigned per_batch = 8 * 4 * p.group;
-        p.heads = (unsigned)p.n_bh > 2 * per_batch ? per_batch : (unsigned)p.n_bh;
-        p.last_heads = (unsigned)p.n_bh % p.heads != 0 ? (unsigned)p.n_bh % p.heads : p.heads;
-        auto magic = [](unsigned long long d) { return d == 1 ? 0xffffffffu : (unsigned)((1ull << 32) / d); };   // (div_magic's correction covers 2^32 - 1 for d = 1)
-        p.batch_magic = magic((unsigned long long)p.n_rb * p.heads);
-        p.heads_magic = magic(p.heads);
-        p.last_heads_magic = magic(p.last_heads);
-        p.group_magic = magic(p.group);
-    };
-    blocks_of(kBR);
     p.scale_log2e = a.softmax_scale * kLog2e;
     p.row_max = a.row_max;
     if (a.row_max) {   // the comparison variant: bf16 K/V only (checked by the caller); two launches
+        set_blocks(p, a, kBR);
         hipError_t e = a.head_dim == 128 ? launch_one<128, false, false, 1>(p, stream) : launch_one<64, false, false, 1>(p, stream);
         if (e != hipSuccess) return e;
         if (a.head_dim == 128) return a.out_f32 ? launch_one<128, false, true, 2>(p, stream) : launch_one<128, false, false, 2>(p, stream);
         return a.out_f32 ? launch_one<64, false, true, 2>(p, stream) : launch_one<64, false, false, 2>(p, stream);
     }
-    // Which form: the modelled times decide (constants from a sweep of 8 head counts, 4 to 512, by 12 lengths, 50 to 4096,
-    // where they pick the fastest form or one within 3 % of it).
-    //   - INT8 K/V are widened to bf16 by the workgroup that stages them, and that is a quarter of the time with row
-    //     blocks of 128 rows; blocks of 256 do it half as often per query row (B=1, 32 heads, S=4096: 175 -> 149 us,
-    //     S=8192 637 -> 562, 64 on 8 heads, S=16384 4.82 -> 4.24 ms), but there are half as many to fill the chip with
-    //     (S=2048 on 32 heads: 64 us instead of 55).
-    //   - bf16 K/V, D = 128: half the ring's requests per matrix phase and no merge are worth 3 to 10 % where there are
-    //     enough items (32 heads: S=4096 142 -> 136 us, S=8192 504 -> 489, B=4, 32 on 8 heads, S=777 39.5 -> 36.6; S=2048
-    //     43 -> 53, stays).  fp32 results stay too (their staging area and 256 query rows are more than the LDS holds),
-    //     and so does D = 64, where the wide form gains and loses 6 % in turn.
-    //   - small calls take the form of prefill_split.hip: the longest row block's latency, or the chip's tiles and items
-    //     (8 heads: S=200 8.9 -> 5.2 us, S=1024 17.0 -> 10.4; 32 heads: S=512 12.8 -> 10.4, S=1024 stays).
     const bool d128 = a.head_dim == 128;
-    bool wide = false;
-    double us = a.kv_int8 ? modelled_us(p, d128 ? 0.50 : 0.42, d128 ? 7.0 : 4.0, kBR, 1)
-                          : modelled_us(p, 0.31, d128 ? 4.2 : 5.0, kBR, 1);
-    if (a.kv_int8 || (d128 && !a.out_f32)) {
-        blocks_of(2 * kBR);
-        const double us_wide = a.kv_int8 ? modelled_us(p, d128 ? 0.44 : 0.37, d128 ? 5.0 : 4.0, 2 * kBR, 2)
-                                         : modelled_us(p, 0.30, 5.5, 2 * kBR, 2);
-        wide = us_wide < us;
-        if (wide) us = us_wide;
-        else blocks_of(kBR);
-    }
-    us += d128 ? (a.kv_int8 ? 1.0 : 1.5) : (a.kv_int8 ? 2.5 : 2.0);
-    const double blocks32 = (a.seq_len + 31) / 32, tiles = blocks32 * p.n_bh * (p.causal ? (blocks32 + 1) / 2 : blocks32);
-    const double us_longest = d128 ? 3.4 + 0.18 * blocks32 : 3.3 + 0.11 * blocks32;
-    const double us_all = (d128 ? 1.5 : 1.2) + ((d128 ? 0.18 : 0.115) * tiles + (d128 ? 2.0 : 1.2) * blocks32 * p.n_bh) / 256;
-    if ((us_longest > us_all ? us_longest : us_all) < us) {
+    const int rows = choose_rows(p, a);
+    if (rows == 32) {
         // (eight waves where a compute unit has hardly more than one workgroup and a row block many tiles)
+        const int blocks32 = (a.seq_len + 31) / 32;
         const bool eight = blocks32 * p.n_bh <= 384 && blocks32 >= (a.kv_int8 ? 24 : 48);
         return launch_prefill_split(a, eight ? 8 : 4, stream);
     }
-    if (wide) {
+    if (rows == 2 * kBR) {
         if (!a.kv_int8) return launch_one<128, false, false, 0, true>(p, stream);
         if (d128) return a.out_f32 ? launch_one<128, true, true, 0, true>(p, stream) : launch_one<128, true, false, 0, true>(p, stream);
         return a.out_f32 ? launch_one<64, true, true, 0, true>(p, stream) : launch_one<64, true, false, 0, true>(p, stream);
     }
-    const int sel = (a.head_dim == 128 ? 4 : 0) | (a.kv_int8 ? 2 : 0) | (a.out_f32 ? 1 : 0);
+    const int sel = (d128 ? 4 : 0) | (a.kv_int8 ? 2 : 0) | (a.out_f32 ? 1 : 0);
     switch (sel) {
         case 0: return launch_one<64, false, false>(p, stream);
         case 1: return launch_one<64, false, true>(p, stream);

@@ -31,6 +31,8 @@ struct PrefillArgs {
     float* row_max;   // null, or (bf16 K/V only) the two-sweep variant's workspace [batch, q_heads, seq_len, 2]
 };
 hipError_t launch_prefill(const PrefillArgs& a, hipStream_t stream);
+// Rows of the row blocks that launch_prefill takes for these sizes and types: 32, 128 or 256 (pointers are not looked at)
+int prefill_block_rows(const PrefillArgs& a);
 // The same for small calls: workgroups of 32 query rows whose waves (4 or 8) split the keys.
 hipError_t launch_prefill_split(const PrefillArgs& a, int waves, hipStream_t stream);
 // The comparison variant that keeps a row block's whole score strip in LDS (bf16 K/V, sequences up to

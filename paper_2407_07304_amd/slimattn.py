@@ -46,6 +46,8 @@ def load():
         lib.kv_quant_int8_append.restype = i
         lib.slim_attn_prefill.argtypes = [p, p, p, p, p, p, i, i, i, i, i, i, f, i, i, p]
         lib.slim_attn_prefill.restype = i
+        lib.slim_attn_prefill_block_rows.argtypes = [i, i, i, i, i, i, i, i]
+        lib.slim_attn_prefill_block_rows.restype = i
         lib.slim_attn_prefill_emit_int8.argtypes = [p, p, p, p, p, p, p, p, i, i, i, i, i, i, f, i, p]
         lib.slim_attn_prefill_emit_int8.restype = i
         lib.slim_attn_prefill_two_sweep_workspace_bytes.argtypes = [i, i, i, i, i]

@@ -231,6 +231,21 @@ def test_probe_library_exports_what_its_header_declares():
     assert lib.slim_probe_gqa_decode_traffic(P(A), P(A), P(A), P(A), P(A), P(A), 1 << 30, 1, 4, 4, 100, 128, None) == 1     # not a grouped shape
 
 
+def test_prefill_form_of_a_call(lib):
+    f = lib.slim_attn_prefill_block_rows
+    assert f(1, 4, 3, 100, 128, 1, 0, 0) == 0 and f(1, 2, 2, 100, 96, 1, 0, 0) == 0 and f(1, 2, 2, 0, 128, 1, 0, 0) == 0
+    assert f(1, 2, 2, 100, 128, 2, 0, 0) == 0 and f(1, 2, 2, 100, 128, 1, 1, 0) == 0 and f(1, 2, 2, 100, 128, 1, 0, 2) == 0
+    # the form with a workgroup of 256 threads per 32 rows and head is taken only where a launch can hold them (less than
+    # 2^32 threads); the item lists of the others need no more workgroups than the chip has compute units
+    short, at_limit = f(170, 30000, 30000, 96, 64, 1, 0, 0), f(200, 30000, 30000, 96, 64, 1, 0, 0)
+    assert 170 * 30000 * 3 * 256 < 2 ** 32 <= 200 * 30000 * 3 * 256 and short == 32 and at_limit == 128
+    for B, H, S in ((600, 30000, 1), (300, 60000, 32), (280, 30000, 64), (200, 30000, 96), (150, 60000, 128)):
+        for D in (64, 128):
+            for kv in (0, 2):
+                for od in (0, 1):
+                    assert f(B, H, H, S, D, 1, kv, od) in (128, 256), (B, H, S, D, kv, od)
+
+
 def test_prefill_emit_rejects_bad_arguments(lib):
     f = lib.slim_attn_prefill_emit_int8
 
