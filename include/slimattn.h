@@ -138,7 +138,8 @@ int slim_attn_prefill_block_rows(int batch, int q_heads, int kv_heads, int seq_l
  * serving loop of section 2.2 keeps K/V in INT8 from the first token on): the attention
  * result is that of slim_attn_prefill with kv_dtype == SLIM_BF16, bit for bit, and
  * codes/scales are those of kv_quant_int8 on k_bf16 and v_bf16, bit for bit.  Each row
- * block's own K and V rows are quantised by the workgroup that just attended over them.
+ * block's own K and V rows are quantised by the workgroups that just attended over them: those of the
+ * query heads that read the KV head share them.
  * k_codes, v_codes  device, out  [batch, kv_heads, seq_len, head_dim] int8
  * k_scale, v_scale  device, out  [batch, kv_heads, seq_len] fp32
  * Everything else as in slim_attn_prefill.

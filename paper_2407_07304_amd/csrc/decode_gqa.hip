@@ -320,9 +320,10 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_gqa_kernel(
 // sweep of 16 row counts, 8 to 1024, by 12 lengths, 128 to 32768, K and V cold): the cache at 6.6 TB/s, or the fullest
 // compute unit's tokens at 5.9 ns each (7 where it holds several workgroups; 4.2 and 5 with 64 codes a token), the longer
 // of the two and a fifth of the shorter, and 5 us and
-// 40 ns a split for the combine launch.  Eight waves where a compute unit has at most one workgroup, four where the grid fills the
-// chip.  (8 rows at T=32768: 30.6 us before, on 512 waves, now 19.2; 128 rows at T=8192: 52.9 before, now 45.3 with 1024
-// waves in 256 workgroups, where 2048 waves take 49; both with the combine launch.)
+// 40 ns a split for the combine launch.  Eight waves where the grid leaves compute units without a workgroup (less than
+// 240 of them), four where it fills the chip: 128 rows at T=8192 take 45.3 us with 1024 waves in 256 workgroups, 49 with
+// 2048 waves (52.9 in the form before, a split per wave; all with the combine launch).  8 rows at T=32768 are 256
+// workgroups of four waves as well (19.2 us; 30.6 before, on 512 waves): eight waves were not measured there.
 DecodePlan decode_gqa_plan(int kv_len, long n_bg, int group, int head_dim) {
     const long n_tiles = ((long)kv_len + kGqaTile - 1) / kGqaTile;
     const double stream_ns = (double)kv_len * n_bg * (2 * head_dim + 8) / 6600.0;

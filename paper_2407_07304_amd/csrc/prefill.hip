@@ -4,7 +4,11 @@
 // being staged; their per-token scales multiply the fp32 score column (K) and the
 // probability before it is rounded to bf16 (V), so dequantisation adds no rounding.
 //
-// Mapping on gfx950 (wave64, v_mfma_f32_32x32x16_bf16):
+// There are three forms, by the query rows of a workgroup's row block, and choose_rows says which one a call takes: 128
+// rows, described here; 256 rows (WIDE: every wave owns 32 rows and goes through all key tiles, nothing is merged, a ring
+// of two slots a tensor for INT8 K/V and four for bf16; see at the kernel); 32 rows for small calls (prefill_split.hip).
+//
+// Mapping of the 128-row form on gfx950 (wave64, v_mfma_f32_32x32x16_bf16):
 //   - A workgroup is 8 waves and owns 128 query rows.  Waves w and w+4 sit on the same SIMD
 //     and own the same 32 rows; the first four waves (group 0) take the even key tiles, the
 //     other four (group 1) the odd ones, each with its own running max, sum and accumulator,
@@ -103,7 +107,7 @@ using int_c = std::integral_constant<int, N>;
 // WIDE (not D = 64 with bf16 K/V): row blocks of 256 rows.  The eight waves own 32 rows each and every wave goes through
 // all key tiles, so a staged tile meets twice the query rows: the two groups stay in opposite phases, but on the same tile
 // one phase apart, group 1 stages K and group 0 V (half the widening, or half the ring's requests, per matrix phase), and
-// there is nothing to merge at the end.  See launch_prefill for when it is taken and what it gives.
+// there is nothing to merge at the end.  See choose_rows for when it is taken and what it gives.
 template <int D, bool KV_I8, bool OUT_F32, int MODE = 0, bool WIDE = false>
 __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const PrefillParams p) {
     static_assert(!(MODE != 0 && (KV_I8 || WIDE)), "the two-sweep variant exists for bf16 K/V and 128 rows only");

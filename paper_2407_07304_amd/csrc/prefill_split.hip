@@ -10,7 +10,7 @@
 //     16 of the tile's 32 keys, V^T comes through the LDS transpose read, the running max is lazy.
 //   - the waves' (max, sum, accumulator) are merged once, in LDS, in wave order.
 // K and V are read once per 32 rows instead of once per 128, from the L2: that is what limits the form to small calls
-// (launch_prefill compares modelled times).
+// (choose_rows in prefill.hip compares modelled times).
 #include <type_traits>
 
 #include "slim_common.h"

@@ -83,10 +83,10 @@ __device__ __forceinline__ float row_group_max(float v) {
 //          y + 1.5 * 2^23, whose low mantissa byte is the code in two's complement (the addition itself rounds to
 //          nearest even).  (|x| <= amax keeps |code| <= 127: the fast path needs no clamp.)
 //   near a tie: y is corrected by its remainder, y + (x - y scale) rcp(scale), two FMAs (Markstein's step to a correctly
-//          rounded quotient): the IEEE quotient itself for every bf16 pair and every reciprocal within 1.5 ulp (swept on
-//          the host).  Such values are common: x = amax / 2 is the tie 63.5, and of normally distributed rows 7 waves
-//          in 10 hold one; while each of them went through eight divisions the quantiser was bound by the vector ALU
-//          (two tensors of 32 heads, 2048 tokens, D = 128: 12.7 us, now 10.0).
+//          rounded quotient): the IEEE quotient itself for every bf16 pair with x >= 2^-10 amax (no other is near a tie) and
+//          every reciprocal within 1.5 ulp (swept on the host).  Such values are common: x = amax / 2 is the tie 63.5,
+//          and of normally distributed rows 7 waves in 10 hold one; while each of them went through eight divisions the
+//          quantiser was bound by the vector ALU (two tensors of 32 heads, 2048 tokens, D = 128: 12.7 us, now 10.0).
 // A row whose amax lies outside the checked range sends its wave through the divisions.
 constexpr float kQuantFastLo = 0x1p-60f, kQuantFastHi = 0x1p60f;   // rows with amax in this range take the fast scale and codes
 constexpr float kQuantTieGuard = 0x1p-14f;

@@ -18,6 +18,13 @@ def host_f64(t: torch.Tensor) -> np.ndarray:
     return t.detach().to(torch.float64).cpu().numpy()
 
 
+def assert_form(sa, rows, B, Hq, Hkv, S, D, causal, kv_int8, out_f32):
+    """The call takes the prefill's form with row blocks of `rows` rows: a test of one form must not end up in another."""
+    got = sa.load().slim_attn_prefill_block_rows(B, Hq, Hkv, S, D, int(causal), sa.SLIM_I8 if kv_int8 else sa.SLIM_BF16,
+                                                 sa.SLIM_F32 if out_f32 else sa.SLIM_BF16)
+    assert got == rows, "row blocks of %d rows, the test is of those of %d" % (got, rows)
+
+
 def check_close(got: np.ndarray, want: np.ndarray, what=""):
     err = np.abs(got - want)
     assert np.isfinite(got).all(), "%s: non-finite output" % what

@@ -1,7 +1,7 @@
 /* Host model of the quantiser's route for values near a tie: y = x * r, r a reciprocal of the scale that is up to one ulp off
  * R = fl32(1 / scale), corrected to y + (x - y * scale) * r with two FMAs, must be the IEEE quotient x / scale.  Every
- * bf16 amax in [lo, hi] (every third binade of the range), every bf16 x in (0, amax] from the binade on where codes are
- * all zero.
+ * bf16 amax in [lo, hi], every bf16 x in (0, amax] down to 2^-10 amax (the quotients below that are less than 1/8: code 0
+ * by either route, and no tie is near).
  * out[0] = cases, out[1] = those within the guard of a tie, out[2] = cases whose quotient or code differs. */
 #include <math.h>
 #include <stdint.h>
@@ -19,7 +19,7 @@ int model_near_tie_sweep(float lo, float hi, float guard, long *out) {
 #pragma omp parallel for schedule(dynamic, 16) reduction(+ : cases, near_ties, bad)
     for (int ab = 1; ab < 0x7f80; ++ab) {
         const float amax = bf16_bits_to_float((uint16_t)ab);
-        if (!(amax >= lo && amax <= hi) || (ab >> 7) % 3 != 0) continue;
+        if (!(amax >= lo && amax <= hi)) continue;
         const float scale = amax / 127.0f, R = 1.0f / scale;
         const float rs[3] = {nextafterf(R, 0.0f), R, nextafterf(R, INFINITY)};
         for (int xb = ab > 10 * 128 ? ab - 10 * 128 : 1; xb <= ab; ++xb) {

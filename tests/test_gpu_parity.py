@@ -23,7 +23,7 @@ def sa():
     return slimattn
 
 
-from _gpu_util import dev, dev_bf16, host_f64, check_close  # noqa: E402
+from _gpu_util import dev, dev_bf16, host_f64, check_close, assert_form  # noqa: E402
 
 
 # ---------------------------------------------------------------- quantiser
@@ -129,8 +129,8 @@ SMALL = [
     # B, Hq, Hkv, S, D
     (1, 2, 2, 1, 128), (1, 2, 1, 5, 64), (2, 4, 2, 127, 128), (1, 2, 2, 128, 64), (1, 4, 1, 129, 128),
     (1, 2, 2, 200, 128), (2, 3, 3, 333, 64), (1, 8, 2, 640, 128), (1, 2, 2, 1000, 64),
-    # two, three and nine row blocks: row-block pairs, a lone middle block, K/V tiles of the second block of a
-    # pair requested while the first one finishes; 96 keys: fewer tiles than ring slots
+    # whole row blocks of every form's size, fewer tiles than waves or ring slots (these sizes take the form for small
+    # calls; the comparison variants go through the item lists with them)
     (1, 2, 2, 256, 128), (1, 2, 1, 384, 64), (1, 1, 1, 1152, 128), (1, 2, 2, 96, 128), (1, 1, 1, 1120, 64),
 ]
 
@@ -148,22 +148,27 @@ def test_prefill_small_shapes(sa, oracle, B, Hq, Hkv, S, D, causal, kv_int8):
     # waves, one tile more than waves; eight waves (few heads, long rows)
     (1, 1, 1, 1, 64, True, True), (3, 4, 2, 31, 128, True, False), (2, 4, 4, 32, 64, False, True), (2, 6, 2, 33, 128, False, False),
     (1, 9, 3, 127, 64, True, False), (1, 8, 8, 129, 128, True, True), (1, 8, 2, 161, 128, False, False),
-    (1, 2, 2, 1590, 128, True, False), (1, 3, 1, 1601, 64, True, True), (1, 2, 1, 800, 128, False, True)])
+    (1, 2, 2, 1590, 128, True, False), (1, 3, 1, 1601, 64, True, True), (1, 2, 1, 800, 128, False, True),
+    # the size of one block of the other forms, and many heads
+    (1, 2, 2, 1, 128, True, False), (2, 3, 1, 97, 64, True, True), (1, 2, 2, 160, 128, False, False), (1, 2, 2, 255, 128, True, True),
+    (1, 4, 2, 256, 64, False, False), (12, 16, 4, 480, 64, True, False)])
 @pytest.mark.parametrize("kv_int8", [False, True])
 def test_prefill_small_calls(sa, oracle, B, Hq, Hkv, S, D, causal, out_f32, kv_int8):
     print("prefill small calls", B, Hq, Hkv, S, D, causal, out_f32, kv_int8, flush=True)
+    assert_form(sa, 32, B, Hq, Hkv, S, D, causal, kv_int8, out_f32)
     _prefill_case(sa, oracle, B, Hq, Hkv, S, D, causal, kv_int8, out_f32, seed=S + Hq)
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,S,D,causal,out_f32", [
-    # one block of 256 rows holds the sequence: row groups of 32 that end inside, key tiles that end inside, one row
-    (1, 2, 2, 1, 128, True, False), (2, 3, 1, 97, 64, True, True), (1, 2, 2, 160, 128, False, False),
-    (1, 2, 2, 255, 128, True, True), (1, 4, 2, 256, 64, False, False),
-    # enough heads for blocks of 256 rows on longer sequences: one row past a block, uneven halves, several blocks
-    (12, 16, 16, 257, 128, True, False), (12, 16, 4, 480, 64, True, False), (16, 16, 8, 300, 128, False, True),
-    (24, 16, 16, 545, 64, True, True), (4, 64, 8, 777, 128, True, False)])
+    # one block of 256 rows holds the sequence: row groups of 32 that end inside, key tiles that end inside
+    (7, 32, 8, 97, 128, True, False), (7, 32, 8, 161, 64, False, True), (4, 40, 8, 160, 128, False, False),
+    (33, 4, 2, 255, 128, True, True), (7, 32, 8, 256, 64, True, False),
+    # longer sequences: one row past a block, uneven halves, several blocks
+    (12, 16, 16, 257, 128, True, False), (4, 40, 8, 480, 64, True, False), (16, 16, 8, 300, 128, False, True),
+    (24, 16, 16, 545, 64, True, True), (4, 64, 8, 777, 128, True, False), (1, 48, 16, 1057, 128, False, False)])
 def test_prefill_int8_wide_row_blocks(sa, oracle, B, Hq, Hkv, S, D, causal, out_f32):
     print("prefill wide", B, Hq, Hkv, S, D, causal, out_f32, flush=True)
+    assert_form(sa, 256, B, Hq, Hkv, S, D, causal, True, out_f32)
     rng = np.random.default_rng(B + S + D)
     q = normal_bf16(rng, (B, Hq, S, D))
     kc, ks = oracle.kv_quant_int8(normal_bf16(rng, (B, Hkv, S, D)))
@@ -175,12 +180,24 @@ def test_prefill_int8_wide_row_blocks(sa, oracle, B, Hq, Hkv, S, D, causal, out_
     check_close(host_f64(out), oracle.attn(q, kc, vc, scale, causal, k_scale=ks, v_scale=vs), "wide row blocks")
 
 
-@pytest.mark.parametrize("Hq,Hkv,S,D,causal", [(32, 32, 1500, 128, True), (40, 8, 1281, 64, True), (48, 16, 1057, 128, False), (36, 36, 1340, 128, True)])
-def test_prefill_int8_128_row_blocks(sa, oracle, Hq, Hkv, S, D, causal):
+@pytest.mark.parametrize("Hq,Hkv,S,D,causal,out_f32", [
+    (32, 32, 1500, 128, True, False), (36, 36, 1340, 128, True, False), (16, 4, 1500, 128, False, True),
+    (40, 8, 1500, 64, True, False), (40, 8, 1500, 64, True, True), (8, 2, 3843, 64, False, True)])
+def test_prefill_int8_128_row_blocks(sa, oracle, Hq, Hkv, S, D, causal, out_f32):
     # between the small calls and those with enough heads for blocks of 256 rows
     rows = np.unique(np.concatenate([np.arange(0, 40), np.arange(S - 150, S), np.arange(0, S, 37)])).astype(np.int32)
-    print("prefill int8 128-row blocks", Hq, Hkv, S, D, causal, flush=True)
-    _prefill_case(sa, oracle, 1, Hq, Hkv, S, D, causal, True, False, seed=S, rows=rows)
+    print("prefill int8 128-row blocks", Hq, Hkv, S, D, causal, out_f32, flush=True)
+    assert_form(sa, 128, 1, Hq, Hkv, S, D, causal, True, out_f32)
+    _prefill_case(sa, oracle, 1, Hq, Hkv, S, D, causal, True, out_f32, seed=S, rows=rows)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,S,D,causal", [
+    (9, 7, 7, 289, 128, True), (26, 2, 2, 300, 128, False), (9, 8, 2, 777, 64, True), (5, 7, 7, 777, 64, False)])
+@pytest.mark.parametrize("out_f32", [False, True])
+def test_prefill_bf16_128_row_blocks(sa, oracle, B, Hq, Hkv, S, D, causal, out_f32):
+    print("prefill bf16 128-row blocks", B, Hq, Hkv, S, D, causal, out_f32, flush=True)
+    assert_form(sa, 128, B, Hq, Hkv, S, D, causal, False, out_f32)
+    _prefill_case(sa, oracle, B, Hq, Hkv, S, D, causal, False, out_f32, seed=S + D)
 
 
 def test_prefill_c1_full(sa, oracle):
@@ -394,11 +411,14 @@ def test_prefill_int8_with_all_zero_tokens(sa, oracle):
     check_close(host_f64(dec)[:, :, 0], want[:, :, S - 1], "decode with zero tokens")
 
 
-def test_prefill_large_scores_and_repeat_runs_are_bit_identical(sa, oracle):
+@pytest.mark.parametrize("B,Hq,Hkv,S,rows", [(1, 4, 2, 700, 32), (9, 8, 2, 777, 128)])
+def test_prefill_large_scores_and_repeat_runs_are_bit_identical(sa, oracle, B, Hq, Hkv, S, rows):
     # scores far from zero (softmax scale 1.0 on N(0,1) data with D=64 gives |s| up to ~40): the lazy
     # running max must still track them; two launches must agree bit for bit
     rng = np.random.default_rng(63)
-    B, Hq, Hkv, S, D = 1, 4, 2, 700, 64
+    D = 64
+    assert_form(sa, rows, B, Hq, Hkv, S, D, True, False, True)
+    assert_form(sa, rows, B, Hq, Hkv, S, D, False, False, True)
     q, k, v = normal_bf16(rng, (B, Hq, S, D)), normal_bf16(rng, (B, Hkv, S, D)), normal_bf16(rng, (B, Hkv, S, D))
     o1 = sa.slim_attn_prefill(dev_bf16(q), dev_bf16(k), dev_bf16(v), 1.0, True, out_dtype=torch.float32)
     o2 = sa.slim_attn_prefill(dev_bf16(q), dev_bf16(k), dev_bf16(v), 1.0, True, out_dtype=torch.float32)
@@ -420,12 +440,17 @@ def test_prefill_batched_gqa_full_tensor(sa, oracle):
     check_close(host_f64(out), oracle.attn(q, k, v, scale, True), "batched GQA prefill")
 
 
-@pytest.mark.parametrize("kv_int8", [False, True])
-def test_prefill_many_launches_are_bit_identical(sa, oracle, kv_int8):
-    # the ring slots are reused from the first phase on: a missing wait between a read and the next request
-    # for the same slot shows as a rare difference between launches, so every launch is compared
+@pytest.mark.parametrize("B,Hq,Hkv,S,kv_int8,form", [
+    (1, 8, 2, 640, False, 32), (1, 8, 2, 640, True, 32), (38, 8, 8, 257, False, 128), (9, 8, 2, 640, True, 128), (16, 32, 8, 256, False, 256),
+    (4, 32, 8, 777, False, 256), (16, 16, 8, 300, True, 256)])
+def test_prefill_many_launches_are_bit_identical(sa, oracle, B, Hq, Hkv, S, kv_int8, form):
+    # the ring slots of the 128- and 256-row forms are reused from the first phase on, and a workgroup's items follow each
+    # other: a missing wait between a read and the next request for the same slot shows as a rare difference between
+    # launches, so every launch is compared
+    print("prefill, 200 launches", B, Hq, Hkv, S, kv_int8, form, flush=True)
     rng = np.random.default_rng(65)
-    B, Hq, Hkv, S, D = 1, 8, 2, 640, 128
+    D = 128
+    assert_form(sa, form, B, Hq, Hkv, S, D, True, kv_int8, False)
     q, k, v = normal_bf16(rng, (B, Hq, S, D)), normal_bf16(rng, (B, Hkv, S, D)), normal_bf16(rng, (B, Hkv, S, D))
     scale = 1.0 / math.sqrt(D)
     dq = dev_bf16(q)
@@ -442,12 +467,8 @@ def test_prefill_many_launches_are_bit_identical(sa, oracle, kv_int8):
     first = sa.slim_attn_prefill(*args, **kw)
     torch.cuda.synchronize()
     check_close(host_f64(first), want, "first launch")
-    differing = 0
-    for _ in range(200):
-        out = sa.slim_attn_prefill(*args, **kw)
-        differing += int(not torch.equal(out, first))
-    torch.cuda.synchronize()
-    assert differing == 0
+    for i in range(200):
+        assert torch.equal(sa.slim_attn_prefill(*args, **kw), first), "launch %d" % i
 
 
 def _random_shape(i):
@@ -986,17 +1007,20 @@ def test_prefill_that_emits_the_int8_cache(sa, oracle, B, Hq, Hkv, S, D, causal)
 
 # ---------------------------------------------------------------- the two-sweep comparison variant
 
-@pytest.mark.parametrize("B,Hq,Hkv,S,D", [
-    # how the row blocks and heads are listed: fewer than eight heads, no multiple of eight, one batch of heads, two and
-    # a rest; a first row block of 1, 32 and 33 rows; lists of several items per workgroup
-    (1, 5, 5, 289, 128), (1, 7, 7, 160, 64), (3, 12, 4, 385, 128), (10, 8, 8, 140, 128), (11, 7, 7, 200, 64),
-    (9, 32, 4, 161, 64), (20, 16, 16, 300, 64), (1, 40, 8, 1281, 64),
-    # the same on calls that are large enough for 128-row blocks
-    (43, 7, 7, 200, 64), (33, 8, 8, 140, 128), (19, 16, 4, 161, 128), (38, 8, 8, 257, 128), (33, 8, 2, 385, 64), (65, 4, 4, 289, 128),
-    (37, 7, 7, 129, 128)])
+@pytest.mark.parametrize("B,Hq,Hkv,S,D,form", [
+    # which workgroup takes which row block and head, and who writes which rows of the cache: fewer than eight heads, no
+    # multiple of eight, many; a first or last block that ends inside.  Small calls
+    (1, 5, 5, 289, 128, 32), (1, 7, 7, 160, 64, 32), (3, 12, 4, 385, 128, 32), (10, 8, 8, 140, 128, 32), (11, 7, 7, 200, 64, 32),
+    (9, 32, 4, 161, 64, 32), (20, 16, 16, 300, 64, 32), (43, 7, 7, 200, 64, 32), (33, 8, 8, 140, 128, 32), (33, 8, 2, 385, 64, 32),
+    (37, 7, 7, 129, 128, 32),
+    # item lists of 128-row blocks: no multiple of eight heads, one batch of heads, two and a rest; a first row block of 1,
+    # 32 and 33 rows; lists of several items per workgroup
+    (9, 7, 7, 289, 128, 128), (11, 7, 7, 257, 128, 128), (3, 40, 8, 140, 128, 128), (19, 16, 4, 161, 128, 128), (38, 8, 8, 257, 128, 128),
+    (65, 4, 4, 289, 128, 128), (1, 40, 8, 1281, 64, 128), (48, 8, 2, 480, 64, 128), (9, 8, 2, 777, 64, 128)])
 @pytest.mark.parametrize("causal", [True, False])
-def test_prefill_item_lists(sa, oracle, B, Hq, Hkv, S, D, causal):
+def test_prefill_item_lists(sa, oracle, B, Hq, Hkv, S, D, form, causal):
     print("prefill item lists", B, Hq, Hkv, S, D, causal, flush=True)
+    assert_form(sa, form, B, Hq, Hkv, S, D, causal, False, False)
     rng = np.random.default_rng(3 * B + Hq + S)
     q, k, v = normal_bf16(rng, (B, Hq, S, D)), normal_bf16(rng, (B, Hkv, S, D)), normal_bf16(rng, (B, Hkv, S, D))
     scale = 1.0 / math.sqrt(D)
@@ -1018,6 +1042,7 @@ def test_prefill_bf16_wide_row_blocks(sa, oracle, B, Hq, Hkv, S, causal):
     print("prefill bf16 wide", B, Hq, Hkv, S, causal, flush=True)
     rng = np.random.default_rng(5 * B + Hq + S)
     D = 128
+    assert_form(sa, 256, B, Hq, Hkv, S, D, causal, False, False)
     q, k, v = normal_bf16(rng, (B, Hq, S, D)), normal_bf16(rng, (B, Hkv, S, D)), normal_bf16(rng, (B, Hkv, S, D))
     scale = 1.0 / math.sqrt(D)
     dq, dk, dv = dev_bf16(q), dev_bf16(k), dev_bf16(v)
@@ -1160,18 +1185,22 @@ def test_non_finite_values_stay_inside_their_kv_head(sa, oracle):
 
 # ---------------------------------------------------------------- sharp softmax: the arithmetic's own bound
 
-@pytest.mark.parametrize("kv_int8", [False, True])
-@pytest.mark.parametrize("out_f32", [False, True])
-def test_sharp_softmax_stays_within_the_rounding_bound(sa, oracle, kv_int8, out_f32):
+@pytest.mark.parametrize("B,Hq,Hkv,S,kv_int8,out_f32,form", [
+    (2, 8, 2, 700, False, False, 32), (2, 8, 2, 700, False, True, 32), (2, 8, 2, 700, True, False, 32), (2, 8, 2, 700, True, True, 32),
+    (38, 8, 8, 257, False, False, 128), (26, 2, 2, 300, False, True, 128), (9, 8, 2, 640, True, False, 128), (26, 4, 2, 256, True, True, 128),
+    (16, 32, 8, 256, False, False, 256), (4, 32, 8, 777, False, False, 256), (26, 5, 5, 385, True, False, 256), (19, 4, 2, 385, True, True, 256)])
+def test_sharp_softmax_stays_within_the_rounding_bound(sa, oracle, B, Hq, Hkv, S, kv_int8, out_f32, form):
     # scale 0.5 on N(0,1) inputs: most rows are carried by one key, so the rounding of P (INT8: of P * v_scale) to
     # bf16 is not averaged over the keys.  One rounding to nearest is off by at most 2^-8 relative, hence per element
     #   |o - o_exact| <= 2^-8 * sum_j p_j |v_j|  (+ 2^-8 |o| for a bf16 output)  + fp32 noise,
     # the first sum being the oracle's attention over |V|.
-    B, Hq, Hkv, S, D, scale = 2, 8, 2, 700, 128, 0.5
+    # (N(0,1) scores of this scale reach far past the 2^8 by which the running maximum may lag: every form's slow path runs)
+    D, scale = 128, 0.5
+    causal = not out_f32
+    assert_form(sa, form, B, Hq, Hkv, S, D, causal, kv_int8, out_f32)
     rng = np.random.default_rng(321)
     q, k, v = normal_bf16(rng, (B, Hq, S, D)), normal_bf16(rng, (B, Hkv, S, D)), normal_bf16(rng, (B, Hkv, S, D))
     od = torch.float32 if out_f32 else torch.bfloat16
-    causal = not out_f32
     if kv_int8:
         kc, ks = oracle.kv_quant_int8(k)
         vc, vs = oracle.kv_quant_int8(v)

@@ -80,4 +80,5 @@ def test_the_corrected_quotient_is_the_ieee_quotient(model, tmp_path):
     out = (ctypes.c_long * 3)()
     assert lib.model_near_tie_sweep(*kernel_constants(), out) == 0
     cases, near_ties, bad = out[0], out[1], out[2]
-    assert cases > 10 ** 7 and near_ties > 10 ** 4 and bad == 0, (cases, near_ties, bad)
+    # 2^7 values of amax in each of 120 binades and 2^60, ten binades of x each and amax itself, three reciprocals
+    assert cases == (120 * 128 + 1) * (10 * 128 + 1) * 3 and near_ties > 10 ** 4 and bad == 0, (cases, near_ties, bad)
