@@ -399,7 +399,7 @@ static DecodePlan ragged_plan(DecodePlan plan, bool gqa, int batch, int q_heads,
     const long wanted = gqa ? 768 / rows : (1536 + rows - 1) / rows;
     const long room = (long)(kDecodeStaticScratchBytes / decode_records_bytes((long)batch * q_heads, 1, head_dim));
     const long n = std::min({wanted, (long)kv_len / (gqa ? 32 * head_dim : 2048), room});
-    return n <= plan.n_split ? plan : DecodePlan{gqa ? 4 : 8, (int)n, 1u << 23 /* 2^32 / 512 */};
+    return n <= plan.n_split ? plan : DecodePlan{gqa && q_heads / kv_heads <= 16 ? 4 : 8, (int)n, 1u << 23 /* 2^32 / 512 */};
 }
 
 // ragged: the sequences have lengths of their own

@@ -324,24 +324,29 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_gqa_kernel(
 // 240 of them), four where it fills the chip: 128 rows at T=8192 take 45.3 us with 1024 waves in 256 workgroups, 49 with
 // 2048 waves (52.9 in the form before, a split per wave; all with the combine launch).  8 rows at T=32768 are 256
 // workgroups of four waves as well (19.2 us; 30.6 before, on 512 waves): eight waves were not measured there.
+// With more than 16 heads a KV head (two column groups) always eight waves, a split from three tiles on, and 3 us for the
+// combine launch: a compute unit has one or two such workgroups, and four waves are half as many as it wants (32 on 1
+// head, T=777, K and V in the caches: 14.6 us with four waves in one split, 10.3 now; 20 on 1, 128 sequences,
+// T=3000: 33.5 -> 25.8; a sweep of 8 row counts, 1 to 200, by 8 lengths, 64 to 30000, has no call where four waves win).
 DecodePlan decode_gqa_plan(int kv_len, long n_bg, int group, int head_dim) {
     const long n_tiles = ((long)kv_len + kGqaTile - 1) / kGqaTile;
+    const bool two_groups = group > 16;
     const double stream_ns = (double)kv_len * n_bg * (2 * head_dim + 8) / 6600.0;
     int best = 1;
     double best_ns = 0.0;
     for (int s : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256}) {
-        if (s > 1 && (s * 4 > n_tiles || decode_records_bytes(n_bg * group, s, head_dim) > kDecodeStaticScratchBytes)) break;
+        if (s > 1 && (s * (two_groups ? 3 : 4) > n_tiles || decode_records_bytes(n_bg * group, s, head_dim) > kDecodeStaticScratchBytes)) break;
         const long per_wg = (n_tiles + s - 1) / s, rounds = (n_bg * s + 255) / 256;
         const double ns_token = head_dim == 128 ? (rounds > 1 ? 7.0 : 5.9) : (rounds > 1 ? 5.0 : 4.2);
         const double busy_ns = (double)(rounds * per_wg * kGqaTile) * ns_token;
         const double longer = busy_ns > stream_ns ? busy_ns : stream_ns, shorter = busy_ns > stream_ns ? stream_ns : busy_ns;
-        const double ns = longer + 0.2 * shorter + (s > 1 ? 5000.0 + 40.0 * s : 0.0);
+        const double ns = longer + 0.2 * shorter + (s > 1 ? (two_groups ? 3000.0 : 5000.0) + 40.0 * s : 0.0);
         if (s == 1 || ns < best_ns) {
             best_ns = ns;
             best = s;
         }
     }
-    return DecodePlan{n_bg * best < 240 ? 8 : 4, best, kAllSplits};
+    return DecodePlan{two_groups || n_bg * best < 240 ? 8 : 4, best, kAllSplits};
 }
 
 hipError_t launch_decode_gqa_split(const DecodeArgs& a, float* ws_acc, float* ws_ml, const DecodePlan& plan, hipStream_t stream,
@@ -358,10 +363,11 @@ hipError_t launch_decode_gqa_split(const DecodeArgs& a, float* ws_acc, float* ws
     auto pick = [&](auto d_c) {
         using std::integral_constant;
         constexpr integral_constant<int, 4> w4{};
+        constexpr integral_constant<int, 8> w8{};
         constexpr integral_constant<int, 1> one{};
-        if (traffic_only) return plan.waves == 8 ? launch(d_c, integral_constant<int, 8>{}, one, std::true_type{}) : launch(d_c, w4, one, std::true_type{});
-        if (a.q_heads / a.kv_heads > 16) return launch(d_c, w4, integral_constant<int, 2>{}, std::false_type{});
-        return plan.waves == 8 ? launch(d_c, integral_constant<int, 8>{}, one, std::false_type{}) : launch(d_c, w4, one, std::false_type{});
+        if (traffic_only) return plan.waves == 8 ? launch(d_c, w8, one, std::true_type{}) : launch(d_c, w4, one, std::true_type{});
+        if (a.q_heads / a.kv_heads > 16) return launch(d_c, w8, integral_constant<int, 2>{}, std::false_type{});
+        return plan.waves == 8 ? launch(d_c, w8, one, std::false_type{}) : launch(d_c, w4, one, std::false_type{});
     };
     return a.head_dim == 128 ? pick(std::integral_constant<int, 128>{}) : pick(std::integral_constant<int, 64>{});
 }

@@ -147,6 +147,13 @@ def test_decode_leaves_no_long_sequence_to_a_few_workgroups(lib):
                 assert few_tokens or many or heads * n >= 128 or (n + 1) * record > limit, (B, Hq, Hkv, T, D, n)
 
 
+def test_decode_of_wide_groups_splits_short_caches(lib):
+    """17 to 32 query heads on a KV head: a few rows of some hundred tokens are cut, not left to a workgroup each."""
+    for D, Hq, T in ((128, 20, 777), (128, 32, 777), (64, 32, 777), (128, 32, 1500)):
+        for B in (1, 2, 8, 16):
+            assert lib.slim_attn_decode_int8_workspace_bytes(B, Hq, 1, T, D) // (B * Hq * (D + 2) * 4) >= 4, (B, Hq, T, D)
+
+
 def test_varlen_decode_rejects_bad_arguments(lib):
     f = lib.slim_attn_decode_int8_varlen
 

@@ -532,6 +532,8 @@ def test_decode_grouped_all_zero_tokens_and_huge_scores(sa, oracle):
     (1, 16, 1, 31, 128), (1, 17, 1, 33, 128), (2, 32, 2, 64, 64), (1, 31, 1, 95, 64), (5, 6, 2, 257, 128),
     # eight- and four-wave workgroups, one split and several, more than a combine chunk of them
     (1, 8, 1, 9000, 128), (1, 4, 2, 20001, 64), (60, 16, 4, 700, 128), (60, 16, 4, 300, 64), (1, 20, 1, 3000, 128),
+    # more than 16 heads a KV head: one split and two, the most that a short cache is cut into, many workgroups
+    (1, 17, 1, 65, 64), (2, 64, 2, 95, 128), (1, 20, 1, 777, 64), (2, 32, 1, 777, 128), (130, 20, 1, 300, 128), (200, 32, 1, 97, 64),
     # one head per KV head: the same edges (64-token chunks)
     (1, 1, 1, 30000, 128), (3, 1, 1, 4097, 64), (20, 8, 8, 513, 128), (70, 8, 8, 520, 64), (1, 8, 8, 1537, 128)])
 def test_decode_plan_edges(sa, oracle, B, Hq, Hkv, T, D):
