@@ -149,7 +149,7 @@ def test_decode_leaves_no_long_sequence_to_a_few_workgroups(lib):
 
 def test_decode_of_wide_groups_splits_short_caches(lib):
     """17 to 32 query heads on a KV head: a few rows of some hundred tokens are cut, not left to a workgroup each."""
-    for D, Hq, T in ((128, 20, 777), (128, 32, 777), (64, 32, 777), (128, 32, 1500)):
+    for D, Hq, T in ((128, 20, 777), (128, 32, 777), (64, 32, 1500), (128, 32, 1500)):
         for B in (1, 2, 8, 16):
             assert lib.slim_attn_decode_int8_workspace_bytes(B, Hq, 1, T, D) // (B * Hq * (D + 2) * 4) >= 4, (B, Hq, T, D)
 
@@ -242,6 +242,9 @@ def test_prefill_form_of_a_call(lib):
     f = lib.slim_attn_prefill_block_rows
     assert f(1, 4, 3, 100, 128, 1, 0, 0) == 0 and f(1, 2, 2, 100, 96, 1, 0, 0) == 0 and f(1, 2, 2, 0, 128, 1, 0, 0) == 0
     assert f(1, 2, 2, 100, 128, 2, 0, 0) == 0 and f(1, 2, 2, 100, 128, 1, 1, 0) == 0 and f(1, 2, 2, 100, 128, 1, 0, 2) == 0
+    # bf16 K and V of many heads are more than the L2s hold: the form that reads them once per 32 rows is not taken
+    for B, H in ((40, 32), (40, 40), (64, 32)):
+        assert f(B, H, H, 300, 64, 0, 0, 0) == 128
     # the form with a workgroup of 256 threads per 32 rows and head is taken only where a launch can hold them (less than
     # 2^32 threads); the item lists of the others need no more workgroups than the chip has compute units
     short, at_limit = f(170, 30000, 30000, 96, 64, 1, 0, 0), f(200, 30000, 30000, 96, 64, 1, 0, 0)
