@@ -996,15 +996,15 @@ static double modelled_us(const PrefillParams& p, double us_phase, double us_ite
     return most;
 }
 
-// The items of row blocks of `rows` rows and how they are listed
-static void set_blocks(PrefillParams& p, const PrefillArgs& a, int rows) {
+// The items of row blocks of `rows` rows and how they are listed, for so many workgroups a compute unit
+static void set_blocks(PrefillParams& p, const PrefillArgs& a, int rows, int per_cu = 1) {
     p.n_rb = (a.seq_len + rows - 1) / rows;
     // Under the causal mask the rows that do not fill a block go to the first one, which has the fewest keys, and not
     // to the last (S = 777: 91 key tiles per head instead of 109); the offset keeps the diagonal on tile bounds.
     p.row_off = p.causal ? (p.n_rb * rows - a.seq_len) / 32 * 32 : 0;
     p.n_bh = a.batch * a.q_heads;
     const int per_xcd = (p.n_rb * p.n_bh + 7) / 8;
-    p.slots = per_xcd < 32 ? per_xcd : 32;
+    p.slots = per_xcd < 32 * per_cu ? per_xcd : 32 * per_cu;
     p.rounds = (per_xcd + p.slots - 1) / p.slots;
     // A batch has 4 KV heads an XCD, or all heads up to twice that: with 32 heads and 32 workgroups an XCD no two of
     // them read the same K/V (B=8, 32 heads, S=4096: 1600 us, 1110 in batches); smaller batches leave ends of
@@ -1089,9 +1089,12 @@ hipError_t launch_prefill(const PrefillArgs& a, hipStream_t stream) {
     p.scale_log2e = a.softmax_scale * kLog2e;
     p.row_max = a.row_max;
     if (a.row_max) {   // the comparison variant: bf16 K/V only (checked by the caller); two launches
-        set_blocks(p, a, kBR);
+        // (the sweep for the maxima fits twice on a compute unit at D = 64, 79 registers and 66 KB, and wants to be there
+        // twice: both sweeps of B=8, 64 on 8 heads, S=1024 220 us with one workgroup, 190 with two)
+        set_blocks(p, a, kBR, a.head_dim == 64 ? 2 : 1);
         hipError_t e = a.head_dim == 128 ? launch_one<128, false, false, 1>(p, stream) : launch_one<64, false, false, 1>(p, stream);
         if (e != hipSuccess) return e;
+        set_blocks(p, a, kBR);
         if (a.head_dim == 128) return a.out_f32 ? launch_one<128, false, true, 2>(p, stream) : launch_one<128, false, false, 2>(p, stream);
         return a.out_f32 ? launch_one<64, false, true, 2>(p, stream) : launch_one<64, false, false, 2>(p, stream);
     }
