@@ -372,9 +372,10 @@ static DecodePlan decode_plan(int kv_len, long n_bh, int head_dim) {
         if (s == 1 || ns < best_ns) {
             best_ns = ns;
             best.n_split = s;
-            // eight waves share a merge where each still gets a few chunks (a chunk each is enough once several
-            // workgroups per compute unit overlap)
-            best.waves = per_wg >= (n_bh * s >= 512 ? 8 : 24) ? 8 : 4;
+            // eight waves share a merge where each still gets a few chunks (a chunk each, two of 64 codes a token, is
+            // enough once several workgroups per compute unit overlap: 800 x 8 heads, T=500, D=64, 77.8 us with eight
+            // waves, 72.4 with four, and with lengths of their own, where half of the eight had nothing, 60.6 and 45.9)
+            best.waves = per_wg >= (n_bh * s >= 512 ? (head_dim == 128 ? 8 : 16) : 24) ? 8 : 4;
         }
     }
     return best;

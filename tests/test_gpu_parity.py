@@ -535,7 +535,9 @@ def test_decode_grouped_all_zero_tokens_and_huge_scores(sa, oracle):
     # more than 16 heads a KV head: one split and two, the most that a short cache is cut into, many workgroups
     (1, 17, 1, 65, 64), (2, 64, 2, 95, 128), (1, 20, 1, 777, 64), (2, 32, 1, 777, 128), (130, 20, 1, 300, 128), (200, 32, 1, 97, 64),
     # one head per KV head: the same edges (64-token chunks)
-    (1, 1, 1, 30000, 128), (3, 1, 1, 4097, 64), (20, 8, 8, 513, 128), (70, 8, 8, 520, 64), (1, 8, 8, 1537, 128)])
+    (1, 1, 1, 30000, 128), (3, 1, 1, 4097, 64), (20, 8, 8, 513, 128), (70, 8, 8, 520, 64), (1, 8, 8, 1537, 128),
+    # many rows of 64 codes a token: four waves up to 15 chunks, eight from 16 on
+    (70, 8, 8, 100, 64), (70, 8, 8, 960, 64), (70, 8, 8, 961, 64)])
 def test_decode_plan_edges(sa, oracle, B, Hq, Hkv, T, D):
     print("decode plan edges", B, Hq, Hkv, T, D, flush=True)
     _decode_case(sa, oracle, B, Hq, Hkv, T, D, seed=T + D + Hq)
