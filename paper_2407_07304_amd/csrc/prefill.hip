@@ -1033,11 +1033,14 @@ static void set_blocks(PrefillParams& p, const PrefillArgs& a, int rows, int per
 //     and so does D = 64, where the wide form gains and loses 6 % in turn.
 //   - small calls take the form of prefill_split.hip: the longest row block's latency, or the chip's tiles and items
 //     (8 heads: S=200 8.9 -> 5.2 us, S=1024 17.0 -> 10.4; 32 heads: S=512 12.8 -> 10.4, S=1024 stays).  All heads go
-//     through one row block before the next, so bf16 K and V that are more than the L2s hold (32 MB) are read again
-//     for every block, at 10 TB/s: without that in the model 40 x 32 heads, S=300, D=64, not causal, took this form at
+//     through one row block before the next, so bf16 K and V that are well over what the L2s hold (32 MB) are read again
+//     for every block, at 10 TB/s (33 MB are not yet worth it: 40 x 32 heads, S=100, D=64, 23.6 us in the caches and
+//     36.9 cold, 27.2 and 34.8 at 128 rows; 66 MB, S=200: 51.6 and 74.7, 55.9 and 67.0): without that in the model 40 x 32 heads, S=300, D=64, not causal, took this form at
 //     145 us (128 rows: 96; the pairs of row blocks before: 132).  (INT8 K and V are half the bytes: the same call
-//     takes 79 us at 32 rows, causal, and 88 at 256.)  The form has a workgroup per row block and head, and a launch
-//     less than 2^32 threads: more of them than that stay with the lists.
+//     takes 79 us at 32 rows, causal, and 88 at 256.)  INT8 tiles are widened once per 32 rows: 0.21 us a tile at D = 128,
+//     where 0.18 as for bf16 put 8 heads, S=5000, at 100 us (128 rows: 89; the pairs before: 97).  The form has a
+//     workgroup per row block and head, and a launch less than 2^32 threads: more of them than that stay with the
+//     lists.
 static int choose_rows(PrefillParams& p, const PrefillArgs& a) {
     const bool d128 = a.head_dim == 128;
     int rows = kBR;
@@ -1059,8 +1062,9 @@ static int choose_rows(PrefillParams& p, const PrefillArgs& a) {
     const double blocks32 = (a.seq_len + 31) / 32, tiles = blocks32 * p.n_bh * (p.causal ? (blocks32 + 1) / 2 : blocks32);
     const double us_longest = d128 ? 3.4 + 0.18 * blocks32 : 3.3 + 0.11 * blocks32;
     const double kv_bytes = 4.0 * a.batch * a.kv_heads * a.seq_len * a.head_dim;
-    const double us_again = !a.kv_int8 && kv_bytes > 32e6 ? kv_bytes * (p.causal ? (blocks32 + 1) / 2 : blocks32) / 10e6 : 0.0;
-    const double us_all = (d128 ? 1.5 : 1.2) + ((d128 ? 0.18 : 0.115) * tiles + (d128 ? 2.0 : 1.2) * blocks32 * p.n_bh) / 256 + us_again;
+    const double us_again = !a.kv_int8 && kv_bytes > 40e6 ? kv_bytes * (p.causal ? (blocks32 + 1) / 2 : blocks32) / 10e6 : 0.0;
+    const double us_tile = d128 ? (a.kv_int8 ? 0.21 : 0.18) : 0.115, us_block = d128 ? (a.kv_int8 ? 1.8 : 2.0) : 1.2;
+    const double us_all = (d128 ? 1.5 : 1.2) + (us_tile * tiles + us_block * blocks32 * p.n_bh) / 256 + us_again;
     const bool launchable = blocks32 * p.n_bh * 256 < 0x1p32;
     return launchable && (us_longest > us_all ? us_longest : us_all) < us ? 32 : rows;
 }

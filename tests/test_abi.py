@@ -245,6 +245,9 @@ def test_prefill_form_of_a_call(lib):
     # bf16 K and V of many heads are more than the L2s hold: the form that reads them once per 32 rows is not taken
     for B, H in ((40, 32), (40, 40), (64, 32)):
         assert f(B, H, H, 300, 64, 0, 0, 0) == 128
+    # long INT8 sequences of few heads, which that form would widen once per 32 rows
+    for Hkv in (8, 2):
+        assert f(1, 8, Hkv, 5000, 128, 1, 2, 0) == f(1, 8, Hkv, 5000, 128, 1, 2, 1) == 128
     # the form with a workgroup of 256 threads per 32 rows and head is taken only where a launch can hold them (less than
     # 2^32 threads); the item lists of the others need no more workgroups than the chip has compute units
     short, at_limit = f(170, 30000, 30000, 96, 64, 1, 0, 0), f(200, 30000, 30000, 96, 64, 1, 0, 0)

@@ -162,7 +162,7 @@ def test_prefill_small_calls(sa, oracle, B, Hq, Hkv, S, D, causal, out_f32, kv_i
 @pytest.mark.parametrize("B,Hq,Hkv,S,D,causal,out_f32", [
     # one block of 256 rows holds the sequence: row groups of 32 that end inside, key tiles that end inside
     (7, 32, 8, 97, 128, True, False), (7, 32, 8, 161, 64, False, True), (4, 40, 8, 160, 128, False, False),
-    (33, 4, 2, 255, 128, True, True), (7, 32, 8, 256, 64, True, False),
+    (40, 4, 2, 255, 128, True, True), (7, 32, 8, 256, 64, True, False),
     # longer sequences: one row past a block, uneven halves, several blocks
     (12, 16, 16, 257, 128, True, False), (4, 40, 8, 480, 64, True, False), (16, 16, 8, 300, 128, False, True),
     (24, 16, 16, 545, 64, True, True), (4, 64, 8, 777, 128, True, False), (1, 48, 16, 1057, 128, False, False)])
