@@ -5,18 +5,22 @@
 // probability before it is rounded to bf16 (V), so dequantisation adds no rounding.
 //
 // There are three forms, by the query rows of a workgroup's row block, and choose_rows says which one a call takes: 128
-// rows, described here; 256 rows (WIDE: every wave owns 32 rows and goes through all key tiles, nothing is merged, a ring
-// of two slots a tensor for INT8 K/V and four for bf16; see at the kernel); 32 rows for small calls (prefill_split.hip).
+// rows, 256 rows (WIDE) and, in prefill_split.hip, 32 rows for small calls.
 //
-// Mapping of the 128-row form on gfx950 (wave64, v_mfma_f32_32x32x16_bf16):
-//   - A workgroup is 8 waves and owns 128 query rows.  Waves w and w+4 sit on the same SIMD
-//     and own the same 32 rows; the first four waves (group 0) take the even key tiles, the
-//     other four (group 1) the odd ones, each with its own running max, sum and accumulator,
-//     merged once at the end of the row block.
-//   - The two groups run in opposite phases, one barrier per phase: while one group does the
-//     softmax of its tile on the vector ALU, the other feeds the matrix pipe (P V of its last
-//     tile, then the score tile two tiles ahead).  A SIMD therefore always holds one wave that
-//     wants the vector ALU and one that wants the MFMA unit.
+// Mapping of the 128- and 256-row forms on gfx950 (wave64, v_mfma_f32_32x32x16_bf16):
+//   - A workgroup is 8 waves, two per SIMD, and a wave owns 32 query rows.  256 rows: every wave goes through all key
+//     tiles, and nothing is merged.  128 rows: waves w and w+4 own the same rows, the first four waves (group 0) take the
+//     even key tiles, the others (group 1) the odd ones, each with its own running max, sum and accumulator, merged once at
+//     the end of the row block.
+//   - An iteration is one tile of every wave and one barrier: the wave issues the scores of its next tile and P V of
+//     its last one, alternately, and between two MFMAs a share of this tile's softmax (a fused multiply-add, an
+//     exponential, an addition, half a conversion), the operand read that replaces the one the MFMA consumed, and a ring
+//     request.  A wave's own vector work so runs in the shadow of its MFMAs (a microbenchmark: 16 MFMAs with four vector
+//     instructions each take 34 cycles an MFMA, alone 32.5).  (Before, two groups of waves in opposite phases, softmax and
+//     MFMAs, met at a barrier per phase: 1590 cycles for what an iteration does in 1390.  B=1, 32 heads, bf16, before and
+//     now: S=2048 42.0 -> 40.8 us, S=8192 490 -> 465, D=64, S=4096 95 -> 88; INT8 S=4096 150.0 -> 146.7, D=64 116 -> 100;
+//     B=4, 32 on 8 heads, S=777 34.1 -> 31.6.)  On N(0,1) operands what is left is power: S=8192, not causal, runs at 1.85
+//     PFLOP/s on zeros and at 1.24 on N(0,1), and operand reads from LDS are 15 % of that, the barrier 4 %.
 //   - The score tile is computed transposed, S^T = K Q^T: the K tile is the A operand
 //     (from LDS), Q^T the B operand (held in registers for the whole row block).  In the
 //     result every lane holds ONE query column and 16 of the 32 keys, so the row max and
@@ -27,17 +31,15 @@
 //   - O^T accumulators: lane = query column, so the online-softmax rescale is a per-lane
 //     scalar multiply; the running max is lazy (it moves only when a row's max grew by more
 //     than 2^8), so the rescale runs a few times per row block.
-//   - K/V tiles live in an LDS ring (eight K slots, four V slots).  bf16 tiles are written by the
-//     memory pipe itself (buffer loads with an LDS destination, issued by the group in its
-//     matrix phase, six (K) and four (V) tiles ahead, one load between two MFMAs, the same
-//     loads and the same wait in every phase: past the last tile they ask for zeros) as unpadded
+//   - K/V tiles live in an LDS ring of four iterations.  bf16 tiles are written by the
+//     memory pipe itself (buffer loads with an LDS destination, four (K) and two (V) iterations ahead, the same
+//     loads and the same wait in every iteration: past the last tile they ask for zeros) as unpadded
 //     rows whose 16-byte chunks are
 //     XOR-swizzled by the row, so both the 128-bit K row reads and the V transpose reads are
 //     free of bank conflicts; INT8 tiles pass through registers, where they are widened, into
 //     padded rows.
-//   - A wave reads its MFMA operands from LDS one matrix phase ahead, each fragment right after
-//     the MFMA that consumed its predecessor: the reads issue in the shadow of the MFMAs and
-//     the softmax phase is pure vector work.
+//   - A wave reads its MFMA operands from LDS half a tile ahead, each fragment right after the MFMA that consumed the
+//     register it refills.
 //   - A workgroup works off a list of (row block, head) items, one after the other; the lists are
 //     dealt so that every workgroup meets about the same number of key tiles, whatever the number
 //     of row blocks and heads (pairs of a short and a long block, as before, left up to half of the
@@ -52,8 +54,7 @@ namespace slim {
 
 constexpr int kBR = 128;   // query rows per row block (4 row groups x 32)
 constexpr int kBC = 32;    // keys per tile
-constexpr int kRingK = 8;  // LDS ring depth, K tiles
-constexpr int kRingV = 4;  // LDS ring depth, V tiles
+constexpr int kRing = 4;   // LDS ring depth, in iterations
 constexpr int kPrefillThreads = 512;
 
 struct PrefillParams {
@@ -104,19 +105,22 @@ using int_c = std::integral_constant<int, N>;
 // to p.row_max), MODE 2 computes them again, exponentiates against those final maxima and multiplies by V:
 // no running maximum, no rescaling of the accumulator, 1.5 times the MFMAs.  MODE 0 is the kernel proper.
 //
-// WIDE (not D = 64 with bf16 K/V): row blocks of 256 rows.  The eight waves own 32 rows each and every wave goes through
-// all key tiles, so a staged tile meets twice the query rows: the two groups stay in opposite phases, but on the same tile
-// one phase apart, group 1 stages K and group 0 V (half the widening, or half the ring's requests, per matrix phase), and
-// there is nothing to merge at the end.  See choose_rows for when it is taken and what it gives.
+// WIDE (not D = 64 with bf16 K/V): row blocks of 256 rows.  A staged tile meets twice the query rows (half the widening, or
+// half the ring's requests, per MFMA), and there is nothing to merge at the end.  See choose_rows for when it is taken and
+// what it gives.
+
 template <int D, bool KV_I8, bool OUT_F32, int MODE = 0, bool WIDE = false>
 __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const PrefillParams p) {
     static_assert(!(MODE != 0 && (KV_I8 || WIDE)), "the two-sweep variant exists for bf16 K/V and 128 rows only");
     constexpr int BR = WIDE ? 2 * kBR : kBR;   // query rows per row block
-    constexpr int RK = WIDE ? (KV_I8 ? 2 : 4) : kRingK, RV = WIDE ? (KV_I8 ? 2 : 4) : kRingV;   // ring depth (see the phases)
+    constexpr int NG = WIDE ? 1 : 2;           // key tiles of an iteration: wave groups that own the same rows
     constexpr bool stats_only = MODE == 1;
     constexpr int KS = D / 16;       // k-steps of the score MFMA
     constexpr int DT = D / 32;       // 32-row tiles of O^T
-    constexpr int ROWB = KV_I8 ? D : 2 * D;   // bytes per K/V row in memory
+    constexpr int NS = 2 * KS;       // MFMAs of an iteration: KS of the scores, 2 DT = KS of P V
+    constexpr int EPS = 16 / NS;     // probabilities of a lane per MFMA
+    constexpr int KP = KS / 2, VP = DT;        // operand fragments read ahead: half a tile's
+    constexpr int ROWB = KV_I8 ? D : 2 * D;    // bytes per K/V row in memory
     // LDS tile layouts.  bf16 K/V: unpadded rows (that is how the memory pipe writes them), the 16-byte
     // chunk c of row r at chunk position c ^ swz(r).  K: the 16 rows a 128-bit read touches in one pass
     // land on 16 different bank groups.  V: the 4 rows x 4 chunks a transpose read touches in one pass do.
@@ -125,29 +129,29 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
     constexpr int ROWL = 2 * D;               // bytes of data per LDS row
     constexpr int ROWLK = KV_I8 ? ROWL + 16 : ROWL, ROWLV = KV_I8 ? ROWL + 64 : ROWL;   // row pitch
     constexpr int TILEBK = kBC * ROWLK, TILEBV = kBC * ROWLV;   // bytes per tile in LDS
-    constexpr int TILEB = TILEBK;             // (bf16: both tensors)
+    constexpr int SLOTK = NG * TILEBK, SLOTV = NG * TILEBV;     // bytes per ring slot (an iteration's tiles)
     constexpr int CPL = ROWL / 16;            // 16-byte chunks per LDS row: 16 or 8
     constexpr int RPL = 256 / ROWL;           // rows per 256-byte line of banks: 1 or 2
-    constexpr int K_BYTES = RK * TILEBK, V_BYTES = RV * TILEBV;
+    constexpr int K_BYTES = kRing * SLOTK, V_BYTES = kRing * SLOTV;
     constexpr int NV = DT / 2 * 4 + 1;        // f32x4 vectors a wave hands to its partner at the merge
     constexpr int OPITCH = (OUT_F32 ? 4 * D : 2 * D) + 16;   // output tile row pitch: spreads the column-wise writes over the banks
-    constexpr int MERGE_BYTES = WIDE ? BR * OPITCH : 8 * NV * 64 * 16;
-    // (the merge buffer takes the place of the ring, which is quiet by then)
+    constexpr int OUT_BYTES = BR * OPITCH, MERGE_BYTES = WIDE || 8 * NV * 64 * 16 < OUT_BYTES ? OUT_BYTES : 8 * NV * 64 * 16;
+    // (the merge buffer and the output tile take the place of the ring, which is quiet by then)
     constexpr int RING_BYTES = K_BYTES + V_BYTES > MERGE_BYTES ? K_BYTES + V_BYTES : MERGE_BYTES;
     auto swz_k = [](int r) { return KV_I8 ? 0 : (r / RPL) & (CPL - 1); };
     auto swz_v = [](int r) { return KV_I8 ? 0 : ((r / RPL) & (CPL / 4 - 1)) << 2; };
 
-    // The row block's Q: 128 unpadded rows, the 16-byte chunk c of row r at chunk position c ^ qswz(r) (the bf16 K tile's layout)
+    // The row block's Q: BR unpadded rows, the 16-byte chunk c of row r at chunk position c ^ qswz(r) (the bf16 K tile's layout)
     constexpr int ROWQ = 2 * D;                // bytes per Q row, in memory and in LDS
     constexpr int CPQ = ROWQ / 16;             // 16-byte chunks per row: 16 or 8
     constexpr int RPQ = 64 / CPQ;              // rows per wave-wide load: 4 or 8
     constexpr int NQ = BR / 8 / RPQ;           // loads per wave and row block (a wave brings in an eighth of the rows)
-    constexpr int Q_OFF = RING_BYTES + kRingK * 2 * kBC * 4;
+    constexpr int SC_BYTES = KV_I8 ? kRing * NG * 2 * kBC * 4 : 0;   // INT8: per slot the k_scales * c, then the v_scales
+    constexpr int Q_OFF = RING_BYTES + SC_BYTES;
     auto qswz = [](int r) { return (r / (256 / ROWQ)) & (CPQ - 1); };
 
     constexpr bool Q_LDS = !KV_I8;             // (the INT8 kernel keeps plain loads into the registers: measured faster there)
     __shared__ __attribute__((aligned(16))) char smem[Q_OFF + (Q_LDS ? BR * ROWQ : 0)];
-    float* const scS = reinterpret_cast<float*>(smem + RING_BYTES);   // INT8: per slot [0,32) k_scale*c, [32,64) v_scale
 
     // Work items are (row block, batch*head).  They are listed in batches of `heads` heads (few enough that what an XCD
     // works on at a time keeps its K/V in the L2), longest row block first within a batch; item j goes to XCD j % 8
@@ -229,15 +233,15 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
     __builtin_amdgcn_sched_barrier(0);
 
     // ---- staging.  The buffer descriptors cover exactly this head's K (V) slab: pieces past the end of
-    // the sequence read as zero (those keys are masked in the softmax).  A tile is staged by the four
-    // waves of ONE group.
+    // the sequence read as zero (those keys are masked in the softmax).  An iteration's tiles are staged by all waves.
     // bf16: one buffer load with an LDS destination moves 64 consecutive 16-byte chunk positions (RPW whole
     // rows); lane i fills position i, so it asks for the chunk the swizzle puts there.  The load is
     // written as inline assembly on purpose: the compiler then keeps no book on it, and neither its
-    // barriers nor its LDS reads wait for requests that are meant to stay in flight for two phases.
+    // barriers nor its LDS reads wait for requests that are meant to stay in flight over an iteration.
     // Completion is tracked by hand (vmcnt) where a tile becomes readable.
     constexpr int RPW = 64 / CPL;              // rows per wave-wide load: 4 or 8
-    constexpr int NLD = kBC / (4 * RPW);       // loads per wave, tile and tensor: 2 or 1
+    constexpr int NLT = NG * kBC / RPW;        // loads per iteration and tensor: 4, 8 or 16
+    constexpr int NLD = NLT >= 8 ? NLT / 8 : 1;   // of which a wave issues (four: the first waves K's, the others V's)
     auto raw_rsrc = [&](const char* base) {    // the same descriptor as four plain dwords
         const unsigned long long a64 = (unsigned long long)base;
         u32x4 d;
@@ -247,117 +251,80 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
         d[3] = 0x00020000u;
         return d;
     };
-    unsigned d_koff[NLD], d_voff[NLD];
-#pragma unroll
-    for (int j = 0; j < NLD; ++j) {
-        const int r = (kBC / NLD) * j + RPW * w + l / CPL, pos = l % CPL;
-        d_koff[j] = (unsigned)r * ROWB + (unsigned)((pos ^ swz_k(r)) * 16);
-        d_voff[j] = (unsigned)r * ROWB + (unsigned)((pos ^ swz_v(r)) * 16);
+    unsigned d_koff, d_voff;
+    const int d_idx = NLT >= 8 ? w8 : w;       // this wave's load of the tile (and every eighth after it)
+    {
+        const int r = RPW * d_idx + l / CPL, pos = l % CPL;
+        d_koff = (unsigned)r * ROWB + (unsigned)((pos ^ swz_k(r)) * 16);
+        d_voff = (unsigned)r * ROWB + (unsigned)((pos ^ swz_v(r)) * 16);
     }
-    auto dma_tile = [&](const u32x4 rs, const unsigned (&off)[NLD], int t, int lds_off, bool wanted = true) {
-        // (a tile that is not wanted is requested past the end of the slab: zeros arrive, no memory is read)
-        const unsigned tbase = wanted ? (unsigned)t * (kBC * ROWB) : (unsigned)S * ROWB;
-#pragma unroll
-        for (int j = 0; j < NLD; ++j) {
-            const unsigned dst = __builtin_amdgcn_readfirstlane(smem_base + (unsigned)(lds_off + ((kBC / NLD) * j + RPW * w) * ROWL));
-            const unsigned voff = tbase + off[j];
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-                         :
-                         : "s"(dst), "v"(voff), "s"(rs)
-                         : "memory", "m0");
-        }
-    };
-
-    // The same, one load at a time: the address work first, the request later, so that a matrix phase can tuck
-    // them between its MFMAs without ever keeping the matrix pipe waiting for the next one.
-    auto dma_prep = [&](const unsigned (&off)[NLD], int j, int t, int lds_off, bool wanted, unsigned& dst, unsigned& voff) {
-        const unsigned tbase = wanted ? (unsigned)t * (kBC * ROWB) : (unsigned)S * ROWB;
-        dst = __builtin_amdgcn_readfirstlane(smem_base + (unsigned)(lds_off + ((kBC / NLD) * j + RPW * w) * ROWL));
-        voff = tbase + off[j];
-    };
     auto dma_fire = [&](const u32x4 rs, unsigned dst, unsigned voff) {
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
                      :
                      : "s"(dst), "v"(voff), "s"(rs)
                      : "memory", "m0");
     };
+    // load n of this wave's share of iteration tile T, to the slot at lds_off (a tile that is not wanted is requested past
+    // the end of the slab: zeros arrive, no memory is read)
+    auto dma_one = [&](const u32x4 rs, unsigned off, int n, int T, int lds_off, bool wanted) {
+        const unsigned tbase = wanted ? (unsigned)T * (NG * kBC * ROWB) + (unsigned)n * (8 * RPW * ROWB) : (unsigned)S * ROWB;
+        dma_fire(rs, __builtin_amdgcn_readfirstlane(smem_base + (unsigned)(lds_off + (d_idx + 8 * n) * 1024)), tbase + off);
+    };
 
-    // INT8: piece gl + 256 i of thread gl (16 codes) goes through registers and leaves as two bf16 chunks.
-    // The last wave of a group also carries the tile's 32 + 32 scales.
+    // INT8: 16 codes go through registers and leave as two bf16 chunks.  A tensor's pieces are 64-piece units; a thread
+    // takes one of K and one of V (TWO), or the first waves take K's and the next ones V's.
     constexpr int CPR = ROWB / 16;            // 16-byte pieces per row in memory
-    constexpr int CH = kBC * CPR;             // pieces per tile and tensor
-    constexpr int NP = CH >= 256 ? CH / 256 : 1;
-    const int gl = tid & 255;
-    const bool has_p = CH >= 256 || w < CH / 64;
-    // The tile's scales: the last wave of a group carries the 32 k_scales, the one before it the 32 v_scales (every
-    // choice here is uniform over the wave: a value that depends on the lane would have to live, as a register or as
-    // a spill, through the whole kernel).  Both halves of the wave load and store the same 32 values.
-    const bool has_s = KV_I8 && w >= 2;
-    const bool s_is_k = w == 3;
-    unsigned p_off[NP];
-    int p_kdst[NP][2], p_vdst[NP][2];
-#pragma unroll
-    for (int i = 0; i < NP; ++i) {
-        const int pid = gl + 256 * i, row = pid / CPR, col = pid % CPR;
-        p_off[i] = (unsigned)row * ROWB + (unsigned)col * 16u;
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-            p_kdst[i][e] = row * ROWLK + (((2 * col + e) ^ swz_k(row)) * 16);
-            p_vdst[i][e] = K_BYTES + row * ROWLV + (((2 * col + e) ^ swz_v(row)) * 16);
-        }
-    }
-    auto load_tile_at = [&](const __amdgpu_buffer_rsrc_t rs, int t, u32x4 (&dst)[NP], const unsigned (&off)[NP]) {
-        if (has_p) {
-#pragma unroll
-            for (int i = 0; i < NP; ++i)
-                dst[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)((unsigned)t * (kBC * ROWB) + off[i]), 0, 0);
-        }
-    };
-    auto load_tile = [&](const __amdgpu_buffer_rsrc_t rs, int t, u32x4 (&dst)[NP]) { load_tile_at(rs, t, dst, p_off); };
+    constexpr int UPT = NG * kBC * CPR / 64;  // units per tensor and iteration: 8, 4 or 2
+    constexpr bool TWO = UPT >= 8;
+    const bool st_k = TWO || w8 < UPT;        // this wave's (first) unit is K's
+    const bool has_p = 2 * UPT >= 8 || w8 < 2 * UPT;
+    const int pid = (TWO ? w8 : w8 % UPT) * 64 + l, prow = pid / CPR, pcol = pid % CPR;
+    const unsigned p_off = (unsigned)prow * ROWB + (unsigned)pcol * 16u;
+    const int p_kdst = prow * ROWLK + 32 * pcol, p_vdst = K_BYTES + prow * ROWLV + 32 * pcol;
+    const int p_dst = st_k ? p_kdst : p_vdst;
+    // The iteration's scales: the last wave carries the k_scales, the one before it the v_scales (every choice here is
+    // uniform over the wave).
+    const bool has_s = KV_I8 && w8 >= 6;
+    const bool s_is_k = w8 == 7;
+    const int s_lane = l & (NG * kBC - 1);
     __amdgpu_buffer_rsrc_t srs;
-    auto load_s_at = [&](int t, float& dst, int lane32, bool wanted) {   // (a key past the end of the sequence gets scale 0: it is masked anyway)
-        if (wanted) dst = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(srs, (t * kBC + lane32) * 4, 0, 0));
+    auto widen_dword = [&](unsigned cw, unsigned& lo, unsigned& hi) {   // 4 codes -> 4 bf16, exact
+        lo = pack_bf16x2(i8_to_f32<0>(cw), i8_to_f32<1>(cw));
+        hi = pack_bf16x2(i8_to_f32<2>(cw), i8_to_f32<3>(cw));
     };
-    auto load_s = [&](int t, float& dst) { load_s_at(t, dst, l32, has_s); };
-    auto store_tile = [&](int slot_off, const int (&dsts)[NP][2], const u32x4 (&src)[NP]) {   // 16 INT8 codes -> 16 bf16 (exact)
-        if (has_p) {
-#pragma unroll
-            for (int i = 0; i < NP; ++i) {
-                const u32x4 cw = src[i];
-                u32x4 lo, hi;
-#pragma unroll
-                for (int e = 0; e < 2; ++e) {
-                    lo[2 * e] = pack_bf16x2(i8_to_f32<0>(cw[e]), i8_to_f32<1>(cw[e]));
-                    lo[2 * e + 1] = pack_bf16x2(i8_to_f32<2>(cw[e]), i8_to_f32<3>(cw[e]));
-                    hi[2 * e] = pack_bf16x2(i8_to_f32<0>(cw[2 + e]), i8_to_f32<1>(cw[2 + e]));
-                    hi[2 * e + 1] = pack_bf16x2(i8_to_f32<2>(cw[2 + e]), i8_to_f32<3>(cw[2 + e]));
-                }
-                *reinterpret_cast<u32x4*>(smem + slot_off + dsts[i][0]) = lo;
-                *reinterpret_cast<u32x4*>(smem + slot_off + dsts[i][1]) = hi;
-            }
-        }
+    auto store_piece = [&](int at, const u32x4 cw) {
+        u32x4 a, b;
+        unsigned x, y;
+        widen_dword(cw[0], x, y); a[0] = x; a[1] = y;
+        widen_dword(cw[1], x, y); a[2] = x; a[3] = y;
+        widen_dword(cw[2], x, y); b[0] = x; b[1] = y;
+        widen_dword(cw[3], x, y); b[2] = x; b[3] = y;
+        *reinterpret_cast<u32x4*>(smem + at) = a;
+        *reinterpret_cast<u32x4*>(smem + at + 16) = b;
     };
-    auto store_s = [&](int slot, float s, bool wanted) {
-        if (wanted) scS[slot * (2 * kBC) + (s_is_k ? 0 : kBC) + l32] = s_is_k ? s * c : s;
+    float* const scS = reinterpret_cast<float*>(smem + RING_BYTES);
+    auto store_s = [&](int slot, float s) {
+        if (has_s) scS[slot * (NG * 2 * kBC) + (s_is_k ? 0 : NG * kBC) + s_lane] = s_is_k ? s * c : s;
     };
-    struct Stage {
-        u32x4 k[NP], v[NP];
-        float s;
+    auto load_s = [&](int T) {   // (a key past the end of the sequence gets scale 0: it is masked anyway)
+        return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(srs, (T * (NG * kBC) + s_lane) * 4, 0, 0));
     };
 
     f32x16 o[DT];
     // LDS read addresses (bytes).  K fragment of k-step s: row l32, chunk 2 s + hh.  V transpose read: the
     // 16 lanes of a group fetch rows k..k+3 (4 lanes per row, 8 bytes each) and lane i of the group
     // receives column i of those 4 rows; per 32-column tile dt the lane reads chunk 4 dt + 2 b4 + (l&3)/2.
+    const int my_tile = NG == 2 ? grp : 0;   // which of an iteration's tiles is this wave's
     int k_addr[KS], v_addr[DT];
 #pragma unroll
-    for (int s2 = 0; s2 < KS; ++s2) k_addr[s2] = l32 * ROWLK + (((2 * s2 + hh) ^ swz_k(l32)) * 16);
+    for (int s2 = 0; s2 < KS; ++s2) k_addr[s2] = my_tile * TILEBK + l32 * ROWLK + (((2 * s2 + hh) ^ swz_k(l32)) * 16);
     {
         const int rv = 4 * hh + ((l & 15) >> 2);
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
-            v_addr[dt] = K_BYTES + rv * ROWLV + (((4 * dt + 2 * ((l >> 4) & 1) + ((l & 3) >> 1)) ^ swz_v(rv)) * 16) + 8 * (l & 1);
+            v_addr[dt] = K_BYTES + my_tile * TILEBV + rv * ROWLV + (((4 * dt + 2 * ((l >> 4) & 1) + ((l & 3) >> 1)) ^ swz_v(rv)) * 16) + 8 * (l & 1);
     }
+    const int sc_addr = RING_BYTES + (my_tile * kBC + 4 * hh) * 4;   // this lane's k_scales: + 32 bytes per 8 keys
 
     for (;;) {   // the workgroup's items
         const int kvh = (int)div_magic((unsigned)bh, p.group, p.group_magic);   // (batch, KV head): heads per batch are a multiple of the group
@@ -365,132 +332,93 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
         // the buffer descriptors cover exactly this head's K (V) slab
         const char* const kslab = (const char*)p.k + kvrow0 * ROWB;
         const char* const vslab = (const char*)p.v + kvrow0 * ROWB;
-        const __amdgpu_buffer_rsrc_t krs = __builtin_amdgcn_make_buffer_rsrc((void*)kslab, 0, (int)((unsigned)S * ROWB), 0x00020000);
-        const __amdgpu_buffer_rsrc_t vrs = __builtin_amdgcn_make_buffer_rsrc((void*)vslab, 0, (int)((unsigned)S * ROWB), 0x00020000);
         const u32x4 krs_raw = raw_rsrc(kslab), vrs_raw = raw_rsrc(vslab);
+        const __amdgpu_buffer_rsrc_t krs = __builtin_amdgcn_make_buffer_rsrc((void*)(st_k ? kslab : vslab), 0, (int)((unsigned)S * ROWB), 0x00020000);   // (the first piece's tensor)
+        const __amdgpu_buffer_rsrc_t vrs = __builtin_amdgcn_make_buffer_rsrc((void*)vslab, 0, (int)((unsigned)S * ROWB), 0x00020000);
         {
             const float* const sbase = KV_I8 ? ((s_is_k ? p.ks : p.vs) + kvrow0) : nullptr;
-            srs = __builtin_amdgcn_make_buffer_rsrc((void*)sbase, 0, KV_I8 ? (int)((unsigned)S * 4u) : 0, 0x00020000);
+            srs = __builtin_amdgcn_make_buffer_rsrc((void*)sbase, 0, KV_I8 && has_s ? (int)((unsigned)S * 4u) : 0, 0x00020000);
         }
         const int i0 = rb * BR - p.row_off;              // (negative in a first block that starts before row 0)
         const int my_q = i0 + 32 * rg + l32;             // this lane's query row (may lie outside [0, S))
         const int wave_q_lo = i0 + 32 * rg;
         const int kend = p.causal ? min(S, i0 + BR) : S;
         const int n_tiles = (kend + kBC - 1) / kBC;
-        const int last_phase = WIDE ? 2 * n_tiles : 2 * ((n_tiles + 1) / 2);   // phases 0..last_phase, one barrier each
-        // last tile of this row group: its diagonal under the causal mask, else the tail of the key axis
-        // (always taken through the masked path); -1 if the row group lies outside the sequence
+        const int n_iter = (n_tiles + NG - 1) / NG;      // one barrier each
+        // last tile of this row group: its diagonal under the causal mask, else the tail of the key axis; -1 if the row
+        // group lies outside the sequence
         // (row_off is a multiple of 32: all of a row group's rows lie before row 0 or none does)
         const int t_last = wave_q_lo >= S || wave_q_lo < 0 ? -1 : (p.causal ? min(n_tiles - 1, wave_q_lo / kBC) : n_tiles - 1);
+        const int last = t_last < my_tile ? -1 : (t_last - my_tile) / NG;   // the iteration of this wave's last tile, or -1
         const int lim = p.causal ? min(my_q, S - 1) : S - 1;   // last key this lane's row may see
 
         // (the first item's Q was requested at the top of the kernel, the next one's is before this one's merge)
         float M = kMasked, lsum = 0.0f;   // running max in scaled (log2) units; per-lane partial row sum
-
-        // ---- prologue.  In the steady state a group stages in its matrix phase phi: bf16 requests K tile
-        // phi+6 and V tile phi+4 (in LDS by the end of its next matrix phase); INT8 stores K tile phi+5
-        // and V tile phi+3 from registers and loads K tile phi+7, V tile phi+5 into them.  Everything
-        // earlier is staged here, all requests issued together.  Every V slot gets a tile (zeros past the
-        // end of the sequence): whatever a skipped tile later leaves in place is finite data of this row
-        // block, never the previous item's merge buffer.
         if constexpr (MODE == 2) {   // the final maximum of this lane's row over this group's tiles
             M = p.row_max[(((long)bh * S + min(max(my_q, 0), S - 1)) * 2) + grp];
         }
-        Stage sg;
+
+        // ---- the ring.  Iteration i reads K tile i+1 (its second half) and i+2 (first half), V tile i-1 (second half)
+        // and i (first half).  It requests K tile i+4, which takes the slot of K tile i (last read in iteration i-1), and
+        // V tile i+2 for the slot of V tile i-2; both are waited for at the end of iteration i+1 and read from i+2 on.
+        // INT8 tiles are stored from registers at those points instead, and what is stored next is loaded.
+        // "V tile -1" meets the zero probabilities of iteration 0: its slot is filled with zeros.
+        u32x4 sg0, sg1;
+        float sgs = 0.0f;
         __syncthreads();   // the previous item has finished with the ring and the merge buffer that lies over it
-        if constexpr (WIDE && !KV_I8) {
-            if (grp == 0) {
-                dma_tile(krs_raw, d_koff, 0, 0);
-                dma_tile(krs_raw, d_koff, 2, 2 * TILEB);
-                dma_tile(vrs_raw, d_voff, 1, K_BYTES + TILEB);
-            } else {
-                dma_tile(krs_raw, d_koff, 1, TILEB);
-                dma_tile(vrs_raw, d_voff, 0, K_BYTES);
-                dma_tile(vrs_raw, d_voff, 2, K_BYTES + 2 * TILEB);
-            }
-            __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): this wave's requests have landed in LDS
-        } else if constexpr (!KV_I8) {
-            if (grp == 0) {
-                dma_tile(krs_raw, d_koff, 0, 0);
-                dma_tile(krs_raw, d_koff, 2, 2 * TILEB);
-                dma_tile(krs_raw, d_koff, 4, 4 * TILEB);
-                if (!stats_only) {
-                    dma_tile(vrs_raw, d_voff, 0, K_BYTES);
-                    dma_tile(vrs_raw, d_voff, 2, K_BYTES + 2 * TILEB);
-                }
-            } else {
-                dma_tile(krs_raw, d_koff, 1, TILEB);
-                dma_tile(krs_raw, d_koff, 3, 3 * TILEB);
-                dma_tile(krs_raw, d_koff, 5, 5 * TILEB);
-                if (!stats_only) {
-                    dma_tile(vrs_raw, d_voff, 1, K_BYTES + TILEB);
-                    dma_tile(vrs_raw, d_voff, 3, K_BYTES + 3 * TILEB);
-                }
-            }
-            __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): this wave's requests have landed in LDS
-        } else if constexpr (WIDE) {
-            // LDS: K tiles 0 and 1, V tiles 0 and 1 (a group stages its number's); registers: what each group stores in its
-            // first matrix phase (group 1 in phase 0: K 2; group 0 in phase 1: V 2).  Addresses as below: put together here.
-            u32x4 ta[NP], td[NP];
-            float sa = 0.0f;
-            unsigned off_now[NP];
+        if constexpr (!KV_I8) {
+            const bool does_k = NLT >= 8 || w8 < 4, does_v = !stats_only && (NLT >= 8 || w8 >= 4);
+            auto k_tile = [&](int T) {
+                if (does_k)
 #pragma unroll
-            for (int i = 0; i < NP; ++i) {
-                off_now[i] = p_off[i];
-                asm volatile("" : "+v"(off_now[i]));
-            }
-            int l32_now = l32, w_now = w;
-            asm volatile("" : "+v"(l32_now));
-            asm volatile("" : "+s"(w_now));
-            load_tile_at(krs, grp, ta, off_now);
-            load_tile_at(vrs, grp, td, off_now);
-            load_s_at(grp, sa, l32_now, w_now >= 2);
-            load_tile_at(grp == 1 ? krs : vrs, 2, sg.k, off_now);
-            load_s_at(2, sg.s, l32_now, w_now == 2 + grp);
-            store_tile(grp * TILEBK, p_kdst, ta);
-            store_tile(grp * TILEBV, p_vdst, td);
-            store_s(grp, sa, has_s);
+                    for (int n = 0; n < NLD; ++n) dma_one(krs_raw, d_koff, n, T, T * SLOTK, T < n_iter);
+            };
+            auto v_tile = [&](int T, bool wanted) {
+                if (does_v)
+#pragma unroll
+                    for (int n = 0; n < NLD; ++n) dma_one(vrs_raw, d_voff, n, T, K_BYTES + T * SLOTV, wanted);
+            };
+            k_tile(0);
+            k_tile(1);
+            k_tile(2);
+            v_tile(0, true);
+            v_tile(3, false);
+            k_tile(3);
+            v_tile(1, 1 < n_iter);
+            __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): this wave's requests have landed in LDS
         } else {
-            // LDS: K tiles 0..4, V tiles 0..2 (group 0: K 0, 2, 4, V 0, 2; group 1: K 1, 3, V 1); registers: what
-            // each group stores in its first matrix phase (group 1 in phase 0: K 5, V 3; group 0 in phase 1: K 6, V 4)
-            u32x4 ta[NP], tb[NP], tc[NP], td[NP], te[NP];
-            float sa = 0.0f, sb = 0.0f, sc3 = 0.0f;
+            u32x4 ta[4], tb[4];
+            float s0, s1, s2;
             // The addresses of these loads are put together here, from copies the compiler cannot see through: left
             // to itself it computes all of them ahead of the item loop, spills them, and reloads them one by one
             // between the loads, and a reload is a memory access that waits, in order, for the tile loads before it
             // (eight trips to cold memory one after the other instead of one).
-            unsigned off_now[NP];
+            unsigned off_now = p_off;
+            asm volatile("" : "+v"(off_now));
+            constexpr unsigned TB = NG * kBC * ROWB;
+            const unsigned beyond = (unsigned)S * ROWB;
 #pragma unroll
-            for (int i = 0; i < NP; ++i) {
-                off_now[i] = p_off[i];
-                asm volatile("" : "+v"(off_now[i]));
-            }
-            int l32_now = l32, w_now = w;
-            asm volatile("" : "+v"(l32_now));
-            asm volatile("" : "+s"(w_now));
-            const bool has_s_now = w_now >= 2;   // (likewise: a flag kept from the top of the kernel comes back as a reload between the loads)
-            load_tile_at(krs, grp, ta, off_now);
-            load_tile_at(krs, 2 + grp, tb, off_now);
-            load_tile_at(vrs, grp, td, off_now);
-            load_s_at(grp, sa, l32_now, has_s_now);
-            load_s_at(2 + grp, sb, l32_now, has_s_now);
-            // (K tile 4 and V tile 2 belong to group 0's share; group 1 brings them in as well and writes the same
-            // bytes to the same place: a branch around these loads makes the compiler spill a tile that has just
-            // been asked for, and waiting for that store lets the loads after it start a memory latency late)
-            load_tile_at(krs, 4, tc, off_now);
-            load_tile_at(vrs, 2, te, off_now);
-            load_s_at(4, sc3, l32_now, has_s_now);
-            load_tile_at(krs, 6 - grp, sg.k, off_now);
-            load_tile_at(vrs, 4 - grp, sg.v, off_now);
-            load_s_at(6 - grp, sg.s, l32_now, has_s_now);
-            store_tile(grp * TILEBK, p_kdst, ta);
-            store_tile((2 + grp) * TILEBK, p_kdst, tb);
-            store_tile(grp * TILEBV, p_vdst, td);
-            store_s(grp, sa, has_s);
-            store_s(2 + grp, sb, has_s);
-            store_tile(4 * TILEBK, p_kdst, tc);
-            store_tile(2 * TILEBV, p_vdst, te);
-            store_s(4, sc3, has_s);
+            for (int n = 0; n < 4; ++n)
+                ta[n] = __builtin_amdgcn_raw_buffer_load_b128(krs, (int)((n == 3 && !st_k ? beyond : n * TB) + off_now), 0, 0);
+            if constexpr (TWO)
+#pragma unroll
+                for (int n = 0; n < 4; ++n)
+                    tb[n] = __builtin_amdgcn_raw_buffer_load_b128(vrs, (int)((n == 3 ? beyond : n * TB) + off_now), 0, 0);
+            s0 = load_s(0);
+            s1 = load_s(1);
+            s2 = load_s(2);
+            sg0 = __builtin_amdgcn_raw_buffer_load_b128(krs, (int)((st_k ? 4 * TB : 2 * TB) + off_now), 0, 0);
+            if constexpr (TWO) sg1 = __builtin_amdgcn_raw_buffer_load_b128(vrs, (int)(2 * TB + off_now), 0, 0);
+            sgs = load_s(3);
+            if (has_p)
+#pragma unroll
+                for (int n = 0; n < 4; ++n) store_piece(p_dst + n * (st_k ? SLOTK : SLOTV), ta[n]);
+            if constexpr (TWO)
+#pragma unroll
+                for (int n = 0; n < 4; ++n) store_piece(p_vdst + n * SLOTV, tb[n]);
+            store_s(0, s0);
+            store_s(1, s1);
+            store_s(2, s2);
         }
         __syncthreads();
         read_q();
@@ -500,111 +428,68 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
 #pragma unroll
             for (int r = 0; r < 16; ++r) o[dt][r] = 0.0f;
 
-        // Operand fragments, read from LDS one matrix phase ahead:
+        // Operand fragments, read from LDS half a tile ahead:
         //   kfr: K tile as A operand, lane = key l32, d = 16 s + 8 hh + [0,8)
-        //   vfr[u]: V^T tile as A operand for keys 16u..16u+15.  Transpose read: the 16 lanes of a group
-        //   fetch rows k..k+3 (4 lanes per row, 4 columns each) and lane i receives column i of those rows.
-        bf16x8 kfr[KS];
-        s16x4 vfr[2][2 * DT];
-        auto fetch_k1 = [&](int s, int slot_off) {   // slot_off: byte offset of the K ring slot
-            kfr[s] = *reinterpret_cast<const bf16x8*>(smem + k_addr[s] + slot_off);
+        //   vfr: V^T tile as A operand for keys 16u..16u+15, d = 32 dt + l32, fragment x = u DT + dt.  Transpose read: the 16
+        //   lanes of a group fetch rows k..k+3 (4 lanes per row, 4 columns each) and lane i receives column i of those rows.
+        bf16x8 kfr[KP];
+        s16x4 vfr[VP][2];
+        auto fetch_k = [&](int s, int slot_off) {   // slot_off: byte offset of the K ring slot
+            kfr[s % KP] = *reinterpret_cast<const bf16x8*>(smem + k_addr[s] + slot_off);
         };
-        auto fetch_v1 = [&](int u, int dt, int slot_off) {   // slot_off: byte offset of the V ring slot
-            const char* va = smem + v_addr[dt] + slot_off + 16 * u * ROWLV;
-            vfr[u][2 * dt] = lds_read_tr16(reinterpret_cast<const uint16_t*>(va));
-            vfr[u][2 * dt + 1] = lds_read_tr16(reinterpret_cast<const uint16_t*>(va + 8 * ROWLV));
+        auto fetch_v = [&](int x, int slot_off) {   // slot_off: byte offset of the V ring slot
+            const char* va = smem + v_addr[x % DT] + slot_off + 16 * (x / DT) * ROWLV;
+            vfr[x % VP][0] = lds_read_tr16(reinterpret_cast<const uint16_t*>(va));
+            vfr[x % VP][1] = lds_read_tr16(reinterpret_cast<const uint16_t*>(va + 8 * ROWLV));
         };
         // One score MFMA, S^T[key][query] += sum over d in [16 s, 16 s + 16) of K[key][d] Q[query][d], and one
         // P V MFMA, O^T[d][query] += sum_key V[key][d] P[query][key] for d in [32 dt, 32 dt + 32); k-step u of
         // the latter covers registers 8u..8u+7 of the probabilities, i.e. keys 16u + {4hh..4hh+3} and
         // 16u + 8 + {4hh..4hh+3} of the tile.
-        auto score_mfma = [&](int s, f32x16& acc) {
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfr[s], qreg[s], acc, 0, 0, 0);
-        };
-        auto pv_mfma = [&](int u, int dt, const u32x4 (&pw)[2]) {
-            const bf16x8 pb = __builtin_bit_cast(bf16x8, pw[u]);
-            const s16x4 lo = vfr[u][2 * dt], hi = vfr[u][2 * dt + 1];
+        auto pv_mfma = [&](int x, const u32x4 (&pw)[2]) {
+            const s16x4 lo = vfr[x % VP][0], hi = vfr[x % VP][1];
             const s16x8 av = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-            o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av), pb, o[dt], 0, 0, 0);
+            o[x % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av), __builtin_bit_cast(bf16x8, pw[x / DT]), o[x % DT], 0, 0, 0);
         };
-        // softmax of tile t (scores in st, register r of this lane is key 32 t + 8 (r/4) + 4 hh + r%4):
-        // probabilities, rounded to bf16, into pw.  Pure vector work.
-        auto softmax = [&](int sc_slot, int t, const f32x16& st, u32x4 (&pw)[2]) {
-            if (t > t_last) {   // tile skipped by this row group: its P V MFMAs run on zeros
+        // The softmax of tile t with the maximum taken exactly (scores in st, register r of this lane is key 32 t + 8 (r/4)
+        // + 4 hh + r%4; sc_slot: the tile's scales): moves the running max, rescales what there is, leaves the probabilities
+        // in pn.  Keys of this lane past offset rel are masked.
+        auto exact_softmax = [&](int sc_off, int rel, bool first, const f32x16& st, u32x4 (&pn)[2]) {
+            float a[16];
 #pragma unroll
-                for (int u = 0; u < 2; ++u)
+            for (int r4 = 0; r4 < 4; ++r4) {
+                f32x4 kf = {c, c, c, c};
+                if constexpr (KV_I8) kf = *reinterpret_cast<const f32x4*>(smem + sc_addr + sc_off + 32 * r4);
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) pw[u][i] = 0u;
-                return;
+                for (int e = 0; e < 4; ++e) a[4 * r4 + e] = 8 * r4 + e <= rel ? st[4 * r4 + e] * kf[e] : kMasked;
             }
-            float cf[16];
-            if (KV_I8) {
+            float umax = fmaxf(a[0], a[1]);
+#pragma unroll
+            for (int r = 2; r < 16; r += 2) umax = fmaxf(umax, fmaxf(a[r], a[r + 1]));
+            const float m_new = fmaxf(M, half_max(umax));
+            const float alpha = fast_exp2(M - m_new);
+            // (the accumulator is still zero on a wave's first tile, and on the diagonal tile the maximum has
+            // usually been met already: the 16 DT multiplications are skipped when they would change nothing)
+            if (!first && __builtin_amdgcn_ballot_w64(m_new > M) != 0) {
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) o[dt][r] *= alpha;
+            }
+            lsum *= alpha;
+            M = m_new;
+            float ps0 = 0.0f, ps1 = 0.0f;
+#pragma unroll
+            for (int r = 0; r < 16; r += 2) {
+                a[r] = fast_exp2(a[r] - m_new);
+                a[r + 1] = fast_exp2(a[r + 1] - m_new);
+                ps0 += a[r];
+                ps1 += a[r + 1];
+            }
+            if constexpr (KV_I8) {   // the probabilities take their token's v_scale before they are rounded to bf16
 #pragma unroll
                 for (int r4 = 0; r4 < 4; ++r4) {
-                    const f32x4 kf = *reinterpret_cast<const f32x4*>(&scS[sc_slot * (2 * kBC) + 8 * r4 + 4 * hh]);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) cf[4 * r4 + e] = kf[e];
-                }
-            } else {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) cf[r] = c;
-            }
-            // Fast path: exponentials against the running max as it stands; the lane's partial sum doubles
-            // as the overflow check (lazy running max: it only moves when the sum of a lane's 16
-            // probabilities exceeds 2^8, so the accumulator is rescaled a few times per row block).
-            const bool full = t == t_last;   // masked tile: recompute the max exactly
-            float a[16], ps = 0.0f;
-            bool redo = full;
-            if (!full) {
-                float ps0 = 0.0f, ps1 = 0.0f;
-#pragma unroll
-                for (int r = 0; r < 16; r += 2) {
-                    a[r] = fast_exp2(fmaf(st[r], cf[r], -M));
-                    a[r + 1] = fast_exp2(fmaf(st[r + 1], cf[r + 1], -M));
-                    ps0 += a[r];
-                    ps1 += a[r + 1];
-                }
-                ps = ps0 + ps1;
-                redo = __builtin_amdgcn_ballot_w64(ps > 256.0f) != 0;
-            }
-            if (redo) {
-                const int rel = full ? lim - (t * kBC + 4 * hh) : kBC;   // keys of this lane up to offset rel are visible
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const float u = st[r] * cf[r];
-                    a[r] = (8 * (r / 4) + (r % 4) <= rel) ? u : kMasked;
-                }
-                float umax = fmaxf(a[0], a[1]);
-#pragma unroll
-                for (int r = 2; r < 16; r += 2) umax = fmaxf(umax, fmaxf(a[r], a[r + 1]));
-                const float m_new = fmaxf(M, half_max(umax));
-                const float alpha = fast_exp2(M - m_new);
-                // (the accumulator is still zero on a group's first tile, and on the diagonal tile the maximum has
-                // usually been met already: the 16 DT multiplications are skipped when they would change nothing)
-                if (KV_I8 || (t >= (WIDE ? 1 : 2) && __builtin_amdgcn_ballot_w64(m_new > M) != 0)) {   // (INT8: the branch costs registers the kernel does not have)
-#pragma unroll
-                    for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) o[dt][r] *= alpha;
-                }
-                lsum *= alpha;
-                M = m_new;
-                float ps0 = 0.0f, ps1 = 0.0f;
-#pragma unroll
-                for (int r = 0; r < 16; r += 2) {
-                    a[r] = fast_exp2(a[r] - m_new);
-                    a[r + 1] = fast_exp2(a[r + 1] - m_new);
-                    ps0 += a[r];
-                    ps1 += a[r + 1];
-                }
-                ps = ps0 + ps1;
-            }
-            lsum += ps;
-            if (KV_I8) {
-                // the probabilities take their token's v_scale before they are rounded to bf16
-#pragma unroll
-                for (int r4 = 0; r4 < 4; ++r4) {
-                    const f32x4 vf = *reinterpret_cast<const f32x4*>(&scS[sc_slot * (2 * kBC) + kBC + 8 * r4 + 4 * hh]);
+                    const f32x4 vf = *reinterpret_cast<const f32x4*>(smem + sc_addr + sc_off + NG * kBC * 4 + 32 * r4);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) a[4 * r4 + e] *= vf[e];
                 }
@@ -612,206 +497,236 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
 #pragma unroll
             for (int u = 0; u < 2; ++u)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) pw[u][i] = pack_bf16x2(a[8 * u + 2 * i], a[8 * u + 2 * i + 1]);
+                for (int i = 0; i < 4; ++i) pn[u][i] = pack_bf16x2(a[8 * u + 2 * i], a[8 * u + 2 * i + 1]);
+            return ps0 + ps1;
         };
-
-        // MODE 1: the tile's scores only raise the row maximum
-        auto row_max_only = [&](int t, const f32x16& st) {
-            if (t > t_last) return;
-            const int rel = t == t_last ? lim - (t * kBC + 4 * hh) : kBC;   // keys of this lane up to offset rel are visible
+        auto max_only = [&](int rel, const f32x16& st) {   // MODE 1: the tile's scores only raise the row maximum
             float umax = kMasked;
 #pragma unroll
             for (int r = 0; r < 16; ++r) umax = fmaxf(umax, (8 * (r / 4) + (r % 4) <= rel) ? st[r] * c : kMasked);
             M = fmaxf(M, half_max(umax));
         };
-        f32x16 st;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) st[r] = 0.0f;
-        u32x4 pw[2] = {{0u, 0u, 0u, 0u}, {0u, 0u, 0u, 0u}};
 
-        // One phase.  The group whose parity matches the phase does the softmax of tile phi; the other one
-        // does the matrix work of tile phi-1 (P V, and the scores of tile phi+1), reads the operands of its
-        // next matrix phase and moves the ring on.
-        auto phase = [&](auto p4_c, auto grp_c, int phi) {
-            constexpr int P4 = decltype(p4_c)::value, G = decltype(grp_c)::value;
-            if constexpr ((P4 & 1) == G) {
-                if constexpr (MODE == 1) {
-                    row_max_only(phi, st);
-                } else {
-                    // (MODE 2: the running maximum starts at the final one, so the overflow watch never
-                    // fires and the masked tile's rescale is by one)
-                    const int t = WIDE ? (phi - G) >> 1 : phi;
-                    softmax(t & (kRingK - 1), t, st, pw);
-                }
+        // this wave's requests (bf16) of iteration i, and the wait for those of iteration i - 1.  Invariant the wait rests
+        // on: an iteration issues exactly REQ requests a wave, and buffer loads complete in the order they were issued.
+        constexpr int REQ = KV_I8 ? 0 : NLT >= 8 && !stats_only ? 2 * NLD : NLD;
+        static_assert(REQ < 16, "vmcnt is written into the low four bits of the wait's immediate");
+        auto request = [&](int n, int i, int p4) {   // n of REQ
+            if constexpr (NLT >= 8) {
+                if (n < NLD) dma_one(krs_raw, d_koff, n, i + 4, p4 * SLOTK, i + 4 < n_iter);
+                else dma_one(vrs_raw, d_voff, n - NLD, i + 2, K_BYTES + ((p4 + 2) & 3) * SLOTV, i + 2 < n_iter);
             } else {
-                // Matrix phase of tile t = phi - 1: its P V MFMAs and the score MFMAs of tile t + 2, always all
-                // sixteen (a skipped tile has P = 0, unused scores are dropped), alternating so that the score
-                // chain never issues two dependent MFMAs back to back.  Every operand fragment is refilled
-                // right after the MFMA that consumed it, with the fragment the next matrix phase of this wave
-                // needs (K tile phi+3, V tile phi+1): the LDS reads, and the ring traffic, are issued in the
-                // shadow of the MFMAs.  (The fences keep the issue order as written.)
-                // WIDE: tile t = (phi - 1) / 2 of group 0, phi / 2 - 1 of group 1; next are K tile t + 2 and V tile t + 1.
-                // INT8: two slots a tensor will do: K tile u is read in phases 2u - 3 and 2u - 2 (by group 0, then 1) and
-                // group 1 stores it in phase 2u - 4, when K tile u - 2 was read for the last time two phases ago; V tile
-                // u is read in phases 2u - 1 and 2u, and group 0 stores it in phase 2u - 3, one after V tile u - 2's last.
-                // bf16: four slots.  Group 1 requests K tile u in phase 2u - 6 and waits for it at the end of phase
-                // 2u - 4 (K tile u - 4 was read last in phase 2u - 10), group 0 V tile u in phase 2u - 5, waiting at the
-                // end of 2u - 3 (V tile u - 4: phase 2u - 8).
-                constexpr int T2 = G == 0 ? (P4 >> 1) & 1 : ((P4 >> 1) + 1) & 1;   // WIDE: t's parity
-                const int t_w = ((phi + G) >> 1) - G;   // WIDE: t
-                const int k_rd = !WIDE ? ((phi + 3) & (kRingK - 1)) * TILEBK : KV_I8 ? T2 * TILEBK : ((t_w + 2) & 3) * TILEBK;
-                const int v_rd = !WIDE ? ((P4 + 1) & 3) * TILEBV : KV_I8 ? (1 - T2) * TILEBV : ((t_w + 1) & 3) * TILEBV;
-                // the wave that feeds the matrix pipe goes first: without this the older wave of the SIMD wins
-                // the issue port whatever it is doing, and the matrix phases of group 1 run 30 % longer
-                __builtin_amdgcn_s_setprio(3);
-                f32x16 acc;
+                const bool ks = w8 < 4;
+                const int T = ks ? i + 4 : i + 2;
+                u32x4 rs;
 #pragma unroll
-                for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
-                __builtin_amdgcn_sched_barrier(0);
-                // bf16: K tile phi+6 and V tile phi+4 go straight into their ring slots, one load per step of
-                // this loop (DT = 2 NLD steps: first the K tile's loads, then the V tile's), the address work
-                // behind the score MFMA and the request behind the P V MFMA.  Always the same number of
-                // requests, so that the wait at the end of the phase is the same instruction every time: past
-                // the last tile this row block needs, zeros are requested from beyond the slab.
-                // Invariant the hand-written wait below rests on: a matrix phase issues exactly REQ ring requests
-                // (steps i < NLD of the loop: the K tile's, the remaining DT - NLD steps: the V tile's, none of
-                // those in the maxima-only sweep), buffer loads complete in the order they were issued, and the
-                // requests of the wave's PREVIOUS matrix phase are the ones that must have landed (WIDE: a phase has one
-                // tensor's, every other step).  So the wait
-                // at the end of the phase is vmcnt(REQ): everything but this phase's own requests.
-                constexpr int REQ = KV_I8 ? 0 : WIDE ? NLD : NLD + (stats_only ? 0 : DT - NLD);
-                static_assert(KV_I8 || DT == 2 * NLD, "one ring load per step of the first MFMA loop");
-                static_assert(KV_I8 || REQ == (stats_only || WIDE ? NLD : 2 * NLD), "requests per matrix phase");
-                static_assert(REQ < 16, "vmcnt is written into the low four bits of the wait's immediate");
-#pragma unroll
-                for (int i = 0; i < DT; ++i) {
-                    unsigned dma_dst = 0, dma_voff = 0;
-                    score_mfma(i, acc);
-                    __builtin_amdgcn_sched_barrier(0);
-                    fetch_k1(i, k_rd);
-                    if constexpr (!KV_I8 && WIDE) {
-                        const int u = G == 1 ? (phi >> 1) + 3 : (phi + 5) >> 1;
-                        if (i % 2 == 0) dma_prep(G == 1 ? d_koff : d_voff, i / 2, u, (G == 1 ? 0 : K_BYTES) + (u & 3) * TILEB, u < n_tiles, dma_dst, dma_voff);
-                    } else if constexpr (!KV_I8) {
-                        if (i < NLD) dma_prep(d_koff, i, phi + 6, ((phi + 6) & (kRingK - 1)) * TILEB, phi + 6 < n_tiles, dma_dst, dma_voff);
-                        else if (!stats_only) dma_prep(d_voff, i - NLD, phi + 4, K_BYTES + P4 * TILEB, phi + 4 < n_tiles, dma_dst, dma_voff);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                    if (!stats_only) {
-                        pv_mfma(0, i, pw);
-                        __builtin_amdgcn_sched_barrier(0);
-                        fetch_v1(0, i, v_rd);
-                    }
-                    if constexpr (!KV_I8 && WIDE) {
-                        if (i % 2 == 0) dma_fire(G == 1 ? krs_raw : vrs_raw, dma_dst, dma_voff);
-                    } else if constexpr (!KV_I8) {
-                        if (i < NLD) dma_fire(krs_raw, dma_dst, dma_voff);
-                        else if (!stats_only) dma_fire(vrs_raw, dma_dst, dma_voff);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
+                for (int e = 0; e < 4; ++e) rs[e] = ks ? krs_raw[e] : vrs_raw[e];
+                dma_one(rs, ks ? d_koff : d_voff, 0, T, ks ? p4 * SLOTK : K_BYTES + ((p4 + 2) & 3) * SLOTV, T < n_iter);
+            }
+        };
+        // INT8: the registers' pieces go to K tile i+4 and V tile i+2, their scales to tile i+3; then the next ones are loaded
+        auto stage_dst = [&](int piece, int p4) {
+            return piece == 1 ? p_vdst + ((p4 + 2) & 3) * SLOTV : p_dst + (st_k ? p4 * SLOTK : ((p4 + 2) & 3) * SLOTV);
+        };
+        auto load_piece0 = [&](int i) {
+            constexpr unsigned TB = NG * kBC * ROWB;
+            sg0 = __builtin_amdgcn_raw_buffer_load_b128(krs, (int)((unsigned)(i + (st_k ? 5 : 3)) * TB + p_off), 0, 0);
+        };
+        auto load_piece1 = [&](int i) {
+            constexpr unsigned TB = NG * kBC * ROWB;
+            sg1 = __builtin_amdgcn_raw_buffer_load_b128(vrs, (int)((unsigned)(i + 3) * TB + p_off), 0, 0);
+        };
+        auto end_iteration = [&]() {
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (!KV_I8) __builtin_amdgcn_s_waitcnt(0x0f70 | REQ);   // vmcnt(REQ), see the invariant above
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+        };
+
+        f32x4 kfs = {c, c, c, c}, vfs, kfs_next, vfs_next;   // INT8: scales of the four keys at work, and of the next four
+        // Iteration i of a wave that has a tile after this one: the scores of tile i+1 into sn, the probabilities of tile i
+        // (scores in st) into pn, P V of tile i-1 (probabilities in pv).  An MFMA, then a share of the vector work,
+        // the refill of the operand the MFMA consumed and of the ring: the fences keep the order as written.
+        auto full = [&](auto p4_c, int i, const f32x16& st, f32x16& sn, const u32x4 (&pv)[2], u32x4 (&pn)[2]) {
+            constexpr int P4 = decltype(p4_c)::value;
+            constexpr int K1 = ((P4 + 1) & 3) * SLOTK, K2 = ((P4 + 2) & 3) * SLOTK;
+            constexpr int VM = ((P4 + 3) & 3) * SLOTV, V0 = P4 * SLOTV;
+            constexpr int SC = P4 * NG * 2 * kBC * 4, SCN = ((P4 + 1) & 3) * NG * 2 * kBC * 4;
+            float a[16], ps0 = 0.0f, ps1 = 0.0f;
+            u32x4 wide;
+            auto finish_p = [&](int r) {
+                if (r & 1) ps1 += a[r];
+                else ps0 += a[r];
+                if constexpr (KV_I8) {
+                    if (r % 4 == 0) vfs = vfs_next;
+                    a[r] *= vfs[r % 4];
+                    if (r % 4 == 1) vfs_next = *reinterpret_cast<const f32x4*>(smem + sc_addr + NG * kBC * 4 + (r < 12 ? SC + 32 * (r / 4 + 1) : SCN));
                 }
-                if constexpr (WIDE && KV_I8) {
-                    if constexpr (G == 1) {   // the pieces loaded two phases ago go to K tile phi / 2 + 2
-                        store_tile(((P4 >> 1) & 1) * TILEBK, p_kdst, sg.k);
-                        store_s(((phi >> 1) + 2) & (kRingK - 1), sg.s, w == 3);
-                    } else {                  // or to V tile (phi + 3) / 2
-                        store_tile((((P4 + 3) >> 1) & 1) * TILEBV, p_vdst, sg.k);
-                        store_s(((phi + 3) >> 1) & (kRingK - 1), sg.s, w == 2);
-                    }
-                } else if constexpr (KV_I8) {
-                    // the pieces loaded two phases ago go to K tile phi+5 and V tile phi+3
-                    store_tile(((phi + 5) & (kRingK - 1)) * TILEBK, p_kdst, sg.k);
-                    store_tile(((P4 + 3) & 3) * TILEBV, p_vdst, sg.v);
-                    store_s((phi + 5) & (kRingK - 1), sg.s, has_s);
+                if (r & 1) {
+                    pn[r / 8][(r % 8) / 2] = pack_bf16x2(a[r - 1], a[r]);
+                    asm volatile("" : "+v"(pn[r / 8][(r % 8) / 2]));   // (packed here and now: else the compiler keeps all sixteen past the overflow check)
+                }
+            };
+#pragma unroll
+            for (int j = 0; j < NS; ++j) {
+                const int x = j / 2;
+                if (j % 2 == 0) {
+                    f32x16 z;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) z[r] = 0.0f;
+                    sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfr[x % KP], qreg[x], x == 0 ? z : sn, 0, 0, 0);
+                } else if (!stats_only) {
+                    pv_mfma(x, pv);
                 }
                 __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int i = 0; i < DT; ++i) {
-                    score_mfma(DT + i, acc);
-                    __builtin_amdgcn_sched_barrier(0);
-                    fetch_k1(DT + i, k_rd);
-                    __builtin_amdgcn_sched_barrier(0);
-                    if (!stats_only) {
-                        pv_mfma(1, i, pw);
-                        __builtin_amdgcn_sched_barrier(0);
-                        fetch_v1(1, i, v_rd);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
+                if (j % 2 == 0) {
+                    if (x < KP) fetch_k(x + KP, K1);
+                    else fetch_k(x - KP, K2);
+                } else if (!stats_only) {
+                    if (x < VP) fetch_v(x + VP, VM);
+                    else fetch_v(x - VP, V0);
                 }
-                st = acc;
-                __builtin_amdgcn_s_setprio(0);
+                if constexpr (!stats_only) {
+#pragma unroll
+                    for (int e = 0; e < EPS; ++e) {
+                        const int r = EPS * j + e;
+                        if constexpr (KV_I8)
+                            if (r % 4 == 0) kfs = kfs_next;
+                        const float u = fmaf(st[r], kfs[r % 4], -M);
+                        if constexpr (KV_I8)
+                            if (r % 4 == 1) kfs_next = *reinterpret_cast<const f32x4*>(smem + sc_addr + (r < 12 ? SC + 32 * (r / 4 + 1) : SCN));
+                        if (r > 0) finish_p(r - 1);
+                        a[r] = fast_exp2(u);
+                    }
+                }
                 if constexpr (!KV_I8) {
-                    // what this wave requested in its previous matrix phase is read from the next phase on
-                    __builtin_amdgcn_s_waitcnt(0x0f70 | REQ);   // vmcnt(REQ), see the invariant above
-                } else if constexpr (WIDE) {
-                    const int u = G == 1 ? (phi >> 1) + 3 : (phi + 5) >> 1;
-                    load_tile(G == 1 ? krs : vrs, u, sg.k);
-                    load_s_at(u, sg.s, l32, w == 2 + G);
+                    if (j % 2 == 1 && j / 2 < REQ) request(j / 2, i, P4);
                 } else {
-                    load_tile(krs, phi + 7, sg.k);
-                    load_tile(vrs, phi + 5, sg.v);
-                    load_s(phi + 7, sg.s);
-                }
-            }
-            // End of phase: this wave's LDS reads and writes are done, then the workgroup barrier.  (Not
-            // __syncthreads(): its fence would also wait for the buffer loads just sent towards LDS.  The
-            // empty statements keep the compiler from moving memory accesses across.)
-            __builtin_amdgcn_sched_barrier(0);
-            asm volatile("" ::: "memory");
-            __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
-            __builtin_amdgcn_sched_barrier(0);
-        };
-        auto run = [&](auto grp_c) {
-            constexpr int G = decltype(grp_c)::value;
-            // Group 0 starts with the scores of tile 0 and then reads the operands of its matrix phase 1 (K
-            // tile 2, V tile 0); group 1 reads those of its matrix phase 0 (K tile 1; there is no tile -1,
-            // and nothing but zeros may meet its zero probabilities).  (WIDE: K tile 1 and K tile 0.)
-            if (G == 0) {
-#pragma unroll
-                for (int s = 0; s < KS; ++s) fetch_k1(s, 0);
-#pragma unroll
-                for (int r = 0; r < 16; ++r) st[r] = 0.0f;
-#pragma unroll
-                for (int s = 0; s < KS; ++s) score_mfma(s, st);
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int s = 0; s < KS; ++s) fetch_k1(s, (WIDE ? 1 : 2) * TILEBK);
-                if (!stats_only) {
-#pragma unroll
-                    for (int dt = 0; dt < DT; ++dt) {
-                        fetch_v1(0, dt, 0);
-                        fetch_v1(1, dt, 0);
+                    // (a dword of a piece per step, and what a thread stores next is asked for right after; which steps, and
+                    // whether the loads come here or at the iteration's end, made no difference)
+                    const int e = j - (NS == 16 ? 4 : 0), piece = e / 4;
+                    if (e >= 0 && e < (TWO ? 8 : 4) && has_p) {
+                        unsigned lo, hi;
+                        widen_dword(piece == 0 ? sg0[e % 4] : sg1[e % 4], lo, hi);
+                        wide[2 * (e % 2)] = lo;
+                        wide[2 * (e % 2) + 1] = hi;
+                        if (e % 2 == 1) *reinterpret_cast<u32x4*>(smem + stage_dst(piece, P4) + 16 * ((e % 4) / 2)) = wide;
+                    }
+                    if (e == 3) load_piece0(i);
+                    if (TWO && e == 7) load_piece1(i);
+                    if (j == NS - 2) {
+                        store_s((P4 + 3) & 3, sgs);
+                        sgs = load_s(i + 4);
                     }
                 }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if constexpr (stats_only) {
+                max_only(kBC, st);
             } else {
-#pragma unroll
-                for (int s = 0; s < KS; ++s) fetch_k1(s, WIDE ? 0 : TILEBK);
-#pragma unroll
-                for (int u = 0; u < 2; ++u)
-#pragma unroll
-                    for (int i = 0; i < 2 * DT; ++i) vfr[u][i] = s16x4{0, 0, 0, 0};
+                finish_p(15);
+                float ps = ps0 + ps1;
+                // Lazy running max: the exponentials were taken against the max as it stands, and it moves only when the sum of
+                // a lane's 16 probabilities exceeds 2^8, so the accumulator is rescaled a few times per row block.
+                if (__builtin_amdgcn_ballot_w64(ps > 256.0f) != 0) ps = exact_softmax(SC, kBC, i == 0, st, pn);
+                lsum += ps;
             }
-            // these reads are done before phase 0 begins: its matrix phase already sends V tile 4 to the slot
-            // of V tile 0
-            asm volatile("" ::: "memory");
-            __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
-            for (int phi = 0; phi <= last_phase; phi += 4) {
-                phase(int_c<0>{}, grp_c, phi);
-                if (phi + 1 > last_phase) break;
-                phase(int_c<1>{}, grp_c, phi + 1);
-                phase(int_c<2>{}, grp_c, phi + 2);   // last_phase is even: phases come in pairs after the first
-                if (phi + 3 > last_phase) break;
-                phase(int_c<3>{}, grp_c, phi + 3);
-            }
+            end_iteration();
         };
-        if (grp == 0) run(int_c<0>{});
-        else run(int_c<1>{});
+
+        f32x16 st_a, st_b;
+        u32x4 p_a[2] = {{0u, 0u, 0u, 0u}, {0u, 0u, 0u, 0u}}, p_b[2] = {{0u, 0u, 0u, 0u}, {0u, 0u, 0u, 0u}};
+        int i = 0;
+        if (last >= 0) {
+            // the scores of tile 0; then the first operands of iteration 0 (there is no tile -1: zeros)
+#pragma unroll
+            for (int s = 0; s < KP; ++s) fetch_k(s, 0);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) st_a[r] = 0.0f;
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                st_a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfr[s % KP], qreg[s], st_a, 0, 0, 0);
+                if (s < KP) fetch_k(s + KP, 0);
+                else fetch_k(s - KP, SLOTK);
+            }
+#pragma unroll
+            for (int x = 0; x < VP; ++x) vfr[x][0] = vfr[x][1] = s16x4{0, 0, 0, 0};
+            if constexpr (KV_I8) {
+                kfs_next = *reinterpret_cast<const f32x4*>(smem + sc_addr);
+                vfs_next = *reinterpret_cast<const f32x4*>(smem + sc_addr + NG * kBC * 4);
+            }
+        }
+        // (K tile 0 has been read: iteration 0 sends K tile 4 to its slot)
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        if (last >= 0) {
+            for (;;) {
+                if (i >= last) break;
+                full(int_c<0>{}, i, st_a, st_b, p_a, p_b);
+                if (++i >= last) {
+                    st_a = st_b;
+                    p_a[0] = p_b[0];
+                    p_a[1] = p_b[1];
+                    break;
+                }
+                full(int_c<1>{}, i, st_b, st_a, p_b, p_a);
+                if (++i >= last) break;
+                full(int_c<2>{}, i, st_a, st_b, p_a, p_b);
+                if (++i >= last) {
+                    st_a = st_b;
+                    p_a[0] = p_b[0];
+                    p_a[1] = p_b[1];
+                    break;
+                }
+                full(int_c<3>{}, i, st_b, st_a, p_b, p_a);
+                ++i;
+            }
+        }
+        // the rest of the row block's iterations: this wave's last tile in the first of them, then only its share of the ring
+        for (; i < n_iter; ++i) {
+            const int p4 = i & 3;
+            if constexpr (!KV_I8) {
+#pragma unroll
+                for (int n = 0; n < REQ; ++n) request(n, i, p4);
+            } else {
+                if (has_p) store_piece(stage_dst(0, p4), sg0);
+                if constexpr (TWO) store_piece(stage_dst(1, p4), sg1);
+                store_s((p4 + 3) & 3, sgs);
+                load_piece0(i);
+                if constexpr (TWO) load_piece1(i);
+                sgs = load_s(i + 4);
+            }
+            if (i == last) {
+                const int rel = lim - ((NG * i + my_tile) * kBC + 4 * hh);
+                if constexpr (stats_only) {
+                    max_only(rel, st_a);
+                } else {
+                    const int vm = ((p4 + 3) & 3) * SLOTV, v0 = p4 * SLOTV;
+#pragma unroll
+                    for (int x = 0; x < 2 * DT; ++x) {
+                        pv_mfma(x, p_a);
+                        if (x < VP) fetch_v(x + VP, vm);
+                        else fetch_v(x - VP, v0);
+                    }
+                    lsum += exact_softmax(p4 * NG * 2 * kBC * 4, rel, i == 0, st_a, p_a);
+#pragma unroll
+                    for (int x = 0; x < 2 * DT; ++x) {
+                        pv_mfma(x, p_a);
+                        if (x < VP) fetch_v(x + VP, v0);
+                    }
+                }
+            }
+            if constexpr (KV_I8) __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): what this wave stored is in LDS
+            end_iteration();
+        }
         if constexpr (!KV_I8) {
-            // the last phases' requests (zeros) have landed before the ring is used for anything else
+            // the last iterations' requests (zeros) have landed before the ring is used for anything else
             __builtin_amdgcn_s_waitcnt(0x0f70);
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
