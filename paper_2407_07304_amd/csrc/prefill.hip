@@ -38,6 +38,9 @@
 //     XOR-swizzled by the row, so both the 128-bit K row reads and the V transpose reads are
 //     free of bank conflicts; INT8 tiles pass through registers, where they are widened, into
 //     padded rows.
+//     The k_scales of a tile come from LDS as vectors of four; its v_scales are one register, from which each probability's
+//     multiplication takes its own by a DPP broadcast (four 128-bit reads a wave and tile less: B=1, 32 heads, S=8192 566 ->
+//     551 us, 64 on 8 heads, S=32768 17.26 -> 16.71 ms).
 //   - A wave reads its MFMA operands from LDS half a tile ahead, each fragment right after the MFMA that consumed the
 //     register it refills.
 //   - A workgroup works off a list of (row block, head) items, one after the other; the lists are
@@ -45,6 +48,7 @@
 //     of row blocks and heads (pairs of a short and a long block, as before, left up to half of the
 //     last round empty: B=1, 32 heads, S=3000 took 96 us and takes 83).  Short blocks go first: the
 //     key tiles they read are still in the L2 when a longer one starts over at tile 0.
+
 #include <type_traits>
 
 #include "slim_common.h"
@@ -94,6 +98,19 @@ __device__ __forceinline__ KernelArgs kernel_args_now() {
     KernelArgs a = (KernelArgs)__builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(a));
     return a;
+}
+
+// lane n of this lane's row of 16, for a constant n: a DPP operand of the instruction that takes it
+__device__ __forceinline__ float row_lane(float v, int n) {
+    const int b = __builtin_bit_cast(int, v);
+    int r = 0;
+    switch (n) {
+#define SLIM_ROW_LANE(N) case N: r = __builtin_amdgcn_update_dpp(0, b, 0x150 + N, 0xf, 0xf, true); break;
+        SLIM_ROW_LANE(0) SLIM_ROW_LANE(1) SLIM_ROW_LANE(2) SLIM_ROW_LANE(3) SLIM_ROW_LANE(4) SLIM_ROW_LANE(5) SLIM_ROW_LANE(6) SLIM_ROW_LANE(7)
+        SLIM_ROW_LANE(8) SLIM_ROW_LANE(9) SLIM_ROW_LANE(10) SLIM_ROW_LANE(11) SLIM_ROW_LANE(12) SLIM_ROW_LANE(13) SLIM_ROW_LANE(14) SLIM_ROW_LANE(15)
+#undef SLIM_ROW_LANE
+    }
+    return __builtin_bit_cast(float, r);
 }
 
 template <int N>
@@ -325,6 +342,7 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
             v_addr[dt] = K_BYTES + my_tile * TILEBV + rv * ROWLV + (((4 * dt + 2 * ((l >> 4) & 1) + ((l & 3) >> 1)) ^ swz_v(rv)) * 16) + 8 * (l & 1);
     }
     const int sc_addr = RING_BYTES + (my_tile * kBC + 4 * hh) * 4;   // this lane's k_scales: + 32 bytes per 8 keys
+    const int scv_addr = sc_addr + (NG * kBC + 8 * ((l & 15) >> 2) + (l & 3)) * 4;
 
     for (;;) {   // the workgroup's items
         const int kvh = (int)div_magic((unsigned)bh, p.group, p.group_magic);   // (batch, KV head): heads per batch are a multiple of the group
@@ -545,7 +563,8 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
             __builtin_amdgcn_sched_barrier(0);
         };
 
-        f32x4 kfs = {c, c, c, c}, vfs, kfs_next, vfs_next;   // INT8: scales of the four keys at work, and of the next four
+        f32x4 kfs = {c, c, c, c}, kfs_next;   // INT8: k_scales of the four keys at work, and of the next four
+        float vfs = 0.0f;                     // INT8: the tile's v_scales, lane n of each 16 the one of this lane's register n
         // Iteration i of a wave that has a tile after this one: the scores of tile i+1 into sn, the probabilities of tile i
         // (scores in st) into pn, P V of tile i-1 (probabilities in pv).  An MFMA, then a share of the vector work,
         // the refill of the operand the MFMA consumed and of the ring: the fences keep the order as written.
@@ -559,11 +578,7 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
             auto finish_p = [&](int r) {
                 if (r & 1) ps1 += a[r];
                 else ps0 += a[r];
-                if constexpr (KV_I8) {
-                    if (r % 4 == 0) vfs = vfs_next;
-                    a[r] *= vfs[r % 4];
-                    if (r % 4 == 1) vfs_next = *reinterpret_cast<const f32x4*>(smem + sc_addr + NG * kBC * 4 + (r < 12 ? SC + 32 * (r / 4 + 1) : SCN));
-                }
+                if constexpr (KV_I8) a[r] *= row_lane(vfs, r);
                 if (r & 1) {
                     pn[r / 8][(r % 8) / 2] = pack_bf16x2(a[r - 1], a[r]);
                     asm volatile("" : "+v"(pn[r / 8][(r % 8) / 2]));   // (packed here and now: else the compiler keeps all sixteen past the overflow check)
@@ -627,6 +642,7 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
                 max_only(kBC, st);
             } else {
                 finish_p(15);
+                if constexpr (KV_I8) vfs = *reinterpret_cast<const float*>(smem + scv_addr + SCN);
                 float ps = ps0 + ps1;
                 // Lazy running max: the exponentials were taken against the max as it stands, and it moves only when the sum of
                 // a lane's 16 probabilities exceeds 2^8, so the accumulator is rescaled a few times per row block.
@@ -655,7 +671,7 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
             for (int x = 0; x < VP; ++x) vfr[x][0] = vfr[x][1] = s16x4{0, 0, 0, 0};
             if constexpr (KV_I8) {
                 kfs_next = *reinterpret_cast<const f32x4*>(smem + sc_addr);
-                vfs_next = *reinterpret_cast<const f32x4*>(smem + sc_addr + NG * kBC * 4);
+                vfs = *reinterpret_cast<const float*>(smem + scv_addr);
             }
         }
         // (K tile 0 has been read: iteration 0 sends K tile 4 to its slot)
