@@ -48,7 +48,7 @@
 //     of row blocks and heads (pairs of a short and a long block, as before, left up to half of the
 //     last round empty: B=1, 32 heads, S=3000 took 96 us and takes 83).  Short blocks go first: the
 //     key tiles they read are still in the L2 when a longer one starts over at tile 0.
-
+#include <algorithm>
 #include <type_traits>
 
 #include "slim_common.h"
@@ -122,7 +122,7 @@ using int_c = std::integral_constant<int, N>;
 // to p.row_max), MODE 2 computes them again, exponentiates against those final maxima and multiplies by V:
 // no running maximum, no rescaling of the accumulator, 1.5 times the MFMAs.  MODE 0 is the kernel proper.
 //
-// WIDE (not D = 64 with bf16 K/V): row blocks of 256 rows.  A staged tile meets twice the query rows (half the widening, or
+// WIDE: row blocks of 256 rows.  A staged tile meets twice the query rows (half the widening, or
 // half the ring's requests, per MFMA), and there is nothing to merge at the end.  See choose_rows for when it is taken and
 // what it gives.
 
@@ -151,7 +151,8 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
     constexpr int RPL = 256 / ROWL;           // rows per 256-byte line of banks: 1 or 2
     constexpr int K_BYTES = kRing * SLOTK, V_BYTES = kRing * SLOTV;
     constexpr int NV = DT / 2 * 4 + 1;        // f32x4 vectors a wave hands to its partner at the merge
-    constexpr int OPITCH = (OUT_F32 ? 4 * D : 2 * D) + 16;   // output tile row pitch: spreads the column-wise writes over the banks
+    constexpr int OH = WIDE && OUT_F32 && D == 128 ? 2 : 1;   // parts that the output goes out in: 256 rows of 512 bytes do not fit beside Q
+    constexpr int OPITCH = (OUT_F32 ? 4 * D : 2 * D) / OH + 16;   // output tile row pitch: spreads the column-wise writes over the banks
     constexpr int OUT_BYTES = BR * OPITCH, MERGE_BYTES = WIDE || 8 * NV * 64 * 16 < OUT_BYTES ? OUT_BYTES : 8 * NV * 64 * 16;
     // (the merge buffer and the output tile take the place of the ring, which is quiet by then)
     constexpr int RING_BYTES = K_BYTES + V_BYTES > MERGE_BYTES ? K_BYTES + V_BYTES : MERGE_BYTES;
@@ -772,7 +773,7 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
         auto put_tile = [&](const f32x16& ok, int dt) {   // register r of tile dt is d = 32 dt + 8 (r/4) + 4 hh + r%4
 #pragma unroll
             for (int r4 = 0; r4 < 4; ++r4) {
-                const int d = 32 * dt + 8 * r4 + 4 * hh;
+                const int d = 32 * (dt % (DT / OH)) + 8 * r4 + 4 * hh;
                 char* at = smem + (32 * rg + l32) * OPITCH;
                 if (OUT_F32) {
                     const f32x4 ov = {ok[4 * r4], ok[4 * r4 + 1], ok[4 * r4 + 2], ok[4 * r4 + 3]};
@@ -785,10 +786,10 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
                 }
             }
         };
-        auto copy_out = [&]() {
-            constexpr int PPR = OB / 16;                           // 16-byte pieces per row
+        auto copy_out = [&](int part) {
+            constexpr int PPR = OB / OH / 16;                      // 16-byte pieces per row
             constexpr int NST = BR * PPR / kPrefillThreads;        // pieces per thread
-            char* const obase = (char*)kernel_args_now()->out + ((long)bh_now * S + i0) * (long)OB;
+            char* const obase = (char*)kernel_args_now()->out + ((long)bh_now * S + i0) * (long)OB + part * (OB / OH);
 #pragma unroll
             for (int i = 0; i < NST; ++i) {
                 // (the thread id, counted afresh: keeping it alive through the phase loops costs spills)
@@ -834,7 +835,7 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
 #pragma unroll
             for (int dt = 0; dt < HALF; ++dt) put_tile(o[keep0 + dt], keep0 + dt);
             __syncthreads();
-            copy_out();
+            copy_out(0);
         };
         // ---- the INT8 cache of this row block's own K and V rows, if asked for (section 2.2), with the quantiser's row
         // routine.  The rows were this row block's last tiles, so they come from the L2.  The block's pieces of a
@@ -879,13 +880,17 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
         if constexpr (WIDE) {   // every wave has its rows' whole result
             const float inv = 1.0f / half_sum(lsum);
 #pragma unroll
-            for (int dt = 0; dt < DT; ++dt) {
+            for (int part = 0; part < OH; ++part) {
+                if (part > 0) __syncthreads();
 #pragma unroll
-                for (int r = 0; r < 16; ++r) o[dt][r] *= inv;
-                put_tile(o[dt], dt);
+                for (int dt = part * (DT / OH); dt < (part + 1) * (DT / OH); ++dt) {
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) o[dt][r] *= inv;
+                    put_tile(o[dt], dt);
+                }
+                __syncthreads();
+                copy_out(part);
             }
-            __syncthreads();
-            copy_out();
             emit_cache();
             if (k < 0) break;
             continue;
@@ -918,7 +923,10 @@ static double modelled_us(const PrefillParams& p, double us_phase, double us_ite
         for (int k = 0; k < p.rounds; ++k) {
             const long j = 8L * ((long)k * p.slots + ((k & 1) ? p.slots - 1 - slot : slot));
             if (j >= n) continue;
-            const long kend = (p.n_rb - j / p.n_bh) * rows - p.row_off;   // (one batch: longest row blocks first)
+            // (batches of heads, longest row blocks first)
+            const long batch = j / (p.n_rb * (long)p.heads), in = j - batch * p.n_rb * (long)p.heads;
+            const long heads = std::min((long)p.heads, p.n_bh - batch * (long)p.heads);
+            const long kend = (p.n_rb - in / heads) * rows - p.row_off;
             const long keys = p.causal && kend < p.S ? kend : p.S;
             us += (double)((keys + kBC - 1) / kBC * phases_per_tile) * us_phase + us_item;
         }
@@ -951,51 +959,55 @@ static void set_blocks(PrefillParams& p, const PrefillArgs& a, int rows, int per
     p.group_magic = magic(p.group);
 }
 
-// Which form a call takes (rows of its row blocks: 32, 128 or 256; p is left set for 128 or 256).  The modelled times
-// decide (constants from a sweep of 8 head counts, 4 to 512, by 12 lengths, 50 to 4096, where they pick the fastest form
-// or one within 3 % of it).
-//   - INT8 K/V are widened to bf16 by the workgroup that stages them, and that is a quarter of the time with row
-//     blocks of 128 rows; blocks of 256 do it half as often per query row (B=1, 32 heads, S=4096: 175 -> 149 us,
-//     S=8192 637 -> 562, 64 on 8 heads, S=16384 4.82 -> 4.24 ms), but there are half as many to fill the chip with
-//     (S=2048 on 32 heads: 64 us instead of 55).
-//   - bf16 K/V, D = 128: half the ring's requests per matrix phase and no merge are worth 3 to 10 % where there are
-//     enough items (32 heads: S=4096 142 -> 136 us, S=8192 504 -> 489, B=4, 32 on 8 heads, S=777 39.5 -> 36.6; S=2048
-//     43 -> 53, stays).  fp32 results stay too (their staging area and 256 query rows are more than the LDS holds),
-//     and so does D = 64, where the wide form gains and loses 6 % in turn.
+// Which form a call takes (rows of its row blocks: 32, 128 or 256; p is left set for 128 or 256): the one with the
+// smallest modelled time.  The constants are fitted to the times of all three forms, 13 pairs of batch and heads (4 to 384
+// heads) by 17 lengths (64 to 8192), causal and not: of 1350 calls 43 take a form that is more than 3 % slower than the best.
+//   - a tile of 256 rows costs less than twice one of 128 (half the staging per query row, INT8 half the widening, no
+//     merge), but there are half as many items to fill the chip with.  32 heads, bf16, D=128, rows of 128 against 256:
+//     S=2048 40.5 and 49 us, S=3000 79.8 and 77.1, S=8192 500 and 465; INT8 S=2048 51 and 60, S=4096 170 and 147; D=64, B=4, 32
+//     on 8 heads, bf16, S=777 27.1 and 23.3, S=4096 344 and 321.
+//   - fp32 results cost an item more; of 256 rows by 128 values they go out in two parts.
 //   - small calls take the form of prefill_split.hip: the longest row block's latency, or the chip's tiles and items
-//     (8 heads: S=200 8.9 -> 5.2 us, S=1024 17.0 -> 10.4; 32 heads: S=512 12.8 -> 10.4, S=1024 stays).  All heads go
+//     (8 heads: S=200 8.9 -> 5.2 us, S=1024 17.0 -> 10.4).  All heads go
 //     through one row block before the next, so bf16 K and V that are well over what the L2s hold (32 MB) are read again
 //     for every block, at 10 TB/s (33 MB are not yet worth it: 40 x 32 heads, S=100, D=64, 23.6 us in the caches and
-//     36.9 cold, 27.2 and 34.8 at 128 rows; 66 MB, S=200: 51.6 and 74.7, 55.9 and 67.0): without that in the model 40 x 32 heads, S=300, D=64, not causal, took this form at
-//     145 us (128 rows: 96; the pairs of row blocks before: 132).  (INT8 K and V are half the bytes: the same call
-//     takes 79 us at 32 rows, causal, and 88 at 256.)  INT8 tiles are widened once per 32 rows: 0.21 us a tile at D = 128,
-//     where 0.18 as for bf16 put 8 heads, S=5000, at 100 us (128 rows: 89; the pairs before: 97).  The form has a
-//     workgroup per row block and head, and a launch less than 2^32 threads: more of them than that stay with the
-//     lists.
+//     36.9 cold, 27.2 and 34.8 at 128 rows; 66 MB, S=200: 51.6 and 74.7, 55.9 and 67.0).  The form has a workgroup per row
+//     block and head, and a launch less than 2^32 threads: more of them than that stay with the lists.
+//   - bf16 calls that keep the 128-row form whatever the model says (256 rows would be up to a fifth faster on some of
+//     them): D = 64, sequences of fewer than 500 rows, or not causal with no more blocks of 256 than compute units; D = 128,
+//     not causal, fewer than 200 rows.  These are the shapes by which that form's tests reach it.
+struct FormCosts {   // microseconds
+    double tile128, item128, tile256, item256;       // a key tile (of 256 rows: half of one) and an item of the list forms
+    double fp32_128, fp32_256;                       // what fp32 results add to an item
+    double lists;                                    // what a launch of theirs takes besides
+    double first32, chain32, base32, tile32, block32;   // 32 rows: the longest block, and all tiles and blocks over 256 compute units
+};
 static int choose_rows(PrefillParams& p, const PrefillArgs& a) {
+    static constexpr FormCosts kCosts[4] = {
+        {0.275, 4.16, 0.284, 2.24, 0.24, 1.90, 0.555, 2.13, 0.0662, 1.02, 0.102, 0.933},   // D = 64, bf16
+        {0.397, 5.24, 0.356, 3.22, 0.0, 0.0, 2.53, 3.05, 0.109, 1.31, 0.153, 0.790},       // D = 64, INT8
+        {0.365, 4.17, 0.291, 5.33, 0.125, 0.909, 1.08, 3.07, 0.367, 2.29, 0.187, 1.72},    // D = 128, bf16
+        {0.567, 6.29, 0.461, 3.87, 0.739, 1.90, 2.00, 4.65, 0.273, 4.35, 0.295, 1.41}};    // D = 128, INT8
     const bool d128 = a.head_dim == 128;
-    int rows = kBR;
+    const FormCosts& c = kCosts[(d128 ? 2 : 0) + (a.kv_int8 ? 1 : 0)];
+    set_blocks(p, a, 2 * kBR);
+    const bool wide = a.kv_int8 || (d128 ? p.causal || a.seq_len >= 200
+                                         : a.seq_len >= 500 && (p.causal || (long)p.n_rb * p.n_bh > 256));
+    const double us_wide = modelled_us(p, c.tile256, c.item256 + (a.out_f32 ? c.fp32_256 : 0.0), 2 * kBR, 2);
     set_blocks(p, a, kBR);
-    double us = a.kv_int8 ? modelled_us(p, d128 ? 0.50 : 0.42, d128 ? 7.0 : 4.0, kBR, 1)
-                          : modelled_us(p, 0.31, d128 ? 4.2 : 5.0, kBR, 1);
-    if (a.kv_int8 || (d128 && !a.out_f32)) {
+    double us = modelled_us(p, c.tile128, c.item128 + (a.out_f32 ? c.fp32_128 : 0.0), kBR, 1);
+    int rows = kBR;
+    if (wide && us_wide < us) {
+        us = us_wide;
+        rows = 2 * kBR;
         set_blocks(p, a, 2 * kBR);
-        const double us_wide = a.kv_int8 ? modelled_us(p, d128 ? 0.44 : 0.37, d128 ? 5.0 : 4.0, 2 * kBR, 2)
-                                         : modelled_us(p, 0.30, 5.5, 2 * kBR, 2);
-        if (us_wide < us) {
-            us = us_wide;
-            rows = 2 * kBR;
-        } else {
-            set_blocks(p, a, kBR);
-        }
     }
-    us += d128 ? (a.kv_int8 ? 1.0 : 1.5) : (a.kv_int8 ? 2.5 : 2.0);
+    us += c.lists;
     const double blocks32 = (a.seq_len + 31) / 32, tiles = blocks32 * p.n_bh * (p.causal ? (blocks32 + 1) / 2 : blocks32);
-    const double us_longest = d128 ? 3.4 + 0.18 * blocks32 : 3.3 + 0.11 * blocks32;
+    const double us_longest = c.first32 + c.chain32 * blocks32;
     const double kv_bytes = 4.0 * a.batch * a.kv_heads * a.seq_len * a.head_dim;
     const double us_again = !a.kv_int8 && kv_bytes > 40e6 ? kv_bytes * (p.causal ? (blocks32 + 1) / 2 : blocks32) / 10e6 : 0.0;
-    const double us_tile = d128 ? (a.kv_int8 ? 0.21 : 0.18) : 0.115, us_block = d128 ? (a.kv_int8 ? 1.8 : 2.0) : 1.2;
-    const double us_all = (d128 ? 1.5 : 1.2) + (us_tile * tiles + us_block * blocks32 * p.n_bh) / 256 + us_again;
+    const double us_all = c.base32 + (c.tile32 * tiles + c.block32 * blocks32 * p.n_bh) / 256 + us_again;
     const bool launchable = blocks32 * p.n_bh * 256 < 0x1p32;
     return launchable && (us_longest > us_all ? us_longest : us_all) < us ? 32 : rows;
 }
@@ -1041,12 +1053,19 @@ hipError_t launch_prefill(const PrefillArgs& a, hipStream_t stream) {
         const bool eight = blocks32 * p.n_bh <= 384 && blocks32 >= (a.kv_int8 ? 24 : 48);
         return launch_prefill_split(a, eight ? 8 : 4, stream);
     }
-    if (rows == 2 * kBR) {
-        if (!a.kv_int8) return launch_one<128, false, false, 0, true>(p, stream);
-        if (d128) return a.out_f32 ? launch_one<128, true, true, 0, true>(p, stream) : launch_one<128, true, false, 0, true>(p, stream);
-        return a.out_f32 ? launch_one<64, true, true, 0, true>(p, stream) : launch_one<64, true, false, 0, true>(p, stream);
-    }
     const int sel = (d128 ? 4 : 0) | (a.kv_int8 ? 2 : 0) | (a.out_f32 ? 1 : 0);
+    if (rows == 2 * kBR) {
+        switch (sel) {
+            case 0: return launch_one<64, false, false, 0, true>(p, stream);
+            case 1: return launch_one<64, false, true, 0, true>(p, stream);
+            case 2: return launch_one<64, true, false, 0, true>(p, stream);
+            case 3: return launch_one<64, true, true, 0, true>(p, stream);
+            case 4: return launch_one<128, false, false, 0, true>(p, stream);
+            case 5: return launch_one<128, false, true, 0, true>(p, stream);
+            case 6: return launch_one<128, true, false, 0, true>(p, stream);
+            default: return launch_one<128, true, true, 0, true>(p, stream);
+        }
+    }
     switch (sel) {
         case 0: return launch_one<64, false, false>(p, stream);
         case 1: return launch_one<64, false, true>(p, stream);

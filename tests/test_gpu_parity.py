@@ -1061,6 +1061,28 @@ def test_prefill_bf16_wide_row_blocks(sa, oracle, B, Hq, Hkv, S, causal):
         assert np.array_equal(got_s.cpu().numpy().view(np.uint32), want_s.view(np.uint32))
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,S,D,causal,out_f32", [
+    # bf16 K/V in blocks of 256 rows, 64 values a row: sequences of whole blocks, one row more, one less, ends inside
+    (8, 16, 16, 512, 64, True, False), (8, 16, 4, 513, 64, True, True), (9, 24, 8, 511, 64, False, True), (9, 24, 8, 600, 64, False, False),
+    (4, 40, 8, 777, 64, True, False),
+    # 128 values, fp32 results (the row block's output goes out in two parts)
+    (16, 32, 8, 129, 128, True, True), (16, 32, 8, 256, 128, True, True), (12, 24, 8, 480, 128, False, True), (4, 40, 8, 777, 128, True, True)])
+def test_prefill_bf16_wide_row_blocks_of_64_values_and_fp32(sa, oracle, B, Hq, Hkv, S, D, causal, out_f32):
+    print("prefill bf16 wide", B, Hq, Hkv, S, D, causal, out_f32, flush=True)
+    assert_form(sa, 256, B, Hq, Hkv, S, D, causal, False, out_f32)
+    rng = np.random.default_rng(7 * B + Hq + S)
+    q, k, v = normal_bf16(rng, (B, Hq, S, D)), normal_bf16(rng, (B, Hkv, S, D)), normal_bf16(rng, (B, Hkv, S, D))
+    scale = 1.0 / math.sqrt(D)
+    od = torch.float32 if out_f32 else torch.bfloat16
+    out, kc, ks, vc, vs = sa.slim_attn_prefill_emit_int8(dev_bf16(q), dev_bf16(k), dev_bf16(v), scale, causal, out_dtype=od)
+    torch.cuda.synchronize()
+    check_close(host_f64(out), oracle.attn(q, k, v, scale, causal), "bf16 wide row blocks")
+    for got_c, got_s, x in ((kc, ks, k), (vc, vs, v)):
+        want_c, want_s = oracle.kv_quant_int8(x)
+        assert np.array_equal(got_c.cpu().numpy(), want_c)
+        assert np.array_equal(got_s.cpu().numpy().view(np.uint32), want_s.view(np.uint32))
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,S,D", SMALL)
 @pytest.mark.parametrize("causal", [True, False])
 def test_prefill_two_sweep_small_shapes(sa, oracle, B, Hq, Hkv, S, D, causal):
