@@ -56,7 +56,7 @@ template <int D, int W>
 __global__ __launch_bounds__(64 * W) void slim_decode_int8_split_kernel(
     const uint16_t* __restrict__ q, const int8_t* __restrict__ kc, const float* __restrict__ ks,
     const int8_t* __restrict__ vc, const float* __restrict__ vs, uint16_t* __restrict__ out,
-    float* __restrict__ ws_acc, float* __restrict__ ws_ml, const int* __restrict__ kv_lens, int Hq, int Hkv, int T_alloc,
+    float* __restrict__ ws_acc, float* __restrict__ ws_ml, const int* __restrict__ kv_lens, int group, int Hkv, int T_alloc,
     int n_split, unsigned split_rate, float scale_log2e) {
     constexpr int LPR = D / 16;        // lanes per token row
     constexpr int SLOTS = 64 / LPR;    // token rows per load instruction of a wave
@@ -72,7 +72,7 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_split_kernel(
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));   // (the wave index as a scalar: everything derived from it stays uniform)
     const int c = lane % LPR, s = lane / LPR;
     const int sp = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-    const int g = h / (Hq / Hkv);
+    const int Hq = group * Hkv, g = group == 1 ? h : h / group;   // (group query heads per KV head)
     // T_alloc is the cache's allocated length (the row stride); this sequence's first T tokens count
     const int T = kv_lens ? min(max(kv_lens[b], 1), T_alloc) : T_alloc;
     const int n_used = splits_of(T, n_split, split_rate);
@@ -90,7 +90,9 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_split_kernel(
     // The sequence's own chunks are dealt evenly over its splits, and a split's chunks to its waves in turn: the
     // waves of a workgroup read adjacent pieces of the cache at a time.
     const int n_all = (T + kChunk - 1) / kChunk;
-    const int c_begin = (int)((long)n_all * sp / n_used) + w, c_end = (int)((long)n_all * (sp + 1) / n_used);
+    int c_begin, c_end;
+    split_span(n_all, n_used, sp, c_begin, c_end);
+    c_begin += w;
     const int n_chunks = c_begin < c_end ? (c_end - c_begin + W - 1) / W : 0;
 
     // this lane's 16 query values, fp32
@@ -459,7 +461,7 @@ hipError_t launch_decode(const DecodeArgs& a, hipStream_t stream) {
         constexpr int D = decltype(d_c)::value, W = decltype(w_c)::value;
         hipLaunchKernelGGL((slim_decode_int8_split_kernel<D, W>), dim3((unsigned)n_split, (unsigned)a.q_heads, (unsigned)a.batch),
                            dim3(64 * W), 0, stream, (const uint16_t*)a.q, a.k_codes, a.k_scale, a.v_codes, a.v_scale,
-                           (uint16_t*)a.out, ws_acc, ws_ml, a.kv_lens, a.q_heads, a.kv_heads, a.kv_len, n_split,
+                           (uint16_t*)a.out, ws_acc, ws_ml, a.kv_lens, a.q_heads / a.kv_heads, a.kv_heads, a.kv_len, n_split,
                            plan.split_rate, a.softmax_scale * kLog2e);
         return hipGetLastError();
     };

@@ -59,7 +59,7 @@ template <int D, int W, int NC, bool TRAFFIC_ONLY = false>
 __global__ __launch_bounds__(64 * W) void slim_decode_int8_gqa_kernel(
     const uint16_t* __restrict__ q, const int8_t* __restrict__ kc, const float* __restrict__ ks,
     const int8_t* __restrict__ vc, const float* __restrict__ vs, uint16_t* __restrict__ out, float* __restrict__ ws_acc,
-    float* __restrict__ ws_ml, const int* __restrict__ kv_lens, int Hq, int Hkv, int T_alloc, int n_split,
+    float* __restrict__ ws_ml, const int* __restrict__ kv_lens, int G, int Hkv, int T_alloc, int n_split,
     unsigned split_rate, float scale_log2e) {
     constexpr int KS = D / 64;            // 16-byte pieces of a K row per lane (two k-steps of the score MFMA each)
     constexpr int DT = D / 16;            // 16-row tiles of O^T
@@ -76,7 +76,7 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_gqa_kernel(
 
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));   // (the wave index as a scalar: everything derived from it stays uniform)
     const int l16 = lane & 15, lq = lane >> 4;
-    const int G = Hq / Hkv;
+    const int Hq = G * Hkv;   // (G query heads per KV head)
     const int sp = blockIdx.x, g = blockIdx.y, b = blockIdx.z;
     char* const kS = smem + w * WAVE_BYTES;
     char* const vS = kS + TILE;
@@ -89,7 +89,9 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_gqa_kernel(
     if (sp >= n_used) return;   // (nobody reads this split's record)
     const long kvrow0 = ((long)b * Hkv + g) * (long)T_alloc;
     const int n_all = (T + kGqaTile - 1) / kGqaTile;
-    const int first = (int)((long)n_all * sp / n_used) + w, end = (int)((long)n_all * (sp + 1) / n_used);
+    int first, end;
+    split_span(n_all, n_used, sp, first, end);
+    first += w;
     const int n_tiles = first < end ? (end - first + W - 1) / W : 0;
 
     // Q^T B operands: lane holds head l16 of its group of 16 (a column past the last head: the last head again),
@@ -357,7 +359,7 @@ hipError_t launch_decode_gqa_split(const DecodeArgs& a, float* ws_acc, float* ws
         constexpr int D = decltype(d_c)::value, W = decltype(w_c)::value, NC = decltype(nc_c)::value;
         hipLaunchKernelGGL((slim_decode_int8_gqa_kernel<D, W, NC, decltype(traffic_c)::value>), grid, dim3(64 * W), 0, stream,
                            (const uint16_t*)a.q, a.k_codes, a.k_scale, a.v_codes, a.v_scale, (uint16_t*)a.out, ws_acc, ws_ml,
-                           a.kv_lens, a.q_heads, a.kv_heads, a.kv_len, plan.n_split, plan.split_rate, scale_log2e);
+                           a.kv_lens, a.q_heads / a.kv_heads, a.kv_heads, a.kv_len, plan.n_split, plan.split_rate, scale_log2e);
         return hipGetLastError();
     };
     auto pick = [&](auto d_c) {
