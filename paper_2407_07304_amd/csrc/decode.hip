@@ -397,12 +397,23 @@ static DecodePlan decode_plan(int kv_len, long n_bh, int head_dim) {
 // (Two, four or eight workgroups a row are the worse choice: the long rows' workgroups meet on the same compute units.
 // With lengths spread as above and a split per T / n tokens 4 a row were 2 to 7 % slower than 6 with 256 rows.)
 static DecodePlan ragged_plan(DecodePlan plan, bool gqa, int batch, int q_heads, int kv_heads, int kv_len, int head_dim) {
+    if (batch == 1) return plan;   // (equal cuts: a lone sequence is dealt over all of them)
     const long heads = gqa ? kv_heads : q_heads, rows = batch * heads;
-    if (batch == 1 || heads * plan.n_split >= 128) return plan;   // (equal cuts: a lone sequence is dealt over all of them)
-    const long wanted = gqa ? 768 / rows : (1536 + rows - 1) / rows;
-    const long room = (long)(kDecodeStaticScratchBytes / decode_records_bytes((long)batch * q_heads, 1, head_dim));
-    const long n = std::min({wanted, (long)kv_len / (gqa ? 32 * head_dim : 2048), room});
-    return n <= plan.n_split ? plan : DecodePlan{gqa && q_heads / kv_heads <= 16 ? 4 : 8, (int)n, 1u << 23 /* 2^32 / 512 */};
+    if (heads * plan.n_split < 128) {
+        const long wanted = gqa ? 768 / rows : (1536 + rows - 1) / rows;
+        const long room = (long)(kDecodeStaticScratchBytes / decode_records_bytes((long)batch * q_heads, 1, head_dim));
+        const long n = std::min({wanted, (long)kv_len / (gqa ? 32 * head_dim : 2048), room});
+        if (n > plan.n_split) plan = DecodePlan{gqa && q_heads / kv_heads <= 16 ? 4 : 8, (int)n, 1u << 23 /* 2^32 / 512 */};
+    }
+    // The grouped kernel's waves: eight where no compute unit has two workgroups (a compute unit left with one sequence
+    // then gets through it with twice the waves, and lengths that differ leave most of them with one), and, of 128 codes a token,
+    // where a split has many tokens.  Steps with lengths spread over an eighth to all of the cache, four waves and
+    // eight: 16 on 2 heads, 128 sequences, T=3000 34.1 and 28.7 us, T=8000 77.7 and 63.5; 64 on 8 heads, 16 sequences, T=12000 62.7 and 51.2;
+    // more workgroups: 40 sequences, 32 on 8 heads, T=8000 79.3 and 74.7, 100 of T=4000 92.5 and 85.5, but 48 of T=700 16.6 and 18.4.
+    // (Of 148 calls of one workgroup a compute unit eight waves are 0 to 28 % faster, 2 of them 4 % slower; all of equal length
+    // they are within 2 %.)
+    if (gqa && (rows * plan.n_split <= 256 || (head_dim == 128 && kv_len / plan.n_split >= 2500))) plan.waves = 8;
+    return plan;
 }
 
 // ragged: the sequences have lengths of their own
