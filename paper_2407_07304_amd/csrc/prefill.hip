@@ -990,26 +990,30 @@ static int choose_rows(PrefillParams& p, const PrefillArgs& a) {
         {0.567, 6.29, 0.461, 3.87, 0.739, 1.90, 2.00, 4.65, 0.273, 4.35, 0.295, 1.41}};    // D = 128, INT8
     const bool d128 = a.head_dim == 128;
     const FormCosts& c = kCosts[(d128 ? 2 : 0) + (a.kv_int8 ? 1 : 0)];
-    set_blocks(p, a, 2 * kBR);
-    const bool wide = a.kv_int8 || (d128 ? p.causal || a.seq_len >= 200
-                                         : a.seq_len >= 500 && (p.causal || (long)p.n_rb * p.n_bh > 256));
-    const double us_wide = modelled_us(p, c.tile256, c.item256 + (a.out_f32 ? c.fp32_256 : 0.0), 2 * kBR, 2);
-    set_blocks(p, a, kBR);
-    double us = modelled_us(p, c.tile128, c.item128 + (a.out_f32 ? c.fp32_128 : 0.0), kBR, 1);
-    int rows = kBR;
-    if (wide && us_wide < us) {
-        us = us_wide;
-        rows = 2 * kBR;
-        set_blocks(p, a, 2 * kBR);
-    }
-    us += c.lists;
+    p.n_bh = a.batch * a.q_heads;
     const double blocks32 = (a.seq_len + 31) / 32, tiles = blocks32 * p.n_bh * (p.causal ? (blocks32 + 1) / 2 : blocks32);
     const double us_longest = c.first32 + c.chain32 * blocks32;
     const double kv_bytes = 4.0 * a.batch * a.kv_heads * a.seq_len * a.head_dim;
     const double us_again = !a.kv_int8 && kv_bytes > 40e6 ? kv_bytes * (p.causal ? (blocks32 + 1) / 2 : blocks32) / 10e6 : 0.0;
     const double us_all = c.base32 + (c.tile32 * tiles + c.block32 * blocks32 * p.n_bh) / 256 + us_again;
     const bool launchable = blocks32 * p.n_bh * 256 < 0x1p32;
-    return launchable && (us_longest > us_all ? us_longest : us_all) < us ? 32 : rows;
+    const double us32 = launchable ? (us_longest > us_all ? us_longest : us_all) : 1e30;
+    // (small calls are bound by what the host does for them: no lists where their longest item alone takes longer)
+    const double item128 = c.item128 + (a.out_f32 ? c.fp32_128 : 0.0), item256 = c.item256 + (a.out_f32 ? c.fp32_256 : 0.0);
+    if (us32 < c.lists + std::min(blocks32 * c.tile128 + item128, 2.0 * blocks32 * c.tile256 + item256)) return 32;
+    set_blocks(p, a, 2 * kBR);
+    const bool wide = a.kv_int8 || (d128 ? p.causal || a.seq_len >= 200
+                                         : a.seq_len >= 500 && (p.causal || (long)p.n_rb * p.n_bh > 256));
+    const double us_wide = modelled_us(p, c.tile256, item256, 2 * kBR, 2);
+    set_blocks(p, a, kBR);
+    double us = modelled_us(p, c.tile128, item128, kBR, 1);
+    int rows = kBR;
+    if (wide && us_wide < us) {
+        us = us_wide;
+        rows = 2 * kBR;
+        set_blocks(p, a, 2 * kBR);
+    }
+    return us32 < us + c.lists ? 32 : rows;
 }
 
 int prefill_block_rows(const PrefillArgs& a) {
