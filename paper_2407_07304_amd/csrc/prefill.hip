@@ -705,9 +705,7 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
                 ++i;
             }
         }
-        // the rest of the row block's iterations: this wave's last tile in the first of them, then only its share of the ring
-        for (; i < n_iter; ++i) {
-            const int p4 = i & 3;
+        auto ring_share = [&](int i, int p4) {   // what an iteration sends or stores to the ring
             if constexpr (!KV_I8) {
 #pragma unroll
                 for (int n = 0; n < REQ; ++n) request(n, i, p4);
@@ -719,27 +717,44 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
                 if constexpr (TWO) load_piece1(i);
                 sgs = load_s(i + 4);
             }
-            if (i == last) {
-                const int rel = lim - ((NG * i + my_tile) * kBC + 4 * hh);
-                if constexpr (stats_only) {
-                    max_only(rel, st_a);
-                } else {
-                    const int vm = ((p4 + 3) & 3) * SLOTV, v0 = p4 * SLOTV;
+        };
+        // This wave's last tile, then its share of the ring for the rest of the row block's iterations.  Two pieces of code, so that
+        // what only the former needs does not stay in registers through the latter (B=4, 32 on 8 heads, S=777 32.0 -> 31.5 us, 32
+        // heads, S=1024 19.1 -> 18.9, D=64, S=4096 83.3 -> 82.3), but one loop where the registers are full either way (INT8:
+        // two pieces spill; D=128, 128 rows 51.4 -> 55.0 us at S=2048, the others the same).
+        constexpr bool APART = !KV_I8;
+        if (APART ? last >= 0 : i < n_iter) {
+            do {
+                const int p4 = i & 3;
+                ring_share(i, p4);
+                if (APART || i == last) {
+                    const int rel = lim - ((NG * i + my_tile) * kBC + 4 * hh);
+                    if constexpr (stats_only) {
+                        max_only(rel, st_a);
+                    } else {
+                        const int vm = ((p4 + 3) & 3) * SLOTV, v0 = p4 * SLOTV;
 #pragma unroll
-                    for (int x = 0; x < 2 * DT; ++x) {
-                        pv_mfma(x, p_a);
-                        if (x < VP) fetch_v(x + VP, vm);
-                        else fetch_v(x - VP, v0);
-                    }
-                    lsum += exact_softmax(p4 * NG * 2 * kBC * 4, rel, i == 0, st_a, p_a);
+                        for (int x = 0; x < 2 * DT; ++x) {
+                            pv_mfma(x, p_a);
+                            if (x < VP) fetch_v(x + VP, vm);
+                            else fetch_v(x - VP, v0);
+                        }
+                        lsum += exact_softmax(p4 * NG * 2 * kBC * 4, rel, i == 0, st_a, p_a);
 #pragma unroll
-                    for (int x = 0; x < 2 * DT; ++x) {
-                        pv_mfma(x, p_a);
-                        if (x < VP) fetch_v(x + VP, v0);
+                        for (int x = 0; x < 2 * DT; ++x) {
+                            pv_mfma(x, p_a);
+                            if (x < VP) fetch_v(x + VP, v0);
+                        }
                     }
                 }
-            }
-            if constexpr (KV_I8) __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): what this wave stored is in LDS
+                if constexpr (KV_I8) __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): what this wave stored is in LDS
+                end_iteration();
+                ++i;
+            } while (!APART && i < n_iter);
+        }
+        for (; i < n_iter; ++i) {
+            ring_share(i, i & 3);
+            if constexpr (KV_I8) __builtin_amdgcn_s_waitcnt(0xc07f);
             end_iteration();
         }
         if constexpr (!KV_I8) {
