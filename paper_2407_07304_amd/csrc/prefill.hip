@@ -12,7 +12,7 @@
 //     tiles, and nothing is merged.  128 rows: waves w and w+4 own the same rows, the first four waves (group 0) take the
 //     even key tiles, the others (group 1) the odd ones, each with its own running max, sum and accumulator, merged once at
 //     the end of the row block.
-//   - An iteration is one tile of every wave and one barrier: the wave issues the scores of its next tile and P V of
+//   - An iteration is one tile of every wave, and a barrier ends it (256 rows: most forms, every second one): the wave issues the scores of its next tile and P V of
 //     its last one, alternately, and between two MFMAs a share of this tile's softmax (a fused multiply-add, an
 //     exponential, an addition, half a conversion), the operand read that replaces the one the MFMA consumed, and a ring
 //     request.  A wave's own vector work so runs in the shadow of its MFMAs (a microbenchmark: 16 MFMAs with four vector
@@ -31,8 +31,8 @@
 //   - O^T accumulators: lane = query column, so the online-softmax rescale is a per-lane
 //     scalar multiply; the running max is lazy (it moves only when a row's max grew by more
 //     than 2^8), so the rescale runs a few times per row block.
-//   - K/V tiles live in an LDS ring of four iterations.  bf16 tiles are written by the
-//     memory pipe itself (buffer loads with an LDS destination, four (K) and two (V) iterations ahead, the same
+//   - K/V tiles live in an LDS ring of four or six iterations.  bf16 tiles are written by the
+//     memory pipe itself (buffer loads with an LDS destination, iterations ahead, the same
 //     loads and the same wait in every iteration: past the last tile they ask for zeros) as unpadded
 //     rows whose 16-byte chunks are
 //     XOR-swizzled by the row, so both the 128-bit K row reads and the V transpose reads are
@@ -58,7 +58,6 @@ namespace slim {
 
 constexpr int kBR = 128;   // query rows per row block (4 row groups x 32)
 constexpr int kBC = 32;    // keys per tile
-constexpr int kRing = 4;   // LDS ring depth, in iterations
 constexpr int kPrefillThreads = 512;
 
 struct PrefillParams {
@@ -147,9 +146,17 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
     constexpr int ROWLK = KV_I8 ? ROWL + 16 : ROWL, ROWLV = KV_I8 ? ROWL + 64 : ROWL;   // row pitch
     constexpr int TILEBK = kBC * ROWLK, TILEBV = kBC * ROWLV;   // bytes per tile in LDS
     constexpr int SLOTK = NG * TILEBK, SLOTV = NG * TILEBV;     // bytes per ring slot (an iteration's tiles)
+    // A barrier every second iteration where six slots a tensor fit (256 rows) and the registers allow it (not INT8, D = 128:
+    // 56 bytes of spills a lane, S=8192 548 -> 559 us): B=1, 32 heads, bf16, S=4096 128.1 -> 126.5 us, S=8192 466 -> 460; B=4, 32
+    // on 8 heads, S=777 31.3 -> 30.4; D=64, S=4096 82.0 -> 80.2, INT8 99.1 -> 97.9.
+    constexpr bool DEEP = WIDE && !(KV_I8 && D == 128);
+    constexpr int RING = DEEP ? 6 : 4;        // ring depth, in iterations
+    constexpr int BARRIERS = DEEP ? 2 : 1;    // iterations per barrier
+    constexpr int LEADK = DEEP ? 5 : 4, LEADV = DEEP ? 3 : 2, LEADS = DEEP ? 4 : 3;   // iterations ahead that K, V and INT8 scales go to the ring
+    auto ring_slot = [](int x) { return x % RING; };
     constexpr int CPL = ROWL / 16;            // 16-byte chunks per LDS row: 16 or 8
     constexpr int RPL = 256 / ROWL;           // rows per 256-byte line of banks: 1 or 2
-    constexpr int K_BYTES = kRing * SLOTK, V_BYTES = kRing * SLOTV;
+    constexpr int K_BYTES = RING * SLOTK, V_BYTES = RING * SLOTV;
     constexpr int NV = DT / 2 * 4 + 1;        // f32x4 vectors a wave hands to its partner at the merge
     constexpr int OH = WIDE && OUT_F32 && D == 128 ? 2 : 1;   // parts that the output goes out in: 256 rows of 512 bytes do not fit beside Q
     constexpr int OPITCH = (OUT_F32 ? 4 * D : 2 * D) / OH + 16;   // output tile row pitch: spreads the column-wise writes over the banks
@@ -164,7 +171,7 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
     constexpr int CPQ = ROWQ / 16;             // 16-byte chunks per row: 16 or 8
     constexpr int RPQ = 64 / CPQ;              // rows per wave-wide load: 4 or 8
     constexpr int NQ = BR / 8 / RPQ;           // loads per wave and row block (a wave brings in an eighth of the rows)
-    constexpr int SC_BYTES = KV_I8 ? kRing * NG * 2 * kBC * 4 : 0;   // INT8: per slot the k_scales * c, then the v_scales
+    constexpr int SC_BYTES = KV_I8 ? RING * NG * 2 * kBC * 4 : 0;   // INT8: per slot the k_scales * c, then the v_scales
     constexpr int Q_OFF = RING_BYTES + SC_BYTES;
     auto qswz = [](int r) { return (r / (256 / ROWQ)) & (CPQ - 1); };
 
@@ -378,8 +385,11 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
         }
 
         // ---- the ring.  Iteration i reads K tile i+1 (its second half) and i+2 (first half), V tile i-1 (second half)
-        // and i (first half).  It requests K tile i+4, which takes the slot of K tile i (last read in iteration i-1), and
-        // V tile i+2 for the slot of V tile i-2; both are waited for at the end of iteration i+1 and read from i+2 on.
+        // and i (first half).  It requests K tile i+LEADK, in the slot of K tile i+LEADK-RING, and V tile i+LEADV, in that of
+        // V tile i+LEADV-RING; both are waited for at the end of iteration i+1.  Four slots: a barrier ends every iteration; the
+        // slots were last read in iteration i-1, and the tiles are read from iteration i+2 on.  Six: a barrier ends the odd
+        // iterations; the slots were last read in iteration i-2, and the tiles are read from
+        // iteration i+3 on, so there is a barrier between in both directions whatever i's parity.
         // INT8 tiles are stored from registers at those points instead, and what is stored next is loaded.
         // "V tile -1" meets the zero probabilities of iteration 0: its slot is filled with zeros.
         u32x4 sg0, sg1;
@@ -397,17 +407,15 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
 #pragma unroll
                     for (int n = 0; n < NLD; ++n) dma_one(vrs_raw, d_voff, n, T, K_BYTES + T * SLOTV, wanted);
             };
-            k_tile(0);
-            k_tile(1);
-            k_tile(2);
-            v_tile(0, true);
-            v_tile(3, false);
-            k_tile(3);
-            v_tile(1, 1 < n_iter);
+#pragma unroll
+            for (int T = 0; T < LEADK; ++T) k_tile(T);
+#pragma unroll
+            for (int T = 0; T < LEADV; ++T) v_tile(T, T < n_iter);
+            v_tile(RING - 1, false);
             __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): this wave's requests have landed in LDS
         } else {
-            u32x4 ta[4], tb[4];
-            float s0, s1, s2;
+            u32x4 ta[LEADK], tb[LEADV + 1];
+            float sc[LEADS];
             // The addresses of these loads are put together here, from copies the compiler cannot see through: left
             // to itself it computes all of them ahead of the item loop, spills them, and reloads them one by one
             // between the loads, and a reload is a memory access that waits, in order, for the tile loads before it
@@ -416,28 +424,29 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
             asm volatile("" : "+v"(off_now));
             constexpr unsigned TB = NG * kBC * ROWB;
             const unsigned beyond = (unsigned)S * ROWB;
+            static_assert(LEADK == LEADV + 2, "V: its tiles, then the zeros, then nothing new");
+            // (a wave that stages V only: its tiles, the zeros of V tile -1 in the ring's last slot, and its first tile again)
+            auto slot_n = [&](int n) { return st_k || n < LEADV ? n : n == LEADV ? RING - 1 : 0; };
 #pragma unroll
-            for (int n = 0; n < 4; ++n)
-                ta[n] = __builtin_amdgcn_raw_buffer_load_b128(krs, (int)((n == 3 && !st_k ? beyond : n * TB) + off_now), 0, 0);
+            for (int n = 0; n < LEADK; ++n)
+                ta[n] = __builtin_amdgcn_raw_buffer_load_b128(krs, (int)((n == LEADV && !st_k ? beyond : n > LEADV && !st_k ? 0u : n * TB) + off_now), 0, 0);
             if constexpr (TWO)
 #pragma unroll
-                for (int n = 0; n < 4; ++n)
-                    tb[n] = __builtin_amdgcn_raw_buffer_load_b128(vrs, (int)((n == 3 ? beyond : n * TB) + off_now), 0, 0);
-            s0 = load_s(0);
-            s1 = load_s(1);
-            s2 = load_s(2);
-            sg0 = __builtin_amdgcn_raw_buffer_load_b128(krs, (int)((st_k ? 4 * TB : 2 * TB) + off_now), 0, 0);
-            if constexpr (TWO) sg1 = __builtin_amdgcn_raw_buffer_load_b128(vrs, (int)(2 * TB + off_now), 0, 0);
-            sgs = load_s(3);
+                for (int n = 0; n <= LEADV; ++n)
+                    tb[n] = __builtin_amdgcn_raw_buffer_load_b128(vrs, (int)((n == LEADV ? beyond : n * TB) + off_now), 0, 0);
+#pragma unroll
+            for (int n = 0; n < LEADS; ++n) sc[n] = load_s(n);
+            sg0 = __builtin_amdgcn_raw_buffer_load_b128(krs, (int)((st_k ? LEADK * TB : LEADV * TB) + off_now), 0, 0);
+            if constexpr (TWO) sg1 = __builtin_amdgcn_raw_buffer_load_b128(vrs, (int)(LEADV * TB + off_now), 0, 0);
+            sgs = load_s(LEADS);
             if (has_p)
 #pragma unroll
-                for (int n = 0; n < 4; ++n) store_piece(p_dst + n * (st_k ? SLOTK : SLOTV), ta[n]);
+                for (int n = 0; n < LEADK; ++n) store_piece(p_dst + slot_n(n) * (st_k ? SLOTK : SLOTV), ta[n]);
             if constexpr (TWO)
 #pragma unroll
-                for (int n = 0; n < 4; ++n) store_piece(p_vdst + n * SLOTV, tb[n]);
-            store_s(0, s0);
-            store_s(1, s1);
-            store_s(2, s2);
+                for (int n = 0; n <= LEADV; ++n) store_piece(p_vdst + (n == LEADV ? RING - 1 : n) * SLOTV, tb[n]);
+#pragma unroll
+            for (int n = 0; n < LEADS; ++n) store_s(n, sc[n]);
         }
         __syncthreads();
         read_q();
@@ -532,34 +541,34 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
         static_assert(REQ < 16, "vmcnt is written into the low four bits of the wait's immediate");
         auto request = [&](int n, int i, int p4) {   // n of REQ
             if constexpr (NLT >= 8) {
-                if (n < NLD) dma_one(krs_raw, d_koff, n, i + 4, p4 * SLOTK, i + 4 < n_iter);
-                else dma_one(vrs_raw, d_voff, n - NLD, i + 2, K_BYTES + ((p4 + 2) & 3) * SLOTV, i + 2 < n_iter);
+                if (n < NLD) dma_one(krs_raw, d_koff, n, i + LEADK, ring_slot(p4 + LEADK) * SLOTK, i + LEADK < n_iter);
+                else dma_one(vrs_raw, d_voff, n - NLD, i + LEADV, K_BYTES + ring_slot(p4 + LEADV) * SLOTV, i + LEADV < n_iter);
             } else {
                 const bool ks = w8 < 4;
-                const int T = ks ? i + 4 : i + 2;
+                const int T = ks ? i + LEADK : i + LEADV;
                 u32x4 rs;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) rs[e] = ks ? krs_raw[e] : vrs_raw[e];
-                dma_one(rs, ks ? d_koff : d_voff, 0, T, ks ? p4 * SLOTK : K_BYTES + ((p4 + 2) & 3) * SLOTV, T < n_iter);
+                dma_one(rs, ks ? d_koff : d_voff, 0, T, ks ? ring_slot(p4 + LEADK) * SLOTK : K_BYTES + ring_slot(p4 + LEADV) * SLOTV, T < n_iter);
             }
         };
-        // INT8: the registers' pieces go to K tile i+4 and V tile i+2, their scales to tile i+3; then the next ones are loaded
+        // INT8: the registers' pieces go to K tile i+LEADK and V tile i+LEADV, their scales to tile i+LEADS; then the next ones are loaded
         auto stage_dst = [&](int piece, int p4) {
-            return piece == 1 ? p_vdst + ((p4 + 2) & 3) * SLOTV : p_dst + (st_k ? p4 * SLOTK : ((p4 + 2) & 3) * SLOTV);
+            return piece == 1 ? p_vdst + ring_slot(p4 + LEADV) * SLOTV : p_dst + (st_k ? ring_slot(p4 + LEADK) * SLOTK : ring_slot(p4 + LEADV) * SLOTV);
         };
         auto load_piece0 = [&](int i) {
             constexpr unsigned TB = NG * kBC * ROWB;
-            sg0 = __builtin_amdgcn_raw_buffer_load_b128(krs, (int)((unsigned)(i + (st_k ? 5 : 3)) * TB + p_off), 0, 0);
+            sg0 = __builtin_amdgcn_raw_buffer_load_b128(krs, (int)((unsigned)(i + 1 + (st_k ? LEADK : LEADV)) * TB + p_off), 0, 0);
         };
         auto load_piece1 = [&](int i) {
             constexpr unsigned TB = NG * kBC * ROWB;
-            sg1 = __builtin_amdgcn_raw_buffer_load_b128(vrs, (int)((unsigned)(i + 3) * TB + p_off), 0, 0);
+            sg1 = __builtin_amdgcn_raw_buffer_load_b128(vrs, (int)((unsigned)(i + 1 + LEADV) * TB + p_off), 0, 0);
         };
-        auto end_iteration = [&]() {
+        auto end_iteration = [&](bool barrier) {
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (!KV_I8) __builtin_amdgcn_s_waitcnt(0x0f70 | REQ);   // vmcnt(REQ), see the invariant above
             asm volatile("" ::: "memory");
-            __builtin_amdgcn_s_barrier();
+            if (barrier) __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
             __builtin_amdgcn_sched_barrier(0);
         };
@@ -571,9 +580,9 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
         // the refill of the operand the MFMA consumed and of the ring: the fences keep the order as written.
         auto full = [&](auto p4_c, int i, const f32x16& st, f32x16& sn, const u32x4 (&pv)[2], u32x4 (&pn)[2]) {
             constexpr int P4 = decltype(p4_c)::value;
-            constexpr int K1 = ((P4 + 1) & 3) * SLOTK, K2 = ((P4 + 2) & 3) * SLOTK;
-            constexpr int VM = ((P4 + 3) & 3) * SLOTV, V0 = P4 * SLOTV;
-            constexpr int SC = P4 * NG * 2 * kBC * 4, SCN = ((P4 + 1) & 3) * NG * 2 * kBC * 4;
+            constexpr int K1 = (P4 + 1) % RING * SLOTK, K2 = (P4 + 2) % RING * SLOTK;
+            constexpr int VM = (P4 + RING - 1) % RING * SLOTV, V0 = P4 * SLOTV;
+            constexpr int SC = P4 * NG * 2 * kBC * 4, SCN = (P4 + 1) % RING * NG * 2 * kBC * 4;
             float a[16], ps0 = 0.0f, ps1 = 0.0f;
             u32x4 wide;
             auto finish_p = [&](int r) {
@@ -633,8 +642,8 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
                     if (e == 3) load_piece0(i);
                     if (TWO && e == 7) load_piece1(i);
                     if (j == NS - 2) {
-                        store_s((P4 + 3) & 3, sgs);
-                        sgs = load_s(i + 4);
+                        store_s(ring_slot(P4 + LEADS), sgs);
+                        sgs = load_s(i + 1 + LEADS);
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);
@@ -650,7 +659,7 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
                 if (__builtin_amdgcn_ballot_w64(ps > 256.0f) != 0) ps = exact_softmax(SC, kBC, i == 0, st, pn);
                 lsum += ps;
             }
-            end_iteration();
+            end_iteration(BARRIERS == 1 || P4 % 2 == 1);
         };
 
         f32x16 st_a, st_b;
@@ -675,7 +684,7 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
                 vfs = *reinterpret_cast<const float*>(smem + scv_addr);
             }
         }
-        // (K tile 0 has been read: iteration 0 sends K tile 4 to its slot)
+        // (K tile 0 has been read: iteration 0 or 1 sends another to its slot)
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
@@ -683,26 +692,37 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
         asm volatile("" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
         if (last >= 0) {
+            auto from_b = [&]() {
+                st_a = st_b;
+                p_a[0] = p_b[0];
+                p_a[1] = p_b[1];
+            };
             for (;;) {
                 if (i >= last) break;
                 full(int_c<0>{}, i, st_a, st_b, p_a, p_b);
                 if (++i >= last) {
-                    st_a = st_b;
-                    p_a[0] = p_b[0];
-                    p_a[1] = p_b[1];
+                    from_b();
                     break;
                 }
                 full(int_c<1>{}, i, st_b, st_a, p_b, p_a);
                 if (++i >= last) break;
                 full(int_c<2>{}, i, st_a, st_b, p_a, p_b);
                 if (++i >= last) {
-                    st_a = st_b;
-                    p_a[0] = p_b[0];
-                    p_a[1] = p_b[1];
+                    from_b();
                     break;
                 }
                 full(int_c<3>{}, i, st_b, st_a, p_b, p_a);
                 ++i;
+                if constexpr (RING == 6) {
+                    if (i >= last) break;
+                    full(int_c<4>{}, i, st_a, st_b, p_a, p_b);
+                    if (++i >= last) {
+                        from_b();
+                        break;
+                    }
+                    full(int_c<5>{}, i, st_b, st_a, p_b, p_a);
+                    ++i;
+                }
             }
         }
         auto ring_share = [&](int i, int p4) {   // what an iteration sends or stores to the ring
@@ -712,10 +732,10 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
             } else {
                 if (has_p) store_piece(stage_dst(0, p4), sg0);
                 if constexpr (TWO) store_piece(stage_dst(1, p4), sg1);
-                store_s((p4 + 3) & 3, sgs);
+                store_s(ring_slot(p4 + LEADS), sgs);
                 load_piece0(i);
                 if constexpr (TWO) load_piece1(i);
-                sgs = load_s(i + 4);
+                sgs = load_s(i + 1 + LEADS);
             }
         };
         // This wave's last tile, then its share of the ring for the rest of the row block's iterations.  Two pieces of code, so that
@@ -725,14 +745,14 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
         constexpr bool APART = !KV_I8;
         if (APART ? last >= 0 : i < n_iter) {
             do {
-                const int p4 = i & 3;
+                const int p4 = ring_slot(i);
                 ring_share(i, p4);
                 if (APART || i == last) {
                     const int rel = lim - ((NG * i + my_tile) * kBC + 4 * hh);
                     if constexpr (stats_only) {
                         max_only(rel, st_a);
                     } else {
-                        const int vm = ((p4 + 3) & 3) * SLOTV, v0 = p4 * SLOTV;
+                        const int vm = ring_slot(p4 + RING - 1) * SLOTV, v0 = p4 * SLOTV;
 #pragma unroll
                         for (int x = 0; x < 2 * DT; ++x) {
                             pv_mfma(x, p_a);
@@ -748,18 +768,18 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
                     }
                 }
                 if constexpr (KV_I8) __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): what this wave stored is in LDS
-                end_iteration();
+                end_iteration(BARRIERS == 1 || (i & 1) != 0);
                 ++i;
             } while (!APART && i < n_iter);
         }
         for (; i < n_iter; ++i) {
-            ring_share(i, i & 3);
+            ring_share(i, ring_slot(i));
             if constexpr (KV_I8) __builtin_amdgcn_s_waitcnt(0xc07f);
-            end_iteration();
+            end_iteration(BARRIERS == 1 || (i & 1) != 0);
         }
-        if constexpr (!KV_I8) {
-            // the last iterations' requests (zeros) have landed before the ring is used for anything else
-            __builtin_amdgcn_s_waitcnt(0x0f70);
+        if constexpr (!KV_I8 || BARRIERS > 1) {
+            // the last iterations' requests (zeros) have landed, and all reads are done, before the ring is used for anything else
+            if constexpr (!KV_I8) __builtin_amdgcn_s_waitcnt(0x0f70);
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
         }
@@ -807,7 +827,7 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
             char* const obase = (char*)kernel_args_now()->out + ((long)bh_now * S + i0) * (long)OB + part * (OB / OH);
 #pragma unroll
             for (int i = 0; i < NST; ++i) {
-                // (the thread id, counted afresh: keeping it alive through the phase loops costs spills)
+                // (the thread id, counted afresh: keeping it alive through the tile loops costs spills)
                 const int lane_now = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
                 const int pid = (w8 * 64 + lane_now) + kPrefillThreads * i, row = pid / PPR, col = pid % PPR;
                 const u32x4 piece = *reinterpret_cast<const u32x4*>(smem + row * OPITCH + col * 16);
@@ -926,12 +946,12 @@ static hipError_t launch_one(const PrefillParams& p, hipStream_t stream) {
     return hipGetLastError();
 }
 
-// Microseconds the fullest workgroup takes: us_phase a phase (phases_per_tile of them a key tile) and us_item an item
+// Microseconds the fullest workgroup takes: us_tile for 128 rows of a key tile (halves of them a block) and us_item an item
 // (prologue, merge and output).  Of a long list of items the mean, else the longest of the first, middle and last lists.
-static double modelled_us(const PrefillParams& p, double us_phase, double us_item, int rows, int phases_per_tile) {
+static double modelled_us(const PrefillParams& p, double us_tile, double us_item, int rows, int halves) {
     const long n = (long)p.n_rb * p.n_bh;
     if (p.rounds > 8)
-        return (double)n / (8.0 * p.slots) * ((p.causal ? ((double)p.S + rows) / 64 : p.S / 32.0) * phases_per_tile * us_phase + us_item);
+        return (double)n / (8.0 * p.slots) * ((p.causal ? ((double)p.S + rows) / 64 : p.S / 32.0) * halves * us_tile + us_item);
     double most = 0.0;
     for (const int slot : {0, p.slots / 2, p.slots - 1}) {
         double us = 0.0;
@@ -943,7 +963,7 @@ static double modelled_us(const PrefillParams& p, double us_phase, double us_ite
             const long heads = std::min((long)p.heads, p.n_bh - batch * (long)p.heads);
             const long kend = (p.n_rb - in / heads) * rows - p.row_off;
             const long keys = p.causal && kend < p.S ? kend : p.S;
-            us += (double)((keys + kBC - 1) / kBC * phases_per_tile) * us_phase + us_item;
+            us += (double)((keys + kBC - 1) / kBC * halves) * us_tile + us_item;
         }
         if (us > most) most = us;
     }
