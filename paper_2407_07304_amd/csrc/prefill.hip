@@ -12,14 +12,14 @@
 //     tiles, and nothing is merged.  128 rows: waves w and w+4 own the same rows, the first four waves (group 0) take the
 //     even key tiles, the others (group 1) the odd ones, each with its own running max, sum and accumulator, merged once at
 //     the end of the row block.
-//   - An iteration is one tile of every wave, and a barrier ends it (256 rows: most forms, every second one): the wave issues the scores of its next tile and P V of
-//     its last one, alternately, and between two MFMAs a share of this tile's softmax (a fused multiply-add, an
-//     exponential, an addition, half a conversion), the operand read that replaces the one the MFMA consumed, and a ring
-//     request.  A wave's own vector work so runs in the shadow of its MFMAs (a microbenchmark: 16 MFMAs with four vector
+//   - An iteration is one tile of every wave, and a barrier ends it (every second one where six ring slots fit, see DEEP):
+//     the wave issues the scores of its next tile and P V of its last one, alternately, and between two MFMAs a share of this
+//     tile's softmax (a fused multiply-add, an exponential, an addition, half a conversion), the operand read that replaces
+//     the one the MFMA consumed, and a ring request.  A wave's own vector work so runs in the shadow of its MFMAs (a microbenchmark: 16 MFMAs with four vector
 //     instructions each take 34 cycles an MFMA, alone 32.5).  (Before, two groups of waves in opposite phases, softmax and
 //     MFMAs, met at a barrier per phase: 1590 cycles for what an iteration does in 1390.  B=1, 32 heads, bf16, before and
-//     now: S=2048 42.0 -> 40.8 us, S=8192 490 -> 465, D=64, S=4096 95 -> 88; INT8 S=4096 150.0 -> 146.7, D=64 116 -> 100;
-//     B=4, 32 on 8 heads, S=777 34.1 -> 31.6.)  On N(0,1) operands what is left is power: S=8192, not causal, runs at 1.85
+//     now: S=2048 41.7 -> 39.9 us, S=8192 490 -> 465, D=64, S=4096 95 -> 88; INT8 S=4096 149.1 -> 147.3, D=64 116 -> 100;
+//     B=4, 32 on 8 heads, S=777 with its cache 37.9 -> 34.6.)  On N(0,1) operands what is left is power: S=8192, not causal, runs at 1.85
 //     PFLOP/s on zeros and at 1.24 on N(0,1), and operand reads from LDS are 15 % of that, the barrier 4 %.
 //   - The score tile is computed transposed, S^T = K Q^T: the K tile is the A operand
 //     (from LDS), Q^T the B operand (held in registers for the whole row block).  In the
@@ -1075,8 +1075,9 @@ hipError_t launch_prefill(const PrefillArgs& a, hipStream_t stream) {
     p.scale_log2e = a.softmax_scale * kLog2e;
     p.row_max = a.row_max;
     if (a.row_max) {   // the comparison variant: bf16 K/V only (checked by the caller); two launches
-        // (the sweep for the maxima fits twice on a compute unit at D = 64, 79 registers and 66 KB, and wants to be there
-        // twice: both sweeps of B=8, 64 on 8 heads, S=1024 220 us with one workgroup, 190 with two)
+        // (the sweep for the maxima fits twice on a compute unit at D = 64, 94 registers and 80 KB, and wants to be there
+        // twice: both sweeps of B=8, 64 on 8 heads, S=1024 220 us with one workgroup, 190 with two, measured when waves still
+        // met at a barrier per half iteration)
         set_blocks(p, a, kBR, a.head_dim == 64 ? 2 : 1);
         hipError_t e = a.head_dim == 128 ? launch_one<128, false, false, 1>(p, stream) : launch_one<64, false, false, 1>(p, stream);
         if (e != hipSuccess) return e;

@@ -444,7 +444,7 @@ def test_prefill_batched_gqa_full_tensor(sa, oracle):
     (1, 8, 2, 640, False, 32), (1, 8, 2, 640, True, 32), (38, 8, 8, 257, False, 128), (9, 8, 2, 640, True, 128), (16, 32, 8, 256, False, 256),
     (4, 32, 8, 777, False, 256), (16, 16, 8, 300, True, 256)])
 def test_prefill_many_launches_are_bit_identical(sa, oracle, B, Hq, Hkv, S, kv_int8, form):
-    # the ring slots of the 128- and 256-row forms are reused from the first phase on, and a workgroup's items follow each
+    # the ring slots of the 128- and 256-row forms are reused from the first iteration on, and a workgroup's items follow each
     # other: a missing wait between a read and the next request for the same slot shows as a rare difference between
     # launches, so every launch is compared
     print("prefill, 200 launches", B, Hq, Hkv, S, kv_int8, form, flush=True)
