@@ -688,6 +688,30 @@ def test_decode_of_one_long_sequence_among_short_ones(sa, oracle, B, Hq, Hkv, T,
     check_close(host_f64(out2), want, "one long sequence, %d splits" % fewer)
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,T,D", [
+    # 256 rows: one workgroup a compute unit; 272 rows: more, and splits on both sides of 2500 tokens; 64 codes a token
+    (32, 32, 8, 300, 128), (34, 16, 8, 2499, 128), (34, 16, 8, 2500, 128), (34, 16, 8, 2500, 64), (128, 4, 2, 300, 64)])
+def test_grouped_decode_waves_with_lengths_of_their_own(sa, oracle, B, Hq, Hkv, T, D):
+    # four or eight waves share a row's tiles of 32 tokens: fewer tiles than waves, as many, one more, a last tile of one token
+    print("grouped decode, lengths", B, Hq, Hkv, T, D, flush=True)
+    rng = np.random.default_rng(3 * T + B + D)
+    lens = np.array(([T, 1, 32, 33, 128, 129, 255, 256, 257, T - 1] * B)[:B], dtype=np.int32)
+    q = normal_bf16(rng, (B, Hq, 1, D))
+    kc = rng.integers(-127, 128, (B, Hkv, T, D), dtype=np.int8)
+    vc = rng.integers(-127, 128, (B, Hkv, T, D), dtype=np.int8)
+    ks, vs = rng.uniform(0.005, 0.02, (B, Hkv, T)).astype(np.float32), rng.uniform(0.005, 0.02, (B, Hkv, T)).astype(np.float32)
+    scale = 1.0 / math.sqrt(D)
+    out = sa.slim_attn_decode_int8_varlen(dev_bf16(q), dev(kc), dev(ks), dev(vc), dev(vs), torch.from_numpy(lens).cuda(), scale)
+    torch.cuda.synchronize()
+    want = np.concatenate([oracle.attn(q[b:b + 1], kc[b:b + 1, :, :m], vc[b:b + 1, :, :m], scale, False, k_scale=ks[b:b + 1, :, :m],
+                                       v_scale=vs[b:b + 1, :, :m]) for b, m in enumerate(lens.tolist())], axis=0)
+    # (a probability times its v_scale and the result are each rounded to bf16: 2^-8 of sum p |v| and half an ulp; |v| < 2.54)
+    err = np.abs(host_f64(out) - want)
+    assert err.max() <= 2.54 * 2.0 ** -8 + 2.0 ** -7
+    # (a row of one token takes both roundings whole, each at most 2^-9 of |v| on average, and |v| <= 1.27 on average; longer rows less)
+    assert err.mean() <= 1.27 * 2 * 2.0 ** -9
+
+
 @pytest.mark.parametrize("D,Hq,Hkv", [(128, 16, 2), (64, 6, 3)])
 def test_grouped_decode_of_extreme_queries(sa, oracle, D, Hq, Hkv):
     # rows around 2^60 and around 2^-50, with sequences that leave most splits empty, and a row with an infinity or a NaN, whose result is not a number while every other row's is
