@@ -479,10 +479,27 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
             const s16x8 av = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
             o[x % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av), __builtin_bit_cast(bf16x8, pw[x / DT]), o[x % DT], 0, 0, 0);
         };
+        // The probabilities of a lane, in a, to pn (INT8: times their token's v_scale, before they are rounded to bf16).
+        auto pack_p = [&](int sc_off, float (&a)[16], u32x4 (&pn)[2]) {
+            if constexpr (KV_I8) {
+#pragma unroll
+                for (int r4 = 0; r4 < 4; ++r4) {
+                    const f32x4 vf = *reinterpret_cast<const f32x4*>(smem + sc_addr + sc_off + NG * kBC * 4 + 32 * r4);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) a[4 * r4 + e] *= vf[e];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) pn[u][i] = pack_bf16x2(a[8 * u + 2 * i], a[8 * u + 2 * i + 1]);
+        };
         // The softmax of tile t with the maximum taken exactly (scores in st, register r of this lane is key 32 t + 8 (r/4)
-        // + 4 hh + r%4; sc_slot: the tile's scales): moves the running max, rescales what there is, leaves the probabilities
-        // in pn.  Keys of this lane past offset rel are masked.
+        // + 4 hh + r%4; sc_off: the tile's scales): moves the running max, rescales what there is, leaves the probabilities
+        // in pn.  Keys of this lane past offset rel are masked.  (No contraction: a product that is masked cannot be one, and a
+        // tile's result must not depend on whether the compiler knows that none is.)
         auto exact_softmax = [&](int sc_off, int rel, bool first, const f32x16& st, u32x4 (&pn)[2]) {
+#pragma clang fp contract(off)
             float a[16];
 #pragma unroll
             for (int r4 = 0; r4 < 4; ++r4) {
@@ -514,19 +531,33 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
                 ps0 += a[r];
                 ps1 += a[r + 1];
             }
-            if constexpr (KV_I8) {   // the probabilities take their token's v_scale before they are rounded to bf16
+            pack_p(sc_off, a, pn);
+            return ps0 + ps1;
+        };
+        // The same for a wave's last tile.  Where that is not its rows' last one (128 rows: the group that does not hold the
+        // diagonal) nothing is masked, and like every other such tile it leaves the running max where it is unless the
+        // probabilities overflow: the maximum that they are rounded against does not depend on which group a tile fell to.
+        auto last_softmax = [&](int sc_off, int rel, bool masked, bool first, const f32x16& st, u32x4 (&pn)[2]) {
+            if (NG > 1 && !masked) {
+                float a[16], ps0 = 0.0f, ps1 = 0.0f;
 #pragma unroll
                 for (int r4 = 0; r4 < 4; ++r4) {
-                    const f32x4 vf = *reinterpret_cast<const f32x4*>(smem + sc_addr + sc_off + NG * kBC * 4 + 32 * r4);
+                    f32x4 kf = {c, c, c, c};
+                    if constexpr (KV_I8) kf = *reinterpret_cast<const f32x4*>(smem + sc_addr + sc_off + 32 * r4);
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) a[4 * r4 + e] *= vf[e];
+                    for (int e = 0; e < 4; ++e) a[4 * r4 + e] = fast_exp2(fmaf(st[4 * r4 + e], kf[e], -M));
+                    ps0 += a[4 * r4];
+                    ps1 += a[4 * r4 + 1];
+                    ps0 += a[4 * r4 + 2];
+                    ps1 += a[4 * r4 + 3];
+                }
+                const float ps = ps0 + ps1;
+                if (__builtin_amdgcn_ballot_w64(ps > 256.0f) == 0) {
+                    pack_p(sc_off, a, pn);
+                    return ps;
                 }
             }
-#pragma unroll
-            for (int u = 0; u < 2; ++u)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) pn[u][i] = pack_bf16x2(a[8 * u + 2 * i], a[8 * u + 2 * i + 1]);
-            return ps0 + ps1;
+            return exact_softmax(sc_off, rel, first, st, pn);
         };
         auto max_only = [&](int rel, const f32x16& st) {   // MODE 1: the tile's scores only raise the row maximum
             float umax = kMasked;
@@ -759,7 +790,7 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
                             if (x < VP) fetch_v(x + VP, vm);
                             else fetch_v(x - VP, v0);
                         }
-                        lsum += exact_softmax(p4 * NG * 2 * kBC * 4, rel, i == 0, st_a, p_a);
+                        lsum += last_softmax(p4 * NG * 2 * kBC * 4, rel, NG * i + my_tile == t_last, i == 0, st_a, p_a);
 #pragma unroll
                         for (int x = 0; x < 2 * DT; ++x) {
                             pv_mfma(x, p_a);

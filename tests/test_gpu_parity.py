@@ -1278,6 +1278,40 @@ def test_sharp_softmax_stays_within_the_rounding_bound(sa, oracle, B, Hq, Hkv, S
     assert np.median(tops) > 0.5
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,S,D,kv_int8", [(1, 32, 32, 2048, 128, False), (9, 8, 2, 777, 64, False), (9, 7, 7, 289, 128, False),
+                                                   (9, 8, 2, 640, 128, True), (1, 40, 8, 1500, 64, True)])
+def test_prefill_last_unmasked_tile_keeps_the_running_maximum(sa, B, Hq, Hkv, S, D, kv_int8):
+    # Row blocks of 128 rows: two groups of waves take the even and the odd key tiles, and one of a row's two last tiles is
+    # not the one on its diagonal.  That one must be treated like every other full tile: its probabilities are taken against
+    # the running maximum as it stands.  Scores: log2 of whole powers of two, so that those probabilities are bf16 values and
+    # an fp32 result is good to its sums, except for one key per even tile with the score 3.75 and V = 0: against ITS maximum
+    # each of the others would be off by 1.4e-3.  Rows whose diagonal is an even tile (which does take its maximum) are left out.
+    rng = np.random.default_rng(S + D)
+    rows = np.arange(S)
+    score = np.where(rows // 32 % 2 == 0, rng.integers(0, 4, S), 0).astype(np.float64)
+    score[:64] = 0.0                         # (both groups' first tiles, which set the running maximum)
+    v = rng.integers(-4, 5, (B, Hkv, S, D)).astype(np.float64)
+    for t in range(2, (S + 31) // 32, 2):
+        score[32 * t] = 3.75
+        v[:, :, 32 * t] = 0.0
+    bits = lambda x: f32_to_bf16_bits(np.ascontiguousarray(x, dtype=np.float32))  # noqa: E731
+    q, k = np.zeros((B, Hq, S, D)), np.zeros((B, Hkv, S, D))
+    q[..., 5], k[..., 5] = 1.0, score
+    if kv_int8:
+        args = (dev_bf16(bits(q)), dev((4 * k).astype(np.int8)), dev(v.astype(np.int8)))
+        kw = dict(k_scale=torch.full((B, Hkv, S), 0.25, device="cuda"), v_scale=torch.ones((B, Hkv, S), device="cuda"))
+    else:
+        args, kw = (dev_bf16(bits(q)), dev_bf16(bits(k)), dev_bf16(bits(v))), {}
+    assert_form(sa, 128, B, Hq, Hkv, S, D, True, kv_int8, True)
+    got = host_f64(sa.slim_attn_prefill(*args, math.log(2.0), True, out_dtype=torch.float32, **kw))
+    p = 2.0 ** score
+    want = np.repeat(np.cumsum(p[:, None] * v, axis=2) / np.cumsum(p)[:, None], Hq // Hkv, axis=1)
+    # (2^-24 for each of at most S additions to numerator and denominator, |v| <= 4, and as much again for the exponentials)
+    bound = 4 * 4.0 * S * 2.0 ** -24
+    checked = rows[rows // 32 % 2 == 1]
+    assert np.abs(got - want)[:, :, checked].max() <= min(bound, 1e-4)
+
+
 @pytest.mark.parametrize("Hq,Hkv", [(4, 4), (8, 2)])
 def test_sharp_softmax_decode_stays_within_the_rounding_bound(sa, oracle, Hq, Hkv):
     # the same bound for the decode kernels (per-head: P * v_scale stays in fp32, only the bf16 output rounds;
