@@ -59,6 +59,17 @@ int slim_probe_gqa_decode_traffic(const void* q_bf16, const int8_t* k_codes, con
                                   const float* v_scale, void* workspace, size_t workspace_bytes, int batch, int q_heads,
                                   int kv_heads, int kv_len, int head_dim, void* stream);
 
+/* ---- exported by libslimattn.so: which of its own forms a call takes.  Host arithmetic only. */
+
+/*
+ * How slim_attn_decode_int8 (per_sequence_lengths 0) or slim_attn_decode_int8_varlen (1, with a workspace of the size that
+ * slim_attn_decode_int8_workspace_bytes() gives) cuts such a call up: waves per workgroup, and workgroups per row (of a
+ * (batch, KV head) with 2 to 32 query heads per KV head, else of a (batch, query head)).  Returns 0, or the status of
+ * slimattn.h that the call itself would return for these sizes; the answer may change from version to version.
+ */
+int slim_attn_decode_int8_plan(int batch, int q_heads, int kv_heads, int kv_len, int head_dim, int per_sequence_lengths,
+                               int* waves, int* n_split);
+
 #ifdef __cplusplus
 }
 #endif

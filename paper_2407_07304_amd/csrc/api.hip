@@ -1,6 +1,7 @@
 // C ABI of the library (declared in include/slimattn.h): argument validation and
 // dispatch only.  Nothing here allocates, synchronises or keeps state.
 #include "../../include/slimattn.h"
+#include "../../include/slimprobe.h"
 
 #include <math.h>
 
@@ -213,6 +214,18 @@ size_t slim_attn_decode_int8_workspace_bytes(int batch, int q_heads, int kv_head
     if (check_shape(batch, q_heads, kv_heads, kv_len, head_dim) != SLIM_OK) return 0;
     // (one answer for both entry points: the plan for sequences of different lengths never has fewer splits)
     return slim::decode_workspace_bytes(batch, q_heads, kv_heads, kv_len, head_dim, true);
+}
+
+int slim_attn_decode_int8_plan(int batch, int q_heads, int kv_heads, int kv_len, int head_dim, int per_sequence_lengths,
+                               int* waves, int* n_split) {
+    if (!waves || !n_split) return SLIM_ERR_NULL;
+    const int st = check_shape(batch, q_heads, kv_heads, kv_len, head_dim);
+    if (st != SLIM_OK) return st;
+    if (per_sequence_lengths != 0 && per_sequence_lengths != 1) return SLIM_ERR_SHAPE;
+    const slim::DecodePlan plan = slim::decode_plan_of(per_sequence_lengths == 1, batch, q_heads, kv_heads, kv_len, head_dim);
+    *waves = plan.waves;
+    *n_split = plan.n_split;
+    return SLIM_OK;
 }
 
 constexpr size_t kUseStaticScratch = ~(size_t)0;   // decode_common: workspace == NULL with this size selects the static array

@@ -405,19 +405,18 @@ static DecodePlan ragged_plan(DecodePlan plan, bool gqa, int batch, int q_heads,
         const long n = std::min({wanted, (long)kv_len / (gqa ? 32 * head_dim : 2048), room});
         if (n > plan.n_split) plan = DecodePlan{gqa && q_heads / kv_heads <= 16 ? 4 : 8, (int)n, 1u << 23 /* 2^32 / 512 */};
     }
-    // The grouped kernel's waves: eight where no compute unit has two workgroups (a compute unit left with one sequence
-    // then gets through it with twice the waves, and lengths that differ leave most of them with one), and, of 128 codes a token,
-    // where a split has many tokens.  Steps with lengths spread over an eighth to all of the cache, four waves and
-    // eight: 16 on 2 heads, 128 sequences, T=3000 34.1 and 28.7 us, T=8000 77.7 and 63.5; 64 on 8 heads, 16 sequences, T=12000 62.7 and 51.2;
-    // more workgroups: 40 sequences, 32 on 8 heads, T=8000 79.3 and 74.7, 100 of T=4000 92.5 and 85.5, but 48 of T=700 16.6 and 18.4.
-    // (Of 148 calls of one workgroup a compute unit eight waves are 0 to 28 % faster, 2 of them 4 % slower; all of equal length
-    // they are within 2 %.)
-    if (gqa && (rows * plan.n_split <= 256 || (head_dim == 128 && kv_len / plan.n_split >= 2500))) plan.waves = 8;
+    // The grouped kernel's waves, 64 codes a token: eight where no compute unit has two workgroups (15 shapes of 240 to 256
+    // workgroups: lengths spread over an eighth to all of the cache 1 to 40 % faster than with four, all equal 1 to 30 %, 32
+    // sequences, 32 on 8 heads, T=3000 20.7 and 14.8 us, 24.5 and 19.3; all of 300 to 700 tokens 2 % slower to 15 % faster).
+    // Not of 128 codes: up to 256 workgroups lengths so spread gain up to 14 %, but equal ones lose 2 to 6 % (16 sequences, 32
+    // on 8 heads, T=8192 46.3 and 49.1 us), and above, where twelve waves of the smaller workgroups fit a compute unit and
+    // eight of the larger, short contexts in a large cache lose (300 to 700 tokens, 32 sequences, T=8192 14.0 and 17.3 us, 16
+    // of T=32768 10.7 and 14.5).
+    if (gqa && head_dim == 64 && rows * plan.n_split <= 256) plan.waves = 8;
     return plan;
 }
 
-// ragged: the sequences have lengths of their own
-static DecodePlan plan_of(bool ragged, int batch, int q_heads, int kv_heads, int kv_len, int head_dim) {
+DecodePlan decode_plan_of(bool ragged, int batch, int q_heads, int kv_heads, int kv_len, int head_dim) {
     const bool gqa = decode_uses_gqa_kernel(q_heads, kv_heads);
     const DecodePlan plan = gqa ? decode_gqa_plan(kv_len, (long)batch * kv_heads, q_heads / kv_heads, head_dim)
                                 : decode_plan(kv_len, (long)batch * q_heads, head_dim);
@@ -430,7 +429,7 @@ bool decode_uses_gqa_kernel(int q_heads, int kv_heads) {
 }
 
 size_t decode_workspace_bytes(int batch, int q_heads, int kv_heads, int kv_len, int head_dim, bool ragged) {
-    int n_split = plan_of(ragged, batch, q_heads, kv_heads, kv_len, head_dim).n_split;
+    int n_split = decode_plan_of(ragged, batch, q_heads, kv_heads, kv_len, head_dim).n_split;
     // (grouped heads: never less than two records a row, so that the shapes the static scratch array is too small for stay what they were)
     if (decode_uses_gqa_kernel(q_heads, kv_heads) && n_split < 2) n_split = 2;
     return decode_records_bytes((long)batch * q_heads, n_split, head_dim);
@@ -464,7 +463,7 @@ hipError_t decode_static_scratch(float** ptr) {
 hipError_t launch_decode(const DecodeArgs& a, hipStream_t stream) {
     // (the query heads of a KV head share one pass over its cache in the grouped-query kernel)
     const bool gqa = decode_uses_gqa_kernel(a.q_heads, a.kv_heads);
-    const DecodePlan plan = plan_of(a.ragged, a.batch, a.q_heads, a.kv_heads, a.kv_len, a.head_dim);
+    const DecodePlan plan = decode_plan_of(a.ragged, a.batch, a.q_heads, a.kv_heads, a.kv_len, a.head_dim);
     const int n_split = plan.n_split;
     float* const ws_acc = a.workspace;
     float* const ws_ml = a.workspace + (size_t)a.batch * a.q_heads * n_split * a.head_dim;

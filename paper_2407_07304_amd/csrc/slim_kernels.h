@@ -66,6 +66,8 @@ DecodePlan decode_gqa_plan(int kv_len, long n_bg, int group, int head_dim);
 // traffic_only: the measurement form (the kernel's loads without its arithmetic; what it writes is meaningless)
 hipError_t launch_decode_gqa_split(const DecodeArgs& a, float* ws_acc, float* ws_ml, const DecodePlan& plan, hipStream_t stream,
                                    bool traffic_only = false);
+// The plan of a call; ragged: the sequences have lengths of their own
+DecodePlan decode_plan_of(bool ragged, int batch, int q_heads, int kv_heads, int kv_len, int head_dim);
 size_t decode_workspace_bytes(int batch, int q_heads, int kv_heads, int kv_len, int head_dim, bool ragged);
 hipError_t launch_decode(const DecodeArgs& a, hipStream_t stream);
 // The library's own decode scratch (one static device array per GPU) for the entry point that may not

@@ -1,4 +1,6 @@
 """Helpers shared by the GPU parity tests: host bits <-> device tensors, error metrics."""
+import ctypes
+
 import numpy as np
 import torch
 
@@ -23,6 +25,13 @@ def assert_form(sa, rows, B, Hq, Hkv, S, D, causal, kv_int8, out_f32):
     got = sa.load().slim_attn_prefill_block_rows(B, Hq, Hkv, S, D, int(causal), sa.SLIM_I8 if kv_int8 else sa.SLIM_BF16,
                                                  sa.SLIM_F32 if out_f32 else sa.SLIM_BF16)
     assert got == rows, "row blocks of %d rows, the test is of those of %d" % (got, rows)
+
+
+def assert_plan(sa, plan, B, Hq, Hkv, T, D):
+    """A decode with lengths of its own takes this plan: (waves per workgroup, workgroups per row)."""
+    w, n = ctypes.c_int(), ctypes.c_int()
+    assert sa.load().slim_attn_decode_int8_plan(B, Hq, Hkv, T, D, 1, ctypes.byref(w), ctypes.byref(n)) == 0
+    assert (w.value, n.value) == plan, "plan %s, the test is of %s" % ((w.value, n.value), plan)
 
 
 def check_close(got: np.ndarray, want: np.ndarray, what=""):

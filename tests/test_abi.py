@@ -259,6 +259,30 @@ def test_prefill_form_of_a_call(lib):
                     assert f(B, H, H, S, D, 1, kv, od) in (128, 256), (B, H, S, D, kv, od)
 
 
+def test_decode_plan_of_a_call(lib):
+    w, n = ctypes.c_int(), ctypes.c_int()
+    f = lib.slim_attn_decode_int8_plan
+    assert f(1, 4, 2, 100, 128, 0, None, ctypes.byref(n)) == 1 and f(1, 4, 3, 100, 128, 0, ctypes.byref(w), ctypes.byref(n)) == 2
+    assert f(1, 4, 2, 100, 96, 0, ctypes.byref(w), ctypes.byref(n)) == 3 and f(1, 4, 2, 100, 128, 2, ctypes.byref(w), ctypes.byref(n)) == 2
+
+    def plan(*shape, ragged=1):
+        assert f(*shape, ragged, ctypes.byref(w), ctypes.byref(n)) == 0
+        assert n.value * shape[0] * shape[1] * (shape[4] + 2) * 4 <= lib.slim_attn_decode_int8_workspace_bytes(*shape)
+        return w.value, n.value
+
+    # grouped heads, 128 codes a token: a batch that fills the chip keeps workgroups of four waves, of which three fit a
+    # compute unit, for lengths of their own too (the allocated length says nothing about how long the contexts are)
+    for shape, splits in (((48, 32, 8, 3001, 128), 1), ((100, 32, 8, 4000, 128), 1), ((32, 32, 8, 3000, 128), 1),
+                          ((16, 64, 8, 8192, 128), 2)):
+        assert plan(*shape) == plan(*shape, ragged=0) == (4, splits), shape
+    for shape, splits in (((16, 32, 8, 32768, 128), 6), ((32, 32, 8, 8192, 128), 2), ((32, 32, 8, 32768, 128), 3), ((100, 16, 2, 6000, 64), 2)):   # cut finer than equal lengths
+        assert plan(*shape) == (4, splits), shape
+    # 64 codes a token: eight waves up to one workgroup a compute unit
+    assert plan(32, 32, 8, 3000, 64) == (8, 1) and plan(33, 32, 8, 300, 64) == (4, 1) and plan(32, 32, 8, 3000, 64, ragged=0) == (4, 1)
+    # fewer workgroups than compute units, and more than sixteen heads a KV head: always eight
+    assert plan(20, 16, 4, 700, 128)[0] == plan(64, 40, 2, 3000, 128)[0] == 8
+
+
 def test_prefill_emit_rejects_bad_arguments(lib):
     f = lib.slim_attn_prefill_emit_int8
 

@@ -23,7 +23,7 @@ def sa():
     return slimattn
 
 
-from _gpu_util import dev, dev_bf16, host_f64, check_close, assert_form  # noqa: E402
+from _gpu_util import dev, dev_bf16, host_f64, check_close, assert_form, assert_plan  # noqa: E402
 
 
 # ---------------------------------------------------------------- quantiser
@@ -688,10 +688,12 @@ def test_decode_of_one_long_sequence_among_short_ones(sa, oracle, B, Hq, Hkv, T,
     check_close(host_f64(out2), want, "one long sequence, %d splits" % fewer)
 
 
-@pytest.mark.parametrize("B,Hq,Hkv,T,D", [
-    # 256 rows: one workgroup a compute unit; 272 rows: more, and splits on both sides of 2500 tokens; 64 codes a token
-    (32, 32, 8, 300, 128), (34, 16, 8, 2499, 128), (34, 16, 8, 2500, 128), (34, 16, 8, 2500, 64), (128, 4, 2, 300, 64)])
-def test_grouped_decode_waves_with_lengths_of_their_own(sa, oracle, B, Hq, Hkv, T, D):
+@pytest.mark.parametrize("B,Hq,Hkv,T,D,plan", [
+    # 256 rows, 64 codes a token: eight waves; one sequence more, and 128 codes: four; four waves and several splits
+    (32, 32, 8, 300, 64, (8, 1)), (128, 4, 2, 300, 64, (8, 1)), (33, 32, 8, 300, 64, (4, 1)), (32, 32, 8, 300, 128, (4, 1)),
+    (34, 16, 8, 2500, 128, (4, 10)), (34, 16, 8, 2500, 64, (4, 10)), (100, 16, 2, 4100, 64, (4, 2))])
+def test_grouped_decode_waves_with_lengths_of_their_own(sa, oracle, B, Hq, Hkv, T, D, plan):
+    assert_plan(sa, plan, B, Hq, Hkv, T, D)
     # four or eight waves share a row's tiles of 32 tokens: fewer tiles than waves, as many, one more, a last tile of one token
     print("grouped decode, lengths", B, Hq, Hkv, T, D, flush=True)
     rng = np.random.default_rng(3 * T + B + D)
