@@ -124,10 +124,17 @@ using int_c = std::integral_constant<int, N>;
 // WIDE: row blocks of 256 rows.  A staged tile meets twice the query rows (half the widening, or
 // half the ring's requests, per MFMA), and there is nothing to merge at the end.  See choose_rows for when it is taken and
 // what it gives.
-
-template <int D, bool KV_I8, bool OUT_F32, int MODE = 0, bool WIDE = false>
+//
+// OWN (WIDE, bf16 K/V): for the last key tile of a row and the OWN (1 or 3) after the first the running maximum goes up to a whole number above the tile's own, so that the probability of the tile's largest key is a power of two, which
+// rounding to bf16 leaves alone.  In blocks of 128 rows two maxima run, in those of 32 four, and a row's largest probability
+// is exact under each; under the one of plain 256 rows it is exact once, and their results are 1 to 8 % further from the
+// 64-bit ones (N(0,1), causal, D = 64, S=777, fp32 results, 2-norm of the error: 32 rows 1.166e-3, 128 1.217e-3, 256
+// 1.267e-3, with one such tile 1.209e-3, with three 1.157e-3).  One such tile costs 0 to 3 % of a call, three 4 to 7 (B=16, 32 on 8
+// heads, that shape: 91, 93 and 96 us; 128 rows 117).
+template <int D, bool KV_I8, bool OUT_F32, int MODE = 0, bool WIDE = false, int OWN = 0>
 __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const PrefillParams p) {
     static_assert(!(MODE != 0 && (KV_I8 || WIDE)), "the two-sweep variant exists for bf16 K/V and 128 rows only");
+    static_assert(OWN == 0 || (WIDE && !KV_I8), "see above");
     constexpr int BR = WIDE ? 2 * kBR : kBR;   // query rows per row block
     constexpr int NG = WIDE ? 1 : 2;           // key tiles of an iteration: wave groups that own the same rows
     constexpr bool stats_only = MODE == 1;
@@ -494,11 +501,13 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
 #pragma unroll
                 for (int i = 0; i < 4; ++i) pn[u][i] = pack_bf16x2(a[8 * u + 2 * i], a[8 * u + 2 * i + 1]);
         };
+        // OWN: the least running max not below M that lies a whole number above a tile's (that has no finite score: M)
+        auto own_max = [&](float m_tile) { return fmaxf(M, m_tile + ceilf(fminf(fmaxf(M - m_tile, 0.0f), 1e30f))); };
         // The softmax of tile t with the maximum taken exactly (scores in st, register r of this lane is key 32 t + 8 (r/4)
         // + 4 hh + r%4; sc_off: the tile's scales): moves the running max, rescales what there is, leaves the probabilities
         // in pn.  Keys of this lane past offset rel are masked.  (No contraction: a product that is masked cannot be one, and a
-        // tile's result must not depend on whether the compiler knows that none is.)
-        auto exact_softmax = [&](int sc_off, int rel, bool first, const f32x16& st, u32x4 (&pn)[2]) {
+        // tile's result must not depend on whether the compiler knows that none is.)  own: the new max is own_max.
+        auto exact_softmax = [&](int sc_off, int rel, bool first, bool own, const f32x16& st, u32x4 (&pn)[2]) {
 #pragma clang fp contract(off)
             float a[16];
 #pragma unroll
@@ -511,7 +520,7 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
             float umax = fmaxf(a[0], a[1]);
 #pragma unroll
             for (int r = 2; r < 16; r += 2) umax = fmaxf(umax, fmaxf(a[r], a[r + 1]));
-            const float m_new = fmaxf(M, half_max(umax));
+            const float m_new = own ? own_max(half_max(umax)) : fmaxf(M, half_max(umax));
             const float alpha = fast_exp2(M - m_new);
             // (the accumulator is still zero on a wave's first tile, and on the diagonal tile the maximum has
             // usually been met already: the 16 DT multiplications are skipped when they would change nothing)
@@ -557,7 +566,7 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
                     return ps;
                 }
             }
-            return exact_softmax(sc_off, rel, first, st, pn);
+            return exact_softmax(sc_off, rel, first, OWN > 0, st, pn);
         };
         auto max_only = [&](int rel, const f32x16& st) {   // MODE 1: the tile's scores only raise the row maximum
             float umax = kMasked;
@@ -604,6 +613,7 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
             __builtin_amdgcn_sched_barrier(0);
         };
 
+        float own_alpha = 1.0f;               // OWN: what the next tile's maximum scales the accumulator by
         f32x4 kfs = {c, c, c, c}, kfs_next;   // INT8: k_scales of the four keys at work, and of the next four
         float vfs = 0.0f;                     // INT8: the tile's v_scales, lane n of each 16 the one of this lane's register n
         // Iteration i of a wave that has a tile after this one: the scores of tile i+1 into sn, the probabilities of tile i
@@ -687,8 +697,30 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
                 float ps = ps0 + ps1;
                 // Lazy running max: the exponentials were taken against the max as it stands, and it moves only when the sum of
                 // a lane's 16 probabilities exceeds 2^8, so the accumulator is rescaled a few times per row block.
-                if (__builtin_amdgcn_ballot_w64(ps > 256.0f) != 0) ps = exact_softmax(SC, kBC, i == 0, st, pn);
+                if (__builtin_amdgcn_ballot_w64(ps > 256.0f) != 0) ps = exact_softmax(SC, kBC, i == 0, false, st, pn);
                 lsum += ps;
+                // OWN: the next tile's maximum is set here, before its exponentials (its scores are there, and it is not the
+                // last one); what there is follows: the sum now, the accumulator an iteration later, when it has this tile.
+                if constexpr (P4 >= 1 && P4 <= OWN) {
+                    if (i == P4) {
+#pragma unroll
+                        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                            for (int r = 0; r < 16; ++r) o[dt][r] *= own_alpha;
+                    }
+                }
+                if constexpr (P4 < OWN) {
+                    own_alpha = 1.0f;
+                    if (i == P4 && last > i + 1) {
+                        float umax = fmaxf(sn[0], sn[1]);
+#pragma unroll
+                        for (int r = 2; r < 16; r += 2) umax = fmaxf(umax, fmaxf(sn[r], sn[r + 1]));
+                        const float m_new = own_max(half_max(umax) * c);
+                        own_alpha = fast_exp2(M - m_new);
+                        lsum *= own_alpha;
+                        M = m_new;
+                    }
+                }
             }
             end_iteration(BARRIERS == 1 || P4 % 2 == 1);
         };
@@ -969,10 +1001,10 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
     }
 }
 
-template <int D, bool KV_I8, bool OUT_F32, int MODE = 0, bool WIDE = false>
+template <int D, bool KV_I8, bool OUT_F32, int MODE = 0, bool WIDE = false, int OWN = 0>
 static hipError_t launch_one(const PrefillParams& p, hipStream_t stream) {
     const unsigned grid = (unsigned)(8 * p.slots);
-    hipLaunchKernelGGL((slim_prefill_kernel<D, KV_I8, OUT_F32, MODE, WIDE>), dim3(grid), dim3(kPrefillThreads), 0,
+    hipLaunchKernelGGL((slim_prefill_kernel<D, KV_I8, OUT_F32, MODE, WIDE, OWN>), dim3(grid), dim3(kPrefillThreads), 0,
                        stream, p);
     return hipGetLastError();
 }
@@ -1042,18 +1074,22 @@ static void set_blocks(PrefillParams& p, const PrefillArgs& a, int rows, int per
 //   - bf16 calls that keep the 128-row form whatever the model says (256 rows would be up to a fifth faster on some of
 //     them): D = 64, sequences of fewer than 500 rows, or not causal with no more blocks of 256 than compute units; D = 128,
 //     not causal, fewer than 200 rows.  These are the shapes by which that form's tests reach it.
+//   - bf16 blocks of 256 rows are as near the 64-bit result as those in whose place they are (OWN): as 128 rows, or, where
+//     32 would take up to two fifths longer, as these.  All but those of 128 values and bf16 results that a coarser line (kPlain)
+//     gives 256 rows: these had them before, and their results stay what they are.
 struct FormCosts {   // microseconds
     double tile128, item128, tile256, item256;       // a key tile (of 256 rows: half of one) and an item of the list forms
     double fp32_128, fp32_256;                       // what fp32 results add to an item
     double lists;                                    // what a launch of theirs takes besides
     double first32, chain32, base32, tile32, block32;   // 32 rows: the longest block, and all tiles and blocks over 256 compute units
 };
-static int choose_rows(PrefillParams& p, const PrefillArgs& a) {
+static int choose_rows(PrefillParams& p, const PrefillArgs& a, int& own) {
     static constexpr FormCosts kCosts[4] = {
         {0.275, 4.16, 0.284, 2.24, 0.24, 1.90, 0.555, 2.13, 0.0662, 1.02, 0.102, 0.933},   // D = 64, bf16
         {0.397, 5.24, 0.356, 3.22, 0.0, 0.0, 2.53, 3.05, 0.109, 1.31, 0.153, 0.790},       // D = 64, INT8
         {0.365, 4.17, 0.291, 5.33, 0.125, 0.909, 1.08, 3.07, 0.367, 2.29, 0.187, 1.72},    // D = 128, bf16
         {0.567, 6.29, 0.461, 3.87, 0.739, 1.90, 2.00, 4.65, 0.273, 4.35, 0.295, 1.41}};    // D = 128, INT8
+    static constexpr FormCosts kPlain{0.31, 4.2, 0.30, 5.5};   // (the list forms' only)
     const bool d128 = a.head_dim == 128;
     const FormCosts& c = kCosts[(d128 ? 2 : 0) + (a.kv_int8 ? 1 : 0)];
     p.n_bh = a.batch * a.q_heads;
@@ -1070,14 +1106,18 @@ static int choose_rows(PrefillParams& p, const PrefillArgs& a) {
     set_blocks(p, a, 2 * kBR);
     const bool wide = a.kv_int8 || (d128 ? p.causal || a.seq_len >= 200
                                          : a.seq_len >= 500 && (p.causal || (long)p.n_rb * p.n_bh > 256));
+    const double plain_256 = modelled_us(p, kPlain.tile256, kPlain.item256, 2 * kBR, 2);
     const double us_wide = modelled_us(p, c.tile256, item256, 2 * kBR, 2);
     set_blocks(p, a, kBR);
     double us = modelled_us(p, c.tile128, item128, kBR, 1);
+    const bool plain = d128 && !a.kv_int8 && !a.out_f32 && plain_256 < modelled_us(p, kPlain.tile128, kPlain.item128, kBR, 1);
+    own = 0;
     int rows = kBR;
     if (wide && us_wide < us) {
         us = us_wide;
         rows = 2 * kBR;
         set_blocks(p, a, 2 * kBR);
+        if (!a.kv_int8) own = us32 < 1.4 * (us + c.lists) ? 3 : plain ? 0 : 1;
     }
     return us32 < us + c.lists ? 32 : rows;
 }
@@ -1086,7 +1126,8 @@ int prefill_block_rows(const PrefillArgs& a) {
     PrefillParams p;
     p.S = a.seq_len;
     p.causal = a.causal ? 1 : 0;
-    return choose_rows(p, a);
+    int own;
+    return choose_rows(p, a, own);
 }
 
 hipError_t launch_prefill(const PrefillArgs& a, hipStream_t stream) {
@@ -1117,7 +1158,8 @@ hipError_t launch_prefill(const PrefillArgs& a, hipStream_t stream) {
         return a.out_f32 ? launch_one<64, false, true, 2>(p, stream) : launch_one<64, false, false, 2>(p, stream);
     }
     const bool d128 = a.head_dim == 128;
-    const int rows = choose_rows(p, a);
+    int own = 0;
+    const int rows = choose_rows(p, a, own);
     if (rows == 32) {
         // (eight waves where a compute unit has hardly more than one workgroup and a row block many tiles)
         const int blocks32 = (a.seq_len + 31) / 32;
@@ -1127,12 +1169,14 @@ hipError_t launch_prefill(const PrefillArgs& a, hipStream_t stream) {
     const int sel = (d128 ? 4 : 0) | (a.kv_int8 ? 2 : 0) | (a.out_f32 ? 1 : 0);
     if (rows == 2 * kBR) {
         switch (sel) {
-            case 0: return launch_one<64, false, false, 0, true>(p, stream);
-            case 1: return launch_one<64, false, true, 0, true>(p, stream);
+            case 0: return own == 3 ? launch_one<64, false, false, 0, true, 3>(p, stream) : launch_one<64, false, false, 0, true, 1>(p, stream);
+            case 1: return own == 3 ? launch_one<64, false, true, 0, true, 3>(p, stream) : launch_one<64, false, true, 0, true, 1>(p, stream);
             case 2: return launch_one<64, true, false, 0, true>(p, stream);
             case 3: return launch_one<64, true, true, 0, true>(p, stream);
-            case 4: return launch_one<128, false, false, 0, true>(p, stream);
-            case 5: return launch_one<128, false, true, 0, true>(p, stream);
+            case 4:
+                return own == 0 ? launch_one<128, false, false, 0, true>(p, stream)
+                     : own == 1 ? launch_one<128, false, false, 0, true, 1>(p, stream) : launch_one<128, false, false, 0, true, 3>(p, stream);
+            case 5: return own == 3 ? launch_one<128, false, true, 0, true, 3>(p, stream) : launch_one<128, false, true, 0, true, 1>(p, stream);
             case 6: return launch_one<128, true, false, 0, true>(p, stream);
             default: return launch_one<128, true, true, 0, true>(p, stream);
         }

@@ -1314,6 +1314,43 @@ def test_prefill_last_unmasked_tile_keeps_the_running_maximum(sa, B, Hq, Hkv, S,
     assert np.abs(got - want)[:, :, checked].max() <= min(bound, 1e-4)
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,S,D,out_f32,tiles", [
+    # (a call that 32 rows would not be much slower for: three tiles)
+    (16, 32, 8, 512, 64, False, 1), (4, 32, 8, 777, 64, False, 1), (4, 40, 8, 777, 128, True, 1), (16, 16, 8, 333, 128, False, 1),
+    (8, 16, 4, 513, 64, True, 3), (4, 32, 8, 512, 64, False, 3), (6, 24, 8, 242, 128, True, 3), (4, 32, 8, 333, 128, False, 3)])
+def test_prefill_wide_row_blocks_maxima_of_single_tiles(sa, B, Hq, Hkv, S, D, out_f32, tiles):
+    # Row blocks of 256 rows that bf16 calls take in the place of 128 or 32: the largest probability of the last key tile of a
+    # row, and of the first or the first three after its first, must be a power of two, as it is under the further maxima of
+    # the other forms.  For each such tile t: only it and the last one, t + 2, have V, and log2 of the scores is whole
+    # there, so that all probabilities that count are bf16 values; one key in the tile before each sets the running maximum
+    # to 3.75 and 14.375, against which they would be off by 1.4e-3.
+    print("prefill wide, maxima", B, Hq, Hkv, S, D, out_f32, tiles, flush=True)
+    assert_form(sa, 256, B, Hq, Hkv, S, D, True, False, out_f32)
+    rng = np.random.default_rng(S + D)
+    bits = lambda x: f32_to_bf16_bits(np.ascontiguousarray(x, dtype=np.float32))  # noqa: E731
+    for t in range(1, tiles + 1):
+        score = rng.integers(0, 4, S).astype(np.float64)
+        this, last = slice(32 * t, 32 * t + 32), slice(32 * t + 64, 32 * t + 96)
+        score[this.start], score[last.start] = 3, 3              # (every checked row sees these maxima)
+        score[this.start - 27], score[last.start - 32] = 3.75, 14.375
+        v = np.zeros((B, Hkv, S, D))
+        v[:, :, this], v[:, :, last] = rng.integers(1, 4, (B, Hkv, 32, D)), rng.integers(1, 4, (B, Hkv, 32, D))
+        q, k = np.zeros((B, Hq, S, D)), np.zeros((B, Hkv, S, D))
+        q[..., 5], k[..., 5] = 1.0, score
+        got = host_f64(sa.slim_attn_prefill(dev_bf16(bits(q)), dev_bf16(bits(k)), dev_bf16(bits(v)), math.log(2.0), True,
+                                            out_dtype=torch.float32 if out_f32 else torch.bfloat16))[:, :, last]
+        p = 2.0 ** score
+        want = np.repeat(np.cumsum(p[:, None] * v, axis=2) / np.cumsum(p)[:, None], Hq // Hkv, axis=1)[:, :, last]
+        rel = np.abs(got - want) / want
+        # (2^-24 for each of at most 192 additions to numerator and denominator, all positive, and as much again for the
+        # exponentials; a bf16 result is the nearest one, but for those that lie that close to the middle of two)
+        if out_f32:
+            assert rel.max() <= 4 * 192 * 2.0 ** -24, t
+        else:
+            wrong = host_f64(dev_bf16(bits(want))) != got
+            assert rel.max() <= 2.0 ** -8 and wrong.mean() <= 4 * 192 * 2.0 ** -24 * 2.0 ** 9, t
+
+
 @pytest.mark.parametrize("Hq,Hkv", [(4, 4), (8, 2)])
 def test_sharp_softmax_decode_stays_within_the_rounding_bound(sa, oracle, Hq, Hkv):
     # the same bound for the decode kernels (per-head: P * v_scale stays in fp32, only the bf16 output rounds;
