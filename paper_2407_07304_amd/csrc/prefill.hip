@@ -125,12 +125,13 @@ using int_c = std::integral_constant<int, N>;
 // half the ring's requests, per MFMA), and there is nothing to merge at the end.  See choose_rows for when it is taken and
 // what it gives.
 //
-// OWN (WIDE, bf16 K/V): for the last key tile of a row and the OWN (1 or 3) after the first the running maximum goes up to a whole number above the tile's own, so that the probability of the tile's largest key is a power of two, which
-// rounding to bf16 leaves alone.  In blocks of 128 rows two maxima run, in those of 32 four, and a row's largest probability
-// is exact under each; under the one of plain 256 rows it is exact once, and their results are 1 to 8 % further from the
-// 64-bit ones (N(0,1), causal, D = 64, S=777, fp32 results, 2-norm of the error: 32 rows 1.166e-3, 128 1.217e-3, 256
-// 1.267e-3, with one such tile 1.209e-3, with three 1.157e-3).  One such tile costs 0 to 3 % of a call, three 4 to 7 (B=16, 32 on 8
-// heads, that shape: 91, 93 and 96 us; 128 rows 117).
+// OWN (WIDE, bf16 K/V): for the last key tile of a row and the OWN (1 or 3) after the first the running maximum goes up to a
+// whole number above the tile's own, so that the probability of the tile's largest key is a power of two, which rounding to
+// bf16 leaves alone.  In blocks of 128 rows two maxima run, in those of 32 four, and a row's largest probability is exact
+// under each; under the one of plain 256 rows it is exact once, and their results are 1 to 8 % further from the 64-bit ones
+// (N(0,1), causal, D = 64, S=777, fp32 results, 2-norm of the error: 32 rows 1.166e-3, 128 1.217e-3, 256 1.267e-3, with one
+// such tile 1.209e-3, with three 1.157e-3).  One such tile costs 0 to 3 % of a call, three 4 to 7 (B=16, 32 on 8 heads, that
+// shape: 91, 93 and 96 us; 128 rows 117).
 template <int D, bool KV_I8, bool OUT_F32, int MODE = 0, bool WIDE = false, int OWN = 0>
 __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const PrefillParams p) {
     static_assert(!(MODE != 0 && (KV_I8 || WIDE)), "the two-sweep variant exists for bf16 K/V and 128 rows only");
@@ -1074,9 +1075,9 @@ static void set_blocks(PrefillParams& p, const PrefillArgs& a, int rows, int per
 //   - bf16 calls that keep the 128-row form whatever the model says (256 rows would be up to a fifth faster on some of
 //     them): D = 64, sequences of fewer than 500 rows, or not causal with no more blocks of 256 than compute units; D = 128,
 //     not causal, fewer than 200 rows.  These are the shapes by which that form's tests reach it.
-//   - bf16 blocks of 256 rows are as near the 64-bit result as those in whose place they are (OWN): as 128 rows, or, where
-//     32 would take up to two fifths longer, as these.  All but those of 128 values and bf16 results that a coarser line (kPlain)
-//     gives 256 rows: these had them before, and their results stay what they are.
+//   - bf16 blocks of 256 rows are as near the 64-bit result as those in whose place they are (OWN, in `own`).  That is said by
+//     coarser lines (kCoarse; 8 head counts, 4 to 512, by 12 lengths, 50 to 4096), which have 256 rows for 128 values and bf16
+//     results only: as near as 32 rows, or as 128, by one more exact maximum a row than these have; or plain ones.
 struct FormCosts {   // microseconds
     double tile128, item128, tile256, item256;       // a key tile (of 256 rows: half of one) and an item of the list forms
     double fp32_128, fp32_256;                       // what fp32 results add to an item
@@ -1089,35 +1090,39 @@ static int choose_rows(PrefillParams& p, const PrefillArgs& a, int& own) {
         {0.397, 5.24, 0.356, 3.22, 0.0, 0.0, 2.53, 3.05, 0.109, 1.31, 0.153, 0.790},       // D = 64, INT8
         {0.365, 4.17, 0.291, 5.33, 0.125, 0.909, 1.08, 3.07, 0.367, 2.29, 0.187, 1.72},    // D = 128, bf16
         {0.567, 6.29, 0.461, 3.87, 0.739, 1.90, 2.00, 4.65, 0.273, 4.35, 0.295, 1.41}};    // D = 128, INT8
-    static constexpr FormCosts kPlain{0.31, 4.2, 0.30, 5.5};   // (the list forms' only)
+    static constexpr FormCosts kCoarse[2] = {{0.31, 5.0, 0.0, 0.0, 0.0, 0.0, 2.0, 3.3, 0.11, 1.2, 0.115, 1.2},    // bf16, D = 64
+                                             {0.31, 4.2, 0.30, 5.5, 0.0, 0.0, 1.5, 3.4, 0.18, 1.5, 0.18, 2.0}};   // and 128
     const bool d128 = a.head_dim == 128;
     const FormCosts& c = kCosts[(d128 ? 2 : 0) + (a.kv_int8 ? 1 : 0)];
     p.n_bh = a.batch * a.q_heads;
     const double blocks32 = (a.seq_len + 31) / 32, tiles = blocks32 * p.n_bh * (p.causal ? (blocks32 + 1) / 2 : blocks32);
-    const double us_longest = c.first32 + c.chain32 * blocks32;
     const double kv_bytes = 4.0 * a.batch * a.kv_heads * a.seq_len * a.head_dim;
     const double us_again = !a.kv_int8 && kv_bytes > 40e6 ? kv_bytes * (p.causal ? (blocks32 + 1) / 2 : blocks32) / 10e6 : 0.0;
-    const double us_all = c.base32 + (c.tile32 * tiles + c.block32 * blocks32 * p.n_bh) / 256 + us_again;
     const bool launchable = blocks32 * p.n_bh * 256 < 0x1p32;
-    const double us32 = launchable ? (us_longest > us_all ? us_longest : us_all) : 1e30;
+    auto small_us = [&](const FormCosts& f) {
+        const double longest = f.first32 + f.chain32 * blocks32;
+        const double all = f.base32 + (f.tile32 * tiles + f.block32 * blocks32 * p.n_bh) / 256 + us_again;
+        return launchable ? std::max(longest, all) : 1e30;
+    };
+    const double us32 = small_us(c);
     // (small calls are bound by what the host does for them: no lists where their longest item alone takes longer)
     const double item128 = c.item128 + (a.out_f32 ? c.fp32_128 : 0.0), item256 = c.item256 + (a.out_f32 ? c.fp32_256 : 0.0);
     if (us32 < c.lists + std::min(blocks32 * c.tile128 + item128, 2.0 * blocks32 * c.tile256 + item256)) return 32;
+    const FormCosts& g = kCoarse[d128];
     set_blocks(p, a, 2 * kBR);
     const bool wide = a.kv_int8 || (d128 ? p.causal || a.seq_len >= 200
                                          : a.seq_len >= 500 && (p.causal || (long)p.n_rb * p.n_bh > 256));
-    const double plain_256 = modelled_us(p, kPlain.tile256, kPlain.item256, 2 * kBR, 2);
     const double us_wide = modelled_us(p, c.tile256, item256, 2 * kBR, 2);
+    const double coarse256 = d128 && !a.out_f32 ? modelled_us(p, g.tile256, g.item256, 2 * kBR, 2) : 1e30;
     set_blocks(p, a, kBR);
     double us = modelled_us(p, c.tile128, item128, kBR, 1);
-    const bool plain = d128 && !a.kv_int8 && !a.out_f32 && plain_256 < modelled_us(p, kPlain.tile128, kPlain.item128, kBR, 1);
-    own = 0;
+    const double coarse128 = modelled_us(p, g.tile128, g.item128, kBR, 1);
+    own = a.kv_int8 ? 0 : small_us(g) < std::min(coarse128, coarse256) + g.lists ? 3 : coarse256 < coarse128 ? 0 : 1;
     int rows = kBR;
     if (wide && us_wide < us) {
         us = us_wide;
         rows = 2 * kBR;
         set_blocks(p, a, 2 * kBR);
-        if (!a.kv_int8) own = us32 < 1.4 * (us + c.lists) ? 3 : plain ? 0 : 1;
     }
     return us32 < us + c.lists ? 32 : rows;
 }

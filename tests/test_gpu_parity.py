@@ -1315,9 +1315,9 @@ def test_prefill_last_unmasked_tile_keeps_the_running_maximum(sa, B, Hq, Hkv, S,
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,S,D,out_f32,tiles", [
-    # (a call that 32 rows would not be much slower for: three tiles)
-    (16, 32, 8, 512, 64, False, 1), (4, 32, 8, 777, 64, False, 1), (4, 40, 8, 777, 128, True, 1), (16, 16, 8, 333, 128, False, 1),
-    (8, 16, 4, 513, 64, True, 3), (4, 32, 8, 512, 64, False, 3), (6, 24, 8, 242, 128, True, 3), (4, 32, 8, 333, 128, False, 3)])
+    # in the place of 128 rows, and of 32
+    (16, 32, 8, 512, 64, False, 1), (16, 32, 8, 777, 64, True, 1), (4, 40, 8, 777, 128, True, 1), (16, 16, 8, 333, 128, False, 1),
+    (8, 16, 4, 513, 64, True, 3), (3, 32, 8, 529, 64, False, 3), (6, 32, 32, 282, 128, True, 3), (9, 8, 8, 426, 128, False, 3)])
 def test_prefill_wide_row_blocks_maxima_of_single_tiles(sa, B, Hq, Hkv, S, D, out_f32, tiles):
     # Row blocks of 256 rows that bf16 calls take in the place of 128 or 32: the largest probability of the last key tile of a
     # row, and of the first or the first three after its first, must be a power of two, as it is under the further maxima of
