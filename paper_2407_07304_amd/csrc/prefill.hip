@@ -1074,7 +1074,9 @@ static void set_blocks(PrefillParams& p, const PrefillArgs& a, int rows, int per
 //     block and head, and a launch less than 2^32 threads: more of them than that stay with the lists.
 //   - bf16 calls that keep the 128-row form whatever the model says (256 rows would be up to a fifth faster on some of
 //     them): D = 64, sequences of fewer than 500 rows, or not causal with no more blocks of 256 than compute units; D = 128,
-//     not causal, fewer than 200 rows.  These are the shapes by which that form's tests reach it.
+//     not causal, fewer than 200 rows, but for those that the coarser lines below give 256 (8 sequences, 24 on 8 heads,
+//     S=134: 10.3 us, at 32 rows 13.6; as near the 64-bit result as these).  These are the shapes by which that form's
+//     tests reach it.
 //   - bf16 blocks of 256 rows are as near the 64-bit result as those in whose place they are (OWN, in `own`).  That is said by
 //     coarser lines (kCoarse; 8 head counts, 4 to 512, by 12 lengths, 50 to 4096), which have 256 rows for 128 values and bf16
 //     results only: as near as 32 rows, or as 128, by one more exact maximum a row than these have; or plain ones.
@@ -1108,16 +1110,18 @@ static int choose_rows(PrefillParams& p, const PrefillArgs& a, int& own) {
     // (small calls are bound by what the host does for them: no lists where their longest item alone takes longer)
     const double item128 = c.item128 + (a.out_f32 ? c.fp32_128 : 0.0), item256 = c.item256 + (a.out_f32 ? c.fp32_256 : 0.0);
     if (us32 < c.lists + std::min(blocks32 * c.tile128 + item128, 2.0 * blocks32 * c.tile256 + item256)) return 32;
-    const FormCosts& g = kCoarse[d128];
     set_blocks(p, a, 2 * kBR);
-    const bool wide = a.kv_int8 || (d128 ? p.causal || a.seq_len >= 200
-                                         : a.seq_len >= 500 && (p.causal || (long)p.n_rb * p.n_bh > 256));
     const double us_wide = modelled_us(p, c.tile256, item256, 2 * kBR, 2);
+    const FormCosts& g = kCoarse[d128];
     const double coarse256 = d128 && !a.out_f32 ? modelled_us(p, g.tile256, g.item256, 2 * kBR, 2) : 1e30;
+    const bool many = (long)p.n_rb * p.n_bh > 256;
     set_blocks(p, a, kBR);
     double us = modelled_us(p, c.tile128, item128, kBR, 1);
     const double coarse128 = modelled_us(p, g.tile128, g.item128, kBR, 1);
-    own = a.kv_int8 ? 0 : small_us(g) < std::min(coarse128, coarse256) + g.lists ? 3 : coarse256 < coarse128 ? 0 : 1;
+    const int coarse = small_us(g) < std::min(coarse128, coarse256) + g.lists ? 32 : coarse256 < coarse128 ? 2 * kBR : kBR;
+    const bool tested128 = d128 ? !p.causal && a.seq_len < 200 : a.seq_len < 500 || !(p.causal || many);
+    const bool wide = a.kv_int8 || coarse == 2 * kBR || !tested128;
+    own = a.kv_int8 ? 0 : coarse == 32 || (coarse == 2 * kBR && tested128) ? 3 : coarse == kBR ? 1 : 0;
     int rows = kBR;
     if (wide && us_wide < us) {
         us = us_wide;

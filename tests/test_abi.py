@@ -245,6 +245,9 @@ def test_prefill_form_of_a_call(lib):
     # bf16 K and V of many heads are more than the L2s hold: the form that reads them once per 32 rows is not taken
     for B, H in ((40, 32), (40, 40), (64, 32)):
         assert f(B, H, H, 300, 64, 0, 0, 0) == 128
+    # short sequences, not causal, bf16 results of 128 values: 256 rows, where 32 take a sixth to a third longer
+    for shape in ((8, 24, 8, 134), (4, 40, 8, 152), (44, 4, 4, 155), (6, 32, 8, 199)):
+        assert f(*shape, 128, 0, 0, 0) == 256, shape
     # long INT8 sequences of few heads, which that form would widen once per 32 rows
     for Hkv in (8, 2):
         assert f(1, 8, Hkv, 5000, 128, 1, 2, 0) == f(1, 8, Hkv, 5000, 128, 1, 2, 1) == 128

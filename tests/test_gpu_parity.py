@@ -1067,7 +1067,7 @@ def test_prefill_item_lists(sa, oracle, B, Hq, Hkv, S, D, form, causal):
     # bf16 K/V in blocks of 256 rows: one block that ends inside, one row less and none, one row past it; row groups and
     # key tiles that end inside, several blocks, several items per workgroup
     (16, 32, 8, 129, True), (25, 16, 16, 255, False), (16, 32, 8, 256, True), (28, 16, 4, 257, True), (20, 16, 16, 480, False),
-    (40, 8, 8, 545, True), (4, 32, 8, 777, True), (4, 32, 32, 777, False), (26, 5, 5, 1025, True)])
+    (40, 8, 8, 545, True), (4, 32, 8, 777, True), (4, 32, 32, 777, False), (26, 5, 5, 1025, True), (8, 24, 8, 134, False)])
 def test_prefill_bf16_wide_row_blocks(sa, oracle, B, Hq, Hkv, S, causal):
     print("prefill bf16 wide", B, Hq, Hkv, S, causal, flush=True)
     rng = np.random.default_rng(5 * B + Hq + S)
