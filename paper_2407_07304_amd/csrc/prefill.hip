@@ -1072,6 +1072,9 @@ static void set_blocks(PrefillParams& p, const PrefillArgs& a, int rows, int per
 //     for every block, at 10 TB/s (33 MB are not yet worth it: 40 x 32 heads, S=100, D=64, 23.6 us in the caches and
 //     36.9 cold, 27.2 and 34.8 at 128 rows; 66 MB, S=200: 51.6 and 74.7, 55.9 and 67.0).  The form has a workgroup per row
 //     block and head, and a launch less than 2^32 threads: more of them than that stay with the lists.
+//   - bf16 calls of 128 values, not causal, that the coarser lines below give 32 rows do not go to 128: they would take 5 %
+//     longer (4 sequences, 32 on 8 heads, S=100 7.3 us at 32 rows, 7.7 at 128; 40 on 8, S=67, fp32 results 7.6 and 8.0) and be
+//     further from the 64-bit result.  (Causal ones go: S=92, 15 sequences, 12 heads 9.6 us at 32 rows, 7.7 at 128.)
 //   - bf16 calls that keep the 128-row form whatever the model says (256 rows would be up to a fifth faster on some of
 //     them): D = 64, sequences of fewer than 500 rows, or not causal with no more blocks of 256 than compute units; D = 128,
 //     not causal, fewer than 200 rows, but for those that the coarser lines below give 256 (8 sequences, 24 on 8 heads,
@@ -1128,7 +1131,8 @@ static int choose_rows(PrefillParams& p, const PrefillArgs& a, int& own) {
         rows = 2 * kBR;
         set_blocks(p, a, 2 * kBR);
     }
-    return us32 < us + c.lists ? 32 : rows;
+    const bool stays32 = rows == kBR && !a.kv_int8 && coarse == 32 && d128 && !p.causal;
+    return us32 < us + c.lists || stays32 ? 32 : rows;
 }
 
 int prefill_block_rows(const PrefillArgs& a) {

@@ -248,6 +248,8 @@ def test_prefill_form_of_a_call(lib):
     # short sequences, not causal, bf16 results of 128 values: 256 rows, where 32 take a sixth to a third longer
     for shape in ((8, 24, 8, 134), (4, 40, 8, 152), (44, 4, 4, 155), (6, 32, 8, 199)):
         assert f(*shape, 128, 0, 0, 0) == 256, shape
+    # few rows in all, not causal: 32, where 128 are slower
+    assert f(4, 32, 8, 100, 128, 0, 0, 0) == f(4, 40, 8, 67, 128, 0, 0, 1) == f(10, 16, 2, 93, 128, 0, 0, 1) == 32
     # long INT8 sequences of few heads, which that form would widen once per 32 rows
     for Hkv in (8, 2):
         assert f(1, 8, Hkv, 5000, 128, 1, 2, 0) == f(1, 8, Hkv, 5000, 128, 1, 2, 1) == 128
