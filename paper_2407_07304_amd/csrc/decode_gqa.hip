@@ -55,7 +55,10 @@ __device__ __forceinline__ bf16x8 widen8(const i32x2 cw) {
 // TRAFFIC_ONLY: the measurement form of the kernel (include/slimprobe.h): the same workgroups, waves, token runs and
 // loads, issued at the same points, but a tile's registers are only XORed together before they are refilled.  What it
 // takes is what the memory system charges for this access pattern on this shape, arithmetic aside.
-template <int D, int W, int NC, bool TRAFFIC_ONLY = false>
+// WHOLE: the running max is a whole number.  A row's largest probability is then some power of two above a half and not 1:
+// times its v_scale it rounds to bf16 like any other, where a v_scale alone is further off than the mean (0.375 of an ulp,
+// codes of N(0,1)), and more waves, each with a maximum of its own, have more such tokens.
+template <int D, int W, int NC, bool TRAFFIC_ONLY = false, bool WHOLE = false>
 __global__ __launch_bounds__(64 * W) void slim_decode_int8_gqa_kernel(
     const uint16_t* __restrict__ q, const int8_t* __restrict__ kc, const float* __restrict__ ks,
     const int8_t* __restrict__ vc, const float* __restrict__ vs, uint16_t* __restrict__ out, float* __restrict__ ws_acc,
@@ -236,6 +239,7 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_gqa_kernel(
                 float m_new = fmaxf(M[nc], umax);
                 m_new = fmaxf(m_new, __shfl_xor(m_new, 16));
                 m_new = fmaxf(m_new, __shfl_xor(m_new, 32));
+                if constexpr (WHOLE) m_new = ceilf(m_new);
                 const float alpha = fast_exp2(M[nc] - m_new);
 #pragma unroll
                 for (int dt = 0; dt < DT; ++dt) o[nc][dt] *= alpha;
@@ -355,9 +359,9 @@ hipError_t launch_decode_gqa_split(const DecodeArgs& a, float* ws_acc, float* ws
                                    bool traffic_only) {
     const float scale_log2e = a.softmax_scale * kLog2e;
     const dim3 grid((unsigned)plan.n_split, (unsigned)a.kv_heads, (unsigned)a.batch);
-    auto launch = [&](auto d_c, auto w_c, auto nc_c, auto traffic_c) {
+    auto launch = [&](auto d_c, auto w_c, auto nc_c, auto traffic_c, auto whole_c) {
         constexpr int D = decltype(d_c)::value, W = decltype(w_c)::value, NC = decltype(nc_c)::value;
-        hipLaunchKernelGGL((slim_decode_int8_gqa_kernel<D, W, NC, decltype(traffic_c)::value>), grid, dim3(64 * W), 0, stream,
+        hipLaunchKernelGGL((slim_decode_int8_gqa_kernel<D, W, NC, decltype(traffic_c)::value, decltype(whole_c)::value>), grid, dim3(64 * W), 0, stream,
                            (const uint16_t*)a.q, a.k_codes, a.k_scale, a.v_codes, a.v_scale, (uint16_t*)a.out, ws_acc, ws_ml,
                            a.kv_lens, a.q_heads / a.kv_heads, a.kv_heads, a.kv_len, plan.n_split, plan.split_rate, scale_log2e);
         return hipGetLastError();
@@ -367,9 +371,13 @@ hipError_t launch_decode_gqa_split(const DecodeArgs& a, float* ws_acc, float* ws
         constexpr integral_constant<int, 4> w4{};
         constexpr integral_constant<int, 8> w8{};
         constexpr integral_constant<int, 1> one{};
-        if (traffic_only) return plan.waves == 8 ? launch(d_c, w8, one, std::true_type{}) : launch(d_c, w4, one, std::true_type{});
-        if (a.q_heads / a.kv_heads > 16) return launch(d_c, w8, integral_constant<int, 2>{}, std::false_type{});
-        return plan.waves == 8 ? launch(d_c, w8, one, std::false_type{}) : launch(d_c, w4, one, std::false_type{});
+        constexpr std::false_type no{};
+        constexpr std::true_type yes{};
+        if (traffic_only) return plan.waves == 8 ? launch(d_c, w8, one, yes, no) : launch(d_c, w4, one, yes, no);
+        if (a.q_heads / a.kv_heads > 16) return launch(d_c, w8, integral_constant<int, 2>{}, no, no);
+        if constexpr (decltype(d_c)::value == 64)
+            if (plan.whole_max) return launch(d_c, w8, one, no, yes);
+        return plan.waves == 8 ? launch(d_c, w8, one, no, no) : launch(d_c, w4, one, no, no);
     };
     return a.head_dim == 128 ? pick(std::integral_constant<int, 128>{}) : pick(std::integral_constant<int, 64>{});
 }

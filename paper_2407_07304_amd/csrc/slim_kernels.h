@@ -54,10 +54,11 @@ struct DecodeArgs {
     bool ragged;          // use the plan for sequences of different lengths (the workspace has room for it)
 };
 // How a decode call is cut up: waves per workgroup, splits of the key axis (workgroups per row), and how many of them a
-// sequence uses (splits_of).
+// sequence uses (splits_of); whole_max: the grouped kernel's running maxima are whole numbers (eight waves, 64 codes).
 struct DecodePlan {
     int waves, n_split;
     unsigned split_rate;
+    bool whole_max = false;
 };
 // Grouped-query variant (2 to 32 query heads per KV head): a workgroup sweeps a run of tokens of one (batch, KV head)
 // for all its query heads and is a split.  n_bg = batch * kv_heads, group = query heads per KV head.

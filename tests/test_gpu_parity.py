@@ -714,6 +714,24 @@ def test_grouped_decode_waves_with_lengths_of_their_own(sa, oracle, B, Hq, Hkv, 
     assert err.mean() <= 1.27 * 2 * 2.0 ** -9
 
 
+def test_grouped_decode_eight_waves_round_like_any_other_token(sa):
+    # Lengths of their own, 64 codes a token, eight waves: sequences of one token, whose probability is that wave's largest.
+    # Were it exactly 1, every result would be off by what its v_scale is off a bf16 value, here half an ulp, upwards: 2^-8.
+    B, Hq, Hkv, T, D = 32, 32, 8, 300, 64
+    assert_plan(sa, (8, 1), B, Hq, Hkv, T, D)
+    rng = np.random.default_rng(77)
+    q = normal_bf16(rng, (B, Hq, 1, D))
+    kc = rng.integers(-127, 128, (B, Hkv, T, D), dtype=np.int8)
+    vc = rng.integers(64, 128, (B, Hkv, T, D)).astype(np.int8)
+    ks = rng.uniform(0.005, 0.02, (B, Hkv, T)).astype(np.float32)
+    vs = np.full((B, Hkv, T), np.float32(2.0 ** -6 * (1 + 1.0001 * 2.0 ** -8)))
+    out = host_f64(sa.slim_attn_decode_int8_varlen(dev_bf16(q), dev(kc), dev(ks), dev(vc), dev(vs), torch.ones(B, dtype=torch.int32, device="cuda"),
+                                                   1.0 / math.sqrt(D)))
+    off = (out / np.repeat(vc[:, :, :1].astype(np.float64) * float(vs[0, 0, 0]), Hq // Hkv, axis=1) - 1).mean()
+    # (1024 heads, each with a rounding of its own of at most 2^-8: five times the mean's standard deviation of a uniform one)
+    assert abs(off) <= 5 * 2.0 ** -8 / math.sqrt(3 * B * Hq), off
+
+
 @pytest.mark.parametrize("D,Hq,Hkv", [(128, 16, 2), (64, 6, 3)])
 def test_grouped_decode_of_extreme_queries(sa, oracle, D, Hq, Hkv):
     # rows around 2^60 and around 2^-50, with sequences that leave most splits empty, and a row with an infinity or a NaN, whose result is not a number while every other row's is
