@@ -440,30 +440,38 @@ def test_prefill_batched_gqa_full_tensor(sa, oracle):
     check_close(host_f64(out), oracle.attn(q, k, v, scale, True), "batched GQA prefill")
 
 
-@pytest.mark.parametrize("B,Hq,Hkv,S,kv_int8,form", [
-    (1, 8, 2, 640, False, 32), (1, 8, 2, 640, True, 32), (38, 8, 8, 257, False, 128), (9, 8, 2, 640, True, 128), (16, 32, 8, 256, False, 256),
-    (4, 32, 8, 777, False, 256), (16, 16, 8, 300, True, 256)])
-def test_prefill_many_launches_are_bit_identical(sa, oracle, B, Hq, Hkv, S, kv_int8, form):
+@pytest.mark.parametrize("B,Hq,Hkv,S,kv_int8,form,D,out_f32,causal", [
+    (1, 8, 2, 640, False, 32, 128, False, True), (1, 8, 2, 640, True, 32, 128, False, True), (38, 8, 8, 257, False, 128, 128, False, True),
+    (9, 8, 2, 640, True, 128, 128, False, True), (16, 32, 8, 256, False, 256, 128, False, True), (4, 32, 8, 777, False, 256, 128, False, True),
+    (16, 16, 8, 300, True, 256, 128, False, True),
+    # 64 values a row: requests of four loads a tensor, INT8 pieces that one store and the next iteration publish; more than
+    # two turns of the ring, several items a workgroup
+    (9, 8, 2, 777, False, 128, 64, False, True), (1, 40, 8, 1500, True, 128, 64, False, True), (4, 40, 8, 777, False, 256, 64, False, True),
+    (8, 16, 4, 513, False, 256, 64, True, True), (24, 16, 16, 545, True, 256, 64, False, True), (9, 24, 8, 511, False, 256, 64, True, False),
+    (8, 16, 16, 512, True, 256, 64, True, False),
+    # fp32 results of 128 values (the output in two parts), not causal, 128-row calls that take 256
+    (4, 40, 8, 777, False, 256, 128, True, True), (9, 24, 8, 480, False, 256, 128, False, False), (12, 24, 8, 480, False, 256, 128, True, False),
+    (16, 16, 8, 300, True, 256, 128, False, False), (38, 8, 8, 257, False, 128, 128, False, False), (16, 16, 8, 333, False, 256, 128, False, True)])
+def test_prefill_many_launches_are_bit_identical(sa, oracle, B, Hq, Hkv, S, kv_int8, form, D, out_f32, causal):
     # the ring slots of the 128- and 256-row forms are reused from the first iteration on, and a workgroup's items follow each
     # other: a missing wait between a read and the next request for the same slot shows as a rare difference between
     # launches, so every launch is compared
-    print("prefill, 200 launches", B, Hq, Hkv, S, kv_int8, form, flush=True)
+    print("prefill, 200 launches", B, Hq, Hkv, S, kv_int8, form, D, out_f32, causal, flush=True)
     rng = np.random.default_rng(65)
-    D = 128
-    assert_form(sa, form, B, Hq, Hkv, S, D, True, kv_int8, False)
+    assert_form(sa, form, B, Hq, Hkv, S, D, causal, kv_int8, out_f32)
     q, k, v = normal_bf16(rng, (B, Hq, S, D)), normal_bf16(rng, (B, Hkv, S, D)), normal_bf16(rng, (B, Hkv, S, D))
     scale = 1.0 / math.sqrt(D)
     dq = dev_bf16(q)
+    kw = dict(out_dtype=torch.float32 if out_f32 else torch.bfloat16)
     if kv_int8:
         kc, ks = oracle.kv_quant_int8(k)
         vc, vs = oracle.kv_quant_int8(v)
-        args = (dq, dev(kc), dev(vc), scale, True)
-        kw = dict(k_scale=dev(ks), v_scale=dev(vs))
-        want = oracle.attn(q, kc, vc, scale, True, k_scale=ks, v_scale=vs)
+        args = (dq, dev(kc), dev(vc), scale, causal)
+        kw.update(k_scale=dev(ks), v_scale=dev(vs))
+        want = oracle.attn(q, kc, vc, scale, causal, k_scale=ks, v_scale=vs)
     else:
-        args = (dq, dev_bf16(k), dev_bf16(v), scale, True)
-        kw = {}
-        want = oracle.attn(q, k, v, scale, True)
+        args = (dq, dev_bf16(k), dev_bf16(v), scale, causal)
+        want = oracle.attn(q, k, v, scale, causal)
     first = sa.slim_attn_prefill(*args, **kw)
     torch.cuda.synchronize()
     check_close(host_f64(first), want, "first launch")
@@ -1255,17 +1263,20 @@ def test_non_finite_values_stay_inside_their_kv_head(sa, oracle):
 
 # ---------------------------------------------------------------- sharp softmax: the arithmetic's own bound
 
-@pytest.mark.parametrize("B,Hq,Hkv,S,kv_int8,out_f32,form", [
+@pytest.mark.parametrize("B,Hq,Hkv,S,kv_int8,out_f32,form,D", [tuple(x) + (128,) for x in (
     (2, 8, 2, 700, False, False, 32), (2, 8, 2, 700, False, True, 32), (2, 8, 2, 700, True, False, 32), (2, 8, 2, 700, True, True, 32),
     (38, 8, 8, 257, False, False, 128), (26, 2, 2, 300, False, True, 128), (9, 8, 2, 640, True, False, 128), (26, 4, 2, 256, True, True, 128),
-    (16, 32, 8, 256, False, False, 256), (4, 32, 8, 777, False, False, 256), (26, 5, 5, 385, True, False, 256), (19, 4, 2, 385, True, True, 256)])
-def test_sharp_softmax_stays_within_the_rounding_bound(sa, oracle, B, Hq, Hkv, S, kv_int8, out_f32, form):
-    # scale 0.5 on N(0,1) inputs: most rows are carried by one key, so the rounding of P (INT8: of P * v_scale) to
+    (16, 32, 8, 256, False, False, 256), (4, 32, 8, 777, False, False, 256), (26, 5, 5, 385, True, False, 256), (19, 4, 2, 385, True, True, 256),
+    (12, 24, 8, 480, False, True, 256), (16, 16, 8, 333, False, False, 256))] + [
+    (9, 8, 2, 777, False, False, 128, 64), (8, 16, 16, 512, False, False, 256, 64), (9, 24, 8, 511, False, True, 256, 64),
+    (8, 16, 16, 512, True, False, 256, 64), (8, 16, 16, 512, True, True, 256, 64)])
+def test_sharp_softmax_stays_within_the_rounding_bound(sa, oracle, B, Hq, Hkv, S, kv_int8, out_f32, form, D):
+    # scale 0.5 on N(0,1) inputs (of 64 values 0.71, for scores as large): most rows are carried by one key, so the rounding of P (INT8: of P * v_scale) to
     # bf16 is not averaged over the keys.  One rounding to nearest is off by at most 2^-8 relative, hence per element
     #   |o - o_exact| <= 2^-8 * sum_j p_j |v_j|  (+ 2^-8 |o| for a bf16 output)  + fp32 noise,
     # the first sum being the oracle's attention over |V|.
     # (N(0,1) scores of this scale reach far past the 2^8 by which the running maximum may lag: every form's slow path runs)
-    D, scale = 128, 0.5
+    scale = 0.5 * math.sqrt(128 / D)
     causal = not out_f32
     assert_form(sa, form, B, Hq, Hkv, S, D, causal, kv_int8, out_f32)
     rng = np.random.default_rng(321)
