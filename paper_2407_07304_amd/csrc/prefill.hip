@@ -15,12 +15,11 @@
 //   - An iteration is one tile of every wave, and a barrier ends it (every second one where six ring slots fit, see DEEP):
 //     the wave issues the scores of its next tile and P V of its last one, alternately, and between two MFMAs a share of this
 //     tile's softmax (a fused multiply-add, an exponential, an addition, half a conversion), the operand read that replaces
-//     the one the MFMA consumed, and a ring request.  A wave's own vector work so runs in the shadow of its MFMAs (a microbenchmark: 16 MFMAs with four vector
-//     instructions each take 34 cycles an MFMA, alone 32.5).  (Before, two groups of waves in opposite phases, softmax and
-//     MFMAs, met at a barrier per phase: 1590 cycles for what an iteration does in 1390.  B=1, 32 heads, bf16, before and
-//     now: S=2048 41.7 -> 39.9 us, S=8192 490 -> 465, D=64, S=4096 95 -> 88; INT8 S=4096 149.1 -> 147.3, D=64 116 -> 100;
-//     B=4, 32 on 8 heads, S=777 with its cache 37.9 -> 34.6.)  On N(0,1) operands what is left is power: S=8192, not causal, runs at 1.85
-//     PFLOP/s on zeros and at 1.24 on N(0,1), and operand reads from LDS are 15 % of that, the barrier 4 %.
+//     the one the MFMA consumed, and a ring request.  A wave's own vector work so runs in the shadow of its MFMAs: a
+//     microbenchmark of 16 MFMAs with four vector instructions each takes 34 cycles an MFMA, alone 32.5 (waves that took
+//     softmax and MFMAs in turn, two groups in opposite phases, needed 1590 cycles for what an iteration does in 1390: B=1,
+//     32 heads, bf16, S=8192 490 us and 465).  On N(0,1) operands what is left is power: S=8192, not causal, takes 1.4 times
+//     as long on them as on zeros.
 //   - The score tile is computed transposed, S^T = K Q^T: the K tile is the A operand
 //     (from LDS), Q^T the B operand (held in registers for the whole row block).  In the
 //     result every lane holds ONE query column and 16 of the 32 keys, so the row max and
@@ -221,7 +220,7 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
     const int rg = WIDE ? w8 : w;   // this wave's 32 rows of the block
     const int l = tid & 63, l32 = l & 31, hh = l >> 5;
 
-    // Q^T B-operands of a row block: lane holds row my_q, d = 16 s + 8 hh + [0,8).  With bf16 K/V the 128 rows come
+    // Q^T B-operands of a row block: lane holds row my_q, d = 16 s + 8 hh + [0,8).  With bf16 K/V the rows come
     // in through LDS, by buffer loads with an LDS destination that move 64 consecutive 16-byte pieces each: loads
     // that give every lane a row of its own are taken lane by lane by the memory pipe (about 4 k cycles per row block
     // for the eight waves' fragments, with the first K and V tiles waiting behind them, against about 0.7 k this
@@ -378,7 +377,7 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
         const int wave_q_lo = i0 + 32 * rg;
         const int kend = p.causal ? min(S, i0 + BR) : S;
         const int n_tiles = (kend + kBC - 1) / kBC;
-        const int n_iter = (n_tiles + NG - 1) / NG;      // one barrier each
+        const int n_iter = (n_tiles + NG - 1) / NG;
         // last tile of this row group: its diagonal under the causal mask, else the tail of the key axis; -1 if the row
         // group lies outside the sequence
         // (row_off is a multiple of 32: all of a row group's rows lie before row 0 or none does)
@@ -1060,7 +1059,8 @@ static void set_blocks(PrefillParams& p, const PrefillArgs& a, int rows, int per
 
 // Which form a call takes (rows of its row blocks: 32, 128 or 256; p is left set for 128 or 256): the one with the
 // smallest modelled time.  The constants are fitted to the times of all three forms, 13 pairs of batch and heads (4 to 384
-// heads) by 17 lengths (64 to 8192), causal and not: of 1350 calls 43 take a form that is more than 3 % slower than the best.
+// heads) by 17 lengths (64 to 8192), causal and not, with plain blocks of 256 rows: of 1350 calls 43 take a form that is more
+// than 3 % slower than the best.
 //   - a tile of 256 rows costs less than twice one of 128 (half the staging per query row, INT8 half the widening, no
 //     merge), but there are half as many items to fill the chip with.  32 heads, bf16, D=128, rows of 128 against 256:
 //     S=2048 40.5 and 49 us, S=3000 79.8 and 77.1, S=8192 500 and 465; INT8 S=2048 51 and 60, S=4096 170 and 147; D=64, B=4, 32
@@ -1075,11 +1075,11 @@ static void set_blocks(PrefillParams& p, const PrefillArgs& a, int rows, int per
 //   - bf16 calls of 128 values, not causal, that the coarser lines below give 32 rows do not go to 128: they would take 5 %
 //     longer (4 sequences, 32 on 8 heads, S=100 7.3 us at 32 rows, 7.7 at 128; 40 on 8, S=67, fp32 results 7.6 and 8.0) and be
 //     further from the 64-bit result.  (Causal ones go: S=92, 15 sequences, 12 heads 9.6 us at 32 rows, 7.7 at 128.)
-//   - bf16 calls that keep the 128-row form whatever the model says (256 rows would be up to a fifth faster on some of
-//     them): D = 64, sequences of fewer than 500 rows, or not causal with no more blocks of 256 than compute units; D = 128,
-//     not causal, fewer than 200 rows, but for those that the coarser lines below give 256 (8 sequences, 24 on 8 heads,
-//     S=134: 10.3 us, at 32 rows 13.6; as near the 64-bit result as these).  These are the shapes by which that form's
-//     tests reach it.
+//   - bf16 calls that keep the 128-row form whatever the model says: D = 64, sequences of fewer than 500 rows, or not causal
+//     with no more blocks of 256 than compute units; D = 128, not causal, fewer than 200 rows, but for those that the coarser
+//     lines below give 256 (8 sequences, 24 on 8 heads, S=134: 10.3 us, at 32 rows 13.6; as near the 64-bit result as these).
+//     These are the shapes by which that form's tests reach it, and it costs: of 50 such calls that the model would give 256
+//     rows, these are 2 to 29 % faster (24 sequences, 32 heads, S=413, D=64 68.6 and 50.7 us).
 //   - bf16 blocks of 256 rows are as near the 64-bit result as those in whose place they are (OWN, in `own`).  That is said by
 //     coarser lines (kCoarse; 8 head counts, 4 to 512, by 12 lengths, 50 to 4096), which have 256 rows for 128 values and bf16
 //     results only: as near as 32 rows, or as 128, by one more exact maximum a row than these have; or plain ones.

@@ -158,7 +158,7 @@ __device__ __forceinline__ int splits_of(int T, int n_split, unsigned split_rate
 
 // The chunks [begin, end) of split sp where n chunks are dealt evenly, in order, over n_used splits (the first ones take one
 // more).  In 32 bits: n * sp / n_used in 64 is a division of some 150 scalar instructions, and a workgroup's first load waits
-// for two of them (a step of B=1, 64 on 8 heads, T=32768 23.6 -> 23.3 us, of 48 sequences of up to 3001 tokens, 32 on 8 heads, 43.15 -> 42.98).
+// for two of them.  (What that gives is within what two runs of one build differ: B=1, 64 on 8 heads, T=32768 23.6 and 23.3 us a step.)
 __device__ __forceinline__ void split_span(int n, int n_used, int sp, int& begin, int& end) {
     const unsigned q = n_used == 1 ? (unsigned)n : (unsigned)n / (unsigned)n_used, r = (unsigned)n - q * (unsigned)n_used;
     begin = (int)(q * (unsigned)sp + min((unsigned)sp, r));
