@@ -175,7 +175,8 @@ __global__ __launch_bounds__(64 * W) void slim_prefill_split_kernel(const SplitP
         // the running max moves only when a score has passed it by 2^8 (always on a wave's first tile: the diagonal tile
         // shows every row its own key)
         if (__builtin_amdgcn_ballot_w64(umax - M > 8.0f) != 0) {
-            const float m_new = fmaxf(M, half_max(umax));
+            float m_new = fmaxf(M, half_max(umax));
+            if constexpr (KV_I8) m_new = ceilf(m_new);   // (whole numbers: see WHOLE in prefill.hip; of these maxima a row has four or eight)
             const float alpha = fast_exp2(M - m_new);
 #pragma unroll
             for (int dt = 0; dt < DT; ++dt)

@@ -722,6 +722,25 @@ def test_grouped_decode_waves_with_lengths_of_their_own(sa, oracle, B, Hq, Hkv, 
     assert err.mean() <= 1.27 * 2 * 2.0 ** -9
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,S,D,form", [(24, 8, 8, 64, 128, 32), (24, 8, 8, 64, 64, 32), (9, 8, 2, 640, 128, 128), (1, 40, 8, 1500, 64, 128)])
+def test_prefill_int8_largest_probability_rounds_like_any_other(sa, B, Hq, Hkv, S, D, form):
+    # A row of one key (the first, causal): its probability is the largest under its maximum.  Were it exactly 1, every such
+    # result would be off by what its v_scale is off a bf16 value, here half an ulp, upwards: 2^-8.
+    print("prefill INT8, one key", B, Hq, Hkv, S, D, form, flush=True)
+    assert_form(sa, form, B, Hq, Hkv, S, D, True, True, True)
+    rng = np.random.default_rng(S + D)
+    q = normal_bf16(rng, (B, Hq, S, D))
+    kc = rng.integers(-127, 128, (B, Hkv, S, D), dtype=np.int8)
+    vc = rng.integers(64, 128, (B, Hkv, S, D)).astype(np.int8)
+    ks = rng.uniform(0.005, 0.02, (B, Hkv, S)).astype(np.float32)
+    vs = np.full((B, Hkv, S), np.float32(2.0 ** -6 * (1 + 1.0001 * 2.0 ** -8)))
+    out = host_f64(sa.slim_attn_prefill(dev_bf16(q), dev(kc), dev(vc), 1.0 / math.sqrt(D), True, k_scale=dev(ks), v_scale=dev(vs),
+                                        out_dtype=torch.float32))[:, :, 0]
+    off = (out / np.repeat(vc[:, :, 0].astype(np.float64) * float(vs[0, 0, 0]), Hq // Hkv, axis=1) - 1).mean()
+    # (a rounding of its own a head, of at most 2^-8: five times the mean's standard deviation of a uniform one)
+    assert abs(off) <= 5 * 2.0 ** -8 / math.sqrt(3 * B * Hq), off
+
+
 def test_grouped_decode_eight_waves_round_like_any_other_token(sa):
     # Lengths of their own, 64 codes a token, eight waves: sequences of one token, whose probability is that wave's largest.
     # Were it exactly 1, every result would be off by what its v_scale is off a bf16 value, here half an ulp, upwards: 2^-8.
