@@ -1122,11 +1122,11 @@ static int choose_rows(PrefillParams& p, const PrefillArgs& a, int& own) {
     set_blocks(p, a, 2 * kBR);
     const double us_wide = modelled_us(p, c.tile256, item256, 2 * kBR, 2);
     const FormCosts& g = kCoarse[d128];
-    const double coarse256 = d128 && !a.out_f32 ? modelled_us(p, g.tile256, g.item256, 2 * kBR, 2) : 1e30;
+    const double coarse256 = d128 && !a.out_f32 && !a.kv_int8 ? modelled_us(p, g.tile256, g.item256, 2 * kBR, 2) : 1e30;
     const bool many = (long)p.n_rb * p.n_bh > 256;
     set_blocks(p, a, kBR);
     double us = modelled_us(p, c.tile128, item128, kBR, 1);
-    const double coarse128 = modelled_us(p, g.tile128, g.item128, kBR, 1);
+    const double coarse128 = a.kv_int8 ? 0.0 : modelled_us(p, g.tile128, g.item128, kBR, 1);
     const int coarse = small_us(g) < std::min(coarse128, coarse256) + g.lists ? 32 : coarse256 < coarse128 ? 2 * kBR : kBR;
     const bool tested128 = d128 ? !p.causal && a.seq_len < 200 : a.seq_len < 500 || !(p.causal || many);
     const bool wide = a.kv_int8 || coarse == 2 * kBR || !tested128;
