@@ -57,7 +57,7 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_split_kernel(
     const uint16_t* __restrict__ q, const int8_t* __restrict__ kc, const float* __restrict__ ks,
     const int8_t* __restrict__ vc, const float* __restrict__ vs, uint16_t* __restrict__ out,
     float* __restrict__ ws_acc, float* __restrict__ ws_ml, const int* __restrict__ kv_lens, int group, int Hkv, int T_alloc,
-    int n_split, unsigned split_rate, float scale_log2e) {
+    int n_split, unsigned split_rate, int ranked, float scale_log2e) {
     constexpr int LPR = D / 16;        // lanes per token row
     constexpr int SLOTS = 64 / LPR;    // token rows per load instruction of a wave
     constexpr int CH = LPR;            // rows per slot per chunk: SLOTS * CH == kChunk, one token per lane
@@ -71,10 +71,18 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_split_kernel(
 
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));   // (the wave index as a scalar: everything derived from it stays uniform)
     const int c = lane % LPR, s = lane / LPR;
-    const int sp = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-    const int Hq = group * Hkv, g = group == 1 ? h : h / group;   // (group query heads per KV head)
     // T_alloc is the cache's allocated length (the row stride); this sequence's first T tokens count
-    const int T = kv_lens ? min(max(kv_lens[b], 1), T_alloc) : T_alloc;
+    int h = blockIdx.y, b = blockIdx.z, T;
+    const int sp = blockIdx.x;
+    if (ranked != 0) {   // (the number of sequences; one split)
+        const SequenceHead row = ranked_row(kv_lens, ranked, group * Hkv, T_alloc, b, h);
+        h = row.h;
+        b = row.b;
+        T = row.T;
+    } else {
+        T = kv_lens ? min(max(kv_lens[b], 1), T_alloc) : T_alloc;
+    }
+    const int Hq = group * Hkv, g = group == 1 ? h : h / group;   // (group query heads per KV head)
     const int n_used = splits_of(T, n_split, split_rate);
     if (sp >= n_used) return;   // (nobody reads this split's record)
     const long kvbase = ((long)b * Hkv + g) * (long)T_alloc;
@@ -419,6 +427,10 @@ static DecodePlan ragged_plan(DecodePlan plan, bool gqa, int batch, int q_heads,
         plan.waves = 8;
         plan.whole_max = true;
     }
+    // Whole rows, more than one on some compute unit: dealt by their lengths (ranked_row).  Up to three a unit, which are there at
+    // once: with more, rows that end early make room for others, and what finding a row takes comes again in each round (64
+    // sequences, 32 heads, T=500, lengths spread 27.0 -> 29.3 us).  Of shorter caches two rows differ by less than that.
+    plan.ranked = plan.n_split == 1 && batch <= kMaxRanked && rows > 256 && rows <= 768 && kv_len >= 1000;
     return plan;
 }
 
@@ -478,7 +490,7 @@ hipError_t launch_decode(const DecodeArgs& a, hipStream_t stream) {
         hipLaunchKernelGGL((slim_decode_int8_split_kernel<D, W>), dim3((unsigned)n_split, (unsigned)a.q_heads, (unsigned)a.batch),
                            dim3(64 * W), 0, stream, (const uint16_t*)a.q, a.k_codes, a.k_scale, a.v_codes, a.v_scale,
                            (uint16_t*)a.out, ws_acc, ws_ml, a.kv_lens, a.q_heads / a.kv_heads, a.kv_heads, a.kv_len, n_split,
-                           plan.split_rate, a.softmax_scale * kLog2e);
+                           plan.split_rate, plan.ranked ? a.batch : 0, a.softmax_scale * kLog2e);
         return hipGetLastError();
     };
     auto pick_w = [&](auto d_c) {

@@ -63,7 +63,7 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_gqa_kernel(
     const uint16_t* __restrict__ q, const int8_t* __restrict__ kc, const float* __restrict__ ks,
     const int8_t* __restrict__ vc, const float* __restrict__ vs, uint16_t* __restrict__ out, float* __restrict__ ws_acc,
     float* __restrict__ ws_ml, const int* __restrict__ kv_lens, int G, int Hkv, int T_alloc, int n_split,
-    unsigned split_rate, float scale_log2e) {
+    unsigned split_rate, int ranked, float scale_log2e) {
     constexpr int KS = D / 64;            // 16-byte pieces of a K row per lane (two k-steps of the score MFMA each)
     constexpr int DT = D / 16;            // 16-row tiles of O^T
     constexpr int CPR = D / 16;           // 16-byte pieces per row
@@ -80,14 +80,22 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_gqa_kernel(
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));   // (the wave index as a scalar: everything derived from it stays uniform)
     const int l16 = lane & 15, lq = lane >> 4;
     const int Hq = G * Hkv;   // (G query heads per KV head)
-    const int sp = blockIdx.x, g = blockIdx.y, b = blockIdx.z;
+    int g = blockIdx.y, b = blockIdx.z, T;
+    const int sp = blockIdx.x;
+    if (ranked != 0) {   // (the number of sequences; one split)
+        const SequenceHead row = ranked_row(kv_lens, ranked, Hkv, T_alloc, b, g);
+        g = row.h;
+        b = row.b;
+        T = row.T;
+    } else {
+        T = kv_lens ? min(max(kv_lens[b], 1), T_alloc) : T_alloc;
+    }
     char* const kS = smem + w * WAVE_BYTES;
     char* const vS = kS + TILE;
     float* const scS = reinterpret_cast<float*>(kS + 2 * TILE);   // [0,32) k_scale * c, [32,64) v_scale
 
     // T_alloc is the cache's allocated length (the row stride); this sequence's first T tokens count.  The sequence's
     // own tiles are dealt evenly over its splits, and a split's tiles to its waves in turn.
-    const int T = kv_lens ? min(max(kv_lens[b], 1), T_alloc) : T_alloc;
     const int n_used = splits_of(T, n_split, split_rate);
     if (sp >= n_used) return;   // (nobody reads this split's record)
     const long kvrow0 = ((long)b * Hkv + g) * (long)T_alloc;
@@ -363,7 +371,7 @@ hipError_t launch_decode_gqa_split(const DecodeArgs& a, float* ws_acc, float* ws
         constexpr int D = decltype(d_c)::value, W = decltype(w_c)::value, NC = decltype(nc_c)::value;
         hipLaunchKernelGGL((slim_decode_int8_gqa_kernel<D, W, NC, decltype(traffic_c)::value, decltype(whole_c)::value>), grid, dim3(64 * W), 0, stream,
                            (const uint16_t*)a.q, a.k_codes, a.k_scale, a.v_codes, a.v_scale, (uint16_t*)a.out, ws_acc, ws_ml,
-                           a.kv_lens, a.q_heads / a.kv_heads, a.kv_heads, a.kv_len, plan.n_split, plan.split_rate, scale_log2e);
+                           a.kv_lens, a.q_heads / a.kv_heads, a.kv_heads, a.kv_len, plan.n_split, plan.split_rate, plan.ranked ? a.batch : 0, scale_log2e);
         return hipGetLastError();
     };
     auto pick = [&](auto d_c) {

@@ -165,4 +165,95 @@ __device__ __forceinline__ void split_span(int n, int n_used, int sp, int& begin
     end = begin + (int)q + ((unsigned)sp < r ? 1 : 0);
 }
 
+// sum and max over a wave, wave-uniform
+__device__ __forceinline__ int wave_sum(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, false);    // quad_perm [1,0,3,2]
+    v += __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xf, 0xf, false);    // quad_perm [2,3,0,1]
+    v += __builtin_amdgcn_update_dpp(0, v, 0x141, 0xf, 0xf, false);   // row_half_mirror
+    v += __builtin_amdgcn_update_dpp(0, v, 0x140, 0xf, 0xf, false);   // row_mirror
+    return __builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16) + __builtin_amdgcn_readlane(v, 32) + __builtin_amdgcn_readlane(v, 48);
+}
+__device__ __forceinline__ int wave_max(int v) {
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x141, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x140, 0xf, 0xf, false));
+    return max(max(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)), max(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
+}
+
+// Decode over `batch` (2 to kMaxRanked) sequences of different lengths, a workgroup for each of a sequence's `heads` rows: the
+// row that workgroup (b0, h0) of the grid takes.  Workgroup ids go to the compute units in turn (id mod 8 is the XCD, whose
+// 32 units each get one before one gets a second: the same unit for ids 256 apart).  In the order of the grid two long rows may meet
+// on one unit while another has two short ones, and the call takes as long as the former.  So the rows are dealt
+// longest first in layers of 256, and every other layer runs backwards: a unit's longest row meets the shortest of the next layer.
+// The last layer runs forwards: where it is not full, the units it leaves out have the longest rows of the layer
+// before.  (Where an id lands only decides about time: every row is worked off as it was, by one workgroup.)
+// Lengths spread over an eighth to all of the cache, a fourth of them full and the others an eighth, all equal, us:
+//   48 sequences, 32 on 8 heads, T=3001 37.9 -> 33.2, 38.2 -> 28.8, 51.0 -> 51.5; 16, 32 heads, T=3000 42.8 -> 39.8, 37.3 ->
+//   26.7, 61.6 -> 61.8; 40, 8 heads, T=1000 14.6 -> 11.7, 13.8 -> 9.5, 18.1 -> 18.3; 64, 64 on 8 heads, D=64, T=2000 19.5 ->
+//   19.2, 19.1 -> 17.9, 24.5 -> 24.7.
+// Every wave finds its row by itself, with one load: lane l has the lengths of sequences l and l + 64 in chunks of 64 tokens, and
+// the chunks of the sequence of a given rank are found bit by bit, by counting lanes.  No LDS and no barrier (ranks counted in LDS
+// took 0.7 us more).  Where the longest is within 256 tokens or an eighth of the mean the rows keep their order.
+constexpr int kMaxRanked = 128;
+struct SequenceHead {
+    int b, h, T;   // sequence, head, the sequence's length
+};
+__device__ __forceinline__ SequenceHead ranked_row(const int* __restrict__ kv_lens, int batch, int heads, int T_alloc, int b0, int h0) {
+    constexpr int NI = kMaxRanked / 64;
+    typedef int lens_t __attribute__((ext_vector_type(NI)));
+    const int lane = (int)threadIdx.x & 63;
+    lens_t len = 0, c;   // (0 past the last sequence)
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+        if (64 * i < batch && lane + 64 * i < batch) len[i] = min(max(kv_lens[lane + 64 * i], 1), T_alloc);
+    c = (len + 63) >> 6;
+    int total = c[0], most = c[0];
+#pragma unroll
+    for (int i = 1; i < NI; ++i) {
+        total += c[i];
+        most = max(most, c[i]);
+    }
+    most = wave_max(most);
+    total = wave_sum(total);
+    auto length_of = [&](int b) {   // (b is uniform)
+        int x = __builtin_amdgcn_readlane(len[0], b & 63);
+        if (batch > 64) {
+#pragma unroll
+            for (int i = 1; i < NI; ++i) {
+                const int y = __builtin_amdgcn_readlane(len[i], b & 63);
+                x = (b >> 6) == i ? y : x;
+            }
+        }
+        return x;
+    };
+    if (most * batch <= max(total + 4 * batch, total + total / 8)) return SequenceHead{b0, h0, length_of(b0)};
+    const int id = b0 * heads + h0, layer = id >> 8, p = id & 255, last = (batch * heads - 1) >> 8;
+    const int row = 256 * layer + (((last - layer) & 1) ? 255 - p : p);
+    // (a row's index is small: the quotient by a reciprocal is off by less than the half that is added keeps it from an integer)
+    const int rank = __builtin_amdgcn_readfirstlane((int)(((float)row + 0.5f) * __builtin_amdgcn_rcpf((float)heads)));
+    // the greatest length that more than `rank` sequences have, and how many are longer
+    int chunks = 0, longer = 0;
+    for (int bit = 1 << (31 - __builtin_clz(most)); bit != 0; bit >>= 1) {
+        int n = __builtin_popcountll(__builtin_amdgcn_ballot_w64(c[0] >= (chunks | bit)));
+        if (batch > 64)
+#pragma unroll
+            for (int i = 1; i < NI; ++i) n += __builtin_popcountll(__builtin_amdgcn_ballot_w64(c[i] >= (chunks | bit)));
+        if (n > rank) chunks |= bit;
+        else longer = n;
+    }
+    // of those that have it, in order
+    int nth = rank - longer, b = 0;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+        if (64 * i >= batch) break;
+        const unsigned long long same = __builtin_amdgcn_ballot_w64(c[i] == chunks);
+        const int before = __builtin_amdgcn_mbcnt_hi((unsigned)(same >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)same, 0u));
+        const unsigned long long here = __builtin_amdgcn_ballot_w64(c[i] == chunks && before == nth);
+        if (here != 0) b = 64 * i + __builtin_ctzll(here);
+        nth -= __builtin_popcountll(same);
+    }
+    return SequenceHead{b, row - rank * heads, length_of(b)};
+}
+
 }  // namespace slim

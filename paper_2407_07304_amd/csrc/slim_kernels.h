@@ -59,6 +59,7 @@ struct DecodePlan {
     int waves, n_split;
     unsigned split_rate;
     bool whole_max = false;
+    bool ranked = false;   // workgroups take the rows in the order of their lengths (ranked_row)
 };
 // Grouped-query variant (2 to 32 query heads per KV head): a workgroup sweeps a run of tokens of one (batch, KV head)
 // for all its query heads and is a split.  n_bg = batch * kv_heads, group = query heads per KV head.

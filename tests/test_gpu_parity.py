@@ -722,6 +722,37 @@ def test_grouped_decode_waves_with_lengths_of_their_own(sa, oracle, B, Hq, Hkv, 
     assert err.mean() <= 1.27 * 2 * 2.0 ** -9
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,T,D", [
+    # whole rows that are dealt to the workgroups by their lengths: two more than a layer of 256, one and a half, two and a
+    # bit, three full layers; 2, 64, 65 and 128 sequences (one and two a lane); grouped heads and not
+    (2, 129, 129, 1000, 64), (64, 6, 6, 1000, 64), (65, 16, 8, 1003, 64), (128, 12, 6, 1000, 128), (33, 8, 8, 1100, 128)])
+def test_decode_rows_dealt_by_their_lengths(sa, oracle, B, Hq, Hkv, T, D):
+    assert_plan(sa, (4, 1), B, Hq, Hkv, T, D)
+    print("decode, rows by length", B, Hq, Hkv, T, D, flush=True)
+    rng = np.random.default_rng(B + T + D)
+    # ties, a sequence of a token, chunk bounds, both ends; then lengths that hardly differ, whose rows keep their order
+    spread = np.array(([T, 1, 64, 65, 700, 700, 63, T - 1, 129, 700, 128, 300] * B)[:B], dtype=np.int32)
+    q = normal_bf16(rng, (B, Hq, 1, D))
+    kc = rng.integers(-127, 128, (B, Hkv, T, D), dtype=np.int8)
+    vc = rng.integers(-127, 128, (B, Hkv, T, D), dtype=np.int8)
+    ks, vs = rng.uniform(0.005, 0.02, (B, Hkv, T)).astype(np.float32), rng.uniform(0.005, 0.02, (B, Hkv, T)).astype(np.float32)
+    scale = 1.0 / math.sqrt(D)
+    args = dev_bf16(q), dev(kc), dev(ks), dev(vc), dev(vs)
+    one = torch.full((B,), T, dtype=torch.int32, device="cuda")
+    for lens in (spread, rng.permutation(spread), np.full(B, T - 3, dtype=np.int32)):
+        out = torch.full((B, Hq, 1, D), float("nan"), dtype=torch.bfloat16, device="cuda")
+        sa.slim_attn_decode_int8_varlen(*args, torch.from_numpy(lens).cuda(), scale, out=out)
+        want = np.concatenate([oracle.attn(q[b:b + 1], kc[b:b + 1, :, :m], vc[b:b + 1, :, :m], scale, False, k_scale=ks[b:b + 1, :, :m],
+                                           v_scale=vs[b:b + 1, :, :m]) for b, m in enumerate(lens.tolist())], axis=0)
+        # (a probability times its v_scale and the result are each rounded to bf16: 2^-8 of sum p |v| and half an ulp; |v| < 2.54)
+        assert np.abs(host_f64(out) - want).max() <= 2.54 * 2.0 ** -8 + 2.0 ** -7
+        # a row is worked off by itself: alone among sequences of full length it is the same, bit for bit
+        for b in (0, 1, B // 2, B - 1):
+            alone = one.clone()
+            alone[b] = int(lens[b])
+            assert torch.equal(sa.slim_attn_decode_int8_varlen(*args, alone, scale)[b], out[b]), b
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,S,D,form", [(24, 8, 8, 64, 128, 32), (24, 8, 8, 64, 64, 32), (9, 8, 2, 640, 128, 128), (1, 40, 8, 1500, 64, 128)])
 def test_prefill_int8_largest_probability_rounds_like_any_other(sa, B, Hq, Hkv, S, D, form):
     # A row of one key (the first, causal): its probability is the largest under its maximum.  Were it exactly 1, every such
