@@ -268,90 +268,118 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_split_kernel(
 }
 
 // Merges the n_split partial (max, sum, accumulator) triples of one (batch, head) in split order and writes the
-// bf16 output row.  The launch is latency-bound (a few kilobytes per workgroup, just written by the split kernel),
-// so all loads of up to kCombineChunk splits are issued before anything is computed: one round trip to memory
-// instead of one for the maxima and another for the sums and accumulators.  Longer runs are merged a chunk at a time
-// with a running (max, sum, accumulator), still in split order; with more than a chunk of splits (short batches of
-// long caches) PARTS groups of D threads take a contiguous share of the splits each and are merged through LDS, so
-// that 64 splits are still one round trip (64 query heads of one sequence at T=32768: 6.1 -> 4.5 us a launch).  Slots past
-// the last split re-read the last one and count as empty (max = kMasked, sum = 0).
-constexpr int kCombineChunk = 16;
-
-template <int D, int PARTS>
-__global__ __launch_bounds__(D * PARTS) void slim_decode_combine_kernel(const float* __restrict__ ws_acc,
-                                                                        const float* __restrict__ ws_ml,
-                                                                        uint16_t* __restrict__ out,
-                                                                        const int* __restrict__ kv_lens, int T_alloc,
-                                                                        int n_split, unsigned split_rate) {
-    constexpr int CH = kCombineChunk;
-    const long bh = (long)blockIdx.y * gridDim.x + blockIdx.x;
-    const int d = threadIdx.x % D, part = threadIdx.x / D;
-    const int n_used = splits_of(kv_lens ? min(max(kv_lens[blockIdx.y], 1), T_alloc) : T_alloc, n_split, split_rate);
+// bf16 output row.  The launch is latency-bound (a few kilobytes per row, just written by the split kernel), so a row's records
+// come in with few, wide loads that are all issued before anything is computed: D/4 lanes read a record with one 128-bit
+// load each, a wave RPW = 256/D records at a time.  Up to U RPW records a row one wave does it, and a workgroup has four
+// rows; more are shared by the four waves of a workgroup and merged through LDS.  Slots past the last split re-read the last
+// one and count as empty (max = kMasked, sum = 0); runs longer than the slots take another pass with a running (max, sum,
+// accumulator).  With a thread for every output value and sixteen records a thread (32-bit loads, 512 threads a row beyond sixteen
+// splits) the wide form's decode took, before -> now: 64 on 8 heads, T=32768, 32 splits 18.6 -> 16.1 us, D=64 14.7 -> 12.6; 8
+// heads, T=16000, 32 splits 11.8 -> 9.5; 32 heads, T=4000, 8 splits 9.5 -> 9.2; 16 sequences, 64 on 8 heads, T=8192, 2 splits 45.2 ->
+// 44.6.
+template <int D, int WAVES, int U>
+__global__ __launch_bounds__(256) void slim_decode_combine_kernel(const float* __restrict__ ws_acc, const float* __restrict__ ws_ml,
+                                                                  uint16_t* __restrict__ out, const int* __restrict__ kv_lens,
+                                                                  int q_heads, long rows, int T_alloc, int n_split, unsigned split_rate) {
+    constexpr int LPR = D / 4, RPW = 64 / LPR;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int c = lane % LPR, sub = lane / LPR;
+    const long bh = (long)blockIdx.x * (4 / WAVES) + (WAVES == 1 ? w : 0);
+    if (bh >= rows) return;
+    const int part = WAVES == 1 ? 0 : w;
+    const int n_used = splits_of(kv_lens ? min(max(kv_lens[(unsigned)bh / (unsigned)q_heads], 1), T_alloc) : T_alloc, n_split, split_rate);
     if (n_used == 1) return;   // (its one workgroup has written the result)
-    const int s_begin = PARTS == 1 ? 0 : n_used * part / PARTS, s_end = PARTS == 1 ? n_used : n_used * (part + 1) / PARTS;
-    const float* const ml = ws_ml + bh * n_split * 2;
-    const float* const acc = ws_acc + bh * n_split * D + d;
-    float M = kMasked, L = 0.0f, o = 0.0f;
-    for (int s0 = s_begin; s0 < s_end; s0 += CH) {
-        float m[CH], l[CH], a[CH];
+    const f32x2* const ml = reinterpret_cast<const f32x2*>(ws_ml) + bh * n_split;
+    const f32x4* const acc = reinterpret_cast<const f32x4*>(ws_acc) + bh * n_split * LPR + c;
+    float M = kMasked, L = 0.0f;
+    f32x4 o = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (int s0 = 0; s0 < n_used; s0 += WAVES * RPW * U) {
+        float m[U], l[U];
+        f32x4 a[U];
 #pragma unroll
-        for (int i = 0; i < CH; ++i) {
-            const int sp = min(s0 + i, s_end - 1);
-            const bool there = s0 + i < s_end;
-            const f32x2 t = *reinterpret_cast<const f32x2*>(ml + 2 * sp);
-            const float av = acc[(long)sp * D];
-            m[i] = there ? t[0] : kMasked;
-            l[i] = there ? t[1] : 0.0f;
-            a[i] = there ? av : 0.0f;
+        for (int i = 0; i < U; ++i) {
+            const int s = s0 + (i * WAVES + part) * RPW + sub, sp = min(s, n_used - 1);
+            const f32x2 t = ml[sp];
+            const f32x4 av = acc[(long)sp * LPR];
+            m[i] = s < n_used ? t[0] : kMasked;
+            l[i] = s < n_used ? t[1] : 0.0f;
+            a[i] = s < n_used ? av : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
         }
         float m_new = M;
 #pragma unroll
-        for (int i = 0; i < CH; ++i) m_new = fmaxf(m_new, m[i]);
-        const float keep = fast_exp2(M - m_new);   // first chunk: L = o = 0, whatever this is
+        for (int i = 0; i < U; ++i) m_new = fmaxf(m_new, m[i]);
+        const float keep = fast_exp2(M - m_new);   // first pass: L = o = 0, whatever this is
         L *= keep;
         o *= keep;
 #pragma unroll
-        for (int i = 0; i < CH; ++i) {
+        for (int i = 0; i < U; ++i) {
             const float f = fast_exp2(m[i] - m_new);   // an empty split has sum = 0 and accumulator = 0
             L = fmaf(f, l[i], L);
-            o = fmaf(f, a[i], o);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = fmaf(f, a[i][e], o[e]);
         }
         M = m_new;
     }
-    if constexpr (PARTS > 1) {
-        __shared__ float oS[PARTS][D], mS[PARTS], lS[PARTS];
-        oS[part][d] = o;
-        if (d == 0) {
-            mS[part] = M;
-            lS[part] = L;
+    // the wave's groups of lanes, by halves
+#pragma unroll
+    for (int x = LPR; x < 64; x *= 2) {
+        const float m_other = __shfl_xor(M, x), l_other = __shfl_xor(L, x), m_new = fmaxf(M, m_other);
+        const float f = fast_exp2(M - m_new), g = fast_exp2(m_other - m_new);
+        L = fmaf(L, f, l_other * g);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = fmaf(o[e], f, __shfl_xor(o[e], x) * g);
+        M = m_new;
+    }
+    if constexpr (WAVES > 1) {
+        __shared__ __attribute__((aligned(16))) f32x4 oS[WAVES][LPR];
+        __shared__ float mS[WAVES], lS[WAVES];
+        if (sub == 0) oS[w][c] = o;
+        if (lane == 0) {
+            mS[w] = M;
+            lS[w] = L;
         }
         __syncthreads();
-        if (part != 0) return;
-        float top = kMasked;
+        if (w != 0) return;
+        M = kMasked;
 #pragma unroll
-        for (int i = 0; i < PARTS; ++i) top = fmaxf(top, mS[i]);
+        for (int i = 0; i < WAVES; ++i) M = fmaxf(M, mS[i]);
         L = 0.0f;
-        o = 0.0f;
+        o = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int i = 0; i < PARTS; ++i) {
-            const float f = fast_exp2(mS[i] - top);
+        for (int i = 0; i < WAVES; ++i) {
+            const float f = fast_exp2(mS[i] - M);
             L = fmaf(f, lS[i], L);
-            o = fmaf(f, oS[i][d], o);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = fmaf(f, oS[i][c][e], o[e]);
         }
     }
-    out[bh * D + d] = (uint16_t)(pack_bf16x2(o / L, 0.0f) & 0xffffu);
+    if (sub == 0) {
+        u32x2 ov;
+        ov[0] = pack_bf16x2(o[0] / L, o[1] / L);
+        ov[1] = pack_bf16x2(o[2] / L, o[3] / L);
+        *reinterpret_cast<u32x2*>(out + bh * D + 4 * c) = ov;
+    }
 }
 
 static hipError_t launch_combine(const DecodeArgs& a, const float* ws_acc, const float* ws_ml, int n_split, unsigned split_rate,
                                  hipStream_t stream) {
-    auto launch = [&](auto d_c, auto parts_c) {
-        constexpr int D = decltype(d_c)::value, PARTS = decltype(parts_c)::value;
-        hipLaunchKernelGGL((slim_decode_combine_kernel<D, PARTS>), dim3((unsigned)a.q_heads, (unsigned)a.batch), dim3(D * PARTS), 0, stream,
-                           ws_acc, ws_ml, (uint16_t*)a.out, a.kv_lens, a.kv_len, n_split, split_rate);
+    const long rows = (long)a.batch * a.q_heads;
+    auto launch = [&](auto d_c, auto waves_c, auto u_c) {
+        constexpr int D = decltype(d_c)::value, WAVES = decltype(waves_c)::value, U = decltype(u_c)::value;
+        const unsigned grid = (unsigned)((rows * WAVES + 3) / 4);
+        hipLaunchKernelGGL((slim_decode_combine_kernel<D, WAVES, U>), dim3(grid), dim3(256), 0, stream, ws_acc, ws_ml, (uint16_t*)a.out,
+                           a.kv_lens, a.q_heads, rows, a.kv_len, n_split, split_rate);
         return hipGetLastError();
     };
     auto pick = [&](auto d_c) {
-        return n_split > kCombineChunk ? launch(d_c, std::integral_constant<int, 4>{}) : launch(d_c, std::integral_constant<int, 1>{});
+        using std::integral_constant;
+        constexpr int RPW = 256 / decltype(d_c)::value;
+        const integral_constant<int, 1> one{};
+        const integral_constant<int, 4> four{};
+        if (n_split <= 2 * RPW) return launch(d_c, one, integral_constant<int, 2>{});
+        if (n_split <= 4 * RPW) return launch(d_c, one, four);
+        if (n_split <= 16 * RPW) return launch(d_c, four, four);
+        return launch(d_c, four, integral_constant<int, 8>{});
     };
     return a.head_dim == 128 ? pick(std::integral_constant<int, 128>{}) : pick(std::integral_constant<int, 64>{});
 }

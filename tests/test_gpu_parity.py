@@ -545,7 +545,12 @@ def test_decode_grouped_all_zero_tokens_and_huge_scores(sa, oracle):
     # one head per KV head: the same edges (64-token chunks)
     (1, 1, 1, 30000, 128), (3, 1, 1, 4097, 64), (20, 8, 8, 513, 128), (70, 8, 8, 520, 64), (1, 8, 8, 1537, 128),
     # many rows of 64 codes a token: four waves up to 15 chunks, eight from 16 on
-    (70, 8, 8, 100, 64), (70, 8, 8, 960, 64), (70, 8, 8, 961, 64)])
+    (70, 8, 8, 100, 64), (70, 8, 8, 960, 64), (70, 8, 8, 961, 64),
+    # records a row by the wave and by the four waves of a workgroup, one pass and two: 4, 6, 12, 32, 48, 96 and 128 splits
+    (3, 5, 5, 1200, 128), (1, 1, 1, 1520, 128), (3, 5, 5, 3020, 128), (1, 1, 1, 8500, 128), (1, 4, 2, 10500, 128), (1, 1, 1, 25000, 128),
+    (1, 1, 1, 1420, 64), (2, 12, 3, 1520, 64), (1, 1, 1, 16500, 64), (1, 1, 1, 33000, 64), (2, 12, 3, 7000, 64),
+    # grouped heads, 64 codes a token, eight waves on every compute unit
+    (16, 16, 8, 4000, 64), (4, 64, 8, 3001, 64)])
 def test_decode_plan_edges(sa, oracle, B, Hq, Hkv, T, D):
     print("decode plan edges", B, Hq, Hkv, T, D, flush=True)
     _decode_case(sa, oracle, B, Hq, Hkv, T, D, seed=T + D + Hq)
