@@ -29,7 +29,6 @@
 namespace slim {
 
 constexpr int kChunk = 64;   // tokens per wave per chunk
-typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 // lane exchange inside a slot via DPP (no LDS traffic); every lane of the slot ends with the slot total
 template <int CTRL>
@@ -258,11 +257,8 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_split_kernel(
             out[bh * D + d] = (uint16_t)(pack_bf16x2(o / L, 0.0f) & 0xffffu);
         } else {
             const long idx = bh * n_split + sp;
-            ws_acc[idx * D + d] = o;
-            if (d == 0) {
-                ws_ml[idx * 2] = M;
-                ws_ml[idx * 2 + 1] = L;
-            }
+            store_through(ws_acc + idx * D + d, o);
+            if (d == 0) store_through(reinterpret_cast<f32x2*>(ws_ml) + idx, f32x2{M, L});
         }
     }
 }

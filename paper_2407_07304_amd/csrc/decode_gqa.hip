@@ -321,11 +321,8 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_gqa_kernel(
             out[bh * D + d] = (uint16_t)(pack_bf16x2(acc / L, 0.0f) & 0xffffu);
         } else {
             const long idx = bh * n_split + sp;
-            ws_acc[idx * D + d] = acc;
-            if (d == 0) {
-                ws_ml[idx * 2] = top;
-                ws_ml[idx * 2 + 1] = L;
-            }
+            store_through(ws_acc + idx * D + d, acc);
+            if (d == 0) store_through(reinterpret_cast<f32x2*>(ws_ml) + idx, f32x2{top, L});
         }
     }
 }

@@ -46,8 +46,11 @@ __device__ __forceinline__ void kv_quant_rows(const uint16_t* __restrict__ x, in
             if (row < n_rows) {
                 u32x2* dst = reinterpret_cast<u32x2*>(codes + row * D + lane_in_row * 8);
                 if (STREAM) __builtin_nontemporal_store(out2, dst);
-                else *dst = out2;
-                if (lane_in_row == 0) scales[row] = scale;
+                else store_through(dst, out2);
+                if (lane_in_row == 0) {
+                    if (STREAM) scales[row] = scale;
+                    else store_through(scales + row, scale);
+                }
             }
         }
     }
@@ -92,8 +95,8 @@ __global__ __launch_bounds__(kAppendThreads) void kv_quant_int8_append_kernel(co
     quant_row_piece<LPR>(raw, out2, scale);
     if (g >= Hkv || pos < 0 || pos >= T) return;   // (no room in this sequence's cache: nothing is written)
     const long out_row = (long)row * T + pos;
-    *reinterpret_cast<u32x2*>(codes + out_row * D + lane_in_row * 8) = out2;
-    if (lane_in_row == 0) scales[out_row] = scale;
+    store_through(reinterpret_cast<u32x2*>(codes + out_row * D + lane_in_row * 8), out2);
+    if (lane_in_row == 0) store_through(scales + out_row, scale);
 }
 
 hipError_t launch_kv_quant_int8(const void* x, int8_t* codes, float* scales, long n_rows, int head_dim,

@@ -900,7 +900,7 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
                 const int lane_now = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
                 const int pid = (w8 * 64 + lane_now) + kPrefillThreads * i, row = pid / PPR, col = pid % PPR;
                 const u32x4 piece = *reinterpret_cast<const u32x4*>(smem + row * OPITCH + col * 16);
-                if (i0 + row >= 0 && i0 + row < S) *reinterpret_cast<u32x4*>(obase + (long)row * OB + col * 16) = piece;
+                if (i0 + row >= 0 && i0 + row < S) store_through_b128(obase, row * OB + col * 16, piece);
             }
         };
         auto finish = [&](auto grp_c) {
@@ -974,8 +974,8 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
                         float scale;
                         quant_row_piece<LPR>(raw[j], cw, scale);
                         if (row >= 0 && row < S) {
-                            *reinterpret_cast<u32x2*>(codes + (long)row * D + piece * 8) = cw;
-                            if (piece == 0) scales[row] = scale;
+                            store_through(reinterpret_cast<u32x2*>(codes + (long)row * D + piece * 8), cw);
+                            if (piece == 0) store_through(scales + row, scale);
                         }
                     }
                 }

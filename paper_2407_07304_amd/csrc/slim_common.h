@@ -3,12 +3,15 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace slim {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
@@ -17,6 +20,25 @@ constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kMasked = -1.0e30f;  // finite stand-in for -inf: exp2(kMasked - m) == 0 for any finite m
 
 __device__ __forceinline__ float bf16_bits_to_f32(unsigned int bits16) { return __uint_as_float(bits16 << 16); }
+
+// Stores of results that nothing in the launch reads again: device scope, so that they go through the L2 to memory at once.  A
+// plain store leaves a dirty line, and what is dirty when a launch ends is written back before the next one starts.  Plain stores
+// -> these, us: K and V quantised, 32 heads, S=2048 9.78 -> 9.40 (the same tensors over and over, in the caches, 9.8 -> 7.8), 12 sequences
+// of 8 heads, S=738 10.4 -> 9.75; prefill, INT8, 2 sequences, 32 on 8 heads, S=793 27.3 -> 26.1, 32 heads, S=2048 39.9 -> 39.4; one
+// sequence's decode step (the appends' stores) 11.87 -> 11.65, 64 on 8 heads, T=32768 (and the splits' records) 20.4 -> 19.9.
+// Not where it gains nothing: a decode's result row, and streams beyond the last-level cache, whose scales (16 bytes of a line at a time)
+// made a 1.6 GB stream 1 % slower.
+template <class T>
+__device__ __forceinline__ void store_through(T* p, const T v) {
+    static_assert(sizeof(T) == 4 || sizeof(T) == 8, "one register or two");
+    using Bits = std::conditional_t<sizeof(T) == 8, unsigned long long, unsigned>;
+    __hip_atomic_store(reinterpret_cast<Bits*>(p), __builtin_bit_cast(Bits, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// 16 bytes at base + off (base uniform, off below 2^31)
+__device__ __forceinline__ void store_through_b128(void* base, int off, u32x4 v) {
+    constexpr int kDeviceScope = 16;   // (the cache policy's sc1 bit)
+    __builtin_amdgcn_raw_buffer_store_b128(v, __builtin_amdgcn_make_buffer_rsrc(base, 0, 0x7fffffff, 0x00020000), off, 0, kDeviceScope);
+}
 
 // fp32 -> bf16, round to nearest even (the hardware conversion on gfx950)
 __device__ __forceinline__ unsigned int pack_bf16x2(float lo, float hi) {
