@@ -385,7 +385,9 @@ static hipError_t launch_combine(const DecodeArgs& a, const float* ws_acc, const
 //   - the cache at 6.6 TB/s, or the fullest compute unit's tokens at its own pace (7.1 ns a token of 128 codes, 5.8 of
 //     64: its vector ALU and its share of the memory): the longer of the two and a fifth of the
 //     shorter;
-//   - 6 us for the combine launch when S > 1.
+//   - 6 us for the combine launch when S > 1.  Where that gives no compute unit a second workgroup and whole rows take longer
+//     than kDecodeLongNs, the splits are chosen again among those of which that holds, with 4.8 us (5.75 of 64 codes a token), and
+//     the last split may have fewer than four chunks (4 sequences, 32 heads, T=2000 a step 19.6 -> 18.2 us, D=64 16.5 -> 14.3).
 // So a (batch, head) is split only where one workgroup each cannot load the chip evenly or soon enough, and whole
 // caches go through one launch from about 150 rows on (B=16, 32 heads, T=8192: 161 us in one launch of eight-wave
 // workgroups, 164 us as 4 splits).  A split has at least a chunk for each of four waves, and a call is not split into more
@@ -395,24 +397,31 @@ static DecodePlan decode_plan(int kv_len, long n_bh, int head_dim) {
     const long n_chunks = ((long)kv_len + kChunk - 1) / kChunk;
     const double ns_token = head_dim == 128 ? 7.1 : 5.8;
     const double stream_ns = (double)kv_len * n_bh * (2 * head_dim + 8) / 6600.0;
-    DecodePlan best{4, 1, kAllSplits};
-    double best_ns = 0.0;
+    int best = 1, alone_best = 1;
+    double best_ns = 0.0, alone_best_ns = 0.0, whole_ns = 0.0;
     for (int s : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256}) {
-        if (s > 1 && (s * 4 > n_chunks || decode_records_bytes(n_bh, s, head_dim) > kDecodeStaticScratchBytes)) break;
+        if (s > 1 && (s * 4 > n_chunks + 3 || decode_records_bytes(n_bh, s, head_dim) > kDecodeStaticScratchBytes)) break;
         const long per_wg = (n_chunks + s - 1) / s, rounds = (n_bh * s + 255) / 256;
         const double busy_ns = (double)(rounds * per_wg * kChunk) * ns_token;
         const double longer = busy_ns > stream_ns ? busy_ns : stream_ns, shorter = busy_ns > stream_ns ? stream_ns : busy_ns;
-        const double ns = longer + 0.2 * shorter + (s > 1 ? 6000.0 : 0.0);
-        if (s == 1 || ns < best_ns) {
+        const double sweep_ns = longer + 0.2 * shorter, ns = sweep_ns + (s > 1 ? 6000.0 : 0.0);
+        if (s == 1) whole_ns = ns;
+        if (s == 1 || (ns < best_ns && s * 4 <= n_chunks)) {
             best_ns = ns;
-            best.n_split = s;
-            // eight waves share a merge where each still gets a few chunks (a chunk each, two of 64 codes a token, is
-            // enough once several workgroups per compute unit overlap: 800 x 8 heads, T=500, D=64, 77.8 us with eight
-            // waves, 72.4 with four, and with lengths of their own, where half of the eight had nothing, 60.6 and 45.9)
-            best.waves = per_wg >= (n_bh * s >= 512 ? (head_dim == 128 ? 8 : 16) : 24) ? 8 : 4;
+            best = s;
+        }
+        const double alone_ns = sweep_ns + (s == 1 ? 0.0 : head_dim == 128 ? 4800.0 : 5750.0);
+        if (s == 1 || (alone_ns < alone_best_ns && n_bh * s <= 256)) {
+            alone_best_ns = alone_ns;
+            alone_best = s;
         }
     }
-    return best;
+    if (whole_ns > kDecodeLongNs && n_bh * best <= 256) best = alone_best;
+    // eight waves share a merge where each still gets a few chunks (a chunk each, two of 64 codes a token, is
+    // enough once several workgroups per compute unit overlap: 800 x 8 heads, T=500, D=64, 77.8 us with eight
+    // waves, 72.4 with four, and with lengths of their own, where half of the eight had nothing, 60.6 and 45.9)
+    const long per_wg = (n_chunks + best - 1) / best;
+    return DecodePlan{per_wg >= (n_bh * best >= 512 ? (head_dim == 128 ? 8 : 16) : 24) ? 8 : 4, best, kAllSplits};
 }
 
 // The plan for sequences of different lengths (kv_lens; the host knows only the allocated length).  The plan for equal
@@ -444,13 +453,7 @@ static DecodePlan ragged_plan(DecodePlan plan, bool gqa, int batch, int q_heads,
     // on 8 heads, T=8192 46.3 and 49.1 us), and above, where twelve waves of the smaller workgroups fit a compute unit and
     // eight of the larger, short contexts in a large cache lose (300 to 700 tokens, 32 sequences, T=8192 14.0 and 17.3 us, 16
     // of T=32768 10.7 and 14.5).
-    // Eight waves in the place of four keep whole maxima (see WHOLE): without, their results are 0.02 to 0.29 % further from
-    // the 64-bit ones than those of four (12 shapes of 250 to 2000 heads, 24 draws of N(0,1) each), with, 0.2 % nearer (0.12 %
-    // further to 1.05 % nearer).  The time is the same.
-    if (gqa && head_dim == 64 && rows * plan.n_split <= 256 && plan.waves == 4) {
-        plan.waves = 8;
-        plan.whole_max = true;
-    }
+    if (gqa && head_dim == 64 && rows * plan.n_split <= 256) plan.waves = 8;
     // Whole rows, more than one on some compute unit: dealt by their lengths (ranked_row).  Up to three a unit, which are there at
     // once: with more, rows that end early make room for others, and what finding a row takes comes again in each round (64
     // sequences, 32 heads, T=500, lengths spread 27.0 -> 29.3 us).  Of shorter caches two rows differ by less than that.

@@ -55,10 +55,10 @@ __device__ __forceinline__ bf16x8 widen8(const i32x2 cw) {
 // TRAFFIC_ONLY: the measurement form of the kernel (include/slimprobe.h): the same workgroups, waves, token runs and
 // loads, issued at the same points, but a tile's registers are only XORed together before they are refilled.  What it
 // takes is what the memory system charges for this access pattern on this shape, arithmetic aside.
-// WHOLE: the running max is a whole number.  A row's largest probability is then some power of two above a half and not 1:
+// The running max is a whole number: a row's largest probability is then some power of two above a half and not 1:
 // times its v_scale it rounds to bf16 like any other, where a v_scale alone is further off than the mean (0.375 of an ulp,
 // codes of N(0,1)), and more waves, each with a maximum of its own, have more such tokens.
-template <int D, int W, int NC, bool TRAFFIC_ONLY = false, bool WHOLE = false>
+template <int D, int W, int NC, bool TRAFFIC_ONLY = false>
 __global__ __launch_bounds__(64 * W) void slim_decode_int8_gqa_kernel(
     const uint16_t* __restrict__ q, const int8_t* __restrict__ kc, const float* __restrict__ ks,
     const int8_t* __restrict__ vc, const float* __restrict__ vs, uint16_t* __restrict__ out, float* __restrict__ ws_acc,
@@ -246,8 +246,7 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_gqa_kernel(
             if (__builtin_amdgcn_ballot_w64(umax - M[nc] > 8.0f) != 0) {
                 float m_new = fmaxf(M[nc], umax);
                 m_new = fmaxf(m_new, __shfl_xor(m_new, 16));
-                m_new = fmaxf(m_new, __shfl_xor(m_new, 32));
-                if constexpr (WHOLE) m_new = ceilf(m_new);
+                m_new = ceilf(fmaxf(m_new, __shfl_xor(m_new, 32)));
                 const float alpha = fast_exp2(M[nc] - m_new);
 #pragma unroll
                 for (int dt = 0; dt < DT; ++dt) o[nc][dt] *= alpha;
@@ -330,8 +329,12 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_gqa_kernel(
 // Splits of the key axis and waves per workgroup, by the model of decode.hip's plan with this kernel's constants (from a
 // sweep of 16 row counts, 8 to 1024, by 12 lengths, 128 to 32768, K and V cold): the cache at 6.6 TB/s, or the fullest
 // compute unit's tokens at 5.9 ns each (7 where it holds several workgroups; 4.2 and 5 with 64 codes a token), the longer
-// of the two and a fifth of the shorter, and 5 us and
-// 40 ns a split for the combine launch.  Eight waves where the grid leaves compute units without a workgroup (less than
+// of the two and a fifth of the shorter, and 5 us and 40 ns a split for the combine launch.  Where that gives no compute unit a second
+// workgroup and whole rows take longer than kDecodeLongNs, the splits are chosen again among those of which that holds, with the
+// combine launch as what it takes by itself, 2.4 us and 25 ns a split (3.6 us and 40 ns of 64 codes a token), and the last split may have fewer
+// than four tiles: one sequence, 64 on 8 heads, T=8192, 24 splits 9.6 us, 32 9.1; 16 of T=2000, one split 17.5, two 16.3; 14, 24 on 8
+// heads, T=2131 a step 23.0 -> 18.8.  (With more splits than compute units it does not hold: 34 sequences, 64 on 8 heads, T=1023 23.4 ->
+// 27.9; nor in the place of such a cut: 11, 32 on 8, T=5328, D=64 20.3 -> 21.4.)  Eight waves where the grid leaves compute units without a workgroup (less than
 // 240 of them), four where it fills the chip: 128 rows at T=8192 take 45.3 us with 1024 waves in 256 workgroups, 49 with
 // 2048 waves (52.9 in the form before, a split per wave; all with the combine launch).  8 rows at T=32768 are 256
 // workgroups of four waves as well (19.2 us; 30.6 before, on 512 waves): eight waves were not measured there.
@@ -343,27 +346,30 @@ DecodePlan decode_gqa_plan(int kv_len, long n_bg, int group, int head_dim) {
     const long n_tiles = ((long)kv_len + kGqaTile - 1) / kGqaTile;
     const bool two_groups = group > 16;
     const double stream_ns = (double)kv_len * n_bg * (2 * head_dim + 8) / 6600.0;
-    int best = 1;
-    double best_ns = 0.0;
+    int best = 1, alone_best = 1;
+    double best_ns = 0.0, alone_best_ns = 0.0, whole_ns = 0.0;
     for (int s : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256}) {
-        if (s > 1 && (s * (two_groups ? 3 : 4) > n_tiles || decode_records_bytes(n_bg * group, s, head_dim) > kDecodeStaticScratchBytes)) break;
+        if (s > 1 && (s * (two_groups ? 3 : 4) > n_tiles + 3 || decode_records_bytes(n_bg * group, s, head_dim) > kDecodeStaticScratchBytes)) break;
         const long per_wg = (n_tiles + s - 1) / s, rounds = (n_bg * s + 255) / 256;
         const double ns_token = head_dim == 128 ? (rounds > 1 ? 7.0 : 5.9) : (rounds > 1 ? 5.0 : 4.2);
         const double busy_ns = (double)(rounds * per_wg * kGqaTile) * ns_token;
         const double longer = busy_ns > stream_ns ? busy_ns : stream_ns, shorter = busy_ns > stream_ns ? stream_ns : busy_ns;
-        const double ns = longer + 0.2 * shorter + (s > 1 ? (two_groups ? 3000.0 : 5000.0) + 40.0 * s : 0.0);
-        if (s == 1 || ns < best_ns) {
+        const double sweep_ns = longer + 0.2 * shorter, ns = sweep_ns + (s > 1 ? (two_groups ? 3000.0 : 5000.0) + 40.0 * s : 0.0);
+        if (s == 1) whole_ns = ns;
+        if (s == 1 || (ns < best_ns && s * (two_groups ? 3 : 4) <= n_tiles)) {
             best_ns = ns;
             best = s;
         }
+        const double alone_ns = sweep_ns + (s == 1 ? 0.0 : head_dim == 128 ? 2400.0 + 25.0 * s : 3600.0 + 40.0 * s);
+        if (s == 1 || (alone_ns < alone_best_ns && n_bg * s <= 256)) {
+            alone_best_ns = alone_ns;
+            alone_best = s;
+        }
     }
+    if (!two_groups && whole_ns > kDecodeLongNs && n_bg * best <= 256) best = alone_best;
     DecodePlan plan{two_groups || n_bg * best < 240 ? 8 : 4, best, kAllSplits};
-    // 64 codes a token, several splits: eight waves as long as no compute unit has two workgroups, with whole maxima (see WHOLE) in
-    // the place of four (16 sequences, 64 on 8 heads, T=8192 33.8 -> 26.8 us, one at T=32768 14.8 -> 13.3).
-    if (head_dim == 64 && plan.waves == 4 && best > 1 && n_bg * best <= 256) {
-        plan.waves = 8;
-        plan.whole_max = true;
-    }
+    // 64 codes a token, several splits: eight waves as long as no compute unit has two workgroups (16 sequences, 64 on 8 heads, T=8192 33.8 -> 26.8 us, one at T=32768 14.8 -> 13.3).
+    if (head_dim == 64 && best > 1 && n_bg * best <= 256) plan.waves = 8;
     return plan;
 }
 
@@ -371,9 +377,9 @@ hipError_t launch_decode_gqa_split(const DecodeArgs& a, float* ws_acc, float* ws
                                    bool traffic_only) {
     const float scale_log2e = a.softmax_scale * kLog2e;
     const dim3 grid((unsigned)plan.n_split, (unsigned)a.kv_heads, (unsigned)a.batch);
-    auto launch = [&](auto d_c, auto w_c, auto nc_c, auto traffic_c, auto whole_c) {
+    auto launch = [&](auto d_c, auto w_c, auto nc_c, auto traffic_c) {
         constexpr int D = decltype(d_c)::value, W = decltype(w_c)::value, NC = decltype(nc_c)::value;
-        hipLaunchKernelGGL((slim_decode_int8_gqa_kernel<D, W, NC, decltype(traffic_c)::value, decltype(whole_c)::value>), grid, dim3(64 * W), 0, stream,
+        hipLaunchKernelGGL((slim_decode_int8_gqa_kernel<D, W, NC, decltype(traffic_c)::value>), grid, dim3(64 * W), 0, stream,
                            (const uint16_t*)a.q, a.k_codes, a.k_scale, a.v_codes, a.v_scale, (uint16_t*)a.out, ws_acc, ws_ml,
                            a.kv_lens, a.q_heads / a.kv_heads, a.kv_heads, a.kv_len, plan.n_split, plan.split_rate, plan.ranked ? a.batch : 0, scale_log2e);
         return hipGetLastError();
@@ -385,11 +391,9 @@ hipError_t launch_decode_gqa_split(const DecodeArgs& a, float* ws_acc, float* ws
         constexpr integral_constant<int, 1> one{};
         constexpr std::false_type no{};
         constexpr std::true_type yes{};
-        if (traffic_only) return plan.waves == 8 ? launch(d_c, w8, one, yes, no) : launch(d_c, w4, one, yes, no);
-        if (a.q_heads / a.kv_heads > 16) return launch(d_c, w8, integral_constant<int, 2>{}, no, no);
-        if constexpr (decltype(d_c)::value == 64)
-            if (plan.whole_max) return launch(d_c, w8, one, no, yes);
-        return plan.waves == 8 ? launch(d_c, w8, one, no, no) : launch(d_c, w4, one, no, no);
+        if (traffic_only) return plan.waves == 8 ? launch(d_c, w8, one, yes) : launch(d_c, w4, one, yes);
+        if (a.q_heads / a.kv_heads > 16) return launch(d_c, w8, integral_constant<int, 2>{}, no);
+        return plan.waves == 8 ? launch(d_c, w8, one, no) : launch(d_c, w4, one, no);
     };
     return a.head_dim == 128 ? pick(std::integral_constant<int, 128>{}) : pick(std::integral_constant<int, 64>{});
 }

@@ -53,12 +53,15 @@ struct DecodeArgs {
     float softmax_scale;
     bool ragged;          // use the plan for sequences of different lengths (the workspace has room for it)
 };
+// A decode whose whole rows would take this long is bound by the GPU also as a step of its own (its appends, then the decode).  A
+// shorter one is bound by the host's 3 to 3.5 us a launch, and the launch that merges splits counts as more than it takes the GPU (32
+// heads, T=1000, a step with 4 splits and one: by the GPU alone 10.3 and 12.0 us, from the host 12.6 to 14.1 and 11.8).
+constexpr double kDecodeLongNs = 9000.0;
 // How a decode call is cut up: waves per workgroup, splits of the key axis (workgroups per row), and how many of them a
-// sequence uses (splits_of); whole_max: the grouped kernel's running maxima are whole numbers (eight waves, 64 codes).
+// sequence uses (splits_of).
 struct DecodePlan {
     int waves, n_split;
     unsigned split_rate;
-    bool whole_max = false;
     bool ranked = false;   // workgroups take the rows in the order of their lengths (ranked_row)
 };
 // Grouped-query variant (2 to 32 query heads per KV head): a workgroup sweeps a run of tokens of one (batch, KV head)

@@ -550,7 +550,9 @@ def test_decode_grouped_all_zero_tokens_and_huge_scores(sa, oracle):
     (3, 5, 5, 1200, 128), (1, 1, 1, 1520, 128), (3, 5, 5, 3020, 128), (1, 1, 1, 8500, 128), (1, 4, 2, 10500, 128), (1, 1, 1, 25000, 128),
     (1, 1, 1, 1420, 64), (2, 12, 3, 1520, 64), (1, 1, 1, 16500, 64), (1, 1, 1, 33000, 64), (2, 12, 3, 7000, 64),
     # grouped heads, 64 codes a token, eight waves on every compute unit
-    (16, 16, 8, 4000, 64), (4, 64, 8, 3001, 64)])
+    (16, 16, 8, 4000, 64), (4, 64, 8, 3001, 64),
+    # splits chosen among those that have a compute unit each, the last one shorter than four chunks or tiles; two of 128 rows
+    (1, 8, 8, 4000, 128), (1, 16, 8, 2000, 128), (1, 8, 4, 4010, 64), (16, 16, 8, 2000, 128), (4, 32, 32, 2000, 64)])
 def test_decode_plan_edges(sa, oracle, B, Hq, Hkv, T, D):
     print("decode plan edges", B, Hq, Hkv, T, D, flush=True)
     _decode_case(sa, oracle, B, Hq, Hkv, T, D, seed=T + D + Hq)
