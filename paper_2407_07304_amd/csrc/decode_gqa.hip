@@ -326,18 +326,19 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_gqa_kernel(
     }
 }
 
-// Splits of the key axis and waves per workgroup, by the model of decode.hip's plan with this kernel's constants (from a
-// sweep of 16 row counts, 8 to 1024, by 12 lengths, 128 to 32768, K and V cold): the cache at 6.6 TB/s, or the fullest
-// compute unit's tokens at 5.9 ns each (7 where it holds several workgroups; 4.2 and 5 with 64 codes a token), the longer
-// of the two and a fifth of the shorter, and 5 us and 40 ns a split for the combine launch.  Where that gives no compute unit a second
-// workgroup and whole rows take longer than kDecodeLongNs, the splits are chosen again among those of which that holds, with the
-// combine launch as what it takes by itself, 2.4 us and 25 ns a split (3.6 us and 40 ns of 64 codes a token), and the last split may have fewer
-// than four tiles: one sequence, 64 on 8 heads, T=8192, 24 splits 9.6 us, 32 9.1; 16 of T=2000, one split 17.5, two 16.3; 14, 24 on 8
-// heads, T=2131 a step 23.0 -> 18.8.  (With more splits than compute units it does not hold: 34 sequences, 64 on 8 heads, T=1023 23.4 ->
-// 27.9; nor in the place of such a cut: 11, 32 on 8, T=5328, D=64 20.3 -> 21.4.)  Eight waves where the grid leaves compute units without a workgroup (less than
-// 240 of them), four where it fills the chip: 128 rows at T=8192 take 45.3 us with 1024 waves in 256 workgroups, 49 with
-// 2048 waves (52.9 in the form before, a split per wave; all with the combine launch).  8 rows at T=32768 are 256
-// workgroups of four waves as well (19.2 us; 30.6 before, on 512 waves): eight waves were not measured there.
+// Splits of the key axis and waves per workgroup, by the model of decode.hip's plan with this kernel's constants (from a sweep
+// of 16 row counts, 8 to 1024, by 12 lengths, 128 to 32768, K and V cold): the cache at 6.6 TB/s, or the fullest compute
+// unit's tokens at 5.9 ns each (7 where it holds several workgroups; 4.2 and 5 with 64 codes a token), the longer of the two
+// and a fifth of the shorter, and 5 us and 40 ns a split for the combine launch.  Where that gives no compute unit a second
+// workgroup and whole rows take longer than kDecodeLongNs, the splits are chosen again among those of which that holds, with
+// the combine launch as what it takes by itself, 2.4 us and 25 ns a split (3.6 us and 40 ns of 64 codes a token), and the last
+// split may have fewer than four tiles: one sequence, 64 on 8 heads, T=8192, 24 splits 9.6 us, 32 9.1; 16 of T=2000, one split
+// 17.5, two 16.3; 14, 24 on 8 heads, T=2131 a step 23.0 -> 18.8.  (With more splits than compute units it does not hold: 34
+// sequences, 64 on 8 heads, T=1023 23.4 -> 27.9; nor in the place of such a cut: 11, 32 on 8, T=5328, D=64 20.3 -> 21.4.)
+// Eight waves where the grid leaves compute units without a workgroup (less than 240 of them), four where it fills the chip:
+// 128 rows at T=8192 take 45.3 us with 1024 waves in 256 workgroups, 49 with 2048 waves (52.9 in the form before, a split per
+// wave; all with the combine launch).  8 rows at T=32768 are 256 workgroups of four waves as well (19.2 us; 30.6 before, on
+// 512 waves): eight waves were not measured there.
 // With more than 16 heads a KV head (two column groups) always eight waves, a split from three tiles on, and 3 us for the
 // combine launch: a compute unit has one or two such workgroups, and four waves are half as many as it wants (32 on 1
 // head, T=777, K and V in the caches: 14.6 us with four waves in one split, 10.3 now; 20 on 1, 128 sequences,

@@ -46,11 +46,8 @@ __device__ __forceinline__ void kv_quant_rows(const uint16_t* __restrict__ x, in
             if (row < n_rows) {
                 u32x2* dst = reinterpret_cast<u32x2*>(codes + row * D + lane_in_row * 8);
                 if (STREAM) __builtin_nontemporal_store(out2, dst);
-                else store_through(dst, out2);
-                if (lane_in_row == 0) {
-                    if (STREAM) scales[row] = scale;
-                    else store_through(scales + row, scale);
-                }
+                else *dst = out2;
+                if (lane_in_row == 0) scales[row] = scale;
             }
         }
     }

@@ -974,8 +974,8 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
                         float scale;
                         quant_row_piece<LPR>(raw[j], cw, scale);
                         if (row >= 0 && row < S) {
-                            store_through(reinterpret_cast<u32x2*>(codes + (long)row * D + piece * 8), cw);
-                            if (piece == 0) store_through(scales + row, scale);
+                            *reinterpret_cast<u32x2*>(codes + (long)row * D + piece * 8) = cw;
+                            if (piece == 0) scales[row] = scale;
                         }
                     }
                 }

@@ -261,16 +261,15 @@ __global__ __launch_bounds__(64 * W) void slim_prefill_split_kernel(const SplitP
         }
         const float inv = 1.0f / L;
         if (i0 + row < S) {
-            const long first = ((long)bh * S + i0) * D;
-            const int at = row * D + d0;
+            const long at = ((long)bh * S + i0 + row) * D + d0;
             if (OUT_F32) {
-                float* const base = (float*)p.out + first;
-                store_through_b128(base, 4 * at, __builtin_bit_cast(u32x4, f32x4{a[0] * inv, a[1] * inv, a[2] * inv, a[3] * inv}));
-                store_through_b128(base, 4 * at + 16, __builtin_bit_cast(u32x4, f32x4{a[4] * inv, a[5] * inv, a[6] * inv, a[7] * inv}));
+                f32x4* dst = reinterpret_cast<f32x4*>((float*)p.out + at);
+                dst[0] = f32x4{a[0] * inv, a[1] * inv, a[2] * inv, a[3] * inv};
+                dst[1] = f32x4{a[4] * inv, a[5] * inv, a[6] * inv, a[7] * inv};
             } else {
                 const u32x4 ov = {pack_bf16x2(a[0] * inv, a[1] * inv), pack_bf16x2(a[2] * inv, a[3] * inv),
                                   pack_bf16x2(a[4] * inv, a[5] * inv), pack_bf16x2(a[6] * inv, a[7] * inv)};
-                store_through_b128((uint16_t*)p.out + first, 2 * at, ov);
+                *reinterpret_cast<u32x4*>((uint16_t*)p.out + at) = ov;
             }
         }
     }
@@ -286,8 +285,8 @@ __global__ __launch_bounds__(64 * W) void slim_prefill_split_kernel(const SplitP
                 float scale;
                 quant_row_piece<LPR>(raw, cw, scale);
                 if (row < S) {
-                    store_through(reinterpret_cast<u32x2*>((is_k ? p.kq : p.vq) + (kvrow0 + row) * D + piece * 8), cw);
-                    if (piece == 0) store_through((is_k ? p.kqs : p.vqs) + kvrow0 + row, scale);
+                    *reinterpret_cast<u32x2*>((is_k ? p.kq : p.vq) + (kvrow0 + row) * D + piece * 8) = cw;
+                    if (piece == 0) (is_k ? p.kqs : p.vqs)[kvrow0 + row] = scale;
                 }
             }
         }

@@ -23,11 +23,11 @@ __device__ __forceinline__ float bf16_bits_to_f32(unsigned int bits16) { return 
 
 // Stores of results that nothing in the launch reads again: device scope, so that they go through the L2 to memory at once.  A
 // plain store leaves a dirty line, and what is dirty when a launch ends is written back before the next one starts.  Plain stores
-// -> these, us: K and V quantised, 32 heads, S=2048 9.78 -> 9.40 (the same tensors over and over, in the caches, 9.8 -> 7.8), 12 sequences
-// of 8 heads, S=738 10.4 -> 9.75; prefill, INT8, 2 sequences, 32 on 8 heads, S=793 27.3 -> 26.1, 32 heads, S=2048 39.9 -> 39.4; one
-// sequence's decode step (the appends' stores) 11.87 -> 11.65, 64 on 8 heads, T=32768 (and the splits' records) 20.4 -> 19.9.
-// Not where it gains nothing: a decode's result row, and streams beyond the last-level cache, whose scales (16 bytes of a line at a time)
-// made a 1.6 GB stream 1 % slower.
+// -> these, us: prefill, bf16, 32 heads, S=2048 38.9 -> 38.4, INT8, 2 sequences, 32 on 8 heads, S=793 27.3 -> 26.1; one sequence's decode
+// step (the appends' stores) 11.8 -> 11.7, 64 on 8 heads, T=32768 (and the splits' records) 20.4 -> 19.9.
+// Not for stores in small pieces or at the very end of many small workgroups, which wait for them: the cache rows that a prefill emits
+// (one sequence, 8 heads, S=300 7.7 -> 8.4), its results in blocks of 32 rows (16 sequences, 32 on 8 heads, S=200 25.4 -> 26.2), the
+// quantiser (32 heads, S=2048 9.7 -> 9.5 to 9.8, 4 sequences, 8 heads, S=4000 16.8 -> 17.2); nor a decode's result row, which gains nothing.
 template <class T>
 __device__ __forceinline__ void store_through(T* p, const T v) {
     static_assert(sizeof(T) == 4 || sizeof(T) == 8, "one register or two");
