@@ -893,14 +893,15 @@ __global__ __launch_bounds__(kPrefillThreads) void slim_prefill_kernel(const Pre
         auto copy_out = [&](int part) {
             constexpr int PPR = OB / OH / 16;                      // 16-byte pieces per row
             constexpr int NST = BR * PPR / kPrefillThreads;        // pieces per thread
+            constexpr int RPI = kPrefillThreads / PPR;             // rows per piece of every thread (a scalar's worth of offset: one lane offset serves them all)
             char* const obase = (char*)kernel_args_now()->out + ((long)bh_now * S + i0) * (long)OB + part * (OB / OH);
 #pragma unroll
             for (int i = 0; i < NST; ++i) {
                 // (the thread id, counted afresh: keeping it alive through the tile loops costs spills)
                 const int lane_now = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-                const int pid = (w8 * 64 + lane_now) + kPrefillThreads * i, row = pid / PPR, col = pid % PPR;
+                const int pid = w8 * 64 + lane_now, row0 = pid / PPR, col = pid % PPR, row = row0 + i * RPI;
                 const u32x4 piece = *reinterpret_cast<const u32x4*>(smem + row * OPITCH + col * 16);
-                if (i0 + row >= 0 && i0 + row < S) store_through_b128(obase, row * OB + col * 16, piece);
+                if (i0 + row >= 0 && i0 + row < S) store_through_b128(obase, row0 * OB + col * 16, i * RPI * OB, piece);
             }
         };
         auto finish = [&](auto grp_c) {

@@ -23,8 +23,10 @@ __device__ __forceinline__ float bf16_bits_to_f32(unsigned int bits16) { return 
 
 // Stores of results that nothing in the launch reads again: device scope, so that they go through the L2 to memory at once.  A
 // plain store leaves a dirty line, and what is dirty when a launch ends is written back before the next one starts.  Plain stores
-// -> these, us: prefill, bf16, 32 heads, S=2048 38.9 -> 38.4, INT8, 2 sequences, 32 on 8 heads, S=793 27.3 -> 26.1; one sequence's decode
-// step (the appends' stores) 11.8 -> 11.7, 64 on 8 heads, T=32768 (and the splits' records) 20.4 -> 19.9.
+// -> these, us (GPU alone, builds in turn): a prefill's rows, bf16, 4 sequences, 32 on 8 heads, S=777 30.7 -> 29.4, one, 32 heads,
+// S=1024 19.4 -> 18.4, INT8, 2 sequences, 32 on 8 heads, S=793 27.7 -> 26.6, fp32 results, INT8, S=512 19.3 -> 17.3, bf16, 4, 16 on 2
+// heads, S=500 15.1 -> 12.7; from some 50 us a call on within what two runs differ.  One sequence's decode step (the appends'
+// stores) 12.2 -> 11.8, 64 on 8 heads, T=32768 (and the splits' records) 20.7 -> 20.5.
 // Not for stores in small pieces or at the very end of many small workgroups, which wait for them: the cache rows that a prefill emits
 // (one sequence, 8 heads, S=300 7.7 -> 8.4), its results in blocks of 32 rows (16 sequences, 32 on 8 heads, S=200 25.4 -> 26.2), the
 // quantiser (32 heads, S=2048 9.7 -> 9.5 to 9.8, 4 sequences, 8 heads, S=4000 16.8 -> 17.2); nor a decode's result row, which gains nothing.
@@ -34,10 +36,11 @@ __device__ __forceinline__ void store_through(T* p, const T v) {
     using Bits = std::conditional_t<sizeof(T) == 8, unsigned long long, unsigned>;
     __hip_atomic_store(reinterpret_cast<Bits*>(p), __builtin_bit_cast(Bits, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// 16 bytes at base + off (base uniform, off below 2^31)
-__device__ __forceinline__ void store_through_b128(void* base, int off, u32x4 v) {
+// 16 bytes at base + off + step (base and step uniform, off + step below 2^31; what is the same for all lanes goes into step, a scalar:
+// added up in vector registers it cost the 128-row INT8 prefill with fp32 results, D=128, two more spilled registers)
+__device__ __forceinline__ void store_through_b128(void* base, int off, int step, u32x4 v) {
     constexpr int kDeviceScope = 16;   // (the cache policy's sc1 bit)
-    __builtin_amdgcn_raw_buffer_store_b128(v, __builtin_amdgcn_make_buffer_rsrc(base, 0, 0x7fffffff, 0x00020000), off, 0, kDeviceScope);
+    __builtin_amdgcn_raw_buffer_store_b128(v, __builtin_amdgcn_make_buffer_rsrc(base, 0, 0x7fffffff, 0x00020000), off, step, kDeviceScope);
 }
 
 // fp32 -> bf16, round to nearest even (the hardware conversion on gfx950)
