@@ -70,6 +70,13 @@ int slim_probe_gqa_decode_traffic(const void* q_bf16, const int8_t* k_codes, con
 int slim_attn_decode_int8_plan(int batch, int q_heads, int kv_heads, int kv_len, int head_dim, int per_sequence_lengths,
                                int* waves, int* n_split);
 
+/*
+ * What else differs between the forms of such a call, each 0 or 1: whether whole rows are dealt to the workgroups by their lengths,
+ * and whether the splits' records are stored through the L2 (0 without splits).  Arguments and return value as above.
+ */
+int slim_attn_decode_int8_plan_options(int batch, int q_heads, int kv_heads, int kv_len, int head_dim, int per_sequence_lengths,
+                                       int* rows_by_length, int* records_through);
+
 #ifdef __cplusplus
 }
 #endif

@@ -228,6 +228,18 @@ int slim_attn_decode_int8_plan(int batch, int q_heads, int kv_heads, int kv_len,
     return SLIM_OK;
 }
 
+int slim_attn_decode_int8_plan_options(int batch, int q_heads, int kv_heads, int kv_len, int head_dim, int per_sequence_lengths,
+                                       int* rows_by_length, int* records_through) {
+    if (!rows_by_length || !records_through) return SLIM_ERR_NULL;
+    const int st = check_shape(batch, q_heads, kv_heads, kv_len, head_dim);
+    if (st != SLIM_OK) return st;
+    if (per_sequence_lengths != 0 && per_sequence_lengths != 1) return SLIM_ERR_SHAPE;
+    const slim::DecodePlan plan = slim::decode_plan_of(per_sequence_lengths == 1, batch, q_heads, kv_heads, kv_len, head_dim);
+    *rows_by_length = plan.ranked ? 1 : 0;
+    *records_through = plan.n_split > 1 && plan.records_through ? 1 : 0;
+    return SLIM_OK;
+}
+
 constexpr size_t kUseStaticScratch = ~(size_t)0;   // decode_common: workspace == NULL with this size selects the static array
 
 static int decode_common(const void* q_bf16, const int8_t* k_codes, const float* k_scale, const int8_t* v_codes,

@@ -56,7 +56,7 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_split_kernel(
     const uint16_t* __restrict__ q, const int8_t* __restrict__ kc, const float* __restrict__ ks,
     const int8_t* __restrict__ vc, const float* __restrict__ vs, uint16_t* __restrict__ out,
     float* __restrict__ ws_acc, float* __restrict__ ws_ml, const int* __restrict__ kv_lens, int group, int Hkv, int T_alloc,
-    int n_split, unsigned split_rate, int ranked, float scale_log2e) {
+    int n_split, unsigned split_rate, int mode, float scale_log2e) {
     constexpr int LPR = D / 16;        // lanes per token row
     constexpr int SLOTS = 64 / LPR;    // token rows per load instruction of a wave
     constexpr int CH = LPR;            // rows per slot per chunk: SLOTS * CH == kChunk, one token per lane
@@ -73,8 +73,8 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_split_kernel(
     // T_alloc is the cache's allocated length (the row stride); this sequence's first T tokens count
     int h = blockIdx.y, b = blockIdx.z, T;
     const int sp = blockIdx.x;
-    if (ranked != 0) {   // (the number of sequences; one split)
-        const SequenceHead row = ranked_row(kv_lens, ranked, group * Hkv, T_alloc, b, h);
+    if (mode > 0) {   // (dealt by length; one split)
+        const SequenceHead row = ranked_row(kv_lens, mode, group * Hkv, T_alloc, b, h);
         h = row.h;
         b = row.b;
         T = row.T;
@@ -256,9 +256,7 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_split_kernel(
         if (n_used == 1) {
             out[bh * D + d] = (uint16_t)(pack_bf16x2(o / L, 0.0f) & 0xffffu);
         } else {
-            const long idx = bh * n_split + sp;
-            store_through(ws_acc + idx * D + d, o);
-            if (d == 0) store_through(reinterpret_cast<f32x2*>(ws_ml) + idx, f32x2{M, L});
+            store_record<D>(ws_acc, ws_ml, bh * n_split + sp, d, o, M, L, mode < 0);
         }
     }
 }
@@ -454,6 +452,12 @@ static DecodePlan ragged_plan(DecodePlan plan, bool gqa, int batch, int q_heads,
     // eight of the larger, short contexts in a large cache lose (300 to 700 tokens, 32 sequences, T=8192 14.0 and 17.3 us, 16
     // of T=32768 10.7 and 14.5).
     if (gqa && head_dim == 64 && rows * plan.n_split <= 256) plan.waves = 8;
+    // Records through the L2 (store_through) as long as a whole cache of that length is at most 64 MB.  Splits of different lengths end
+    // while others still read, and from about there on the records' writes cost the reads more than their write-back at the end
+    // costs the merge.  Through -> plain, us: 41 sequences, 16 on 2 heads, T=23692, D=64 40.9 -> 39.1, 8, 64 on 8, T=40000 82.1 ->
+    // 79.8; of 93 shapes of 20 to 110 MB those of 80 and 110 are 0.9 % faster plain, those of 20 to 45 0.8 % slower (24 sequences, 16 on 2
+    // heads, T=2525 14.3 -> 14.8).  Of equal lengths, which end together, none was faster plain (one, 64 on 8, T=32768 20.5 -> 20.7 to 21.4).
+    plan.records_through = (double)kv_len * batch * kv_heads * (2 * head_dim + 8) <= 64e6;
     // Whole rows, more than one on some compute unit: dealt by their lengths (ranked_row).  Up to three a unit, which are there at
     // once: with more, rows that end early make room for others, and what finding a row takes comes again in each round (64
     // sequences, 32 heads, T=500, lengths spread 27.0 -> 29.3 us).  Of shorter caches two rows differ by less than that.
@@ -517,7 +521,7 @@ hipError_t launch_decode(const DecodeArgs& a, hipStream_t stream) {
         hipLaunchKernelGGL((slim_decode_int8_split_kernel<D, W>), dim3((unsigned)n_split, (unsigned)a.q_heads, (unsigned)a.batch),
                            dim3(64 * W), 0, stream, (const uint16_t*)a.q, a.k_codes, a.k_scale, a.v_codes, a.v_scale,
                            (uint16_t*)a.out, ws_acc, ws_ml, a.kv_lens, a.q_heads / a.kv_heads, a.kv_heads, a.kv_len, n_split,
-                           plan.split_rate, plan.ranked ? a.batch : 0, a.softmax_scale * kLog2e);
+                           plan.split_rate, decode_mode(plan, a.batch), a.softmax_scale * kLog2e);
         return hipGetLastError();
     };
     auto pick_w = [&](auto d_c) {

@@ -63,7 +63,7 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_gqa_kernel(
     const uint16_t* __restrict__ q, const int8_t* __restrict__ kc, const float* __restrict__ ks,
     const int8_t* __restrict__ vc, const float* __restrict__ vs, uint16_t* __restrict__ out, float* __restrict__ ws_acc,
     float* __restrict__ ws_ml, const int* __restrict__ kv_lens, int G, int Hkv, int T_alloc, int n_split,
-    unsigned split_rate, int ranked, float scale_log2e) {
+    unsigned split_rate, int mode, float scale_log2e) {
     constexpr int KS = D / 64;            // 16-byte pieces of a K row per lane (two k-steps of the score MFMA each)
     constexpr int DT = D / 16;            // 16-row tiles of O^T
     constexpr int CPR = D / 16;           // 16-byte pieces per row
@@ -82,8 +82,8 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_gqa_kernel(
     const int Hq = G * Hkv;   // (G query heads per KV head)
     int g = blockIdx.y, b = blockIdx.z, T;
     const int sp = blockIdx.x;
-    if (ranked != 0) {   // (the number of sequences; one split)
-        const SequenceHead row = ranked_row(kv_lens, ranked, Hkv, T_alloc, b, g);
+    if (mode > 0) {   // (dealt by length; one split)
+        const SequenceHead row = ranked_row(kv_lens, mode, Hkv, T_alloc, b, g);
         g = row.h;
         b = row.b;
         T = row.T;
@@ -319,9 +319,7 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_gqa_kernel(
         if (!TRAFFIC_ONLY && n_used == 1) {   // (the measurement form has a workspace only)
             out[bh * D + d] = (uint16_t)(pack_bf16x2(acc / L, 0.0f) & 0xffffu);
         } else {
-            const long idx = bh * n_split + sp;
-            store_through(ws_acc + idx * D + d, acc);
-            if (d == 0) store_through(reinterpret_cast<f32x2*>(ws_ml) + idx, f32x2{top, L});
+            store_record<D>(ws_acc, ws_ml, bh * n_split + sp, d, acc, top, L, mode < 0);
         }
     }
 }
@@ -382,7 +380,7 @@ hipError_t launch_decode_gqa_split(const DecodeArgs& a, float* ws_acc, float* ws
         constexpr int D = decltype(d_c)::value, W = decltype(w_c)::value, NC = decltype(nc_c)::value;
         hipLaunchKernelGGL((slim_decode_int8_gqa_kernel<D, W, NC, decltype(traffic_c)::value>), grid, dim3(64 * W), 0, stream,
                            (const uint16_t*)a.q, a.k_codes, a.k_scale, a.v_codes, a.v_scale, (uint16_t*)a.out, ws_acc, ws_ml,
-                           a.kv_lens, a.q_heads / a.kv_heads, a.kv_heads, a.kv_len, plan.n_split, plan.split_rate, plan.ranked ? a.batch : 0, scale_log2e);
+                           a.kv_lens, a.q_heads / a.kv_heads, a.kv_heads, a.kv_len, plan.n_split, plan.split_rate, decode_mode(plan, a.batch), scale_log2e);
         return hipGetLastError();
     };
     auto pick = [&](auto d_c) {

@@ -190,6 +190,21 @@ __device__ __forceinline__ void split_span(int n, int n_used, int sp, int& begin
     end = begin + (int)q + ((unsigned)sp < r ? 1 : 0);
 }
 
+// A split's record for the launch that merges: accumulator (a thread a value), max and sum.  `through`: see store_through; the rule
+// is with the plan.
+template <int D>
+__device__ __forceinline__ void store_record(float* ws_acc, float* ws_ml, long idx, int d, float acc, float M, float L, bool through) {
+    float* const ap = ws_acc + idx * D + d;
+    f32x2* const mlp = reinterpret_cast<f32x2*>(ws_ml) + idx;
+    if (through) {
+        store_through(ap, acc);
+        if (d == 0) store_through(mlp, f32x2{M, L});
+    } else {
+        *ap = acc;
+        if (d == 0) *mlp = f32x2{M, L};
+    }
+}
+
 // sum and max over a wave, wave-uniform
 __device__ __forceinline__ int wave_sum(int v) {
     v += __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, false);    // quad_perm [1,0,3,2]

@@ -62,8 +62,12 @@ constexpr double kDecodeLongNs = 9000.0;
 struct DecodePlan {
     int waves, n_split;
     unsigned split_rate;
-    bool ranked = false;   // workgroups take the rows in the order of their lengths (ranked_row)
+    bool ranked = false;            // workgroups take the rows in the order of their lengths (ranked_row)
+    bool records_through = true;    // the splits' records go through the L2 (store_record)
 };
+// The plan's options in the kernels' one argument for them: the number of sequences where rows are dealt by length (then there are no
+// records), else -1 for records through the L2, 0 for plain ones
+inline int decode_mode(const DecodePlan& plan, int batch) { return plan.ranked ? batch : plan.records_through ? -1 : 0; }
 // Grouped-query variant (2 to 32 query heads per KV head): a workgroup sweeps a run of tokens of one (batch, KV head)
 // for all its query heads and is a split.  n_bg = batch * kv_heads, group = query heads per KV head.
 bool decode_uses_gqa_kernel(int q_heads, int kv_heads);

@@ -70,6 +70,8 @@ def load():
         lib.slim_attn_decode_int8_varlen.restype = i
         lib.slim_attn_decode_int8_plan.argtypes = [i, i, i, i, i, i, ctypes.POINTER(i), ctypes.POINTER(i)]
         lib.slim_attn_decode_int8_plan.restype = i
+        lib.slim_attn_decode_int8_plan_options.argtypes = [i, i, i, i, i, i, ctypes.POINTER(i), ctypes.POINTER(i)]
+        lib.slim_attn_decode_int8_plan_options.restype = i
         lib.slim_status_string.argtypes = [i]
         lib.slim_status_string.restype = ctypes.c_char_p
         _lib = lib

@@ -288,6 +288,25 @@ def test_decode_plan_of_a_call(lib):
     assert plan(20, 16, 4, 700, 128)[0] == plan(64, 40, 2, 3000, 128)[0] == 8
 
 
+def test_decode_records_of_a_call(lib):
+    r, t = ctypes.c_int(), ctypes.c_int()
+    f = lib.slim_attn_decode_int8_plan_options
+    assert f(1, 4, 2, 100, 128, 0, None, ctypes.byref(t)) == 1 and f(1, 4, 3, 100, 128, 0, ctypes.byref(r), ctypes.byref(t)) == 2
+    assert f(1, 4, 2, 100, 96, 0, ctypes.byref(r), ctypes.byref(t)) == 3 and f(1, 4, 2, 100, 128, 2, ctypes.byref(r), ctypes.byref(t)) == 2
+
+    def through(*shape, ragged=1):
+        assert f(*shape, ragged, ctypes.byref(r), ctypes.byref(t)) == 0
+        return t.value
+
+    # splits of different lengths: plain stores where the caches are long (through the L2 these took 2 to 4 % longer), not where they
+    # are short; equal lengths, and a sequence alone, end together
+    for shape in ((41, 16, 2, 23692, 64), (30, 16, 2, 41089, 64), (15, 64, 8, 26557, 64), (8, 64, 8, 40000, 128), (32, 16, 2, 8000, 64)):
+        assert through(*shape) == 0 and through(*shape, ragged=0) == 1, shape
+    for shape in ((24, 16, 2, 2525, 128), (2, 64, 8, 4734, 128), (3, 32, 32, 2450, 64), (1, 64, 8, 100000, 128)):
+        assert through(*shape) == 1, shape
+    assert through(48, 32, 8, 3001, 128) == through(16, 32, 32, 8192, 128, ragged=0) == 0   # (no records)
+
+
 def test_prefill_emit_rejects_bad_arguments(lib):
     f = lib.slim_attn_prefill_emit_int8
 
