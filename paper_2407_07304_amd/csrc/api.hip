@@ -212,8 +212,10 @@ int slim_attn_prefill_emit_int8(const void* q_bf16, const void* k_bf16, const vo
 
 size_t slim_attn_decode_int8_workspace_bytes(int batch, int q_heads, int kv_heads, int kv_len, int head_dim) {
     if (check_shape(batch, q_heads, kv_heads, kv_len, head_dim) != SLIM_OK) return 0;
-    // (one answer for both entry points: the plan for sequences of different lengths never has fewer splits)
-    return slim::decode_workspace_bytes(batch, q_heads, kv_heads, kv_len, head_dim, true);
+    // one answer for both entry points, which the plan for sequences of different lengths may cut finer or less
+    const size_t equal = slim::decode_workspace_bytes(batch, q_heads, kv_heads, kv_len, head_dim, false);
+    const size_t ragged = slim::decode_workspace_bytes(batch, q_heads, kv_heads, kv_len, head_dim, true);
+    return equal > ragged ? equal : ragged;
 }
 
 int slim_attn_decode_int8_plan(int batch, int q_heads, int kv_heads, int kv_len, int head_dim, int per_sequence_lengths,

@@ -383,15 +383,21 @@ static hipError_t launch_combine(const DecodeArgs& a, const float* ws_acc, const
 //   - the cache at 6.6 TB/s, or the fullest compute unit's tokens at its own pace (7.1 ns a token of 128 codes, 5.8 of
 //     64: its vector ALU and its share of the memory): the longer of the two and a fifth of the
 //     shorter;
-//   - 6 us for the combine launch when S > 1.  Where that gives no compute unit a second workgroup and whole rows take longer
-//     than kDecodeLongNs, the splits are chosen again among those of which that holds, with 4.8 us (5.75 of 64 codes a token), and
-//     the last split may have fewer than four chunks (4 sequences, 32 heads, T=2000 a step 19.6 -> 18.2 us, D=64 16.5 -> 14.3).
+//   - 6 us for the combine launch when S > 1.  Where that gives no compute unit a second workgroup and the step is long enough, the
+//     splits are chosen again among those of which that holds, with 4.8 us (5.75 of 64 codes a token), and up to three splits may
+//     have three chunks and leave a wave idle (4 sequences, 32 heads, T=2000 a step 19.6 -> 18.2 us, D=64 16.5 -> 14.3).
+// Long enough (appends, decode, merge: from the host a step of four launches takes 13.4 to 13.9 us whatever it computes): rows that are
+// split anyway from kDecodeLongNs on; whole ones from 9.4 us on (10 of 64 codes), lengths of their own by the longest of as many
+// lengths spread over an eighth to all of the cache, which is what the call then waits for.  Over 44 shapes about those lines, D=128 and
+// 64, steps that stay whole would lose 0 to 21 %, those that are split gain 1 to 11 % (21 sequences, 4 heads, T=1590, D=64, lengths
+// spread: 11.3 us whole, 13.7 in three; 3, 32 heads, T=1466 13.1 and 13.7, T=1500 14.3 and 13.8).
 // So a (batch, head) is split only where one workgroup each cannot load the chip evenly or soon enough, and whole
 // caches go through one launch from about 150 rows on (B=16, 32 heads, T=8192: 161 us in one launch of eight-wave
 // workgroups, 164 us as 4 splits).  A split has at least a chunk for each of four waves, and a call is not split into more
 // records than the library's own scratch holds (that many are 126 workgroups per compute unit and more, where a finer
 // split gains nothing): what decides whether slim_attn_decode_int8_static takes a shape is then its rows alone.
-static DecodePlan decode_plan(int kv_len, long n_bh, int head_dim) {
+// longest: of sequences with lengths of their own, the expected part of kv_len that the longest has
+static DecodePlan decode_plan(int kv_len, long n_bh, int head_dim, double longest) {
     const long n_chunks = ((long)kv_len + kChunk - 1) / kChunk;
     const double ns_token = head_dim == 128 ? 7.1 : 5.8;
     const double stream_ns = (double)kv_len * n_bh * (2 * head_dim + 8) / 6600.0;
@@ -414,7 +420,8 @@ static DecodePlan decode_plan(int kv_len, long n_bh, int head_dim) {
             alone_best = s;
         }
     }
-    if (whole_ns > kDecodeLongNs && n_bh * best <= 256) best = alone_best;
+    const bool long_enough = best > 1 ? whole_ns > kDecodeLongNs : whole_ns * longest > (head_dim == 128 ? 9400.0 : 10000.0);
+    if (long_enough && n_bh * best <= 256) best = alone_best;
     // eight waves share a merge where each still gets a few chunks (a chunk each, two of 64 codes a token, is
     // enough once several workgroups per compute unit overlap: 800 x 8 heads, T=500, D=64, 77.8 us with eight
     // waves, 72.4 with four, and with lengths of their own, where half of the eight had nothing, 60.6 and 45.9)
@@ -467,8 +474,10 @@ static DecodePlan ragged_plan(DecodePlan plan, bool gqa, int batch, int q_heads,
 
 DecodePlan decode_plan_of(bool ragged, int batch, int q_heads, int kv_heads, int kv_len, int head_dim) {
     const bool gqa = decode_uses_gqa_kernel(q_heads, kv_heads);
+    // (B lengths spread evenly over an eighth to all of the cache)
+    const double longest = ragged && batch > 1 ? (batch + 0.125) / (batch + 1) : 1.0;
     const DecodePlan plan = gqa ? decode_gqa_plan(kv_len, (long)batch * kv_heads, q_heads / kv_heads, head_dim)
-                                : decode_plan(kv_len, (long)batch * q_heads, head_dim);
+                                : decode_plan(kv_len, (long)batch * q_heads, head_dim, longest);
     return ragged ? ragged_plan(plan, gqa, batch, q_heads, kv_heads, kv_len, head_dim) : plan;
 }
 

@@ -53,9 +53,10 @@ struct DecodeArgs {
     float softmax_scale;
     bool ragged;          // use the plan for sequences of different lengths (the workspace has room for it)
 };
-// A decode whose whole rows would take this long is bound by the GPU also as a step of its own (its appends, then the decode).  A
-// shorter one is bound by the host's 3 to 3.5 us a launch, and the launch that merges splits counts as more than it takes the GPU (32
-// heads, T=1000, a step with 4 splits and one: by the GPU alone 10.3 and 12.0 us, from the host 12.6 to 14.1 and 11.8).
+// From this long on (whole rows, as the plans model them) a decode is cut with the merge's launch as what it takes the GPU, below with
+// more: its step (two appends, then the decode) is then over before the host has issued a fourth launch.  32 heads, T=1000, four splits
+// and one: by the GPU alone 10.3 and 12.0 us, from the host 12.6 to 14.1 (bound by the fourth launch) and 11.8 (by the GPU).  A captured
+// step, whose launches the host does not issue, loses those 14 % to this.
 constexpr double kDecodeLongNs = 9000.0;
 // How a decode call is cut up: waves per workgroup, splits of the key axis (workgroups per row), and how many of them a
 // sequence uses (splits_of).

@@ -288,6 +288,26 @@ def test_decode_plan_of_a_call(lib):
     assert plan(20, 16, 4, 700, 128)[0] == plan(64, 40, 2, 3000, 128)[0] == 8
 
 
+def test_decode_short_steps_keep_whole_rows(lib):
+    w, n = ctypes.c_int(), ctypes.c_int()
+
+    def splits(*shape, ragged):
+        assert lib.slim_attn_decode_int8_plan(*shape, ragged, ctypes.byref(w), ctypes.byref(n)) == 0
+        # (the workspace that the library asks for is enough for both entry points, whichever plan has more splits)
+        assert n.value * shape[0] * shape[1] * (shape[4] + 2) * 4 <= lib.slim_attn_decode_int8_workspace_bytes(*shape)
+        return n.value
+
+    # a second launch would outlast the step: 3 to 21 % longer from the host
+    for shape in ((21, 4, 4, 1590, 64), (9, 8, 8, 1483, 64), (3, 32, 32, 1437, 128), (16, 4, 4, 1172, 128)):
+        assert splits(*shape, ragged=1) == 1, shape
+    for shape in ((2, 32, 32, 1210, 128), (20, 4, 4, 1186, 128), (2, 32, 32, 1400, 64)):
+        assert splits(*shape, ragged=0) == 1, shape
+    # longer ones gain by it; three lengths of up to 1437 tokens are shorter than three of 1437
+    for shape in ((20, 4, 4, 1300, 128), (3, 32, 32, 1600, 128), (16, 8, 8, 2000, 64), (30, 4, 4, 2229, 128)):
+        assert splits(*shape, ragged=0) > 1 and splits(*shape, ragged=1) > 1, shape
+    assert splits(3, 32, 32, 1437, 128, ragged=0) == 2
+
+
 def test_decode_records_of_a_call(lib):
     r, t = ctypes.c_int(), ctypes.c_int()
     f = lib.slim_attn_decode_int8_plan_options
