@@ -27,11 +27,14 @@ def assert_form(sa, rows, B, Hq, Hkv, S, D, causal, kv_int8, out_f32):
     assert got == rows, "row blocks of %d rows, the test is of those of %d" % (got, rows)
 
 
-def assert_plan(sa, plan, B, Hq, Hkv, T, D):
-    """A decode with lengths of its own takes this plan: (waves per workgroup, workgroups per row)."""
+def assert_plan(sa, plan, B, Hq, Hkv, T, D, by_length=None):
+    """A decode with lengths of its own takes this plan: (waves per workgroup, workgroups per row), and deals its rows by length or not."""
     w, n = ctypes.c_int(), ctypes.c_int()
     assert sa.load().slim_attn_decode_int8_plan(B, Hq, Hkv, T, D, 1, ctypes.byref(w), ctypes.byref(n)) == 0
     assert (w.value, n.value) == plan, "plan %s, the test is of %s" % ((w.value, n.value), plan)
+    if by_length is not None:
+        assert sa.load().slim_attn_decode_int8_plan_options(B, Hq, Hkv, T, D, 1, ctypes.byref(w), ctypes.byref(n)) == 0
+        assert w.value == by_length, "rows dealt by length: %d" % w.value
 
 
 def check_close(got: np.ndarray, want: np.ndarray, what=""):

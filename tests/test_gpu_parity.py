@@ -729,12 +729,14 @@ def test_grouped_decode_waves_with_lengths_of_their_own(sa, oracle, B, Hq, Hkv, 
     assert err.mean() <= 1.27 * 2 * 2.0 ** -9
 
 
-@pytest.mark.parametrize("B,Hq,Hkv,T,D", [
+@pytest.mark.parametrize("B,Hq,Hkv,T,D,waves", [
     # whole rows that are dealt to the workgroups by their lengths: two more than a layer of 256, one and a half, two and a
-    # bit, three full layers; 2, 64, 65 and 128 sequences (one and two a lane); grouped heads and not
-    (2, 129, 129, 1000, 64), (64, 6, 6, 1000, 64), (65, 16, 8, 1003, 64), (128, 12, 6, 1000, 128), (33, 8, 8, 1100, 128)])
-def test_decode_rows_dealt_by_their_lengths(sa, oracle, B, Hq, Hkv, T, D):
-    assert_plan(sa, (4, 1), B, Hq, Hkv, T, D)
+    # bit, three full layers; 2, 64, 65 and 128 sequences (one and two a lane); grouped heads and not; eight waves, of which one
+    # workgroup or two fit a compute unit: a head each, and more than sixteen heads a KV head
+    (2, 129, 129, 1000, 64, 4), (64, 6, 6, 1000, 64, 4), (65, 16, 8, 1003, 64, 4), (128, 12, 6, 1000, 128, 4), (33, 8, 8, 1100, 128, 4),
+    (24, 11, 11, 1540, 64, 8), (96, 8, 8, 1500, 128, 8), (128, 68, 4, 1000, 128, 8), (128, 68, 4, 1000, 64, 8)])
+def test_decode_rows_dealt_by_their_lengths(sa, oracle, B, Hq, Hkv, T, D, waves):
+    assert_plan(sa, (waves, 1), B, Hq, Hkv, T, D, by_length=1)
     print("decode, rows by length", B, Hq, Hkv, T, D, flush=True)
     rng = np.random.default_rng(B + T + D)
     # ties, a sequence of a token, chunk bounds, both ends; then lengths that hardly differ, whose rows keep their order
@@ -779,11 +781,14 @@ def test_prefill_int8_largest_probability_rounds_like_any_other(sa, B, Hq, Hkv, 
     assert abs(off) <= 5 * 2.0 ** -8 / math.sqrt(3 * B * Hq), off
 
 
-def test_grouped_decode_eight_waves_round_like_any_other_token(sa):
-    # Lengths of their own, 64 codes a token, eight waves: sequences of one token, whose probability is that wave's largest.
+@pytest.mark.parametrize("B,Hq,Hkv,T,D,plan", [
+    # every form of the kernel: eight and four waves, 64 and 128 codes, more than sixteen heads a KV head
+    (32, 32, 8, 300, 64, (8, 1)), (33, 32, 8, 300, 64, (4, 1)), (29, 32, 8, 300, 128, (8, 1)), (32, 32, 8, 300, 128, (4, 1)),
+    (16, 80, 4, 300, 64, (8, 1)), (16, 80, 4, 300, 128, (8, 1))])
+def test_grouped_decode_eight_waves_round_like_any_other_token(sa, B, Hq, Hkv, T, D, plan):
+    # Lengths of their own: sequences of one token, whose probability is that wave's largest.
     # Were it exactly 1, every result would be off by what its v_scale is off a bf16 value, here half an ulp, upwards: 2^-8.
-    B, Hq, Hkv, T, D = 32, 32, 8, 300, 64
-    assert_plan(sa, (8, 1), B, Hq, Hkv, T, D)
+    assert_plan(sa, plan, B, Hq, Hkv, T, D)
     rng = np.random.default_rng(77)
     q = normal_bf16(rng, (B, Hq, 1, D))
     kc = rng.integers(-127, 128, (B, Hkv, T, D), dtype=np.int8)
@@ -793,7 +798,7 @@ def test_grouped_decode_eight_waves_round_like_any_other_token(sa):
     out = host_f64(sa.slim_attn_decode_int8_varlen(dev_bf16(q), dev(kc), dev(ks), dev(vc), dev(vs), torch.ones(B, dtype=torch.int32, device="cuda"),
                                                    1.0 / math.sqrt(D)))
     off = (out / np.repeat(vc[:, :, :1].astype(np.float64) * float(vs[0, 0, 0]), Hq // Hkv, axis=1) - 1).mean()
-    # (1024 heads, each with a rounding of its own of at most 2^-8: five times the mean's standard deviation of a uniform one)
+    # (B Hq heads, each with a rounding of its own of at most 2^-8: five times the mean's standard deviation of a uniform one)
     assert abs(off) <= 5 * 2.0 ** -8 / math.sqrt(3 * B * Hq), off
 
 
