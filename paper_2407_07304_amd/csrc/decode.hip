@@ -261,8 +261,8 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_split_kernel(
     }
 }
 
-// Merges the n_split partial (max, sum, accumulator) triples of one (batch, head) in split order and writes the
-// bf16 output row.  The launch is latency-bound (a few kilobytes per row, just written by the split kernel), so a row's records
+// Merges the n_split partial (max, sum, accumulator) triples of one (batch, head) in a fixed order (records dealt to lane
+// groups and waves, each group's in turn, then the groups by halves, then the waves) and writes the bf16 output row.  The launch is latency-bound (a few kilobytes per row, just written by the split kernel), so a row's records
 // come in with few, wide loads that are all issued before anything is computed: D/4 lanes read a record with one 128-bit
 // load each, a wave RPW = 256/D records at a time.  Up to U RPW records a row one wave does it, and a workgroup has four
 // rows; more are shared by the four waves of a workgroup and merged through LDS.  Slots past the last split re-read the last
@@ -386,6 +386,9 @@ static hipError_t launch_combine(const DecodeArgs& a, const float* ws_acc, const
 //   - 6 us for the combine launch when S > 1.  Where that gives no compute unit a second workgroup and the step is long enough, the
 //     splits are chosen again among those of which that holds, with 4.8 us (5.75 of 64 codes a token), and up to three splits may
 //     have three chunks and leave a wave idle (4 sequences, 32 heads, T=2000 a step 19.6 -> 18.2 us, D=64 16.5 -> 14.3).
+//     That is at the upper end of what splitting whole rows costs beyond the sweep as modelled (the merge's launch takes 2.1 to 2.7
+//     us, the rest is what a second set of workgroups takes to start and end): over 19 shapes of 64 to 128 rows, T=1000 to
+//     3000, cut in 2 to 4, 3.0 to 4.7 us by the GPU alone, over 7 of 64 codes 3.9 to 4.5.  The grouped kernel's is less (its plan).
 // Long enough (appends, decode, merge: from the host a step of four launches takes 13.4 to 13.9 us whatever it computes): rows that are
 // split anyway from kDecodeLongNs on; whole ones from 9.4 us on (10 of 64 codes), lengths of their own by the longest of as many
 // lengths spread over an eighth to all of the cache, which is what the call then waits for.  Over 44 shapes about those lines, D=128 and
@@ -393,8 +396,8 @@ static hipError_t launch_combine(const DecodeArgs& a, const float* ws_acc, const
 // spread: 11.3 us whole, 13.7 in three; 3, 32 heads, T=1466 13.1 and 13.7, T=1500 14.3 and 13.8).
 // So a (batch, head) is split only where one workgroup each cannot load the chip evenly or soon enough, and whole
 // caches go through one launch from about 150 rows on (B=16, 32 heads, T=8192: 161 us in one launch of eight-wave
-// workgroups, 164 us as 4 splits).  A split has at least a chunk for each of four waves, and a call is not split into more
-// records than the library's own scratch holds (that many are 126 workgroups per compute unit and more, where a finer
+// workgroups, 164 us as 4 splits).  A split has a chunk for each of four waves, but for the up to three above, and a call is not
+// split into more records than the library's own scratch holds (that many are 126 workgroups per compute unit and more, where a finer
 // split gains nothing): what decides whether slim_attn_decode_int8_static takes a shape is then its rows alone.
 // longest: of sequences with lengths of their own, the expected part of kv_len that the longest has
 static DecodePlan decode_plan(int kv_len, long n_bh, int head_dim, double longest) {
@@ -465,9 +468,14 @@ static DecodePlan ragged_plan(DecodePlan plan, bool gqa, int batch, int q_heads,
     // 79.8; of 93 shapes of 20 to 110 MB those of 80 and 110 are 0.9 % faster plain, those of 20 to 45 0.8 % slower (24 sequences, 16 on 2
     // heads, T=2525 14.3 -> 14.8).  Of equal lengths, which end together, none was faster plain (one, 64 on 8, T=32768 20.5 -> 20.7 to 21.4).
     plan.records_through = (double)kv_len * batch * kv_heads * (2 * head_dim + 8) <= 64e6;
-    // Whole rows, more than one on some compute unit: dealt by their lengths (ranked_row).  Up to three a unit, which are there at
-    // once: with more, rows that end early make room for others, and what finding a row takes comes again in each round (64
-    // sequences, 32 heads, T=500, lengths spread 27.0 -> 29.3 us).  Of shorter caches two rows differ by less than that.
+    // Whole rows, more than one on some compute unit: dealt by their lengths (ranked_row).  Up to three a unit: with more, rows that end
+    // early make room for others, and what finding a row takes comes again with each (64 sequences, 32 heads, T=500, lengths spread
+    // 27.0 -> 29.3 us).  Of shorter caches two rows differ by less than that.  A unit holds three workgroups of the grouped kernel's
+    // four waves (five of 64 codes), four or five of the other kernel's, two of its eight waves and one of two column groups: where a
+    // layer does not fit, its rows go to the units that are free first, and that is still better than the grid's order.  Lengths spread / a fourth full and the others
+    // an eighth / equal, us: 24 sequences, 32 heads, T=2500 (eight waves) 53.7 -> 50.9 / 40.4 -> 34.2 / 75.9 -> 76.1; 96, 8 heads,
+    // T=4000, D=64 59.3 -> 48.5 / 48.1 -> 33.1 / 70.3 -> 70.9; 90, 160 on 8 heads, T=1200 (two groups) 42.1 -> 40.4 / 38.1 -> 34.1 /
+    // 55.7 -> 56.5.  What it costs equal lengths is 0.3 us a layer: up to 3 % of 64 codes a token (96, 32 on 8, T=2000 35.9 -> 37.0).
     plan.ranked = plan.n_split == 1 && batch <= kMaxRanked && rows > 256 && rows <= 768 && kv_len >= 1000;
     return plan;
 }

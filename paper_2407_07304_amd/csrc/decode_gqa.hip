@@ -55,9 +55,11 @@ __device__ __forceinline__ bf16x8 widen8(const i32x2 cw) {
 // TRAFFIC_ONLY: the measurement form of the kernel (include/slimprobe.h): the same workgroups, waves, token runs and
 // loads, issued at the same points, but a tile's registers are only XORed together before they are refilled.  What it
 // takes is what the memory system charges for this access pattern on this shape, arithmetic aside.
-// The running max is a whole number: a row's largest probability is then some power of two above a half and not 1:
-// times its v_scale it rounds to bf16 like any other, where a v_scale alone is further off than the mean (0.375 of an ulp,
-// codes of N(0,1)), and more waves, each with a maximum of its own, have more such tokens.
+// The running max is a whole number: the token that sets it has the probability 2^(score - ceil(score)), above a half and 1 only if
+// the score itself is whole (later ones have up to 2^8, until the max moves), and times its v_scale that rounds to bf16 like any
+// other.  Were the max the score, it would be exactly 1, and a v_scale alone is further off than the mean (0.375 of an ulp, codes of
+// N(0,1)); more waves, each with a maximum of its own, have more such tokens.  Distance from the 64-bit result, whole maxima / the
+// scores themselves, over 33 shapes, 660 draws of N(0,1): 0.981 on average, 0.960 to 1.000.
 template <int D, int W, int NC, bool TRAFFIC_ONLY = false>
 __global__ __launch_bounds__(64 * W) void slim_decode_int8_gqa_kernel(
     const uint16_t* __restrict__ q, const int8_t* __restrict__ kc, const float* __restrict__ ks,
@@ -329,14 +331,15 @@ __global__ __launch_bounds__(64 * W) void slim_decode_int8_gqa_kernel(
 // unit's tokens at 5.9 ns each (7 where it holds several workgroups; 4.2 and 5 with 64 codes a token), the longer of the two
 // and a fifth of the shorter, and 5 us and 40 ns a split for the combine launch.  Where that gives no compute unit a second
 // workgroup and whole rows take longer than kDecodeLongNs, the splits are chosen again among those of which that holds, with
-// the combine launch as what it takes by itself, 2.4 us and 25 ns a split (3.6 us and 40 ns of 64 codes a token), and the last
-// split may have fewer than four tiles: one sequence, 64 on 8 heads, T=8192, 24 splits 9.6 us, 32 9.1; 16 of T=2000, one split
-// 17.5, two 16.3; 14, 24 on 8 heads, T=2131 a step 23.0 -> 18.8.  (With more splits than compute units it does not hold: 34
-// sequences, 64 on 8 heads, T=1023 23.4 -> 27.9; nor in the place of such a cut: 11, 32 on 8, T=5328, D=64 20.3 -> 21.4.)
+// 2.4 us and 25 ns a split (3.6 us and 40 ns of 64 codes a token), and up to three splits may have three tiles.  What splitting whole rows
+// costs beyond the sweep as modelled, over 23 shapes of 64 to 128 rows, T=900 to 2200, cut in 2 to 4: 1.2 to 2.8 us by the GPU alone,
+// over 8 of 64 codes 2.6 to 3.1.  Steps, us: 16 sequences, 64 on 8 heads, T=2000, one split 21.1, two 20.0; 14, 24 on 8 heads, T=2131
+// 23.0 -> 18.8; 10, 64 on 8, T=1409 17.0 -> 14.6; 63, 16 on 2, lengths of up to 3776 29.0 -> 26.6.  (With more splits than
+// compute units it does not hold: 34 sequences, 64 on 8 heads, T=1023 23.4 -> 27.9; nor in the place of such a cut: 11, 32 on 8,
+// T=5328, D=64 20.3 -> 21.4.)
 // Eight waves where the grid leaves compute units without a workgroup (less than 240 of them), four where it fills the chip:
 // 128 rows at T=8192 take 45.3 us with 1024 waves in 256 workgroups, 49 with 2048 waves (52.9 in the form before, a split per
-// wave; all with the combine launch).  8 rows at T=32768 are 256 workgroups of four waves as well (19.2 us; 30.6 before, on
-// 512 waves): eight waves were not measured there.
+// wave; all with the combine launch).  8 rows at T=32768 are 256 workgroups of four waves as well: 16.6 us, with eight waves 17.2.
 // With more than 16 heads a KV head (two column groups) always eight waves, a split from three tiles on, and 3 us for the
 // combine launch: a compute unit has one or two such workgroups, and four waves are half as many as it wants (32 on 1
 // head, T=777, K and V in the caches: 14.6 us with four waves in one split, 10.3 now; 20 on 1, 128 sequences,

@@ -227,7 +227,8 @@ __device__ __forceinline__ int wave_max(int v) {
 // on one unit while another has two short ones, and the call takes as long as the former.  So the rows are dealt
 // longest first in layers of 256, and every other layer runs backwards: a unit's longest row meets the shortest of the next layer.
 // The last layer runs forwards: where it is not full, the units it leaves out have the longest rows of the layer
-// before.  (Where an id lands only decides about time: every row is worked off as it was, by one workgroup.)
+// before.  (Where an id lands only decides about time: every row is worked off as it was, by one workgroup.  Forms of which fewer
+// workgroups fit a unit than there are layers take the later rows where one ends, layer by layer: the figures are with the plan.)
 // Lengths spread over an eighth to all of the cache, a fourth of them full and the others an eighth, all equal, us:
 //   48 sequences, 32 on 8 heads, T=3001 37.9 -> 33.2, 38.2 -> 28.8, 51.0 -> 51.5; 16, 32 heads, T=3000 42.8 -> 39.8, 37.3 ->
 //   26.7, 61.6 -> 61.8; 40, 8 heads, T=1000 14.6 -> 11.7, 13.8 -> 9.5, 18.1 -> 18.3; 64, 64 on 8 heads, D=64, T=2000 19.5 ->
