@@ -36,8 +36,7 @@ __device__ __forceinline__ void store_through(T* p, const T v) {
     using Bits = std::conditional_t<sizeof(T) == 8, unsigned long long, unsigned>;
     __hip_atomic_store(reinterpret_cast<Bits*>(p), __builtin_bit_cast(Bits, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// 16 bytes at base + off + step (base and step uniform, off + step below 2^31; what is the same for all lanes goes into step, a scalar:
-// added up in vector registers it cost the 128-row INT8 prefill with fp32 results, D=128, two more spilled registers)
+// 16 bytes at base + off + step (base and step uniform, off + step below 2^31)
 __device__ __forceinline__ void store_through_b128(void* base, int off, int step, u32x4 v) {
     constexpr int kDeviceScope = 16;   // (the cache policy's sc1 bit)
     __builtin_amdgcn_raw_buffer_store_b128(v, __builtin_amdgcn_make_buffer_rsrc(base, 0, 0x7fffffff, 0x00020000), off, step, kDeviceScope);
