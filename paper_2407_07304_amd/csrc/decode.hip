@@ -386,9 +386,10 @@ static hipError_t launch_combine(const DecodeArgs& a, const float* ws_acc, const
 //   - 6 us for the combine launch when S > 1.  Where that gives no compute unit a second workgroup and the step is long enough, the
 //     splits are chosen again among those of which that holds, with 4.8 us (5.75 of 64 codes a token), and up to three splits may
 //     have three chunks and leave a wave idle (4 sequences, 32 heads, T=2000 a step 19.6 -> 18.2 us, D=64 16.5 -> 14.3).
-//     That is at the upper end of what splitting whole rows costs beyond the sweep as modelled (the merge's launch takes 2.1 to 2.7
-//     us, the rest is what a second set of workgroups takes to start and end): over 19 shapes of 64 to 128 rows, T=1000 to
-//     3000, cut in 2 to 4, 3.0 to 4.7 us by the GPU alone, over 7 of 64 codes 3.9 to 4.5.  The grouped kernel's is less (its plan).
+//     That is at the upper end of what splitting whole rows costs beyond the sweep as modelled: over 19 shapes of 64 to 128 rows,
+//     T=1000 to 3000, cut in 2 to 4, 3.0 to 4.7 us by the GPU alone, over 7 of 64 codes 3.9 to 4.5.  (Of the grouped kernel's, less: a
+//     fit of its model, not of the merge, which is one kernel: in a trace 2.0 to 5.5 us, 3.7 on average for 64 rows of 32 records, 4.6
+//     for 1024 of 2.)
 // Long enough (appends, decode, merge: from the host a step of four launches takes 13.4 to 13.9 us whatever it computes): rows that are
 // split anyway from kDecodeLongNs on; whole ones from 9.4 us on (10 of 64 codes), lengths of their own by the longest of as many
 // lengths spread over an eighth to all of the cache, which is what the call then waits for.  Over 44 shapes about those lines, D=128 and
